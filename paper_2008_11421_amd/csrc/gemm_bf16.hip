@@ -585,12 +585,17 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
       bon = b_origin(n0n, kbn);
       if constexpr (CONV == 1) conv_decode(m0n, c_pix_next);
     }
+    // (EDGE: a wavefront issues no load for a piece that lies outside with all its lanes, so how many loads are
+    // younger than tile 0's is not known: tile 0 is waited for before tile 1 is requested)
+    if (EDGE) wait_vm<0>();
     lds_barrier_visible();   // the previous item's strip (which overlays stage s0 ^ 1) has been read out by every wavefront
     if (KT > 1) issue(s0 ^ 1, ao, bo, 1, m0, n0, kb, ke);
     else if (have_next) issue(s0 ^ 1, aon, bon, 0, m0n, n0n, kbn, ken, true);
-    if (KT > 1 || have_next) wait_vm<LPT>();   // everything older than the loads just issued: tile 0 has landed
-    else wait_vm<0>();
-    lds_barrier_visible();
+    if (!EDGE) {
+      if (KT > 1 || have_next) wait_vm<LPT>();   // everything older than the loads just issued: tile 0 has landed
+      else wait_vm<0>();
+      lds_barrier_visible();
+    }
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
