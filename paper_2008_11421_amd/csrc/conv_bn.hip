@@ -10,33 +10,12 @@
 #include <hip/hip_runtime.h>
 
 #include "karma.h"
+#include "device_utils.h"
 #include "kernels.h"
 
 namespace karma {
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-
-__device__ __forceinline__ bf16_t f2bf_(float f) {   // round to nearest even, NaN kept
-  unsigned u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f_(bf16_t b) { return __uint_as_float((unsigned)b << 16); }
-__device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f[2 * i] = __uint_as_float(v[i] << 16);
-    f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ u32x4 pack8(const float* f) {
-  u32x4 v;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = (unsigned)f2bf_(f[2 * i]) | ((unsigned)f2bf_(f[2 * i + 1]) << 16);
-  return v;
-}
 static inline int ok() { return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP; }
 static inline unsigned blocks_for(size_t n, unsigned per) { return (unsigned)((n + per - 1) / per); }
 
@@ -168,7 +147,7 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const float* __restrict_
       const float inv = 1.f / (float)rows;
       const float m = t0 * inv;                       // mean of (x - pivot)
       const float var = fmaxf(t1 * inv - m * m, 0.f);
-      out0[c] = bf2f_(x_row0[c]) + m;
+      out0[c] = bf2f(x_row0[c]) + m;
       out1[c] = 1.f / sqrtf(var + BN_EPS);
     }
   }

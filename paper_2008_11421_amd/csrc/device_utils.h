@@ -35,6 +35,22 @@ __device__ __forceinline__ unsigned pack2(float lo, float hi) {
   return __builtin_bit_cast(unsigned, b);
 }
 
+// eight bf16 (one 16-byte vector) <-> eight floats; packing rounds to nearest even with the hardware converter
+// (four instructions; rounding in integer arithmetic takes about fifty, more than the rest of most kernels that use it)
+__device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[2 * i] = __uint_as_float(v[i] << 16);
+    f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ u32x4 pack8(const float* f) {
+  u32x4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = pack2(f[2 * i], f[2 * i + 1]);
+  return v;
+}
+
 // GELU, tanh form: 0.5 x (1 + tanh(u)), u = sqrt(2/pi) (x + 0.044715 x^3).  With
 // sig = 1 / (1 + e^(-2u)) = (1 + tanh u) / 2 this is x * sig, and the derivative is
 // sig + 2 x sig (1 - sig) u'(x): one hardware exponential and one reciprocal per element.

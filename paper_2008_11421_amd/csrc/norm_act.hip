@@ -12,26 +12,6 @@
 
 namespace karma {
 
-__device__ __forceinline__ float bf2f_(bf16_t b) { return __uint_as_float((unsigned)b << 16); }
-__device__ __forceinline__ bf16_t f2bf_(float f) {
-  unsigned u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
-__device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f[2 * i] = __uint_as_float(v[i] << 16);
-    f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ u32x4 pack8(const float* f) {
-  u32x4 v;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = (unsigned)f2bf_(f[2 * i]) | ((unsigned)f2bf_(f[2 * i + 1]) << 16);
-  return v;
-}
 // Wavefront reductions with data-parallel-primitive moves (full-rate vector instructions; a cross-lane read
 // through the LDS crossbar costs an LDS round trip per step, and a row's two reductions are a chain of twelve).
 // Steps: the other lane of a pair, the other pair of a quad, the other quad of a half-row (row_half_mirror), the
@@ -261,7 +241,7 @@ __global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restr
     float t = red[0][cl];
 #pragma unroll
     for (int k = 1; k < 8; ++k) t += red[k][cl];
-    if (out_bf16) out_bf16[c] = f2bf_(t);
+    if (out_bf16) out_bf16[c] = f2bf(t);
     if (out_f32) {
       if (c < split) out_f32[c] = t;
       else if (c < split2) out_f32_b[c - split] = t;
@@ -468,7 +448,7 @@ __global__ __launch_bounds__(CE_THREADS) void softmax_ce_kernel(bf16_t* __restri
   for (int k = 1; k < CE_WAVES; ++k) sum += red[CE_WAVES + k];
   const float lse = mx + __logf(sum);
   const int label = labels[r];
-  if (threadIdx.x == 0) rowloss[r] = lse - bf2f_(row[label]);
+  if (threadIdx.x == 0) rowloss[r] = lse - bf2f(row[label]);
   const float inv = 1.f / sum;
   for (int c = threadIdx.x; c < nv; c += CE_THREADS) {
     float f[8];
@@ -549,7 +529,7 @@ __global__ void fill_u32_kernel(unsigned* __restrict__ p, unsigned v, size_t n) 
 }
 __global__ void f32_to_bf16_kernel(const float* __restrict__ x, bf16_t* __restrict__ y, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] = f2bf_(x[i]);
+  if (i < n) y[i] = f2bf(x[i]);
 }
 
 // ------------------------------------------------------------------------------ launchers
