@@ -11,6 +11,7 @@
 
 #include "karma.h"
 #include "device_utils.h"
+#include "gemm_ring.h"
 #include "kernels.h"
 
 namespace karma {
@@ -443,6 +444,26 @@ __global__ void conv_weight_transpose_kernel(const bf16_t* __restrict__ w, bf16_
   wt[i] = w[((size_t)co * taps + t) * Cin + ci];
 }
 
+// The same for a stride-2 convolution's gradient by parity of the output pixel: wt [oy][ox][Cin][taps of that parity][Cout]
+__global__ void conv_weight_parity_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wt, int Cout, int R, int S, int pad,
+                                          int Cin) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)Cout * R * S * Cin) return;
+  const int co = (int)(i % Cout);
+  int j = (int)(i / Cout);   // (parity, ci, tap of that parity)
+  for (int oy = 0; oy < 2; ++oy)
+    for (int ox = 0; ox < 2; ++ox) {
+      const DgradTaps ty = dgrad_taps(R, pad, oy), tx = dgrad_taps(S, pad, ox);
+      const int taps = ty.count * tx.count;
+      if (j < taps * Cin) {
+        const int ci = j / taps, t = j % taps, r = ty.first + 2 * (t / tx.count), s = tx.first + 2 * (t % tx.count);
+        wt[i] = w[((size_t)co * R * S + r * S + s) * Cin + ci];
+        return;
+      }
+      j -= taps * Cin;
+    }
+}
+
 bool plain_gemm(const ConvShape& c) { return c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0; }
 bool shape_ok(const ConvShape& c) {
   return c.N > 0 && c.H > 0 && c.W > 0 && c.Cin > 0 && c.Cout > 0 && c.R > 0 && c.S > 0 && c.stride > 0 && c.pad >= 0 &&
@@ -490,15 +511,18 @@ int conv2d_dgrad(const bf16_t* dy, const bf16_t* w, bf16_t* wt_ws, const bf16_t*
   }
   if (!wt_ws) return KARMA_E_INVAL;
   const size_t n = (size_t)c.R * c.S * c.Cin * c.Cout;
-  hipLaunchKernelGGL(conv_weight_transpose_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R * c.S,
-                     c.Cin);
   g.B = wt_ws;          // [Cin][R*S*Cout], reduction index contiguous
   g.K = c.R * c.S * c.Cout;
   g.a_kc = g.b_kc = true;
   g.lda = g.K; g.ldb = g.K;
   g.conv_mode = 1;
   // rows are the pixels of x (H x W grid); the gathered tensor is dy (Ho x Wo x Cout)
-  g.conv = ConvGather{Ho, Wo, c.Cout, c.H, c.W, c.R, c.S, c.stride, c.pad, 1};
+  g.conv = ConvGather{Ho, Wo, c.Cout, c.H, c.W, c.R, c.S, c.stride, c.pad, 1, c.stride == 2};
+  if (g.conv.phased && !gemm_ring_takes(g)) g.conv.phased = 0;
+  if (g.conv.phased)
+    hipLaunchKernelGGL(conv_weight_parity_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R, c.S, c.pad, c.Cin);
+  else
+    hipLaunchKernelGGL(conv_weight_transpose_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R * c.S, c.Cin);
   return gemm_bf16(g, s);
 }
 

@@ -83,6 +83,20 @@ __device__ __forceinline__ void load_to_lds16_s(const void* base, unsigned byte_
                "v"(byte_off), "s"(base)
                : "memory");
 }
+// Buffer descriptor over everything from `base` (wavefront-uniform) on: a lane whose byte offset is LOAD_NOTHING
+// lies beyond its record count, so a load brings zeros for that lane and touches no memory.
+constexpr unsigned LOAD_NOTHING = 0xFFFFFFF0u;
+__device__ __forceinline__ u32x4 buffer_desc(const void* base) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  return u32x4{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, LOAD_NOTHING, 0x00020000u};
+}
+// As load_to_lds16_s through a buffer descriptor: lanes with byte_off = LOAD_NOTHING write zeros to LDS.  Every
+// wavefront issues exactly one load however many of its lanes lie outside, so outstanding loads can be counted.
+__device__ __forceinline__ void buffer_load_to_lds16(const u32x4& desc, unsigned byte_off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(lds)),
+               "v"(byte_off), "s"(desc)
+               : "memory");
+}
 // LDS-only workgroup barrier written with builtins, so that the compiler's own wait-count
 // bookkeeping knows that every LDS read issued before it has returned.
 __device__ __forceinline__ void lds_barrier_visible() {

@@ -5,9 +5,10 @@
 //
 // Operands may have the reduction index contiguous ("k-contiguous": A[M][K], B[N][K]) or
 // strided (A[K][M], B[K][N]); strided tiles are transposed in registers on their way into
-// LDS, so the MFMA loop always reads 16-byte k-runs.  Tiles are staged through LDS with
-// one register-resident tile in flight (double buffer); v_mfma_f32_32x32x16_bf16 does the
-// arithmetic; the workgroup -> tile map keeps each XCD's L2 on a compact patch of C.
+// LDS, so the MFMA loop always reads 16-byte k-runs.  v_mfma_f32_32x32x16_bf16 does the arithmetic; the workgroup ->
+// tile map keeps each XCD's L2 on a compact patch of C.  Three kernels: the direct-load one below (256 x 256 and 256 x 64
+// tiles, persistent), gemm_ring.hip (128 x 128, what does not fill the chip with the large tile), and for sizes and
+// alignments neither takes the first one here, which stages tiles through registers; gemm_bf16_launch chooses.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cstdint>
@@ -15,97 +16,11 @@
 
 #include "karma.h"
 #include "device_utils.h"
+#include "gemm_epilogue.h"
+#include "gemm_ring.h"
 #include "kernels.h"
 
 namespace karma {
-
-struct GemmEpilogue {
-  void* C;                 // bf16 or fp32 [M][ldc]
-  const bf16_t* bias;      // [N] or null
-  const bf16_t* residual;  // [M][ldc] or null (bf16 output only)
-  int ldc;
-  int out_f32;             // store fp32 instead of bf16
-  int accumulate;          // fp32 output only: C += result
-  bf16_t* aux;             // [M][ldc]: octet<1> writes GELU(C) there, octet<2> multiplies the result by GELU'(aux) (bf16 C only)
-  float* colsum;           // direct-load kernel, octet<2> only, or null: [tiles_m * 2][N] partial column sums of the result
-  // eight consecutive columns n..n+7 of row m (n multiple of 8); cols = how many are inside the matrix
-  // pre (when have_pre): the eight residual (or, ACT 2, pre-activation) values of this octet, fetched by the caller
-  template <int ACT = 0>
-  __device__ __forceinline__ void octet(int m, int n, int cols, const float4& lo, const float4& hi,
-                                        bool have_pre = false, u32x4 pre = u32x4{0, 0, 0, 0}) const {
-    float unused[8];
-    octet<ACT>(m, n, cols, lo, hi, have_pre, pre, false, unused);
-  }
-  // do_sum (octet<2>, full octets): the eight results are also added to sum8
-  template <int ACT>
-  __device__ __forceinline__ void octet(int m, int n, int cols, const float4& lo, const float4& hi, bool have_pre, u32x4 pre,
-                                        bool do_sum, float (&sum8)[8]) const {
-    float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    const size_t at = (size_t)m * ldc + n;
-    if (cols == 8 && (ldc & 7) == 0) {
-      if (bias) {
-        u32x4 b = *(const u32x4*)(bias + n);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(b[e] << 16); v[2 * e + 1] += __uint_as_float(b[e] & 0xffff0000u); }
-      }
-      if (out_f32) {
-        float4* c = (float4*)((float*)C + at);
-        float4 o0 = make_float4(v[0], v[1], v[2], v[3]), o1 = make_float4(v[4], v[5], v[6], v[7]);
-        if (accumulate) {
-          float4 p0 = c[0], p1 = c[1];
-          o0.x += p0.x; o0.y += p0.y; o0.z += p0.z; o0.w += p0.w;
-          o1.x += p1.x; o1.y += p1.y; o1.z += p1.z; o1.w += p1.w;
-        }
-        c[0] = o0;
-        c[1] = o1;
-      } else {
-        if (residual) {
-          u32x4 r = have_pre ? pre : *(const u32x4*)(residual + at);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(r[e] << 16); v[2 * e + 1] += __uint_as_float(r[e] & 0xffff0000u); }
-        }
-        if (ACT == 2) {
-          u32x4 r = have_pre ? pre : *(const u32x4*)(aux + at);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[2 * e] *= gelu_grad_f(__uint_as_float(r[e] << 16));
-            v[2 * e + 1] *= gelu_grad_f(__uint_as_float(r[e] & 0xffff0000u));
-          }
-          if (do_sum) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sum8[e] += v[e];
-          }
-        }
-        u32x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = pack2(v[2 * e], v[2 * e + 1]);
-        *(u32x4*)((bf16_t*)C + at) = o;
-        if (ACT == 1) {   // the activation of the value as stored (what a separate pass over C would compute)
-          u32x4 a2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            a2[e] = pack2(gelu_f(__uint_as_float(o[e] << 16)), gelu_f(__uint_as_float(o[e] & 0xffff0000u)));
-          *(u32x4*)(aux + at) = a2;
-        }
-      }
-    } else {
-      for (int e = 0; e < cols; ++e) {
-        float x = v[e];
-        if (bias) x += bf2f(bias[n + e]);
-        if (out_f32) {
-          float* c = (float*)C;
-          c[at + e] = accumulate ? c[at + e] + x : x;
-        } else {
-          if (residual) x += bf2f(residual[at + e]);
-          if (ACT == 2) x *= gelu_grad_f(bf2f(aux[at + e]));
-          const bf16_t stored = f2bf(x);
-          ((bf16_t*)C)[at + e] = stored;
-          if (ACT == 1) aux[at + e] = f2bf(gelu_f(bf2f(stored)));
-        }
-      }
-    }
-  }
-};
 
 // Persistent kernel: each workgroup walks the work items (output tile x k-split) of its
 // XCD's range.  Per item: the first k-tile is already in registers (loaded while the previous
@@ -784,6 +699,53 @@ __global__ __launch_bounds__(256) void splitk_reduce_sliced_kernel(const float* 
   }
 }
 
+// Both reductions for rows of whole octets: 32 bytes of a partial per thread, four partials in flight, the epilogue's
+// vector form.  SLICES threads share an octet (1, or 8 from 16 splits on); the orders of the sums are those above.
+// With the scalar form -> with this one, product and reduction: 3000 x 2344 x 1416 in 2 ranges 63 -> 54 us,
+// 1024 x 256 x 1024 in 4 ranges 13.2 -> 11.0 us.
+template <int SLICES>
+__global__ __launch_bounds__(256) void splitk_reduce_octets_kernel(const float* __restrict__ partial, int splits, size_t mn,
+                                                                    GemmEpilogue ep, int N) {
+  constexpr int PER = 256 / SLICES;
+  __shared__ float4 red[SLICES > 1 ? SLICES : 1][PER][2];
+  const int q = threadIdx.x % PER, slice = threadIdx.x / PER;
+  const unsigned o = blockIdx.x * PER + q;
+  const bool in = (size_t)o * 8 < mn;
+  float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+  auto add = [](float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; };
+  if (in) {
+    const float* src = partial + (size_t)o * 8;
+    int s = slice;
+    for (; s + 3 * SLICES < splits; s += 4 * SLICES) {
+      float4 a[4], b[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4* p = (const float4*)(src + (size_t)(s + k * SLICES) * mn);
+        a[k] = p[0];
+        b[k] = p[1];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) { add(lo, a[k]); add(hi, b[k]); }
+    }
+    for (; s < splits; s += SLICES) {
+      const float4* p = (const float4*)(src + (size_t)s * mn);
+      add(lo, p[0]);
+      add(hi, p[1]);
+    }
+  }
+  if constexpr (SLICES > 1) {
+    red[slice][q][0] = lo;
+    red[slice][q][1] = hi;
+    __syncthreads();
+    if (slice != 0) return;
+    for (int k = 1; k < SLICES; ++k) { add(lo, red[k][q][0]); add(hi, red[k][q][1]); }
+  }
+  if (in) {
+    const unsigned per_row = (unsigned)N / 8u, m = o / per_row;
+    ep.octet<0>((int)m, (int)(o - m * per_row) * 8, 8, lo, hi);
+  }
+}
+
 static int g_cus = 0;
 static int compute_units() {
   if (!g_cus) {
@@ -793,6 +755,22 @@ static int compute_units() {
     if (g_cus <= 0) g_cus = 256;
   }
   return g_cus;
+}
+
+static void launch_reduce(const GemmArgs& g, const GemmEpilogue& ep, int splits, hipStream_t s) {
+  const size_t mn = (size_t)g.M * g.N;
+  if (g.N % 8 == 0 && mn < (1ull << 32)) {
+    const unsigned octets = (unsigned)(mn / 8);
+    if (splits >= 16)
+      hipLaunchKernelGGL(splitk_reduce_octets_kernel<8>, dim3((octets + 31) / 32), dim3(256), 0, s, (const float*)g.ws, splits, mn, ep, g.N);
+    else
+      hipLaunchKernelGGL(splitk_reduce_octets_kernel<1>, dim3((octets + 255) / 256), dim3(256), 0, s, (const float*)g.ws, splits, mn, ep, g.N);
+  } else if (splits >= 16)
+    hipLaunchKernelGGL(splitk_reduce_sliced_kernel, dim3((unsigned)((mn / 4 + 31) / 32 + 1)), dim3(256), 0, s,
+                       (const float*)g.ws, splits, mn, ep, g.N);
+  else
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((mn / 4 + 255) / 256 + 1)), dim3(256), 0, s,
+                       (const float*)g.ws, splits, mn, ep, g.N);
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, bool EDGE>
@@ -849,20 +827,100 @@ static void launch_direct(const GemmArgs& g, hipStream_t s, dim3 grid, dim3 bloc
   }
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, bool CONVS = false>
-static int launch_cfg(const GemmArgs& g, hipStream_t s) {
+// How a product is cut up: tile and number of ranges of the reduction
+struct GemmPlan {
+  int tile;     // 256: the direct-load kernel above, 128: gemm_ring.hip
+  int splits;
+  bool deep;    // 128: four stages
+};
+
+// The cheaper of the two tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
+// item for every place on the chip (one per compute unit with the 256 tile, two with the 128 tile); a k-tile of 64 costs,
+// in a full round and with the places of the last one partly empty, what was measured on products from 64 x 1000 x 2048
+// to 8192 x 3072 x 3072 and on convolutions (all within 15 %): 1.5 us down to 1.25 us for the large tile (2.0 to 1.4 where
+// its first operand is gathered), 1.0 us for two workgroups of the small tile per compute unit, 0.45 to 0.6 us for one.
+// Dividing the reduction costs a launch and two trips of M x N floats per range through memory at 5 TB/s.
+//   4096 x 1024 x 1024: 256 tile, 8 ranges 46.7 us -> 128 tile 13.9 us     3072 x 3072 x 8192: 275 -> 181 us
+//   3000 x 2344 x 1416: 58.5 -> 34 us     4096 x 4096 x 4096: 108 us with the 256 tile, 132 us with the 128 tile
+static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may_split) {
+  const int cus = compute_units(), k_tiles = (g.K + 63) / 64;
+  const double full256 = g.conv_mode == 1 ? 2.0 : 1.5, alone256 = g.conv_mode == 1 ? 1.4 : 1.25;
+  const double ragged = g.M % 256 || g.N % 256 || g.K % 64 ? 1.05 : 1.0;
+  GemmPlan best{0, 1, false};
+  double best_us = 1e30;
+  const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
+  for (int tile = 128; tile <= 256; tile += 128) {
+    if (!(tile == 256 ? large : small)) continue;
+    const long tiles = (long)((g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile);
+    for (int sp = 1; sp <= max_splits; ++sp) {
+      if (sp > 1 && ((uint64_t)sp * g.M * g.N * sizeof(float) > g.ws_bytes || tiles * sp > 8l * cus)) break;
+      const long items = tiles * sp, places = tile == 256 ? cus : 2l * cus, full = items / places, rest = items % places;
+      const int kt = (k_tiles + sp - 1) / sp;
+      const long rounds = full + (rest ? 1 : 0);
+      double us;
+      if (tile == 256) {
+        const double f = (double)rest / cus;
+        us = 9.0 + 4.0 * (rounds - 1) + ragged * kt * (full * full256 + (rest ? alone256 + (full256 - alone256) * f : 0.0));
+      } else {
+        const double f = (double)rest / cus;   // workgroups per compute unit in the last round
+        us = 5.5 + 2.5 * (rounds - 1) + kt * (full * 1.0 + (!rest ? 0.0 : f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0)));
+      }
+      if (sp > 1) us += 3.5 + (double)sp * g.M * g.N * 8.0 / 5e6;
+      // (four stages instead of two: 1000 x 1000 x 4000 in 33 us instead of 47, one k-tile in flight per workgroup having
+      // nobody to hide behind; below 24 k-tiles per item there is no difference)
+      if (us < best_us) { best_us = us; best = GemmPlan{tile, sp, items <= cus && kt >= 24}; }
+    }
+  }
+  return best;
+}
+
+static GemmEpilogue epilogue_of(const GemmArgs& g) {
+  return GemmEpilogue{g.C, g.bias, g.residual, g.ldc, g.out_f32, g.accumulate, (bf16_t*)g.aux, nullptr};
+}
+// k per range: whole k-tiles, and the number of ranges that are then not empty
+static int range_length(int K, int& splits) {
+  const int len = ((K + splits - 1) / splits + 63) / 64 * 64;
+  splits = (K + len - 1) / len;
+  return len;
+}
+static int finish(const GemmArgs& g, const GemmEpilogue& ep, int splits, hipStream_t s) {
+  if (splits > 1) launch_reduce(g, ep, splits, s);
+  return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
+}
+
+// The direct-load kernel with the 256 x 256 or (64 output channels) 256 x 64 tile; eligibility was checked by the caller.
+template <int BN, int WGM, int WGN>
+static int launch_large(const GemmArgs& g, int splits, hipStream_t s) {
+  constexpr int BM = 256, BK = 64;
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const int tiles = tiles_m * tiles_n;
-  // workgroups that run at once: the small tile leaves LDS and registers for two per compute unit
-  const int cus = compute_units() * ((BM <= 128 && BN <= 128) || (BM == 256 && BN == 64) ? 2 : 1);
-  // split the reduction when the tiles alone cannot fill the chip (weight gradients:
-  // small M x N, K = tokens); partial sums are reduced in a fixed order afterwards
+  const int k_per_split = range_length(g.K, splits);
+  GemmEpilogue ep = epilogue_of(g);
+  if (g.act == 2 && g.colsum_partial && splits == 1 && g.ldc == g.N) {
+    ep.colsum = g.colsum_partial;
+    if (g.colsum_rows) *g.colsum_rows = tiles_m * WGM;
+  }
+  // a multiple of 8 workgroups, at most what runs at once: the kernel deals work items out per XCD
+  const int cus = compute_units() * (BN == 64 ? 2 : 1);
+  const dim3 grid(std::min((tiles_m * tiles_n * splits + 7) / 8 * 8, std::max(8, cus / 8 * 8))), block(WGM * WGN * 64);
+  if (!g.conv_mode && g.M % BM == 0 && g.N % BN == 0 && g.K % BK == 0)
+    launch_direct<BM, BN, BK, WGM, WGN, false>(g, s, grid, block, tiles_m, tiles_n, splits, k_per_split, ep);
+  else
+    launch_direct<BM, BN, BK, WGM, WGN, true>(g, s, grid, block, tiles_m, tiles_n, splits, k_per_split, ep);
+  return finish(g, ep, splits, s);
+}
+
+// Operands whose sizes or alignment do not allow 16-byte pieces (4-element runs), and gradients of convolutions with a
+// stride above 2: tiles go through registers.
+static int launch_general(const GemmArgs& g, hipStream_t s) {
+  constexpr int BM = 128, BN = 128, BK = 64, WGM = 2, WGN = 2;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, tiles = tiles_m * tiles_n;
+  const int cus = compute_units() * 2;   // two workgroups per compute unit
+  // split the reduction when the tiles alone cannot fill the chip (weight gradients: small M x N, K = tokens); partial
+  // sums are reduced in a fixed order afterwards
   int splits = 1;
   if (g.ws && g.ldc == g.N && tiles < cus && !g.act) {
-    // the split count that best fills whole rounds of the chip, fewer splits preferred: every
-    // split writes and re-reads an M x N fp32 partial, which is weighed against the operand
-    // bytes of the whole product (a skinny weight gradient with a very long reduction takes
-    // hundreds of splits, a square one a handful)
+    // the split count that best fills whole rounds of the chip, fewer splits preferred: every split writes and re-reads
+    // an M x N fp32 partial, which is weighed against the operand bytes of the whole product
     const int max_splits = std::min(256, std::max(1, g.K / (4 * BK)));
     const double per_split = std::min(0.01, 0.5 * (8.0 * g.M * g.N) / (2.0 * ((double)g.M + g.N) * g.K));
     double best = -1.0;
@@ -873,68 +931,81 @@ static int launch_cfg(const GemmArgs& g, hipStream_t s) {
       if (score > best) { best = score; splits = sp; }
     }
   }
-  int k_per_split = (g.K + splits - 1) / splits;
-  k_per_split = (k_per_split + BK - 1) / BK * BK;
-  splits = (g.K + k_per_split - 1) / k_per_split;
+  const int k_per_split = range_length(g.K, splits);
   const size_t lds = (size_t)2 * (BM + BN) * (BK + LDS_PAD) * sizeof(bf16_t);
-  GemmEpilogue ep{g.C, g.bias, g.residual, g.ldc, g.out_f32, g.accumulate, (bf16_t*)g.aux, nullptr};
-  // a multiple of 8 workgroups: the kernel deals work items out per XCD
-  dim3 grid(std::min((tiles * splits + 7) / 8 * 8, std::max(8, cus / 8 * 8))), block(WGM * WGN * 64);
-#define KARMA_GEMM_LAUNCH(AK, BKC, CV, ACT)                                                                 \
+  GemmEpilogue ep = epilogue_of(g);
+  const dim3 grid(std::min((tiles * splits + 7) / 8 * 8, std::max(8, cus / 8 * 8))), block(WGM * WGN * 64);
+#define KARMA_GEMM_LAUNCH(AK, BKC, CV, ACT)                                                             \
   do {                                                                                                  \
     auto kern = gemm_bf16_kernel<BM, BN, BK, WGM, WGN, AK, BKC, CV, ACT>;                               \
     if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     hipLaunchKernelGGL(kern, grid, block, lds, s, g.A, g.B, g.M, g.N, g.K, g.lda, g.ldb, tiles_m, tiles_n, splits,  \
                        k_per_split, ep, (float*)g.ws, g.conv);                                          \
   } while (0)
-  // whole tiles, 16-byte aligned rows: the direct-to-LDS kernel
-  bool direct = false, whole = false;
-  if constexpr (CONVS && BM == 256) {
-    // a gathered first operand through the direct-to-LDS kernel (eligibility was checked by the caller)
-    launch_direct<BM, BN, BK, WGM, WGN, true>(g, s, grid, block, tiles_m, tiles_n, splits, k_per_split, ep);
-  } else {
-  if (!CONVS && BM == 256 && BN == 256 && BK == 64 && WGM == 2 && WGN == 4) {
-    // (a lane's piece offsets inside a tile are kept as 32-bit byte counts)
-    direct = g.M % 8 == 0 && g.N % 8 == 0 && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
-             ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0 && g.ldc % 8 == 0 &&
-             (uint64_t)g.lda * 2 * 256 < (1ull << 31) && (uint64_t)g.ldb * 2 * 256 < (1ull << 31) &&
-             // tiles that hang over the matrix pay for a whole tile: worth it when most of the work lies inside
-             g.M >= BM && g.N >= BN && g.K >= 2 * BK;
-    whole = g.M % BM == 0 && g.N % BN == 0 && g.K % BK == 0;
-  }
-  if (direct) {
-    if (g.act == 2 && g.colsum_partial && splits == 1 && g.ldc == g.N) {
-      ep.colsum = g.colsum_partial;
-      if (g.colsum_rows) *g.colsum_rows = tiles_m * WGM;
-    }
-    if (whole) launch_direct<BM, BN, BK, WGM, WGN, false>(g, s, grid, block, tiles_m, tiles_n, splits, k_per_split, ep);
-    else launch_direct<BM, BN, BK, WGM, WGN, true>(g, s, grid, block, tiles_m, tiles_n, splits, k_per_split, ep);
-  } else if (CONVS) {   // the convolution variants exist for one tile shape only
-    if (g.conv_mode == 1) KARMA_GEMM_LAUNCH(true, true, (CONVS ? 1 : 0), 0);
-    else KARMA_GEMM_LAUNCH(false, false, (CONVS ? 2 : 0), 0);
-  } else if (g.act == 1) KARMA_GEMM_LAUNCH(true, true, 0, 1);
+  if (g.conv_mode == 1) KARMA_GEMM_LAUNCH(true, true, 1, 0);
+  else if (g.conv_mode == 2) KARMA_GEMM_LAUNCH(false, false, 2, 0);
+  else if (g.act == 1) KARMA_GEMM_LAUNCH(true, true, 0, 1);
   else if (g.act == 2) KARMA_GEMM_LAUNCH(true, false, 0, 2);
   else if (g.a_kc && g.b_kc) KARMA_GEMM_LAUNCH(true, true, 0, 0);
   else if (g.a_kc && !g.b_kc) KARMA_GEMM_LAUNCH(true, false, 0, 0);
   else if (!g.a_kc && g.b_kc) KARMA_GEMM_LAUNCH(false, true, 0, 0);
   else KARMA_GEMM_LAUNCH(false, false, 0, 0);
-  }
 #undef KARMA_GEMM_LAUNCH
-  if (splits > 1) {
-    const size_t mn = (size_t)g.M * g.N;
-    if (splits >= 16)
-      hipLaunchKernelGGL(splitk_reduce_sliced_kernel, dim3((unsigned)((mn / 4 + 31) / 32 + 1)), dim3(256), 0, s,
-                         (const float*)g.ws, splits, mn, ep, g.N);
-    else
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((mn / 4 + 255) / 256 + 1)), dim3(256), 0, s,
-                         (const float*)g.ws, splits, mn, ep, g.N);
-  }
-  return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
+  return finish(g, ep, splits, s);
 }
 
 thread_local GemmTimer* g_gemm_timer = nullptr;
 
 static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s);
+
+// The 128 x 128 tile: geometry of the gathered forms, then the launch
+static int launch_ring(const GemmArgs& g, int splits, bool deep, hipStream_t s) {
+  const int k_per_split = range_length(g.K, splits);
+  GemmEpilogue ep = epilogue_of(g);
+  const int tiles_m = (g.M + RING_TILE - 1) / RING_TILE;
+  // (two rows of sums per tile: not where that is more than the caller's room of one per 64 rows)
+  if (g.act == 2 && g.colsum_partial && splits == 1 && g.ldc == g.N && g.N % 8 == 0 && 2 * tiles_m <= (g.M + 63) / 64) {
+    ep.colsum = g.colsum_partial;
+    if (g.colsum_rows) *g.colsum_rows = 2 * tiles_m;
+  }
+  RingConv rc{};
+  if (g.conv_mode) {
+    const ConvGather& cg = g.conv;
+    auto magic = [](int d) { return d > 1 ? (unsigned)((1ull << 32) / (unsigned)d + 1) : 0u; };
+    rc.magic_c = magic(cg.C);
+    rc.out_stride = 1;
+    if (cg.transposed && cg.stride == 2) {
+      const int images = g.M / (cg.Ho * cg.Wo);
+      unsigned at = 0;
+      rc.out_stride = 2;
+      rc.oh = cg.Ho;
+      rc.ow = cg.Wo;
+      for (int oy = 0; oy < 2; ++oy)
+        for (int ox = 0; ox < 2; ++ox) {
+          const DgradTaps ty = dgrad_taps(cg.R, cg.pad, oy), tx = dgrad_taps(cg.S, cg.pad, ox);
+          const int rows = (cg.Ho - oy + 1) / 2, cols = (cg.Wo - ox + 1) / 2, k = ty.count * tx.count * cg.C;
+          if (rows > 0 && cols > 0) {
+            RingPhase& p = rc.p[rc.phases++];
+            p.cg = ConvGather{cg.H, cg.W, cg.C, rows, cols, ty.count, tx.count, 1, 0, 1};
+            p.pad_y = ty.shift;
+            p.pad_x = tx.shift;
+            p.M = images * rows * cols;
+            p.K = k;
+            p.b_off = at;
+            p.magic_s = magic(tx.count);
+            p.oy = oy;
+            p.ox = ox;
+          }
+          at += (unsigned)k * (unsigned)g.N;
+        }
+    } else {
+      rc.phases = 1;
+      rc.p[0] = RingPhase{cg, g.M, g.K, 0u, magic(cg.S), 0, 0, cg.pad, cg.pad};
+    }
+  }
+  const int st = gemm_ring_launch(g, ep, splits, k_per_split, deep, g.conv_mode ? &rc : nullptr, s);
+  return st == KARMA_OK ? finish(g, ep, splits, s) : st;
+}
 
 int gemm_bf16(const GemmArgs& g, hipStream_t s) {
   GemmTimer* t = g_gemm_timer;
@@ -974,40 +1045,47 @@ static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
     // the gathered operand's index ranges must be what the convolution spans
     const long pixels = (long)cg.Ho * cg.Wo, taps_c = (long)cg.R * cg.S * cg.C;
     if (g.conv_mode == 1 ? (g.M % pixels || g.K != taps_c) : (g.K % pixels || g.N != taps_c)) return KARMA_E_INVAL;
-    // Large products with a gathered first operand (forward and input gradient) take the direct-to-LDS kernel
-    // with its 256 x 256 tile: worth it from 128 output channels on (below that most of the tile is empty).
-    // Its piece offsets are 32-bit byte counts and its index arithmetic assumes strides 1 and 2.
-    const uint64_t gathered_bytes = (uint64_t)(g.M / pixels) * cg.H * cg.W * cg.C * 2;
-    const long tiles256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);   // enough of the large tiles to fill the chip
-    if (g.conv_mode == 1 && g.N >= 128 && tiles256 >= 192 && g.K >= 128 && g.N % 8 == 0 && g.ldc % 8 == 0 && cg.stride <= 2 &&
-        cg.H * cg.stride + cg.pad + 64 < 1024 && cg.W * cg.stride + cg.pad + 64 < 1024 && cg.Ho + cg.pad + 64 < 1024 &&
-        cg.Wo + cg.pad + 64 < 1024 && g.M / pixels < 4095 && gathered_bytes < (1ull << 32) && (uint64_t)g.K * cg.C < (1ull << 31) &&
-        ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0 && (uint64_t)g.ldb * 2 * 256 < (1ull << 31))
-      return launch_cfg<256, 256, 64, 2, 4, true>(g, s);
-    // The same with 64 output channels (the first stage of the bottleneck network, the full-resolution level of the
-    // fully convolutional one): a 256 x 64 tile, eight wavefronts of 64 x 32, two workgroups per compute unit (a
-    // k-tile of this shape carries 16 MFMAs per wavefront, less than its loads' round trip: the second workgroup
-    // multiplies while the first one waits)
-    if (g.conv_mode == 1 && g.N == 64 && (g.M + 255) / 256 >= 384 && g.K >= 128 && g.ldc % 8 == 0 && cg.stride <= 2 &&
-        cg.H * cg.stride + cg.pad + 64 < 1024 && cg.W * cg.stride + cg.pad + 64 < 1024 && cg.Ho + cg.pad + 64 < 1024 &&
-        cg.Wo + cg.pad + 64 < 1024 && g.M / pixels < 4095 && gathered_bytes < (1ull << 32) && (uint64_t)g.K * cg.C < (1ull << 31) &&
-        ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0 && (uint64_t)g.ldb * 2 * 256 < (1ull << 31))
-      return launch_cfg<256, 64, 64, 4, 2, true>(g, s);
-    // The weight gradient (second operand gathered, reduction over the pixels): few output tiles and a very long
-    // reduction, which the split fills the chip with; worth the large tile from 64 x 512 results on (with 64 output
-    // channels three quarters of the tile's rows are zeros, and it is still faster than the small tile's gather).
-    // (pixels * Wo < 2^32: the reciprocal multiplication by magic_w = 2^32 / Wo + 1 is exact for every n with
-    // n * (magic_w * Wo - 2^32) < 2^32, and that excess is at most Wo)
-    if (g.conv_mode == 2 && g.M >= 64 && g.N >= 512 && g.K >= 4096 && g.M % 8 == 0 && g.lda % 8 == 0 && g.ldc % 8 == 0 &&
-        g.ws != nullptr && cg.H * cg.stride + cg.pad + 64 < 1024 && cg.W * cg.stride + cg.pad + 64 < 1024 &&
-        (uint64_t)(g.K / pixels) * cg.H * cg.W * cg.C * 2 < (1ull << 32) && (uint64_t)g.N * cg.C < (1ull << 31) &&
-        (uint64_t)pixels * cg.Wo < (1ull << 32) && g.K < (1 << 24) && ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0 &&
-        (uint64_t)g.lda * 2 * 256 < (1ull << 31))
-      return launch_cfg<256, 256, 64, 2, 4, true>(g, s);
-    return launch_cfg<128, 128, 64, 2, 2, true>(g, s);
+    if (cg.phased && (g.conv_mode != 1 || !cg.transposed || cg.stride != 2 || !gemm_ring_takes(g))) return KARMA_E_INVAL;
   }
-  if (g.M > 128 && g.N > 128) return launch_cfg<256, 256, 64, 2, 4>(g, s);
-  return launch_cfg<128, 128, 64, 2, 2>(g, s);
+  const bool small = gemm_ring_takes(g);
+  if (g.conv_mode && g.conv.phased) return launch_ring(g, 1, false, s);
+  const bool may_split = g.ws && g.ldc == g.N && !g.act;
+  bool large;
+  if (g.conv_mode) {
+    const ConvGather& cg = g.conv;
+    const long pixels = (long)cg.Ho * cg.Wo;
+    // What the direct-load kernel's gathers assume: piece offsets are 32-bit byte counts, packed coordinates ten bits wide,
+    // strides 1 and 2; (tap, channel) from reciprocals.  A gathered second operand: pixels * Wo < 2^32, the
+    // reciprocal multiplication by magic_w = 2^32 / Wo + 1 being exact for every n with n * (magic_w * Wo - 2^32) < 2^32,
+    // and that excess is at most Wo.
+    const uint64_t gathered_bytes = (uint64_t)((g.conv_mode == 1 ? g.M : g.K) / pixels) * cg.H * cg.W * cg.C * 2;
+    large = g.ldc % 8 == 0 && cg.H * cg.stride + cg.pad + 64 < 1024 && cg.W * cg.stride + cg.pad + 64 < 1024 &&
+            gathered_bytes < (1ull << 32) && ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0 &&
+            (cg.S > 1 || cg.R == 1) && (cg.Wo > 1 || cg.Ho == 1);   // (no reciprocal of 1 in 32 bits)
+    if (g.conv_mode == 1)
+      large = large && g.K >= 128 && g.N % 8 == 0 && cg.stride <= 2 && cg.Ho + cg.pad + 64 < 1024 && cg.Wo + cg.pad + 64 < 1024 &&
+              g.M / pixels < 4095 && (uint64_t)g.K * cg.C < (1ull << 31) && (uint64_t)g.ldb * 2 * 256 < (1ull << 31);
+    else
+      large = large && g.M >= 64 && g.N >= 512 && g.K >= 4096 && g.M % 8 == 0 && g.lda % 8 == 0 && g.ws != nullptr &&
+              (uint64_t)g.N * cg.C < (1ull << 31) && (uint64_t)pixels * cg.Wo < (1ull << 32) && g.K < (1 << 24) &&
+              (uint64_t)g.lda * 2 * 256 < (1ull << 31);
+    // 64 output channels (the first stage of the bottleneck network, the full-resolution level of the fully convolutional
+    // one): a 256 x 64 tile, eight wavefronts of 64 x 32, two workgroups per compute unit (a k-tile of this shape carries
+    // 16 MFMAs per wavefront, less than its loads' round trip: the second workgroup multiplies while the first one waits).
+    // 8 x 256 x 256 pixels, 3 x 3 x 64: 84 us, 99 us with half of a 128 x 128 tile empty.
+    if (g.conv_mode == 1 && large && g.N == 64 && (g.M + 255) / 256 >= 384) return launch_large<64, 4, 2>(g, 1, s);
+    // below 128 output channels most of the large tile is empty
+    if (g.conv_mode == 1 && g.N < 128) large = false;
+  } else {
+    // (a lane's piece offsets inside a tile are kept as 32-bit byte counts; tiles that hang over the matrix pay for a
+    // whole tile)
+    large = g.M % 8 == 0 && g.N % 8 == 0 && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && ((uintptr_t)g.A % 16) == 0 &&
+            ((uintptr_t)g.B % 16) == 0 && g.ldc % 8 == 0 && (uint64_t)g.lda * 2 * 256 < (1ull << 31) &&
+            (uint64_t)g.ldb * 2 * 256 < (1ull << 31) && g.M >= 256 && g.N >= 256 && g.K >= 128;
+  }
+  if (!large && !small) return launch_general(g, s);
+  const GemmPlan p = plan_product(g, large, small, may_split);
+  return p.tile == 256 ? launch_large<256, 2, 4>(g, p.splits, s) : launch_ring(g, p.splits, p.deep, s);
 }
 
 }  // namespace karma

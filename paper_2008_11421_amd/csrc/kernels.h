@@ -28,7 +28,17 @@ int mse_f32(const float* y, const float* t, float* dy, float* loss, float* parti
 //   the gradient of a strided convolution w.r.t. its input); positions outside count as zero.
 struct ConvGather {
   int H, W, C, Ho, Wo, R, S, stride, pad, transposed;
+  // transposed, stride 2: the weights are laid out by the parity of the output pixel, [oy][ox][N][taps of that parity][C]
+  // (dgrad_taps, oy and ox from 0 to 1), and each parity is a stride-1 product over its own taps
+  int phased;
 };
+// The taps that reach output pixels of parity o (in one direction) of a stride-2 convolution's input gradient:
+// first, first + 2, ...; pixel 2 i + o meets the j-th of them at gathered pixel i + shift - j.
+struct DgradTaps { int first, count, shift; };
+inline __host__ __device__ DgradTaps dgrad_taps(int taps, int pad, int o) {
+  const int first = (o + pad) & 1;
+  return DgradTaps{first, taps > first ? (taps - first + 1) / 2 : 0, (o + pad - first) / 2};
+}
 
 // C[M,N] = sum_k A(m,k) B(n,k) (+ bias[n]) (+ residual[m,n]).  a_kc: A is [M][lda] with k
 // contiguous, else [K][lda] with m contiguous; same for B with n.
