@@ -76,3 +76,23 @@ def test_stride_2_gradient_by_parity(g, n, h, w, ci, co, r, pad):
         ref = dxo + (add if with_add else 0)
         assert g.rel_l2(back(dx), ref) <= TOL or not np.any(ref), with_add
         assert np.all(np.abs(back(dx) - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-4 * max(np.abs(ref).max(), 1e-30)), with_add
+
+
+# below, at and past a tile of 16 and a wavefront's 16 and 256 k; dx over dy, as a caller may place it
+@pytest.mark.parametrize("m,n,k", [(1, 15, 17), (16, 16, 16), (17, 64, 256), (33, 260, 260), (8, 516, 516)])
+def test_linear_relu_backward_in_place(g, m, n, k):
+    import torch
+    x, w, dy, z = (si.normal(20 + i, s).astype(np.float32) for i, s in enumerate([(m, k), (n, k), (m, n), (m, n)]))
+    dzo = dy.astype(np.float64) * (z > 0)
+    wants = dzo @ w.astype(np.float64), dzo.T @ x.astype(np.float64), dzo.sum(axis=0)
+    for in_place in (False, True):
+        xd, wd, zd = (g.dev(a, torch.float32) for a in (x, w, z))
+        buf = torch.zeros(m * max(n, k), device="cuda")
+        buf[:m * n] = g.dev(dy, torch.float32).reshape(-1)
+        dx = buf if in_place else torch.empty(m * k, device="cuda")
+        dz = torch.empty(m, n, device="cuda"); dw = torch.empty(n, k, device="cuda"); db = torch.empty(n, device="cuda")
+        g.call(K.lib().karma_k_linear_relu_bwd_f32, g.ptr(xd), g.ptr(wd), g.ptr(zd), g.ptr(buf), g.ptr(dz), g.ptr(dx), g.ptr(dw),
+               g.ptr(db), m, n, k, g.stream_ptr())
+        assert np.array_equal(dz.cpu().numpy(), dzo.astype(np.float32))
+        for got, want in zip((dx[:m * k].reshape(m, k), dw, db), wants):     # fp32 sums of up to 516 terms
+            assert g.rel_l2(got.cpu().numpy(), want) <= 1e-5 or not np.any(want)
