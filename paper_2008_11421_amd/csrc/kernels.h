@@ -141,7 +141,7 @@ int avgpool_bwd(const bf16_t* dy, bf16_t* dx, int n, int hw, int c, hipStream_t 
 int optim_update_dev(int kind, float* w, float* m, float* v, const void* g, bool g_bf16, size_t n, float lr, float beta1,
                      float beta2, float eps, uint64_t step, void* out, bool out_bf16, hipStream_t s);
 
-// ---- fused causal attention (attention.hip); seq multiple of 128, d in {64, 128}
+// ---- fused causal attention (attention.hip); seq multiple of 128, d in {64, 128, 152}
 int attention_fwd(const bf16_t* qkv, bf16_t* ctx, float* lse, int batch, int seq, int heads, int d, hipStream_t s);
 int attention_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta,
                   bf16_t* dqkv, int batch, int seq, int heads, int d, hipStream_t s, float* colsum_partial = nullptr,
