@@ -212,6 +212,138 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
   }
 }
 
+// The same in two launches, rows and columns apart.  dx: a wavefront per row, which holds the row's vectors as they came
+// (no running column sums beside them, so that wide rows do not spill and every row has a wavefront of its own).
+template <int LN_MAXV>
+__global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                                  const float* __restrict__ stats, const bf16_t* __restrict__ g,
+                                                                  const bf16_t* __restrict__ add, bf16_t* __restrict__ dx, int rows,
+                                                                  int h) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const int nv = h / 8;
+  const size_t at = (size_t)row * h;
+  u32x4 rx[LN_MAXV], rd[LN_MAXV], rg[LN_MAXV], ra[LN_MAXV];
+#pragma unroll
+  for (int i = 0; i < LN_MAXV; ++i) {
+    const int c = lane + i * 64;
+    if (c < nv) {
+      rx[i] = *(const u32x4*)(x + at + c * 8);
+      rd[i] = *(const u32x4*)(dy + at + c * 8);
+      rg[i] = *(const u32x4*)(g + c * 8);
+      if (add) ra[i] = *(const u32x4*)(add + at + c * 8);
+    }
+  }
+  const float mean = stats[2 * row], rstd = stats[2 * row + 1];
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int i = 0; i < LN_MAXV; ++i) {
+    if (lane + i * 64 < nv) {
+      float xv[8], dv[8], gv[8];
+      unpack8(rx[i], xv);
+      unpack8(rd[i], dv);
+      unpack8(rg[i], gv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float t = dv[e] * gv[e];
+        s1 += t;
+        s2 = fmaf(t, (xv[e] - mean) * rstd, s2);
+      }
+    }
+  }
+  const float m1 = wave_sum(s1) / (float)h, m2 = wave_sum(s2) / (float)h;
+#pragma unroll
+  for (int i = 0; i < LN_MAXV; ++i) {
+    const int c = lane + i * 64;
+    if (c < nv) {
+      float xv[8], dv[8], gv[8], av[8], o[8];
+      unpack8(rx[i], xv);
+      unpack8(rd[i], dv);
+      unpack8(rg[i], gv);
+      if (add) unpack8(ra[i], av);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        o[e] = rstd * (dv[e] * gv[e] - m1 - (xv[e] - mean) * rstd * m2);
+        if (add) o[e] += av[e];
+      }
+      *(u32x4*)(dx + at + c * 8) = pack8(o);
+    }
+  }
+}
+
+// Column sums: VC vector columns (8 channels each) times 256 / VC row lanes per workgroup, over a band of `band` rows;
+// the row lanes are added in ascending order.  One band: these are the results (out_*); otherwise one partial row of
+// NS * h per band, finished as those of the kernel above.
+template <int VC, bool ADDSUM>
+__global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                                  const float* __restrict__ stats, const bf16_t* __restrict__ add,
+                                                                  float* __restrict__ partial, float* __restrict__ dgamma,
+                                                                  float* __restrict__ dbeta, float* __restrict__ addsum, int rows,
+                                                                  int h, int band) {
+  constexpr int NS = ADDSUM ? 3 : 2, RL = 256 / VC, U = 4;
+  __shared__ float red[NS][RL][VC * 8];
+  const int vc = threadIdx.x % VC, rl = threadIdx.x / VC;
+  const int c8 = (blockIdx.x * VC + vc) * 8;
+  const int r0 = blockIdx.y * band, r1 = min(rows, r0 + band);
+  float sum[NS][8];
+#pragma unroll
+  for (int k = 0; k < NS; ++k)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[k][e] = 0.f;
+  if (c8 < h) {
+    for (int r = r0 + rl; r < r1; r += U * RL) {   // U rows in flight, added in ascending order
+      u32x4 qx[U], qd[U], qa[U];
+      float2 st[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int row = min(r + k * RL, rows - 1);
+        const size_t at = (size_t)row * h + c8;
+        qx[k] = *(const u32x4*)(x + at);
+        qd[k] = *(const u32x4*)(dy + at);
+        if (ADDSUM) qa[k] = *(const u32x4*)(add + at);
+        st[k] = *(const float2*)(stats + 2 * row);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        if (r + k * RL < r1) {
+          float xv[8], dv[8], av[8];
+          unpack8(qx[k], xv);
+          unpack8(qd[k], dv);
+          if (ADDSUM) unpack8(qa[k], av);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            sum[0][e] = fmaf(dv[e], (xv[e] - st[k].x) * st[k].y, sum[0][e]);
+            sum[1][e] += dv[e];
+            if (ADDSUM) sum[NS - 1][e] += av[e];
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NS; ++k)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[k][rl][vc * 8 + e] = sum[k][e];
+  __syncthreads();
+  // halve the row lanes until eight are left (a fixed order, neighbours first), then add those
+  for (int n = RL / 2; n >= 8; n /= 2) {
+    for (int t = threadIdx.x; t < NS * n * VC * 8; t += 256) {
+      const int k = t / (n * VC * 8), l = t / (VC * 8) % n, c = t % (VC * 8);
+      red[k][l][c] += red[k][l + n][c];
+    }
+    __syncthreads();
+  }
+  for (int t = threadIdx.x; t < NS * VC * 8; t += 256) {
+    const int k = t / (VC * 8), c = t % (VC * 8), col = blockIdx.x * VC * 8 + c;
+    if (col >= h) continue;
+    float v = red[k][0][c];
+#pragma unroll
+    for (int l = 1; l < (RL < 8 ? RL : 8); ++l) v += red[k][l][c];
+    if (gridDim.y == 1) (k == 0 ? dgamma : k == 1 ? dbeta : addsum)[col] = v;
+    else partial[((size_t)blockIdx.y * NS + k) * h + col] = v;
+  }
+}
+
 // out[c] = sum_p partial[p][c]: eight slices of threads sum every eighth partial, then the
 // slices are added in ascending order (a fixed association, so results are reproducible)
 // Columns split.. go to out_f32_b (two results that lie side by side in the partials, one launch).
@@ -559,33 +691,43 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
   if (h % 8 || h > 64 * 8 * LN_MAXV_LIMIT || rows <= 0 || (add_colsum && !add)) return KARMA_E_INVAL;
   const int parts = (rows + LNB_ROWS - 1) / LNB_ROWS;
   const int per_lane = (h / 8 + 63) / 64;
-  // rows too wide for three vectors per wavefront in LDS: the plain kernel, then a pass of its own over add
-  if (add_colsum && (size_t)4 * 3 * h * sizeof(float) > 160 * 1024) {
-    int st = layernorm_bwd(dy, x, stats, g, add, dx, dgamma, dbeta, partial_ws, rows, h, s, nullptr);
-    if (st) return st;
-    return colsum_bf16(add, add_colsum, partial_ws, rows, h, s);
-  }
   const int ns = add_colsum ? 3 : 2;
-  const size_t lds = (size_t)4 * ns * h * sizeof(float);
-#define KARMA_LN_BWD_K(V, AS)                                                                                    \
+  // One pass where its workgroups of 64 rows fill the chip with work enough to hide their start and end, and a row fits
+  // a wavefront's registers beside its column sums; else two launches.  us, one pass / two, with add_colsum: 1024 x 256
+  // 17.9 / 12.9, 1024 x 1024 28.6 / 13.0, 8192 x 1024 38 / 30, 8192 x 3072 84 / 75, 16384 x 256 23 / 19;
+  // 24576 x 512 38.3 / 40.0, 16384 x 1024 44 / 50, 16384 x 1536 58 / 74, 16384 x 3072 106 / 145, 32768 x 1024 66 / 92.
+  // 4096 x 4256 (spilled registers, and a third pass for the column sums of add): 295 + 20 / 64.
+  const bool one_pass = rows >= 16384 && (size_t)rows * h >= 12u << 20 && per_lane <= 6;
+  if (one_pass) {
+    const size_t lds = (size_t)4 * ns * h * sizeof(float);
+#define KARMA_LN_BWD(V)                                                                                          \
   do {                                                                                                           \
-    auto kern = layernorm_bwd_kernel<V, AS>;                                                                     \
+    auto kern = add_colsum ? layernorm_bwd_kernel<V, true> : layernorm_bwd_kernel<V, false>;                     \
     if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     hipLaunchKernelGGL(kern, dim3(parts), dim3(256), lds, s, dy, x, stats, g, add, dx, partial_ws, rows, h);      \
   } while (0)
-#define KARMA_LN_BWD(V)                   \
-  do {                                    \
-    if (add_colsum) KARMA_LN_BWD_K(V, true); \
-    else KARMA_LN_BWD_K(V, false);        \
-  } while (0)
-  if (per_lane <= 2) KARMA_LN_BWD(2);
-  else if (per_lane <= 4) KARMA_LN_BWD(4);
-  else if (per_lane <= 6) KARMA_LN_BWD(6);
-  else if (per_lane <= 9) KARMA_LN_BWD(9);
-  else KARMA_LN_BWD(12);
+    if (per_lane <= 2) KARMA_LN_BWD(2);
+    else if (per_lane <= 4) KARMA_LN_BWD(4);
+    else KARMA_LN_BWD(6);
 #undef KARMA_LN_BWD
-#undef KARMA_LN_BWD_K
-  launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
+    launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
+    return ok();
+  }
+  // The columns first: dx may replace dy or add.  Up to 512 rows a workgroup of two vector columns walks them all, which
+  // saves the launch that adds partial rows (512 x 512: 12.9 -> 10.7 us; 1024 x 1024: 13.0 -> 14.8).
+  const bool direct = rows <= 512;
+  const int vc = direct ? 2 : 32, band = direct ? rows : LNB_ROWS;
+  const dim3 grid((h / 8 + vc - 1) / vc, direct ? 1 : parts);
+  auto cols = direct ? (add_colsum ? layernorm_bwd_cols_kernel<2, true> : layernorm_bwd_cols_kernel<2, false>)
+                     : (add_colsum ? layernorm_bwd_cols_kernel<32, true> : layernorm_bwd_cols_kernel<32, false>);
+  hipLaunchKernelGGL(cols, grid, dim3(256), 0, s, dy, x, stats, add, partial_ws, dgamma, dbeta, add_colsum, rows, h, band);
+  if (!direct) launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
+  auto rowk = per_lane <= 2   ? layernorm_bwd_rows_kernel<2>
+              : per_lane <= 4 ? layernorm_bwd_rows_kernel<4>
+              : per_lane <= 6 ? layernorm_bwd_rows_kernel<6>
+              : per_lane <= 9 ? layernorm_bwd_rows_kernel<9>
+                              : layernorm_bwd_rows_kernel<12>;
+  hipLaunchKernelGGL(rowk, dim3((rows + 3) / 4), dim3(256), 0, s, dy, x, stats, g, add, dx, rows, h);
   return ok();
 }
 
