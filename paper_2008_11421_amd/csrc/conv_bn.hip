@@ -30,6 +30,8 @@ __host__ __device__ inline int bn_band(int C) {
   return band < 16 ? 16 : band;
 }
 
+// Rows of pixels that a thread has in flight.
+constexpr int BN_U = 4;
 // Rows per workgroup of the partial sums: the band above, or longer when that would make more than 2048 bands (a
 // million pixels in 96-row bands are 11 000 partial rows, which the few workgroups of the finishing kernel then
 // take longer to add up than the sums themselves took).
@@ -69,26 +71,36 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const bf16_t* __restric
     }
     const int band = bn_sum_band(rows, C);
     const int r0 = blockIdx.x * band, r1 = min(rows, r0 + band);
-#pragma unroll 2
-    for (int r = r0 + rl; r < r1; r += RL) {
-      float v[8];
-      unpack8(*(const u32x4*)(x + (size_t)r * C + c8), v);
-      if (BWD) {
-        float d[8];
-        unpack8(*(const u32x4*)(dy + (size_t)r * C + c8), d);
+    for (int r = r0 + rl; r < r1; r += BN_U * RL) {   // BN_U rows in flight, added in ascending order
+      u32x4 qx[BN_U], qd[BN_U];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float xh = (v[e] - p0[e]) * p1[e];
-          const float dd = (relu && !(xh * gg[e] + bb[e] > 0.f)) ? 0.f : d[e];
-          a0[e] += dd;
-          a1[e] += dd * xh;
-        }
-      } else {
+      for (int k = 0; k < BN_U; ++k) {
+        const size_t at = (size_t)min(r + k * RL, rows - 1) * C + c8;
+        qx[k] = *(const u32x4*)(x + at);
+        if (BWD) qd[k] = *(const u32x4*)(dy + at);
+      }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float t = v[e] - p0[e];
-          a0[e] += t;
-          a1[e] += t * t;
+      for (int k = 0; k < BN_U; ++k) {
+        if (r + k * RL >= r1) break;
+        float v[8];
+        unpack8(qx[k], v);
+        if (BWD) {
+          float d[8];
+          unpack8(qd[k], d);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float xh = (v[e] - p0[e]) * p1[e];
+            const float dd = (relu && !(xh * gg[e] + bb[e] > 0.f)) ? 0.f : d[e];
+            a0[e] += dd;
+            a1[e] += dd * xh;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float t = v[e] - p0[e];
+            a0[e] += t;
+            a1[e] += t * t;
+          }
         }
       }
     }
@@ -106,41 +118,46 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const bf16_t* __restric
   }
 }
 
-// Adds the band partials in a fixed order: 32 interleaved slices of the bands per channel,
-// then the slices in ascending order.
+// Adds the band partials in a fixed order: 128 interleaved slices of the bands per channel, then the slices in
+// ascending order, sixteen groups of eight first.
 //   forward:  stats[0][c] = mean, stats[1][c] = 1/sqrt(var + eps) (biased variance)
 //   backward: out0[c] = dbeta, out1[c] = dgamma
-__global__ __launch_bounds__(256) void bn_finish_kernel(const float* __restrict__ partial, int bands, int C, int rows,
-                                                         const bf16_t* __restrict__ x_row0, float* __restrict__ out0,
-                                                         float* __restrict__ out1, int bwd) {
-  __shared__ float red[2][32][8];
+__global__ __launch_bounds__(1024) void bn_finish_kernel(const float* __restrict__ partial, int bands, int C, int rows,
+                                                          const bf16_t* __restrict__ x_row0, float* __restrict__ out0,
+                                                          float* __restrict__ out1, int bwd) {
+  __shared__ float red[2][128][8], grp[2][16][8];
   const int cl = threadIdx.x & 7, slice = threadIdx.x >> 3;
   const int c = blockIdx.x * 8 + cl;
   float s0 = 0.f, s1 = 0.f;
   if (c < C) {
-    int p = slice;
-    for (; p + 96 < bands; p += 128) {   // four bands in flight, added in ascending order
+    for (int p = slice; p < bands; p += 512) {   // four bands in flight, added in ascending order
       float a[4], b[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        a[k] = partial[(size_t)(p + 32 * k) * 2 * C + c];
-        b[k] = partial[(size_t)(p + 32 * k) * 2 * C + C + c];
+        const float* at = partial + (size_t)min(p + 128 * k, bands - 1) * 2 * C + c;
+        a[k] = at[0];
+        b[k] = at[C];
       }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { s0 += a[k]; s1 += b[k]; }
-    }
-    for (; p < bands; p += 32) {
-      s0 += partial[(size_t)p * 2 * C + c];
-      s1 += partial[(size_t)p * 2 * C + C + c];
+      for (int k = 0; k < 4; ++k)
+        if (p + 128 * k < bands) { s0 += a[k]; s1 += b[k]; }
     }
   }
   red[0][slice][cl] = s0;
   red[1][slice][cl] = s1;
   __syncthreads();
-  if (slice == 0 && c < C) {
-    float t0 = red[0][0][cl], t1 = red[1][0][cl];
+  if (threadIdx.x < 256) {
+    const int which = threadIdx.x >> 7, group = threadIdx.x >> 3 & 15;
+    float t = red[which][8 * group][cl];
 #pragma unroll
-    for (int k = 1; k < 32; ++k) { t0 += red[0][k][cl]; t1 += red[1][k][cl]; }
+    for (int k = 1; k < 8; ++k) t += red[which][8 * group + k][cl];
+    grp[which][group][cl] = t;
+  }
+  __syncthreads();
+  if (slice == 0 && c < C) {
+    float t0 = grp[0][0][cl], t1 = grp[1][0][cl];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) { t0 += grp[0][k][cl]; t1 += grp[1][k][cl]; }
     if (bwd) {
       out0[c] = t0;
       out1[c] = t1;
@@ -174,29 +191,39 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_kernel(const bf16_t* __restr
   for (int e = 0; e < 8; ++e) { mean[e] = stats[c8 + e]; rstd[e] = stats[C + c8 + e]; }
   const int band = bn_band(C);
   const int r0 = blockIdx.x * band, r1 = min(rows, r0 + band);
-  for (int r = r0 + rl; r < r1; r += RL) {
-    const size_t at = (size_t)r * C + c8;
-    float v[8], a[8];
-    unpack8(*(const u32x4*)(x + at), v);
-    if (add) unpack8(*(const u32x4*)(add + at), a);
+  for (int r = r0 + rl; r < r1; r += BN_U * RL) {
+    u32x4 qx[BN_U], qa[BN_U], qg[BN_U];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      // kept as (x - mean) * rstd * g + b: the backward pass recomputes exactly this expression
-      float t = (v[e] - mean[e]) * rstd[e] * gg[e] + bb[e];
-      if (add) t += a[e];
-      v[e] = relu ? fmaxf(t, 0.f) : t;
+    for (int k = 0; k < BN_U; ++k) {
+      const size_t at = (size_t)min(r + k * RL, rows - 1) * C + c8;
+      qx[k] = *(const u32x4*)(x + at);
+      if (add) qa[k] = *(const u32x4*)(add + at);
+      if (gate) qg[k] = *(const u32x4*)(gate + at);
     }
-    u32x4 out = pack8(v);
-    if (gate) {
-      const u32x4 gv = *(const u32x4*)(gate + at);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const unsigned w = out[k];
-        const unsigned keep = ((w & 0x7fffu) && !(w & 0x8000u) ? 0xffffu : 0u) | ((w & 0x7fff0000u) && !(w & 0x80000000u) ? 0xffff0000u : 0u);
-        out[k] = gv[k] & keep;
+    for (int k = 0; k < BN_U; ++k) {
+      if (r + k * RL >= r1) break;
+      float v[8], a[8];
+      unpack8(qx[k], v);
+      if (add) unpack8(qa[k], a);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        // kept as (x - mean) * rstd * g + b: the backward pass recomputes exactly this expression
+        float t = (v[e] - mean[e]) * rstd[e] * gg[e] + bb[e];
+        if (add) t += a[e];
+        v[e] = relu ? fmaxf(t, 0.f) : t;
       }
+      u32x4 out = pack8(v);
+      if (gate) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const unsigned w = out[j];
+          const unsigned keep = ((w & 0x7fffu) && !(w & 0x8000u) ? 0xffffu : 0u) | ((w & 0x7fff0000u) && !(w & 0x80000000u) ? 0xffff0000u : 0u);
+          out[j] = qg[k][j] & keep;
+        }
+      }
+      *(u32x4*)(y + (size_t)(r + k * RL) * C + c8) = out;
     }
-    *(u32x4*)(y + at) = out;
   }
 }
 
@@ -223,24 +250,35 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_kernel(const bf16_t* __restr
   }
   const int band = bn_band(C);
   const int r0 = blockIdx.x * band, r1 = min(rows, r0 + band);
-  for (int r = r0 + rl; r < r1; r += RL) {
-    const size_t at = (size_t)r * C + c8;
-    float v[8], d[8];
-    unpack8(*(const u32x4*)(x + at), v);
-    unpack8(*(const u32x4*)(dy + at), d);
+  for (int r = r0 + rl; r < r1; r += BN_U * RL) {
+    u32x4 qx[BN_U], qd[BN_U], qa[BN_U];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float xh = (v[e] - mean[e]) * rstd[e];
-      const float dd = (relu && !(xh * gg[e] + bb[e] > 0.f)) ? 0.f : d[e];
-      v[e] = gg[e] * rstd[e] * (dd - k0[e] - xh * k1[e]);
+    for (int k = 0; k < BN_U; ++k) {
+      const size_t at = (size_t)min(r + k * RL, rows - 1) * C + c8;
+      qx[k] = *(const u32x4*)(x + at);
+      qd[k] = *(const u32x4*)(dy + at);
+      if (add) qa[k] = *(const u32x4*)(add + at);
     }
-    if (add) {
-      float a[8];
-      unpack8(*(const u32x4*)(add + at), a);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += a[e];
+    for (int k = 0; k < BN_U; ++k) {
+      if (r + k * RL >= r1) break;
+      float v[8], d[8];
+      unpack8(qx[k], v);
+      unpack8(qd[k], d);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float xh = (v[e] - mean[e]) * rstd[e];
+        const float dd = (relu && !(xh * gg[e] + bb[e] > 0.f)) ? 0.f : d[e];
+        v[e] = gg[e] * rstd[e] * (dd - k0[e] - xh * k1[e]);
+      }
+      if (add) {
+        float a[8];
+        unpack8(qa[k], a);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += a[e];
+      }
+      *(u32x4*)(dx + (size_t)(r + k * RL) * C + c8) = pack8(v);
     }
-    *(u32x4*)(dx + at) = pack8(v);
   }
 }
 
@@ -601,7 +639,7 @@ int bn_fwd(const bf16_t* x, const bf16_t* g, const bf16_t* b, const bf16_t* add,
   const int bands = (rows + bn_sum_band(rows, c) - 1) / bn_sum_band(rows, c);
   hipLaunchKernelGGL(bn_partial_kernel<false>, dim3(bands, (c / 8 + 255) / 256), dim3(256), 0, s, x, (const bf16_t*)nullptr,
                      (const float*)nullptr, g, b, ws, rows, c, 0);
-  hipLaunchKernelGGL(bn_finish_kernel, dim3((c + 7) / 8), dim3(256), 0, s, ws, bands, c, rows, x, stats, stats + c, 0);
+  hipLaunchKernelGGL(bn_finish_kernel, dim3((c + 7) / 8), dim3(1024), 0, s, ws, bands, c, rows, x, stats, stats + c, 0);
   hipLaunchKernelGGL(bn_apply_fwd_kernel, dim3((rows + bn_band(c) - 1) / bn_band(c), (c / 8 + 255) / 256), dim3(256), 0, s, x, stats,
                      g, b, add, (const bf16_t*)nullptr, y, rows, c, relu);
   return ok();
@@ -621,7 +659,7 @@ int bn_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const bf16_t* 
   const int bands = (rows + bn_sum_band(rows, c) - 1) / bn_sum_band(rows, c);
   hipLaunchKernelGGL(bn_partial_kernel<true>, dim3(bands, (c / 8 + 255) / 256), dim3(256), 0, s, x, dy, stats, g, b, ws, rows,
                      c, relu);
-  hipLaunchKernelGGL(bn_finish_kernel, dim3((c + 7) / 8), dim3(256), 0, s, ws, bands, c, rows, (const bf16_t*)nullptr, dbeta,
+  hipLaunchKernelGGL(bn_finish_kernel, dim3((c + 7) / 8), dim3(1024), 0, s, ws, bands, c, rows, (const bf16_t*)nullptr, dbeta,
                      dgamma, 1);
   hipLaunchKernelGGL(bn_apply_bwd_kernel, dim3((rows + bn_band(c) - 1) / bn_band(c), (c / 8 + 255) / 256), dim3(256), 0, s, dy, x, stats, g, b, dgamma, dbeta,
                      add, dx, rows, c, 1.f / (float)rows, relu);
