@@ -299,7 +299,7 @@ int ffn_half_bwd(const Dims& d, const bf16_t* dy, const bf16_t* r1, const FfnBuf
   // df1 = (dy W2) * GELU'(f1); where the kernel can, it leaves partial column sums of df1 (FC1's bias gradient)
   int sum_rows = 0;
   TRY(gemm_gelu(dy, W(W2), w.wide, nullptr, b.f1, d.T, d.ffn, d.h, true, false, 2, s, w.part, &sum_rows));
-  TRY(colsum_finish(w.part, sum_rows, d.ffn, (float*)G(B1), s));
+  if (sum_rows) TRY(colsum_finish(w.part, sum_rows, d.ffn, (float*)G(B1), s));
   TRY(gemm(dy, b.g, G(W2), nullptr, nullptr, d.h, d.ffn, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));        // dW2 = dy^T g
   TRY(gemm(w.wide, W(W1), w.t1, nullptr, nullptr, d.T, d.h, d.ffn, true, false, false, false, s));      // dm = df1 W1
   TRY(gemm(w.wide, b.m, G(W1), nullptr, nullptr, d.ffn, d.h, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));    // dW1 = df1^T m
