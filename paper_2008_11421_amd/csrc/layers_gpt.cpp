@@ -72,7 +72,7 @@ struct FfnSaved {
   }
 };
 
-// backward workspace of one block
+// workspace of one block, backward (forward: the partial sums alone)
 struct BlockWs {
   uint64_t wide, t1, t2, t3, delta, part, splitk, splitk_bytes, total;
   explicit BlockWs(const Dims& d) {
@@ -270,25 +270,29 @@ struct AttnBufs {
 struct FfnBufs {
   float* stats2; bf16_t* m; bf16_t* f1; bf16_t* g;
 };
+// room for partial sums of products whose reduction is divided
+struct SplitWs {
+  char* at; uint64_t bytes;
+};
 struct BwdBufs {
   bf16_t* wide; bf16_t* t1; bf16_t* t3; float* delta; float* part; char* splitk; uint64_t splitk_bytes;
 };
 
 template <class WF>
-int attn_half_fwd(const Dims& d, const bf16_t* x, const AttnBufs& b, bf16_t* r1, WF W, hipStream_t s) {
+int attn_half_fwd(const Dims& d, const bf16_t* x, const AttnBufs& b, const SplitWs& w, bf16_t* r1, WF W, hipStream_t s) {
   TRY(layernorm_fwd(x, W(LN1_G), W(LN1_B), b.a, b.stats1, d.T, d.h, s));
-  TRY(gemm(b.a, W(WQKV), b.qkv, W(BQKV), nullptr, d.T, 3 * d.h, d.h, true, true, false, false, s));
+  TRY(gemm(b.a, W(WQKV), b.qkv, W(BQKV), nullptr, d.T, 3 * d.h, d.h, true, true, false, false, s, w.at, w.bytes));
   TRY(attention_fwd(b.qkv, b.ctx, b.lse, d.B, d.S, d.H, d.D, s));
   // a recompute whose output nobody needs stops here: backward only reads the internals
-  if (r1) TRY(gemm(b.ctx, W(WO), r1, W(BO), x, d.T, d.h, d.h, true, true, false, false, s));
+  if (r1) TRY(gemm(b.ctx, W(WO), r1, W(BO), x, d.T, d.h, d.h, true, true, false, false, s, w.at, w.bytes));
   return KARMA_OK;
 }
 
 template <class WF>
-int ffn_half_fwd(const Dims& d, const bf16_t* r1, const FfnBufs& b, bf16_t* out, WF W, hipStream_t s) {
+int ffn_half_fwd(const Dims& d, const bf16_t* r1, const FfnBufs& b, const SplitWs& w, bf16_t* out, WF W, hipStream_t s) {
   TRY(layernorm_fwd(r1, W(LN2_G), W(LN2_B), b.m, b.stats2, d.T, d.h, s));
   TRY(gemm_gelu(b.m, W(W1), b.f1, W(B1), b.g, d.T, d.ffn, d.h, true, true, 1, s));   // f1 = m W1^T + b1, g = GELU(f1)
-  if (out) TRY(gemm(b.g, W(W2), out, W(B2), r1, d.T, d.h, d.ffn, true, true, false, false, s));
+  if (out) TRY(gemm(b.g, W(W2), out, W(B2), r1, d.T, d.h, d.ffn, true, true, false, false, s, w.at, w.bytes));
   return KARMA_OK;
 }
 
@@ -343,22 +347,24 @@ int gpt_forward(Ctx& c, uint32_t i, const LayerIO& io, hipStream_t s) {
   // a split record holds six of the block's twelve tensors: the feed-forward half's start at LN2_G
   const int first = kind == REC_FFN ? (int)LN2_G : 0;
   auto W = [&](int t) { return (const bf16_t*)c.w_ptr(i, t - first, io.w); };
+  const BlockWs wl(d);
+  const SplitWs ws{(char*)io.ws + wl.splitk, wl.splitk_bytes};
   if (kind == REC_ATTN) {
     AttnSaved sv(d);
     AttnBufs ab{(bf16_t*)(S + sv.a), (float*)(S + sv.stats1), (bf16_t*)(S + sv.qkv), (bf16_t*)(S + sv.ctx), (float*)(S + sv.lse)};
-    return attn_half_fwd(d, x, ab, (bf16_t*)io.out, W, s);
+    return attn_half_fwd(d, x, ab, ws, (bf16_t*)io.out, W, s);
   }
   if (kind == REC_FFN) {
     FfnSaved sv(d);
     FfnBufs fb{(float*)(S + sv.stats2), (bf16_t*)(S + sv.m), (bf16_t*)(S + sv.f1), (bf16_t*)(S + sv.g)};
-    return ffn_half_fwd(d, x, fb, (bf16_t*)io.out, W, s);
+    return ffn_half_fwd(d, x, fb, ws, (bf16_t*)io.out, W, s);
   }
   BlockSaved sv(d);
   AttnBufs ab{(bf16_t*)(S + sv.a), (float*)(S + sv.stats1), (bf16_t*)(S + sv.qkv), (bf16_t*)(S + sv.ctx), (float*)(S + sv.lse)};
   FfnBufs fb{(float*)(S + sv.stats2), (bf16_t*)(S + sv.m), (bf16_t*)(S + sv.f1), (bf16_t*)(S + sv.g)};
   bf16_t* r1 = (bf16_t*)(S + sv.r1);
-  TRY(attn_half_fwd(d, x, ab, r1, W, s));
-  return ffn_half_fwd(d, r1, fb, (bf16_t*)io.out, W, s);
+  TRY(attn_half_fwd(d, x, ab, ws, r1, W, s));
+  return ffn_half_fwd(d, r1, fb, ws, (bf16_t*)io.out, W, s);
 }
 
 int gpt_backward(Ctx& c, uint32_t i, const LayerIO& io, hipStream_t s) {
