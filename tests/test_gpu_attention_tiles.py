@@ -23,7 +23,7 @@ def g():
     return gpu_util
 
 
-@pytest.mark.parametrize("B,S,H,D", [(1, 128, 1, 128), (4, 512, 17, 128), (1, 128, 1, 152), (1, 384, 3, 152), (3, 512, 22, 152)])
+@pytest.mark.parametrize("B,S,H,D", [(1, 1152, 2, 64), (1, 1024, 1, 152), (1, 640, 2, 128), (1, 128, 1, 128), (4, 512, 17, 128), (1, 128, 1, 152), (1, 384, 3, 152), (3, 512, 22, 152)])
 @pytest.mark.parametrize("huge_head", [False, True])
 def test_forward_backward_and_bias_gradient(g, B, S, H, D, huge_head):
     import torch
