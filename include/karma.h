@@ -436,7 +436,8 @@ int karma_get_op_starts(karma_ctx* ctx, float* start_ms_out, uint32_t* n_inout);
  * x [m,k], w [n,k], b [n], z and y [m,n]. */
 int karma_k_linear_relu_fwd_f32(const float* x_dev, const float* w_dev, const float* b_dev, float* z_dev,
                                 float* y_dev, uint32_t m, uint32_t n, uint32_t k, void* stream);
-/* dz = dy * (z > 0); dx = dz W (skipped when dx_dev is NULL); dW = dz^T x; db = colsum dz. */
+/* dz = dy * (z > 0); dx = dz W (skipped when dx_dev is NULL); dW = dz^T x; db = colsum dz.  dz_ws_dev may be z_dev or
+ * dy_dev; dx, dW and db may lie over dy_dev or z_dev, dW and db also over w_dev, db over x_dev (four launches then). */
 int karma_k_linear_relu_bwd_f32(const float* x_dev, const float* w_dev, const float* z_dev, const float* dy_dev,
                                 float* dz_ws_dev, float* dx_dev, float* dw_dev, float* db_dev, uint32_t m,
                                 uint32_t n, uint32_t k, void* stream);

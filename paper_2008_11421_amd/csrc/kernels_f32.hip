@@ -123,13 +123,72 @@ __global__ __launch_bounds__(256) void linear_relu_bwd_kernel(const float* __res
   db[c] = s;
 }
 
-// dx alone, from dz
-__global__ __launch_bounds__(256) void linear_relu_dx_kernel(const float* __restrict__ w, const float* __restrict__ dz,
-                                                             float* __restrict__ dx, int m, int n, int k, bool vec) {
-  __shared__ f32x4 part[4][64];
-  const int across = (k + TS - 1) / TS, id = blockIdx.x;
-  tile_f32(Operand<true>{dz, nullptr, m, n, vec}, Operand<false>{w, nullptr, k, n, false}, id / across * TS, id % across * TS,
-           [&](int r, int c, float v) { dx[(size_t)r * k + c] = v; }, part);
+// ---- the backward pass as ordered launches, for results that lie over inputs: a 32 x 32 tile per workgroup, 16 k at a time
+// through LDS, each of the 16 x 16 threads a 2 x 2 patch.
+constexpr int TSL = 32, TKL = 16;
+
+// C[m,n] = sum_k A(m,k) * B(n,k);  A row-major [M,K] (or [K,M] when A_T), B row-major [N,K] (or [K,N] when B_T).
+template <bool A_T, bool B_T, class Epilogue>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* A, const float* B, int M, int N, int K, Epilogue ep) {
+  __shared__ float As[TKL][TSL + 1];
+  __shared__ float Bs[TKL][TSL + 1];
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int m0 = blockIdx.y * TSL, n0 = blockIdx.x * TSL;
+  float acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+  for (int k0 = 0; k0 < K; k0 += TKL) {
+    // 512 elements per operand tile, 2 per thread
+    for (int e = threadIdx.x; e < TSL * TKL; e += 256) {
+      int r, c;   // r: row within tile (m or n), c: k within step
+      if (A_T) { r = e % TSL; c = e / TSL; } else { r = e / TKL; c = e % TKL; }
+      int gm = m0 + r, gk = k0 + c;
+      float v = 0.f;
+      if (gm < M && gk < K) v = A_T ? A[(size_t)gk * M + gm] : A[(size_t)gm * K + gk];
+      As[c][r] = v;
+      if (B_T) { r = e % TSL; c = e / TSL; } else { r = e / TKL; c = e % TKL; }
+      int gn = n0 + r;
+      gk = k0 + c;
+      v = 0.f;
+      if (gn < N && gk < K) v = B_T ? B[(size_t)gk * N + gn] : B[(size_t)gn * K + gk];
+      Bs[c][r] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TKL; ++k) {
+      float a0 = As[k][ty], a1 = As[k][ty + 16], b0 = Bs[k][tx], b1 = Bs[k][tx + 16];
+      acc[0][0] = fmaf(a0, b0, acc[0][0]);
+      acc[0][1] = fmaf(a0, b1, acc[0][1]);
+      acc[1][0] = fmaf(a1, b0, acc[1][0]);
+      acc[1][1] = fmaf(a1, b1, acc[1][1]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      int m = m0 + ty + 16 * i, n = n0 + tx + 16 * j;
+      if (m < M && n < N) ep(m, n, acc[i][j]);
+    }
+}
+
+struct EpStore {
+  float* c; int N;
+  __device__ void operator()(int m, int n, float v) const { c[(size_t)m * N + n] = v; }
+};
+
+// dz = dy * (z > 0)
+__global__ void relu_mask_kernel(const float* z, const float* dy, float* dz, size_t n) {
+  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) dz[i] = z[i] > 0.f ? dy[i] : 0.f;
+}
+
+// db[n] = sum_m dz[m,n], rows in ascending order
+__global__ void colsum_kernel(const float* __restrict__ dz, float* __restrict__ db, int M, int N) {
+  int n = blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= N) return;
+  float s = 0.f;
+  for (int m = 0; m < M; ++m) s += dz[(size_t)m * N + n];
+  db[n] = s;
 }
 
 // stage 1 of the loss: dy and per-block partial sums of (y - t)^2
@@ -168,32 +227,41 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restri
 }
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+static inline dim3 large_tiles(int M, int N) { return dim3((N + TSL - 1) / TSL, (M + TSL - 1) / TSL); }
+static inline size_t small_tiles(int M, int N) { return (size_t)((N + TS - 1) / TS) * ((M + TS - 1) / TS); }
 
 int linear_relu_fwd_f32(const float* x, const float* w, const float* b, float* z, float* y, int m, int n, int k,
                         hipStream_t s) {
   const bool vec = k % 4 == 0;
-  hipLaunchKernelGGL(linear_relu_fwd_kernel, dim3((unsigned)((n + TS - 1) / TS) * (unsigned)((m + TS - 1) / TS)), dim3(256), 0, s,
+  hipLaunchKernelGGL(linear_relu_fwd_kernel, dim3((unsigned)small_tiles(m, n)), dim3(256), 0, s,
                      (Operand<true>{x, nullptr, m, k, vec && aligned16(x)}), (Operand<true>{w, nullptr, n, k, vec && aligned16(w)}), b, z, y);
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
 }
 
 int linear_relu_bwd_f32(const float* x, const float* w, const float* z, const float* dy, float* dz, float* dx,
                         float* dw, float* db, int m, int n, int k, hipStream_t s) {
-  const int across = (k + TS - 1) / TS, dw_tiles = (n + TS - 1) / TS * across, sums = (n + 255) / 256;
-  const int dx_tiles = dx ? (m + TS - 1) / TS * across : 0;
-  const bool vec = n % 4 == 0 && aligned16(z) && aligned16(dy) && aligned16(dz);
-  auto launch = [&](int first) {
-    hipLaunchKernelGGL(linear_relu_bwd_kernel, dim3(first + dw_tiles + sums), dim3(256), 0, s, x, w, z, dy, dz, dx, dw, db, m, n, k,
-                       first, dw_tiles, vec);
+  const size_t mn = (size_t)m * n, mk = (size_t)m * k, nk = (size_t)n * k;
+  // One launch, whose workgroups read and write side by side: only where no result lies over anything that others still
+  // read.  (dz over dy is harmless: an element is replaced by itself or by the zero that it is read as.)
+  auto meet = [](const float* p, size_t np, const float* q, size_t nq) { return p && q && p < q + nq && q < p + np; };
+  auto over_inputs = [&](const float* out, size_t cnt) {
+    return meet(out, cnt, x, mk) || meet(out, cnt, w, nk) || meet(out, cnt, z, mn) || meet(out, cnt, dy, mn);
   };
-  // dx written over its own inputs: everything else reads them first, and dx is made from dz
-  auto meets = [&](const float* q) { return dx && dx < q + (size_t)m * n && q < dx + (size_t)m * k; };
-  if (meets(dy) || meets(z)) {
-    launch(0);
-    hipLaunchKernelGGL(linear_relu_dx_kernel, dim3(dx_tiles), dim3(256), 0, s, w, dz, dx, m, n, k, vec);
-  } else {
-    launch(dx_tiles);
+  const bool apart = !(meet(dz, mn, x, mk) || meet(dz, mn, w, nk) || meet(dz, mn, z, mn) || (dz != dy && meet(dz, mn, dy, mn))) &&
+                     !over_inputs(dx, mk) && !over_inputs(dw, nk) && !over_inputs(db, n);
+  if (apart) {
+    const int dx_tiles = dx ? (int)small_tiles(m, k) : 0, dw_tiles = (int)small_tiles(n, k), sums = (n + 255) / 256;
+    hipLaunchKernelGGL(linear_relu_bwd_kernel, dim3(dx_tiles + dw_tiles + sums), dim3(256), 0, s, x, w, z, dy, dz, dx, dw, db, m, n, k,
+                       dx_tiles, dw_tiles, n % 4 == 0 && aligned16(z) && aligned16(dy));
+    return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
   }
+  hipLaunchKernelGGL(relu_mask_kernel, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s, z, dy, dz, mn);
+  // dx[m,k] = sum_n dz[m,n] w[n,k]  -> A = dz [M,N] (reduction contiguous), B = w as [N,K] read transposed
+  if (dx)
+    hipLaunchKernelGGL((gemm_f32_kernel<false, true, EpStore>), large_tiles(m, k), dim3(256), 0, s, dz, w, m, k, n, EpStore{dx, k});
+  // dw[n,k] = sum_m dz[m,n] x[m,k] -> both operands read transposed, reduction over m
+  hipLaunchKernelGGL((gemm_f32_kernel<true, true, EpStore>), large_tiles(n, k), dim3(256), 0, s, dz, x, n, k, m, EpStore{dw, k});
+  hipLaunchKernelGGL(colsum_kernel, dim3((n + 255) / 256), dim3(256), 0, s, dz, db, m, n);
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
 }
 
