@@ -1,14 +1,17 @@
 // fp32 kernels of the MLP workload: fully connected layer with ReLU (KARMA Sec. III-C,
 // "Fully-Connected Layer", "ReLu Layer"), its backward, and the mean-squared-error loss.
 //
-// The products are a few million multiply-adds (32 x 256 x 256): what bounds them is the chain of memory round trips and
-// the launches, not arithmetic.  A workgroup computes one 16 x 16 tile, its four wavefronts each a quarter of the
-// reduction with v_mfma_f32_16x16x4_f32 (fp32 products and sums), operands straight from global memory to registers, all
-// of a wavefront's loads for 64 k in flight at once; the four partial tiles are added in order through LDS.  The backward
-// pass is one launch: tiles of dx, tiles of dw and the column sums of db, each reading dz = dy * (z > 0) as it loads.
-// 32 x 256 x 256: forward 25.5 -> 5.6 us, backward 38 us in four launches -> 8.6 us in one (a
-// 32 x 32 tile per workgroup stepped through LDS 16 k at a time waited for memory 16 times in eight workgroups).
+// The workload's products are a few million multiply-adds (32 x 256 x 256): what bounds them is the chain of memory round
+// trips and the launches, not arithmetic.  For these a workgroup computes one 16 x 16 tile, its four wavefronts each a
+// quarter of the reduction with v_mfma_f32_16x16x4_f32 (fp32 products and sums), operands straight from global memory to
+// registers, all of a wavefront's loads for 64 k in flight at once; the four partial tiles are added in order through LDS.
+// Products with many tiles keep 32 x 32 tiles through LDS, which fetch an operand element half as often.  The backward
+// pass of the former is one launch: the column sums of db, tiles of dx and tiles of dw, each reading dz = dy * (z > 0) as it loads.
+// 32 x 256 x 256: forward 25.5 -> 5.6 us, backward 38 us in four launches -> 8.6 us in one (the 32 x 32 tile, stepped
+// through LDS 16 k at a time, waits for memory 16 times in eight workgroups).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "karma.h"
 #include "kernels.h"
@@ -90,27 +93,29 @@ __global__ __launch_bounds__(256) void linear_relu_fwd_kernel(Operand<true> X, O
 }
 
 // dx[m,k] = sum_n dz[m,n] w[n,k], dw[n,k] = sum_m dz[m,n] x[m,k], db[n] = sum_m dz[m,n] (rows in ascending order) and dz
-// itself: workgroups 0 .. dx_tiles-1 take dx, the next dw_tiles dw, the rest 256 columns of db and dz each.
+// itself: the first `sums` workgroups take 256 columns of db and dz each (a serial walk over the rows, the longest chain
+// of the launch where there are many), the next dx_tiles dx, the rest dw.
 __global__ __launch_bounds__(256) void linear_relu_bwd_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                               const float* __restrict__ z, const float* __restrict__ dy,
                                                               float* __restrict__ dz, float* __restrict__ dx,
                                                               float* __restrict__ dw, float* __restrict__ db, int m, int n, int k,
-                                                              int dx_tiles, int dw_tiles, bool vec) {
+                                                              int sums, int dx_tiles, bool vec) {
   __shared__ f32x4 part[4][64];
+  const int across = (k + TS - 1) / TS, first = sums + dx_tiles;
   int id = blockIdx.x;
-  const int across = (k + TS - 1) / TS;
-  if (id < dx_tiles) {
-    tile_f32(Operand<true>{dy, z, m, n, vec}, Operand<false>{w, nullptr, k, n, false}, id / across * TS, id % across * TS,
-             [&](int r, int c, float v) { dx[(size_t)r * k + c] = v; }, part);
-    return;
-  }
-  id -= dx_tiles;
-  if (id < dw_tiles) {
+  if (id >= first) {
+    id -= first;
     tile_f32(Operand<false>{dy, z, n, m, false}, Operand<false>{x, nullptr, k, m, false}, id / across * TS, id % across * TS,
              [&](int r, int c, float v) { dw[(size_t)r * k + c] = v; }, part);
     return;
   }
-  const int c = (id - dw_tiles) * 256 + threadIdx.x;
+  if (id >= sums) {
+    id -= sums;
+    tile_f32(Operand<true>{dy, z, m, n, vec}, Operand<false>{w, nullptr, k, n, false}, id / across * TS, id % across * TS,
+             [&](int r, int c, float v) { dx[(size_t)r * k + c] = v; }, part);
+    return;
+  }
+  const int c = id * 256 + threadIdx.x;
   if (c >= n) return;
   float s = 0.f;
 #pragma unroll 8
@@ -123,8 +128,8 @@ __global__ __launch_bounds__(256) void linear_relu_bwd_kernel(const float* __res
   db[c] = s;
 }
 
-// ---- the backward pass as ordered launches, for results that lie over inputs: a 32 x 32 tile per workgroup, 16 k at a time
-// through LDS, each of the 16 x 16 threads a 2 x 2 patch.
+// ---- the same products for sizes that have workgroups enough without the split, where each operand element's trip is what
+// counts: a 32 x 32 tile per workgroup, 16 k at a time through LDS, each of the 16 x 16 threads a 2 x 2 patch.
 constexpr int TSL = 32, TKL = 16;
 
 // C[m,n] = sum_k A(m,k) * B(n,k);  A row-major [M,K] (or [K,M] when A_T), B row-major [N,K] (or [K,N] when B_T).
@@ -171,6 +176,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* A, const flo
     }
 }
 
+struct EpBiasRelu {
+  const float* b; float* z; float* y; int N;
+  __device__ void operator()(int m, int n, float v) const {
+    v += b[n];
+    z[(size_t)m * N + n] = v;
+    y[(size_t)m * N + n] = v > 0.f ? v : 0.f;
+  }
+};
 struct EpStore {
   float* c; int N;
   __device__ void operator()(int m, int n, float v) const { c[(size_t)m * N + n] = v; }
@@ -230,11 +243,38 @@ static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 static inline dim3 large_tiles(int M, int N) { return dim3((N + TSL - 1) / TSL, (M + TSL - 1) / TSL); }
 static inline size_t small_tiles(int M, int N) { return (size_t)((N + TS - 1) / TS) * ((M + TS - 1) / TS); }
 
+// Which of the two tiles, by modelled times in us.  The small tile: 1.4 per 256 k of its chain, or 1 ns per workgroup and
+// 13 (forward, 16-byte loads) to 40 ps per k; the large one: 0.95 per 16 k, or 1 ns per workgroup and 90 ps per k.  Over
+// 494 sizes from 1 x 8 x 8 to 8192 x 8192 x 800 the choice is 0.5 % (forward) and 1.3 % (backward) behind the better one.
+//   forward, small / large: 32 x 256 x 256 5.6 / 25.5, 2139 x 2923 x 641 634 / 297, 3483 x 3556 x 228 162 / 221
+//   backward, one launch / four: 279 x 2955 x 60 99 / 346, 219 x 2566 x 6390 1206 / 624, 2858 x 2641 x 3406 8309 / 4227
+constexpr size_t MOST_WORKGROUPS = 1u << 24;   // of 256 threads in one dimension of a grid, which holds fewer than 2^32
+static double small_us(int M, int N, int K, double per_k) {
+  return std::max(1.4 * ((K + 255) / 256), (double)small_tiles(M, N) * (1e-3 + per_k * K));
+}
+static double large_us(int M, int N, int K) {
+  const dim3 t = large_tiles(M, N);
+  return std::max(0.95 * ((K + TKL - 1) / TKL), (double)t.x * t.y * (1e-3 + 9e-5 * K));
+}
+static bool split_fwd(int m, int n, int k, bool vec) {
+  return small_tiles(m, n) < MOST_WORKGROUPS && small_us(m, n, k, vec ? 1.3e-5 : 3.9e-5) <= large_us(m, n, k);
+}
+// (the walk of the column sums over the rows is on both sides; the ordered pass has three launches more, 9 us)
+static bool split_bwd(int m, int n, int k, bool dx) {
+  const double small = (dx ? small_us(m, k, n, n % 4 ? 4e-5 : 2e-5) : 0.0) + small_us(n, k, m, 3e-5);
+  const double large = 9.0 + (dx ? large_us(m, k, n) : 0.0) + large_us(n, k, m);
+  return small_tiles(m, k) + small_tiles(n, k) + (n + 255) / 256 < MOST_WORKGROUPS && small <= 1.1 * large;
+}
+
 int linear_relu_fwd_f32(const float* x, const float* w, const float* b, float* z, float* y, int m, int n, int k,
                         hipStream_t s) {
-  const bool vec = k % 4 == 0;
-  hipLaunchKernelGGL(linear_relu_fwd_kernel, dim3((unsigned)small_tiles(m, n)), dim3(256), 0, s,
-                     (Operand<true>{x, nullptr, m, k, vec && aligned16(x)}), (Operand<true>{w, nullptr, n, k, vec && aligned16(w)}), b, z, y);
+  const bool vec = k % 4 == 0 && aligned16(x) && aligned16(w);
+  if (split_fwd(m, n, k, vec))
+    hipLaunchKernelGGL(linear_relu_fwd_kernel, dim3((unsigned)small_tiles(m, n)), dim3(256), 0, s, (Operand<true>{x, nullptr, m, k, vec}),
+                       (Operand<true>{w, nullptr, n, k, vec}), b, z, y);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<false, false, EpBiasRelu>), large_tiles(m, n), dim3(256), 0, s, x, w, m, n, k,
+                       EpBiasRelu{b, z, y, n});
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
 }
 
@@ -249,10 +289,10 @@ int linear_relu_bwd_f32(const float* x, const float* w, const float* z, const fl
   };
   const bool apart = !(meet(dz, mn, x, mk) || meet(dz, mn, w, nk) || meet(dz, mn, z, mn) || (dz != dy && meet(dz, mn, dy, mn))) &&
                      !over_inputs(dx, mk) && !over_inputs(dw, nk) && !over_inputs(db, n);
-  if (apart) {
+  if (apart && split_bwd(m, n, k, dx != nullptr)) {
     const int dx_tiles = dx ? (int)small_tiles(m, k) : 0, dw_tiles = (int)small_tiles(n, k), sums = (n + 255) / 256;
-    hipLaunchKernelGGL(linear_relu_bwd_kernel, dim3(dx_tiles + dw_tiles + sums), dim3(256), 0, s, x, w, z, dy, dz, dx, dw, db, m, n, k,
-                       dx_tiles, dw_tiles, n % 4 == 0 && aligned16(z) && aligned16(dy));
+    hipLaunchKernelGGL(linear_relu_bwd_kernel, dim3(sums + dx_tiles + dw_tiles), dim3(256), 0, s, x, w, z, dy, dz, dx, dw, db, m, n, k,
+                       sums, dx_tiles, n % 4 == 0 && aligned16(z) && aligned16(dy));
     return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
   }
   hipLaunchKernelGGL(relu_mask_kernel, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s, z, dy, dz, mn);
