@@ -272,8 +272,8 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const bf16_t* _
 }
 
 // Column sums: VC vector columns (8 channels each) times 256 / VC row lanes per workgroup, over a band of `band` rows;
-// the row lanes are added in ascending order.  One band: these are the results (out_*); otherwise one partial row of
-// NS * h per band, finished as those of the kernel above.
+// the row lanes are added in ascending order.  No `partial`: one band, and these are the results (dgamma, dbeta, addsum);
+// otherwise one partial row of NS * h per band, finished as those of the kernel above.
 template <int VC, bool ADDSUM>
 __global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                   const float* __restrict__ stats, const bf16_t* __restrict__ add,
@@ -283,8 +283,9 @@ __global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* _
   constexpr int NS = ADDSUM ? 3 : 2, RL = 256 / VC, U = 4;
   __shared__ float red[NS][RL][VC * 8];
   const int vc = threadIdx.x % VC, rl = threadIdx.x / VC;
-  const int c8 = (blockIdx.x * VC + vc) * 8;
-  const int r0 = blockIdx.y * band, r1 = min(rows, r0 + band);
+  const int group = blockIdx.x, part = blockIdx.y;
+  const int c8 = (group * VC + vc) * 8;
+  const int r0 = part * band, r1 = min(rows, r0 + band);
   float sum[NS][8];
 #pragma unroll
   for (int k = 0; k < NS; ++k)
@@ -334,13 +335,13 @@ __global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* _
     __syncthreads();
   }
   for (int t = threadIdx.x; t < NS * VC * 8; t += 256) {
-    const int k = t / (VC * 8), c = t % (VC * 8), col = blockIdx.x * VC * 8 + c;
+    const int k = t / (VC * 8), c = t % (VC * 8), col = group * VC * 8 + c;
     if (col >= h) continue;
     float v = red[k][0][c];
 #pragma unroll
     for (int l = 1; l < (RL < 8 ? RL : 8); ++l) v += red[k][l][c];
-    if (gridDim.y == 1) (k == 0 ? dgamma : k == 1 ? dbeta : addsum)[col] = v;
-    else partial[((size_t)blockIdx.y * NS + k) * h + col] = v;
+    if (!partial) (k == 0 ? dgamma : k == 1 ? dbeta : addsum)[col] = v;
+    else partial[((size_t)part * NS + k) * h + col] = v;
   }
 }
 
@@ -713,21 +714,30 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
     launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
     return ok();
   }
-  // The columns first: dx may replace dy or add.  Up to 512 rows a workgroup of two vector columns walks them all, which
-  // saves the launch that adds partial rows (512 x 512: 12.9 -> 10.7 us; 1024 x 1024: 13.0 -> 14.8).
-  const bool direct = rows <= 512;
+  // The columns before the rows: dx may replace dy, x or add.  Their results after the rows, as they may lie over what the
+  // rows read.  Up to 512 rows, where they do not, a workgroup of two vector columns walks all rows and writes the results
+  // itself, which saves the launch that adds partial rows (512 x 512: 12.9 -> 10.7 us; 1024 x 1024: 13.0 -> 14.8).
+  auto over_inputs = [&](const float* out) {
+    auto meets = [&](const void* in, size_t bytes) {
+      return out && in && (const char*)out < (const char*)in + bytes && (const char*)in < (const char*)(out + h);
+    };
+    const size_t tensor = (size_t)rows * h * sizeof(bf16_t);
+    return meets(dy, tensor) || meets(x, tensor) || meets(add, tensor) || meets(g, h * sizeof(bf16_t)) ||
+           meets(stats, (size_t)rows * 2 * sizeof(float));
+  };
+  const bool direct = rows <= 512 && !over_inputs(dgamma) && !over_inputs(dbeta) && !over_inputs(add_colsum);
   const int vc = direct ? 2 : 32, band = direct ? rows : LNB_ROWS;
-  const dim3 grid((h / 8 + vc - 1) / vc, direct ? 1 : parts);
   auto cols = direct ? (add_colsum ? layernorm_bwd_cols_kernel<2, true> : layernorm_bwd_cols_kernel<2, false>)
                      : (add_colsum ? layernorm_bwd_cols_kernel<32, true> : layernorm_bwd_cols_kernel<32, false>);
-  hipLaunchKernelGGL(cols, grid, dim3(256), 0, s, dy, x, stats, add, partial_ws, dgamma, dbeta, add_colsum, rows, h, band);
-  if (!direct) launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
+  hipLaunchKernelGGL(cols, dim3((h / 8 + vc - 1) / vc, direct ? 1 : parts), dim3(256), 0, s, dy, x, stats, add,
+                     direct ? nullptr : partial_ws, dgamma, dbeta, add_colsum, rows, h, band);
   auto rowk = per_lane <= 2   ? layernorm_bwd_rows_kernel<2>
               : per_lane <= 4 ? layernorm_bwd_rows_kernel<4>
               : per_lane <= 6 ? layernorm_bwd_rows_kernel<6>
               : per_lane <= 9 ? layernorm_bwd_rows_kernel<9>
                               : layernorm_bwd_rows_kernel<12>;
   hipLaunchKernelGGL(rowk, dim3((rows + 3) / 4), dim3(256), 0, s, dy, x, stats, g, add, dx, rows, h);
+  if (!direct) launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
   return ok();
 }
 

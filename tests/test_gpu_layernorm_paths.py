@@ -1,0 +1,68 @@
+"""LayerNorm backward where its launches meet: results that lie over inputs, as a caller may place them once these are not
+needed any more.  A bf16 result carries one rounding (2^-8 of the norm allowed); fp32 sums of n terms stay within
+n * 2^-24 of the terms."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import paper_2008_11421_amd as K
+
+
+@pytest.fixture(scope="module")
+def g():
+    import gpu_util
+    return gpu_util
+
+
+def problem(rows, h, seed):
+    """bf16 inputs on the device and, in float64, dx + add and the three column sums with the sums of their terms' sizes."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    make = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    x, dy, add = (make(rows, h) * 2 + 0.5).bfloat16(), make(rows, h).bfloat16(), make(rows, h).bfloat16()
+    gamma = (1 + 0.2 * make(h)).bfloat16()
+    mean = x.double().mean(1, keepdim=True)
+    rstd = 1 / (x.double().var(1, unbiased=False, keepdim=True) + 1e-5).sqrt()
+    stats = torch.cat([mean, rstd], 1).float()
+    return x, dy, add, gamma, stats
+
+
+def reference(x, dy, add, gamma, stats):
+    xh = (x.double() - stats[:, :1].double()) * stats[:, 1:].double()
+    t = dy.double() * gamma.double()
+    dx = stats[:, 1:].double() * (t - t.mean(1, keepdim=True) - xh * (t * xh).mean(1, keepdim=True)) + add.double()
+    sums = dict(dg=(dy.double() * xh), db=dy.double(), asum=add.double())
+    return dx, {name: (v.sum(0), v.abs().sum(0)) for name, v in sums.items()}
+
+
+def close_sums(got, want, rows):
+    return bool(((got.double() - want[0]).abs() <= (rows + 4) * 2.0 ** -24 * want[1] + 1e-6).all())
+
+
+def run(g, bufs, ws, rows, h):
+    g.call(K.lib().karma_k_layernorm_bwd_addsum_bf16, *(g.ptr(bufs[n]) for n in ("dy", "x", "stats", "gamma", "add", "dx", "dg", "db", "asum")),
+           g.ptr(ws), C.c_uint64(ws.numel() * 4), rows, h, g.stream_ptr())
+
+
+@pytest.mark.parametrize("rows,h", [(300, 264), (700, 264), (130, 4256), (16400, 776)])
+@pytest.mark.parametrize("out", ["dg", "db", "asum"])
+@pytest.mark.parametrize("over", ["dy", "x", "add", "stats", "gamma"])
+def test_sums_over_inputs(g, rows, h, out, over):
+    import torch
+    x, dy, add, gamma, stats = problem(rows, h, rows + h)
+    dx, sums = reference(x, dy, add, gamma, stats)
+    bufs = dict(x=x, dy=dy, add=add, stats=stats, gamma=gamma, dx=torch.empty_like(x), dg=torch.empty(h, device="cuda"),
+                db=torch.empty(h, device="cuda"), asum=torch.empty(h, device="cuda"))
+    shared = torch.zeros(max(bufs[over].numel() * bufs[over].element_size(), 4 * h) // 4, device="cuda")
+    bytes_of = lambda t: t.reshape(-1).view(torch.uint8)
+    bytes_of(shared)[:bytes_of(bufs[over]).numel()] = bytes_of(bufs[over])
+    bufs[over] = bufs[out] = shared
+    ws = torch.empty((rows + 63) // 64 * 3 * h, device="cuda")
+    run(g, bufs, ws, rows, h)
+    assert ((bufs["dx"].double() - dx).norm() / dx.norm()).item() <= 2.0 ** -8
+    for name in ("dg", "db", "asum"):
+        assert close_sums(bufs[name][:h], sums[name], rows), name
