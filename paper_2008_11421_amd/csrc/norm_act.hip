@@ -273,17 +273,18 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const bf16_t* _
 
 // Column sums: VC vector columns (8 channels each) times 256 / VC row lanes per workgroup, over a band of `band` rows;
 // the row lanes are added in ascending order.  No `partial`: one band, and these are the results (dgamma, dbeta, addsum);
-// otherwise one partial row of NS * h per band, finished as those of the kernel above.
+// otherwise one partial row of NS * h per band, finished as those of the kernel above.  Workgroup (band, column group) is
+// number band * col_groups + group of a one-dimensional grid (4 million rows are more bands than a second dimension holds).
 template <int VC, bool ADDSUM>
 __global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                   const float* __restrict__ stats, const bf16_t* __restrict__ add,
                                                                   float* __restrict__ partial, float* __restrict__ dgamma,
                                                                   float* __restrict__ dbeta, float* __restrict__ addsum, int rows,
-                                                                  int h, int band) {
+                                                                  int h, int band, int col_groups) {
   constexpr int NS = ADDSUM ? 3 : 2, RL = 256 / VC, U = 4;
   __shared__ float red[NS][RL][VC * 8];
   const int vc = threadIdx.x % VC, rl = threadIdx.x / VC;
-  const int group = blockIdx.x, part = blockIdx.y;
+  const int group = blockIdx.x % col_groups, part = blockIdx.x / col_groups;
   const int c8 = (group * VC + vc) * 8;
   const int r0 = part * band, r1 = min(rows, r0 + band);
   float sum[NS][8];
@@ -726,11 +727,11 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
            meets(stats, (size_t)rows * 2 * sizeof(float));
   };
   const bool direct = rows <= 512 && !over_inputs(dgamma) && !over_inputs(dbeta) && !over_inputs(add_colsum);
-  const int vc = direct ? 2 : 32, band = direct ? rows : LNB_ROWS;
+  const int vc = direct ? 2 : 32, band = direct ? rows : LNB_ROWS, col_groups = (h / 8 + vc - 1) / vc;
   auto cols = direct ? (add_colsum ? layernorm_bwd_cols_kernel<2, true> : layernorm_bwd_cols_kernel<2, false>)
                      : (add_colsum ? layernorm_bwd_cols_kernel<32, true> : layernorm_bwd_cols_kernel<32, false>);
-  hipLaunchKernelGGL(cols, dim3((h / 8 + vc - 1) / vc, direct ? 1 : parts), dim3(256), 0, s, dy, x, stats, add,
-                     direct ? nullptr : partial_ws, dgamma, dbeta, add_colsum, rows, h, band);
+  hipLaunchKernelGGL(cols, dim3((unsigned)col_groups * (direct ? 1u : (unsigned)parts)), dim3(256), 0, s, dy, x, stats, add,
+                     direct ? nullptr : partial_ws, dgamma, dbeta, add_colsum, rows, h, band, col_groups);
   auto rowk = per_lane <= 2   ? layernorm_bwd_rows_kernel<2>
               : per_lane <= 4 ? layernorm_bwd_rows_kernel<4>
               : per_lane <= 6 ? layernorm_bwd_rows_kernel<6>

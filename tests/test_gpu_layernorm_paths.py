@@ -1,5 +1,5 @@
 """LayerNorm backward where its launches meet: results that lie over inputs, as a caller may place them once these are not
-needed any more.  A bf16 result carries one rounding (2^-8 of the norm allowed); fp32 sums of n terms stay within
+needed any more, and more bands of rows than a grid's second dimension holds.  A bf16 result carries one rounding (2^-8 of the norm allowed); fp32 sums of n terms stay within
 n * 2^-24 of the terms."""
 import ctypes as C
 
@@ -66,3 +66,27 @@ def test_sums_over_inputs(g, rows, h, out, over):
     assert ((bufs["dx"].double() - dx).norm() / dx.norm()).item() <= 2.0 ** -8
     for name in ("dg", "db", "asum"):
         assert close_sums(bufs[name][:h], sums[name], rows), name
+
+
+def test_more_bands_than_a_second_grid_dimension_holds(g):
+    """h above 3072 takes two launches at any number of rows; 65536 bands of 64 rows and one row more."""
+    import torch
+    rows, h = 64 * 65536 + 1, 3080
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    x = torch.empty(rows, h, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    dy = torch.zeros_like(x)
+    some = torch.tensor([0, 1, 63, 64, rows // 2, rows - 66, rows - 2, rows - 1], device="cuda")
+    dy[some] = torch.randn(len(some), h, device="cuda", generator=gen).bfloat16()
+    gamma = torch.randn(h, device="cuda", generator=gen).bfloat16()
+    stats = torch.zeros(rows, 2, device="cuda")
+    stats[:, 1] = 1
+    mean = x[some].double().mean(1, keepdim=True)
+    stats[some] = torch.cat([mean, 1 / (x[some].double().var(1, unbiased=False, keepdim=True) + 1e-5).sqrt()], 1).float()
+    dx, sums = reference(x[some], dy[some], torch.zeros_like(dy[some]), gamma, stats[some])
+    dg, db, ws = torch.empty(h, device="cuda"), torch.empty(h, device="cuda"), torch.empty((rows + 63) // 64 * 3 * h, device="cuda")
+    g.call(K.lib().karma_k_layernorm_bwd_bf16, g.ptr(dy), g.ptr(x), g.ptr(stats), g.ptr(gamma), None, g.ptr(dy), g.ptr(dg), g.ptr(db),
+           g.ptr(ws), C.c_uint64(ws.numel() * 4), rows, h, g.stream_ptr())
+    assert ((dy[some].double() - dx).norm() / dx.norm()).item() <= 2.0 ** -8
+    assert close_sums(dg, sums["dg"], len(some)) and close_sums(db, sums["db"], len(some))
+    assert not dy[100].any() and not dy[rows - 100].any()
