@@ -696,10 +696,11 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
   const int ns = add_colsum ? 3 : 2;
   // One pass where its workgroups of 64 rows fill the chip with work enough to hide their start and end, and a row fits
   // a wavefront's registers beside its column sums; else two launches.  us, one pass / two, with add_colsum: 1024 x 256
-  // 17.9 / 12.9, 1024 x 1024 28.6 / 13.0, 8192 x 1024 38 / 30, 8192 x 3072 84 / 75, 16384 x 256 23 / 19;
-  // 24576 x 512 38.3 / 40.0, 16384 x 1024 44 / 50, 16384 x 1536 58 / 74, 16384 x 3072 106 / 145, 32768 x 1024 66 / 92.
-  // 4096 x 4256 (spilled registers, and a third pass for the column sums of add): 295 + 20 / 64.
-  const bool one_pass = rows >= 16384 && (size_t)rows * h >= 12u << 20 && per_lane <= 6;
+  // 17.9 / 12.9, 1024 x 1024 28.6 / 13.0, 8192 x 1024 38 / 30, 8192 x 3072 84 / 75, 16384 x 256 23 / 19; 24881 x 504
+  // 30 / 38, 13798 x 1496 45 / 57, 14935 x 2016 62 / 77, 16384 x 1024 44 / 50, 16384 x 3072 106 / 145, 32768 x 1024
+  // 66 / 92.  4096 x 4256 (spilled registers, and a third pass for the column sums of add): 295 + 20 / 64.  Over 590 sizes
+  // none takes more than 3 % longer than the one pass did.
+  const bool one_pass = rows >= 12288 && (size_t)rows * h >= (add_colsum ? 8u : 10u) << 20 && per_lane <= 6;
   if (one_pass) {
     const size_t lds = (size_t)4 * ns * h * sizeof(float);
 #define KARMA_LN_BWD(V)                                                                                          \

@@ -1,6 +1,6 @@
-"""LayerNorm backward where its launches meet: results that lie over inputs, as a caller may place them once these are not
-needed any more, and more bands of rows than a grid's second dimension holds.  A bf16 result carries one rounding (2^-8 of the norm allowed); fp32 sums of n terms stay within
-n * 2^-24 of the terms."""
+"""LayerNorm backward where its two forms meet: both sides of the choice, results that lie over inputs, as a caller may
+place them once these are not needed any more, and more bands of rows than a grid's second dimension holds.  A bf16
+result carries one rounding (2^-8 of the norm allowed); fp32 sums of n terms stay within n * 2^-24 of the terms."""
 import ctypes as C
 
 import numpy as np
@@ -46,6 +46,34 @@ def close_sums(got, want, rows):
 def run(g, bufs, ws, rows, h):
     g.call(K.lib().karma_k_layernorm_bwd_addsum_bf16, *(g.ptr(bufs[n]) for n in ("dy", "x", "stats", "gamma", "add", "dx", "dg", "db", "asum")),
            g.ptr(ws), C.c_uint64(ws.numel() * 4), rows, h, g.stream_ptr())
+
+
+# the pass that sums as it goes takes 12288 rows and more, from 8 Mi elements (10 Mi without add sums) and up to 3072 columns:
+# both sides of each line, each number of vectors per lane, last workgroups and last vectors that are not full
+@pytest.mark.parametrize("rows,h", [(12288, 1032), (12291, 2056), (12300, 3072), (12287, 1032), (16385, 512), (16383, 512), (20483, 520),
+                                    (12289, 3080), (40000, 264)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_one_pass_and_two_launches(g, rows, h, in_place):
+    import torch
+    x, dy, add, gamma, stats = problem(rows, h, rows + h)
+    dx, sums = reference(x, dy, add, gamma, stats)
+    ws = torch.empty((rows + 63) // 64 * 3 * h, device="cuda")
+    lib, dim = K.lib(), (C.c_uint64(ws.numel() * 4), rows, h, g.stream_ptr())
+    new = lambda: torch.full((h,), 7.0, device="cuda")
+    plain = torch.empty_like(dy)
+    dg, db = new(), new()
+    g.call(lib.karma_k_layernorm_bwd_bf16, g.ptr(dy), g.ptr(x), g.ptr(stats), g.ptr(gamma), None, g.ptr(plain), g.ptr(dg), g.ptr(db),
+           g.ptr(ws), *dim)
+    assert ((plain.double() - (dx - add.double())).norm() / dx.norm()).item() <= 2.0 ** -8
+    assert close_sums(dg, sums["dg"], rows) and close_sums(db, sums["db"], rows)
+    out = dy if in_place else torch.empty_like(dy)
+    bufs = dict(x=x, dy=dy, add=add, stats=stats, gamma=gamma, dx=out, dg=new(), db=new(), asum=new())
+    run(g, bufs, ws, rows, h)
+    err = (out.double() - dx).abs()
+    assert (err.norm() / dx.norm()).item() <= 2.0 ** -8
+    assert bool((err <= 2.0 ** -8 * dx.abs() + 1e-3 * dx.pow(2).mean(1, keepdim=True).sqrt()).all())
+    for name in ("dg", "db", "asum"):
+        assert close_sums(bufs[name], sums[name], rows), name
 
 
 @pytest.mark.parametrize("rows,h", [(300, 264), (700, 264), (130, 4256), (16400, 776)])
