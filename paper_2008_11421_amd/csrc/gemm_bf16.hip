@@ -932,28 +932,53 @@ static int launch_large(const GemmArgs& g, int splits, hipStream_t s) {
   return finish(g, ep, splits, s);
 }
 
-// Operands whose sizes or alignment do not allow 16-byte pieces (4-element runs), and gradients of convolutions with a
-// stride above 2: tiles go through registers.
-static int launch_general(const GemmArgs& g, hipStream_t s) {
-  constexpr int BM = 128, BN = 128, BK = 64, WGM = 2, WGN = 2;
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, tiles = tiles_m * tiles_n;
-  const int cus = compute_units() * 2;   // two workgroups per compute unit
+// The register-staged kernel's work: its tile leaves room for `places` workgroups on the chip at a time
+struct GeneralPlan {
+  int tiles_m, tiles_n, places, splits;
+};
+static GeneralPlan plan_general(const GemmArgs& g, int tile) {
+  GeneralPlan p{(g.M + tile - 1) / tile, (g.N + tile - 1) / tile, compute_units() * (tile == 128 ? 2 : 1), 1};
+  const int tiles = p.tiles_m * p.tiles_n;
   // split the reduction when the tiles alone cannot fill the chip (weight gradients: small M x N, K = tokens); partial
   // sums are reduced in a fixed order afterwards
-  int splits = 1;
-  if (g.ws && g.ldc == g.N && tiles < cus && !g.act) {
+  if (g.ws && g.ldc == g.N && tiles < p.places && !g.act) {
     // the split count that best fills whole rounds of the chip, fewer splits preferred: every split writes and re-reads
     // an M x N fp32 partial, which is weighed against the operand bytes of the whole product
-    const int max_splits = std::min(256, std::max(1, g.K / (4 * BK)));
+    const int max_splits = std::min(256, std::max(1, g.K / (4 * 64)));
     const double per_split = std::min(0.01, 0.5 * (8.0 * g.M * g.N) / (2.0 * ((double)g.M + g.N) * g.K));
     double best = -1.0;
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && (size_t)sp * g.M * g.N * sizeof(float) > g.ws_bytes) break;
-      const int items = tiles * sp, rounds = (items + cus - 1) / cus;
-      const double score = (double)items / ((double)rounds * cus) - per_split * sp;
-      if (score > best) { best = score; splits = sp; }
+      const int items = tiles * sp, rounds = (items + p.places - 1) / p.places;
+      const double score = (double)items / ((double)rounds * p.places) - per_split * sp;
+      if (score > best) { best = score; p.splits = sp; }
     }
   }
+  return p;
+}
+
+// Modelled time in us: what a round costs beside its k-tiles (more where the rows of C are no whole octets and are stored
+// element by element), and a k-tile in a full round and in one with few of the places taken, with the number of strided
+// operands, which are transposed on their way.  Fitted to 250 sizes, within 17 % (rms); the choice by it is 0.5 % behind
+// the better tile.
+static double general_us(const GemmArgs& g, const GeneralPlan& p, int tile) {
+  const bool scalar = g.N % 8 != 0, large = tile == 256;
+  const int strided = !g.a_kc + !g.b_kc;
+  const long items = (long)p.tiles_m * p.tiles_n * p.splits, full = items / p.places, rest = items % p.places;
+  const int kt = ((g.K + 63) / 64 + p.splits - 1) / p.splits;
+  const double first = large ? (scalar ? 41.0 : 10.0) : (scalar ? 19.5 : 5.5);
+  const double next = large ? (scalar ? 46.5 : 10.5) : (scalar ? 22.0 : 4.5);
+  const double k_full = large ? 2.15 : 1.25 + 0.27 * strided, k_few = large ? 1.65 + 0.26 * strided : 0.72 + 0.32 * strided;
+  double us = first + next * (full + (rest ? 1 : 0) - 1) + kt * (full * k_full + (rest ? k_few + (k_full - k_few) * rest / p.places : 0.0));
+  if (p.splits > 1) us += 3.5 + (double)p.splits * g.M * g.N * 8.0 / 5e6;
+  return us;
+}
+
+template <int BM, int BN, int WGM, int WGN>
+static int launch_general_tile(const GemmArgs& g, const GeneralPlan& p, hipStream_t s) {
+  constexpr int BK = 64;
+  const int tiles_m = p.tiles_m, tiles_n = p.tiles_n, tiles = tiles_m * tiles_n, cus = p.places;
+  int splits = p.splits;
   const int k_per_split = range_length(g.K, splits);
   const size_t lds = (size_t)2 * (BM + BN) * (BK + LDS_PAD) * sizeof(bf16_t);
   GemmEpilogue ep = epilogue_of(g);
@@ -965,9 +990,15 @@ static int launch_general(const GemmArgs& g, hipStream_t s) {
     hipLaunchKernelGGL(kern, grid, block, lds, s, g.A, g.B, g.M, g.N, g.K, g.lda, g.ldb, tiles_m, tiles_n, splits,  \
                        k_per_split, ep, (float*)g.ws, g.conv);                                          \
   } while (0)
-  if (g.conv_mode == 1) KARMA_GEMM_LAUNCH(true, true, 1, 0);
-  else if (g.conv_mode == 2) KARMA_GEMM_LAUNCH(false, false, 2, 0);
-  else if (g.act == 1) KARMA_GEMM_LAUNCH(true, true, 0, 1);
+  constexpr bool CONVS = BM == 128;   // the gathered forms exist for the small tile only
+  if (g.conv_mode) {
+    if constexpr (CONVS) {
+      if (g.conv_mode == 1) KARMA_GEMM_LAUNCH(true, true, 1, 0);
+      else KARMA_GEMM_LAUNCH(false, false, 2, 0);
+    } else {
+      return KARMA_E_INVAL;
+    }
+  } else if (g.act == 1) KARMA_GEMM_LAUNCH(true, true, 0, 1);
   else if (g.act == 2) KARMA_GEMM_LAUNCH(true, false, 0, 2);
   else if (g.a_kc && g.b_kc) KARMA_GEMM_LAUNCH(true, true, 0, 0);
   else if (g.a_kc && !g.b_kc) KARMA_GEMM_LAUNCH(true, false, 0, 0);
@@ -975,6 +1006,19 @@ static int launch_general(const GemmArgs& g, hipStream_t s) {
   else KARMA_GEMM_LAUNCH(false, false, 0, 0);
 #undef KARMA_GEMM_LAUNCH
   return finish(g, ep, splits, s);
+}
+
+// Operands whose sizes or alignment do not allow 16-byte pieces (4-element runs), and gradients of convolutions with a
+// stride above 2: tiles go through registers, of the size whose modelled time is the shorter.  us, 256 / 128: 3940 x 3084 x
+// 16304 both operands strided 617 / 934, 2836 x 4540 x 5848 254 / 309, 1156 x 5484 x 8136 with a workspace 191 / 258;
+// 2288 x 536 x 776 33 / 16.5, 132 x 236 x 776 60 / 33.
+static int launch_general(const GemmArgs& g, hipStream_t s) {
+  const GeneralPlan small = plan_general(g, 128);
+  if (!g.conv_mode && g.M > 128 && g.N > 128) {
+    const GeneralPlan large = plan_general(g, 256);
+    if (general_us(g, large, 256) < general_us(g, small, 128)) return launch_general_tile<256, 256, 2, 4>(g, large, s);
+  }
+  return launch_general_tile<128, 128, 2, 2>(g, small, s);
 }
 
 thread_local GemmTimer* g_gemm_timer = nullptr;
