@@ -486,6 +486,22 @@ int karma_k_gemm_bf16_static_ws(const void* a_dev, const void* b_dev, void* c_de
 int karma_k_gemm_gelu_bf16(const void* a_dev, const void* b_dev, void* c_dev, const void* bias_dev, void* aux_dev,
                            uint32_t m, uint32_t n, uint32_t k, uint32_t flags, uint32_t mode, void* stream);
 
+/* How a product would be carried out on 256 compute units or on the current device: one launch, or two where it is cut
+ * into whole rounds of large tiles and a rest.  Host only, needs no GPU; for tests and for reading timings.
+ * kernel: the tile and the way operands travel; m, n: rows and columns of the part; splits: ranges of the reduction.
+ * Arguments as those of karma_k_gemm_bf16 and karma_k_gemm_gelu_bf16 (gelu_mode 0: neither); misaligned != 0: operands
+ * that do not start on 16-byte boundaries.  parts_out: room for two.  Errors: KARMA_E_INVAL. */
+#define KARMA_PRODUCT_STAGED_SMALL 0u /* 128 x 128, through registers */
+#define KARMA_PRODUCT_STAGED_LARGE 1u /* 256 x 256, through registers */
+#define KARMA_PRODUCT_SMALL 2u        /* 128 x 128, straight into LDS */
+#define KARMA_PRODUCT_LARGE 3u        /* 256 x 256, straight into LDS */
+#define KARMA_PRODUCT_NARROW 4u       /* 256 x 64, straight into LDS */
+typedef struct {
+  uint32_t kernel, m, n, splits;
+} karma_product_part;
+int karma_k_gemm_plan(uint32_t m, uint32_t n, uint32_t k, uint32_t flags, uint32_t gelu_mode, uint32_t misaligned,
+                      uint64_t ws_bytes, karma_product_part* parts_out, uint32_t* n_out);
+
 /* karma_k_attention_bwd_bf16 together with the column sums of dqkv over all batch * seq tokens, colsum_out_dev fp32
  * [3 * heads * d]: the gradient of the QKV projection's bias.  They are taken inside the kernels (one row of partial
  * sums per 32 tokens, from the fp32 values).
@@ -580,6 +596,14 @@ int karma_k_conv2d_dgrad_bf16(const void* dy_dev, const void* w_dev, void* wt_ws
  * are reproducible either way. */
 int karma_k_conv2d_wgrad_bf16(const void* dy_dev, const void* x_dev, void* dw_dev, void* ws_dev, uint64_t ws_bytes,
                               const karma_conv_shape* shape, void* stream);
+
+/* karma_k_gemm_plan for a convolution's products (which: forward, input gradient, weight gradient).  A stride-2 input
+ * gradient that runs by parity of its pixels is one part. */
+#define KARMA_CONV_FWD 0u
+#define KARMA_CONV_DGRAD 1u
+#define KARMA_CONV_WGRAD 2u
+int karma_k_conv2d_plan(const karma_conv_shape* shape, uint32_t which, uint64_t ws_bytes, karma_product_part* parts_out,
+                        uint32_t* n_out);
 
 /* Training-mode batch normalisation of x_dev bf16 [rows][c] over its rows (rows = n*h*w):
  * mean and biased variance per channel, eps 1e-5; y = xhat*gamma + beta (+ add_dev, may be

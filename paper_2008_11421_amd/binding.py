@@ -19,6 +19,8 @@ STEP_PROFILE = 2
 STEP_KERNEL_TIMES = 4
 GEMM_A_STRIDED, GEMM_B_STRIDED, GEMM_OUT_F32, GEMM_ACCUMULATE = 1, 2, 4, 8
 GEMM_GELU_FWD, GEMM_GELU_BWD = 1, 2
+PRODUCT_STAGED_SMALL, PRODUCT_STAGED_LARGE, PRODUCT_SMALL, PRODUCT_LARGE, PRODUCT_NARROW = range(5)
+CONV_FWD, CONV_DGRAD, CONV_WGRAD = range(3)
 
 
 class LayerCost(C.Structure):
@@ -63,6 +65,10 @@ class ConvShape(C.Structure):
                 ("r", C.c_uint32), ("s", C.c_uint32), ("stride", C.c_uint32), ("pad", C.c_uint32)]
 
 
+class ProductPart(C.Structure):
+    _fields_ = [("kernel", C.c_uint32), ("m", C.c_uint32), ("n", C.c_uint32), ("splits", C.c_uint32)]
+
+
 class Config(C.Structure):
     _fields_ = [("optimizer", C.c_uint32), ("lr", C.c_float), ("beta1", C.c_float), ("beta2", C.c_float),
                 ("eps", C.c_float), ("host_threads", C.c_uint32), ("device_update_first", C.c_uint32)]
@@ -102,6 +108,22 @@ def lib():
         _lib.karma_destroy.restype = None
         _lib.karma_destroy.argtypes = [C.c_void_p]
     return _lib
+
+
+def _parts(fn, *args):
+    parts, n = (ProductPart * 2)(), C.c_uint32()
+    _check(fn(*args, parts, C.byref(n)), "product plan")
+    return [(p.kernel, p.m, p.n, p.splits) for p in parts[:n.value]]
+
+
+def gemm_plan(m, n, k, flags=0, gelu_mode=0, misaligned=False, ws_bytes=0):
+    """How the product would be carried out: [(kernel, rows, columns, ranges of the reduction)], one or two parts."""
+    return _parts(lib().karma_k_gemm_plan, m, n, k, flags, gelu_mode, int(misaligned), C.c_uint64(ws_bytes))
+
+
+def conv_plan(shape, which, ws_bytes=0):
+    """gemm_plan for one of a convolution's three products (CONV_FWD, CONV_DGRAD, CONV_WGRAD)."""
+    return _parts(lib().karma_k_conv2d_plan, C.byref(shape), which, C.c_uint64(ws_bytes))
 
 
 def _layers_array(layers):

@@ -558,9 +558,8 @@ bool shape_ok(const ConvShape& c) {
 
 int conv_out_dim(int n, int k, int stride, int pad) { return (n + 2 * pad - k) / stride + 1; }
 
-int conv2d_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, const ConvShape& c, hipStream_t s, void* ws, size_t ws_bytes,
-               const bf16_t* add) {
-  if (!x || !w || !y || !shape_ok(c)) return KARMA_E_INVAL;
+// The three products of a convolution (shapes were checked)
+static GemmArgs fwd_product(const bf16_t* x, const bf16_t* w, bf16_t* y, const ConvShape& c, void* ws, size_t ws_bytes, const bf16_t* add) {
   const int Ho = conv_out_dim(c.H, c.R, c.stride, c.pad), Wo = conv_out_dim(c.W, c.S, c.stride, c.pad);
   GemmArgs g{};
   g.A = x; g.B = w; g.C = y; g.residual = add;
@@ -572,14 +571,11 @@ int conv2d_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, const ConvShape& c, 
     g.conv_mode = 1;
     g.conv = ConvGather{c.H, c.W, c.Cin, Ho, Wo, c.R, c.S, c.stride, c.pad, 0};
   }
-  return gemm_bf16(g, s);
+  return g;
 }
 
-size_t conv2d_dgrad_ws_elems(const ConvShape& c) { return plain_gemm(c) ? 0 : (size_t)c.R * c.S * c.Cin * c.Cout; }
-
-int conv2d_dgrad(const bf16_t* dy, const bf16_t* w, bf16_t* wt_ws, const bf16_t* add, bf16_t* dx, const ConvShape& c,
-                 hipStream_t s, void* ws, size_t ws_bytes) {
-  if (!dy || !w || !dx || !shape_ok(c)) return KARMA_E_INVAL;
+static GemmArgs dgrad_product(const bf16_t* dy, const bf16_t* w, const bf16_t* wt, const bf16_t* add, bf16_t* dx, const ConvShape& c,
+                              void* ws, size_t ws_bytes) {
   const int Ho = conv_out_dim(c.H, c.R, c.stride, c.pad), Wo = conv_out_dim(c.W, c.S, c.stride, c.pad);
   GemmArgs g{};
   g.A = dy; g.C = dx; g.residual = add;
@@ -590,11 +586,9 @@ int conv2d_dgrad(const bf16_t* dy, const bf16_t* w, bf16_t* wt_ws, const bf16_t*
     g.K = c.Cout;
     g.a_kc = true; g.b_kc = false;
     g.lda = g.K; g.ldb = c.Cin;
-    return gemm_bf16(g, s);
+    return g;
   }
-  if (!wt_ws) return KARMA_E_INVAL;
-  const size_t n = (size_t)c.R * c.S * c.Cin * c.Cout;
-  g.B = wt_ws;          // [Cin][R*S*Cout], reduction index contiguous
+  g.B = wt;             // [Cin][R*S*Cout], reduction index contiguous
   g.K = c.R * c.S * c.Cout;
   g.a_kc = g.b_kc = true;
   g.lda = g.K; g.ldb = g.K;
@@ -602,16 +596,10 @@ int conv2d_dgrad(const bf16_t* dy, const bf16_t* w, bf16_t* wt_ws, const bf16_t*
   // rows are the pixels of x (H x W grid); the gathered tensor is dy (Ho x Wo x Cout)
   g.conv = ConvGather{Ho, Wo, c.Cout, c.H, c.W, c.R, c.S, c.stride, c.pad, 1, c.stride == 2};
   if (g.conv.phased && !gemm_ring_takes(g)) g.conv.phased = 0;
-  if (g.conv.phased)
-    hipLaunchKernelGGL(conv_weight_parity_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R, c.S, c.pad, c.Cin);
-  else
-    hipLaunchKernelGGL(conv_weight_transpose_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R * c.S, c.Cin);
-  return gemm_bf16(g, s);
+  return g;
 }
 
-int conv2d_wgrad(const bf16_t* dy, const bf16_t* x, bf16_t* dw, void* ws, size_t ws_bytes, const ConvShape& c,
-                 hipStream_t s) {
-  if (!dy || !x || !dw || !shape_ok(c)) return KARMA_E_INVAL;
+static GemmArgs wgrad_product(const bf16_t* dy, const bf16_t* x, bf16_t* dw, void* ws, size_t ws_bytes, const ConvShape& c) {
   const int Ho = conv_out_dim(c.H, c.R, c.stride, c.pad), Wo = conv_out_dim(c.W, c.S, c.stride, c.pad);
   GemmArgs g{};
   g.A = dy;             // A(m = co, k = pixel) = dy[pixel][co]: strided
@@ -625,7 +613,33 @@ int conv2d_wgrad(const bf16_t* dy, const bf16_t* x, bf16_t* dw, void* ws, size_t
     g.conv_mode = 2;
     g.conv = ConvGather{c.H, c.W, c.Cin, Ho, Wo, c.R, c.S, c.stride, c.pad, 0};
   }
+  return g;
+}
+
+int conv2d_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, const ConvShape& c, hipStream_t s, void* ws, size_t ws_bytes,
+               const bf16_t* add) {
+  if (!x || !w || !y || !shape_ok(c)) return KARMA_E_INVAL;
+  return gemm_bf16(fwd_product(x, w, y, c, ws, ws_bytes, add), s);
+}
+
+size_t conv2d_dgrad_ws_elems(const ConvShape& c) { return plain_gemm(c) ? 0 : (size_t)c.R * c.S * c.Cin * c.Cout; }
+
+int conv2d_dgrad(const bf16_t* dy, const bf16_t* w, bf16_t* wt_ws, const bf16_t* add, bf16_t* dx, const ConvShape& c,
+                 hipStream_t s, void* ws, size_t ws_bytes) {
+  if (!dy || !w || !dx || !shape_ok(c) || (!wt_ws && !plain_gemm(c))) return KARMA_E_INVAL;
+  const GemmArgs g = dgrad_product(dy, w, wt_ws, add, dx, c, ws, ws_bytes);
+  const size_t n = conv2d_dgrad_ws_elems(c);
+  if (g.conv_mode && g.conv.phased)
+    hipLaunchKernelGGL(conv_weight_parity_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R, c.S, c.pad, c.Cin);
+  else if (g.conv_mode)
+    hipLaunchKernelGGL(conv_weight_transpose_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, wt_ws, c.Cout, c.R * c.S, c.Cin);
   return gemm_bf16(g, s);
+}
+
+int conv2d_wgrad(const bf16_t* dy, const bf16_t* x, bf16_t* dw, void* ws, size_t ws_bytes, const ConvShape& c,
+                 hipStream_t s) {
+  if (!dy || !x || !dw || !shape_ok(c)) return KARMA_E_INVAL;
+  return gemm_bf16(wgrad_product(dy, x, dw, ws, ws_bytes, c), s);
 }
 
 size_t bn_ws_bytes(int rows, int c) {
@@ -756,6 +770,18 @@ extern "C" int karma_k_conv2d_wgrad_bf16(const void* dy, const void* x, void* dw
                                          const karma_conv_shape* c, void* stream) {
   if (!c) return KARMA_E_INVAL;
   return conv2d_wgrad((const bf16_t*)dy, (const bf16_t*)x, (bf16_t*)dw, ws, (size_t)ws_bytes, shape_of(c), (hipStream_t)stream);
+}
+
+extern "C" int karma_k_conv2d_plan(const karma_conv_shape* c, uint32_t which, uint64_t ws_bytes, karma_product_part* parts_out,
+                                   uint32_t* n_out) {
+  if (!c || !parts_out || !n_out || which > KARMA_CONV_WGRAD || !shape_ok(shape_of(c))) return KARMA_E_INVAL;
+  bf16_t* const at = (bf16_t*)(uintptr_t)4096;   // (addresses are only looked at)
+  void* const ws = ws_bytes ? at : nullptr;
+  const ConvShape sh = shape_of(c);
+  return gemm_plan(which == KARMA_CONV_FWD     ? fwd_product(at, at, at, sh, ws, ws_bytes, nullptr)
+                   : which == KARMA_CONV_DGRAD ? dgrad_product(at, at, at, nullptr, at, sh, ws, ws_bytes)
+                                               : wgrad_product(at, at, at, ws, ws_bytes, sh),
+                   parts_out, n_out);
 }
 
 extern "C" uint64_t karma_k_batchnorm_ws_bytes(uint32_t rows, uint32_t c) { return (uint64_t)bn_ws_bytes((int)rows, (int)c); }

@@ -975,10 +975,10 @@ static double general_us(const GemmArgs& g, const GeneralPlan& p, int tile) {
 }
 
 template <int BM, int BN, int WGM, int WGN>
-static int launch_general_tile(const GemmArgs& g, const GeneralPlan& p, hipStream_t s) {
+static int launch_general(const GemmArgs& g, int splits, hipStream_t s) {
   constexpr int BK = 64;
-  const int tiles_m = p.tiles_m, tiles_n = p.tiles_n, tiles = tiles_m * tiles_n, cus = p.places;
-  int splits = p.splits;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, tiles = tiles_m * tiles_n;
+  const int cus = compute_units() * (BM == 128 ? 2 : 1);
   const int k_per_split = range_length(g.K, splits);
   const size_t lds = (size_t)2 * (BM + BN) * (BK + LDS_PAD) * sizeof(bf16_t);
   GemmEpilogue ep = epilogue_of(g);
@@ -1006,19 +1006,6 @@ static int launch_general_tile(const GemmArgs& g, const GeneralPlan& p, hipStrea
   else KARMA_GEMM_LAUNCH(false, false, 0, 0);
 #undef KARMA_GEMM_LAUNCH
   return finish(g, ep, splits, s);
-}
-
-// Operands whose sizes or alignment do not allow 16-byte pieces (4-element runs), and gradients of convolutions with a
-// stride above 2: tiles go through registers, of the size whose modelled time is the shorter.  us, 256 / 128: 3940 x 3084 x
-// 16304 both operands strided 617 / 934, 2836 x 4540 x 5848 254 / 309, 1156 x 5484 x 8136 with a workspace 191 / 258;
-// 2288 x 536 x 776 33 / 16.5, 132 x 236 x 776 60 / 33.
-static int launch_general(const GemmArgs& g, hipStream_t s) {
-  const GeneralPlan small = plan_general(g, 128);
-  if (!g.conv_mode && g.M > 128 && g.N > 128) {
-    const GeneralPlan large = plan_general(g, 256);
-    if (general_us(g, large, 256) < general_us(g, small, 128)) return launch_general_tile<256, 256, 2, 4>(g, large, s);
-  }
-  return launch_general_tile<128, 128, 2, 2>(g, small, s);
 }
 
 thread_local GemmTimer* g_gemm_timer = nullptr;
@@ -1091,8 +1078,37 @@ int gemm_bf16(const GemmArgs& g, hipStream_t s) {
   return st;
 }
 
-static int launch_planned(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
-  return p.tile == 256 ? launch_large<256, 2, 4>(g, p.splits, s) : launch_ring(g, p.splits, p.deep, s);
+// One launch of a product (with the sum of its ranges): what gemm_choose decides and launch_piece carries out
+struct Piece {
+  GemmArgs g;
+  uint32_t kernel;   // KARMA_PRODUCT_*
+  int splits;
+  bool deep;    // the 128 x 128 tile: four stages
+};
+static Piece planned(const GemmArgs& g, const GemmPlan& p) {
+  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : KARMA_PRODUCT_SMALL, p.splits, p.deep};
+}
+static int launch_piece(const Piece& p, hipStream_t s) {
+  switch (p.kernel) {
+    case KARMA_PRODUCT_LARGE: return launch_large<256, 2, 4>(p.g, p.splits, s);
+    case KARMA_PRODUCT_NARROW: return launch_large<64, 4, 2>(p.g, p.splits, s);
+    case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, s);
+    case KARMA_PRODUCT_STAGED_LARGE: return launch_general<256, 256, 2, 4>(p.g, p.splits, s);
+    default: return launch_general<128, 128, 2, 2>(p.g, p.splits, s);
+  }
+}
+
+// Operands whose sizes or alignment do not allow 16-byte pieces (4-element runs), and gradients of convolutions with a
+// stride above 2: tiles go through registers, of the size whose modelled time is the shorter.  us, 256 / 128: 3940 x 3084 x
+// 16304 both operands strided 617 / 934, 2836 x 4540 x 5848 254 / 309, 1156 x 5484 x 8136 with a workspace 191 / 258;
+// 2288 x 536 x 776 33 / 16.5, 132 x 236 x 776 60 / 33.
+static Piece choose_general(const GemmArgs& g) {
+  const GeneralPlan small = plan_general(g, 128);
+  if (!g.conv_mode && g.M > 128 && g.N > 128) {
+    const GeneralPlan large = plan_general(g, 256);
+    if (general_us(g, large, 256) < general_us(g, small, 128)) return Piece{g, KARMA_PRODUCT_STAGED_LARGE, large.splits, false};
+  }
+  return Piece{g, KARMA_PRODUCT_STAGED_SMALL, small.splits, false};
 }
 
 // A product whose large tiles leave a last round nearly empty, cut in two along its columns or rows: as many whole tiles
@@ -1101,7 +1117,7 @@ static int launch_planned(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
 //   4096 x 4256 x 17024 (272 tiles on 256 compute units): 795 -> 681 / 492      4096 x 4256 x 4256: 187 -> 161 / 143
 //   8192 x 3072 x 12288 (one and a half rounds): 549 -> 515 / 497               8192 x 9216 x 3072: 385 -> 372
 //   12768 x 4256 x 4096: 439 -> 407
-static bool plan_cut(const GemmArgs& g, double whole_us, GemmArgs* part, GemmPlan* plan) {
+static bool plan_cut(const GemmArgs& g, double whole_us, Piece* part) {
   const int cus = compute_units(), tm = (g.M + 255) / 256, tn = (g.N + 255) / 256;
   const long whole_rounds = (long)tm * tn / cus * cus;      // tiles in them
   double best_us = 0.96 * whole_us;
@@ -1119,14 +1135,16 @@ static bool plan_cut(const GemmArgs& g, double whole_us, GemmArgs* part, GemmPla
     const double us = pa.us + pb.us + 3.0;
     if (us >= best_us) continue;
     best_us = us;
-    part[0] = a; part[1] = b;
-    plan[0] = pa; plan[1] = pb;
+    part[0] = planned(a, pa);
+    part[1] = planned(b, pb);
     found = true;
   }
   return found;
 }
 
-static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
+// Checks the arguments and decides how the product is carried out: one piece, or two.  Host only.
+static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
+  *pieces = 1;
   if (!g.A || !g.B || !g.C || g.M <= 0 || g.N <= 0 || g.K <= 0) return KARMA_E_INVAL;
   // 16-byte k-runs (k-contiguous) or 8-byte row runs (strided) must stay aligned and whole
   if ((g.a_kc || g.b_kc) && g.K % 8) return KARMA_E_INVAL;   // strided operands take any K: every k-row is bounds-checked
@@ -1150,7 +1168,10 @@ static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
     if (cg.phased && (g.conv_mode != 1 || !cg.transposed || cg.stride != 2 || !gemm_ring_takes(g))) return KARMA_E_INVAL;
   }
   const bool small = gemm_ring_takes(g);
-  if (g.conv_mode && g.conv.phased) return launch_ring(g, 1, false, s);
+  if (g.conv_mode && g.conv.phased) {
+    piece[0] = Piece{g, KARMA_PRODUCT_SMALL, 1, false};
+    return KARMA_OK;
+  }
   const bool may_split = g.ws && g.ldc == g.N && !g.act;
   bool large;
   if (g.conv_mode) {
@@ -1175,23 +1196,44 @@ static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
     // one): a 256 x 64 tile, eight wavefronts of 64 x 32, two workgroups per compute unit (a k-tile of this shape carries
     // 16 MFMAs per wavefront, less than its loads' round trip: the second workgroup multiplies while the first one waits).
     // 8 x 256 x 256 pixels, 3 x 3 x 64: 84 us, 99 us with half of a 128 x 128 tile empty.
-    if (g.conv_mode == 1 && large && g.N == 64 && (g.M + 255) / 256 >= 384) return launch_large<64, 4, 2>(g, 1, s);
+    if (g.conv_mode == 1 && large && g.N == 64 && (g.M + 255) / 256 >= 384) {
+      piece[0] = Piece{g, KARMA_PRODUCT_NARROW, 1, false};
+      return KARMA_OK;
+    }
     // below 128 output channels most of the large tile is empty
     if (g.conv_mode == 1 && g.N < 128) large = false;
   } else {
     large = large_tile_takes(g);
   }
-  if (!large && !small) return launch_general(g, s);
-  const GemmPlan p = plan_product(g, large, small, may_split);
-  if (large && small && !g.conv_mode && !g.colsum_partial) {
-    GemmArgs part[2];
-    GemmPlan plan[2];
-    if (plan_cut(g, p.us, part, plan)) {
-      const int st = launch_planned(part[0], plan[0], s);
-      return st ? st : launch_planned(part[1], plan[1], s);
-    }
+  if (!large && !small) {
+    piece[0] = choose_general(g);
+    return KARMA_OK;
   }
-  return launch_planned(g, p, s);
+  const GemmPlan p = plan_product(g, large, small, may_split);
+  if (large && small && !g.conv_mode && !g.colsum_partial && plan_cut(g, p.us, piece)) *pieces = 2;
+  else piece[0] = planned(g, p);
+  return KARMA_OK;
+}
+
+static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
+  Piece piece[2];
+  int pieces = 0, st = gemm_choose(g, piece, &pieces);
+  for (int i = 0; i < pieces && st == KARMA_OK; ++i) st = launch_piece(piece[i], s);
+  return st;
+}
+
+int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n) {
+  Piece piece[2];
+  int pieces = 0;
+  const int st = gemm_choose(g, piece, &pieces);
+  if (st != KARMA_OK) return st;
+  for (int i = 0; i < pieces; ++i) {
+    int splits = piece[i].splits;
+    (void)range_length(piece[i].g.K, splits);   // (ranges are whole k-tiles: the last may come to nothing)
+    parts[i] = karma_product_part{piece[i].kernel, (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
+  }
+  *n = (uint32_t)pieces;
+  return KARMA_OK;
 }
 
 }  // namespace karma
@@ -1245,9 +1287,8 @@ extern "C" int karma_k_gemm_gelu_bwd_colsum_bf16(const void* a, const void* b, v
   return colsum_bf16((const bf16_t*)c, colsum_out, ws, (int)m, (int)n, (hipStream_t)stream);
 }
 
-extern "C" int karma_k_gemm_bf16(const void* a, const void* b, void* c, const void* bias, const void* residual,
-                                 uint32_t m, uint32_t n, uint32_t k, uint32_t flags, void* ws, uint64_t ws_bytes,
-                                 void* stream) {
+static GemmArgs product_args(const void* a, const void* b, void* c, const void* bias, const void* residual, uint32_t m, uint32_t n,
+                             uint32_t k, uint32_t flags, void* ws, uint64_t ws_bytes) {
   GemmArgs g{};
   g.A = (const bf16_t*)a;
   g.B = (const bf16_t*)b;
@@ -1264,7 +1305,23 @@ extern "C" int karma_k_gemm_bf16(const void* a, const void* b, void* c, const vo
   g.accumulate = (flags & KARMA_GEMM_ACCUMULATE) != 0;
   g.ws = ws;
   g.ws_bytes = ws ? (size_t)ws_bytes : 0;
-  return gemm_bf16(g, (hipStream_t)stream);
+  return g;
+}
+
+extern "C" int karma_k_gemm_bf16(const void* a, const void* b, void* c, const void* bias, const void* residual,
+                                 uint32_t m, uint32_t n, uint32_t k, uint32_t flags, void* ws, uint64_t ws_bytes,
+                                 void* stream) {
+  return gemm_bf16(product_args(a, b, c, bias, residual, m, n, k, flags, ws, ws_bytes), (hipStream_t)stream);
+}
+
+extern "C" int karma_k_gemm_plan(uint32_t m, uint32_t n, uint32_t k, uint32_t flags, uint32_t gelu_mode, uint32_t misaligned,
+                                 uint64_t ws_bytes, karma_product_part* parts_out, uint32_t* n_out) {
+  if (!parts_out || !n_out || gelu_mode > KARMA_GEMM_GELU_BWD) return KARMA_E_INVAL;
+  void* const somewhere = (void*)(uintptr_t)(4096 + (misaligned ? 8 : 0));   // (addresses are only looked at)
+  GemmArgs g = product_args(somewhere, somewhere, somewhere, nullptr, nullptr, m, n, k, flags, ws_bytes ? somewhere : nullptr, ws_bytes);
+  g.act = (int)gelu_mode;
+  g.aux = gelu_mode ? somewhere : nullptr;
+  return gemm_plan(g, parts_out, n_out);
 }
 
 // ---- the product for callers that cannot allocate -------------------------------------------

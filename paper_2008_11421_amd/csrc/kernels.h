@@ -8,6 +8,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "karma.h"
+
 namespace karma {
 
 typedef uint16_t bf16_t;   // bit pattern of a bfloat16
@@ -64,6 +66,8 @@ struct GemmArgs {
   int* colsum_rows;
 };
 int gemm_bf16(const GemmArgs& g, hipStream_t s);
+// How gemm_bf16 would carry the product out (at most two parts; host only, addresses are looked at and not followed)
+int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n);
 // While non-null on the calling thread, gemm_bf16 calls record an event before and after
 // their launch (pairs appended from *used on, created on demand) and their flop count: the
 // benchmark's per-launch timing of the dominant kernel.  One call in `stride` is timed (the

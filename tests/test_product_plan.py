@@ -1,0 +1,94 @@
+"""The choice of kernel, ranges and cut of a bf16 product (karma_k_gemm_plan, karma_k_conv2d_plan), over the whole range of
+sizes, layouts and workspaces: parts cover the product once, partial sums fit the workspace, and a kernel is given only
+what it takes."""
+import random
+
+import pytest
+
+import paper_2008_11421_amd as K
+
+A, B = K.GEMM_A_STRIDED, K.GEMM_B_STRIDED
+
+
+def log_int(rng, lo, hi, step=1):
+    return max(lo, int(2 ** rng.uniform(lo.bit_length() - 1, hi.bit_length() - 1)) // step * step)
+
+
+def check(parts, m, n, k, ws, may_split, pieces16, gathered=False):
+    assert 1 <= len(parts) <= 2
+    if len(parts) == 1:
+        assert parts[0][1:3] == (m, n)
+    else:       # cut along whole large tiles; the first part is whole rounds of them, undivided
+        (k0, m0, n0, s0), (_, m1, n1, _) = parts
+        assert k0 == K.PRODUCT_LARGE and s0 == 1
+        assert (m0 == m1 == m and n0 + n1 == n and n0 % 256 == 0) or (n0 == n1 == n and m0 + m1 == m and m0 % 256 == 0)
+    for kernel, pm, pn, splits in parts:
+        assert 1 <= splits <= max(1, (k + 63) // 64)
+        assert splits == 1 or (may_split and splits * pm * pn * 4 <= ws)
+        if not pieces16:
+            assert kernel in (K.PRODUCT_STAGED_SMALL, K.PRODUCT_STAGED_LARGE)
+        if kernel == K.PRODUCT_LARGE and not gathered:
+            assert pm >= 256 and pn >= 256 and k >= 128 and pm % 8 == 0 and pn % 8 == 0 and k % 8 == 0
+        if kernel == K.PRODUCT_STAGED_LARGE:
+            assert pm > 128 and pn > 128 and not gathered
+
+
+def test_products_over_the_whole_range():
+    rng = random.Random(11)
+    seen = set()
+    for _ in range(3000):
+        flags, mode = rng.choice([(0, 0), (A, 0), (B, 0), (A | B, 0), (0, K.GEMM_GELU_FWD), (B, K.GEMM_GELU_BWD)])
+        step = rng.choice([1, 4, 8, 8, 256])
+        m = log_int(rng, 1, 40000, max(step, 4) if flags & A else step)
+        n = log_int(rng, 1, 40000, max(step, 4) if flags & B else step)
+        m, n = max(m, 4 if flags & A else 1), max(n, 4 if flags & B else 1)
+        k = max(8, log_int(rng, 8, 40000, rng.choice([8, 64])))
+        misaligned, ws = rng.random() < 0.2, rng.choice([0, 4 * m * n, 8 * m * n, 64 << 20])
+        parts = K.gemm_plan(m, n, k, flags, mode, misaligned, ws)
+        pieces16 = not misaligned and (not flags & A or m % 8 == 0) and (not flags & B or n % 8 == 0)
+        check(parts, m, n, k, ws, mode == 0, pieces16)
+        seen.add((parts[0][0], len(parts), parts[-1][3] > 1))
+    assert {kernel for kernel, _, _ in seen} == {K.PRODUCT_STAGED_SMALL, K.PRODUCT_STAGED_LARGE, K.PRODUCT_SMALL, K.PRODUCT_LARGE}
+    assert any(pieces == 2 for _, pieces, _ in seen) and any(divided for _, _, divided in seen)
+
+
+def test_convolutions_over_the_whole_range():
+    rng = random.Random(12)
+    seen = set()
+    for _ in range(3000):
+        c = K.ConvShape(log_int(rng, 1, 256), log_int(rng, 1, 600), log_int(rng, 1, 600), log_int(rng, 8, 1024, 8), log_int(rng, 8, 1024, 8),
+                        *([rng.choice([1, 2, 3, 3, 5, 7])] * 2), rng.choice([1, 1, 2, 2, 3]), rng.choice([0, 0, 1, 3]))
+        ho, wo = (c.h + 2 * c.pad - c.r) // c.stride + 1, (c.w + 2 * c.pad - c.s) // c.stride + 1
+        if c.h + 2 * c.pad < c.r or c.w + 2 * c.pad < c.s or max(c.n * c.h * c.w, c.n * ho * wo) >= 1 << 26:
+            continue
+        plain = c.r == 1 and c.stride == 1 and c.pad == 0
+        for which, (m, n, k) in enumerate([(c.n * ho * wo, c.c_out, c.r * c.s * c.c_in), (c.n * c.h * c.w, c.c_in, c.r * c.s * c.c_out),
+                                           (c.c_out, c.r * c.s * c.c_in, c.n * ho * wo)]):
+            ws = rng.choice([0, 16 * c.c_out * c.r * c.s * c.c_in * 4])
+            parts = K.conv_plan(c, which, ws)
+            check(parts, m, n, k, ws, True, True if plain else parts[0][0] >= K.PRODUCT_SMALL, gathered=not plain)
+            bytes_gathered = 2 * c.n * (ho * wo * c.c_out if which == K.CONV_DGRAD else c.h * c.w * c.c_in)
+            if not plain and (bytes_gathered >= 1 << 32 or (which == K.CONV_DGRAD and c.stride == 3)):
+                assert parts[0][0] == K.PRODUCT_STAGED_SMALL
+            seen.add((which, parts[0][0]))
+    assert {(w, k) for w in range(3) for k in (K.PRODUCT_STAGED_SMALL, K.PRODUCT_SMALL, K.PRODUCT_LARGE)} <= seen
+
+
+@pytest.mark.parametrize("args", [(8, 8, 12, 0), (6, 8, 8, A), (8, 6, 8, B), (0, 8, 8, 0), (8, 8, 8, A, K.GEMM_GELU_FWD), (8, 8, 8, 0, K.GEMM_GELU_BWD)])
+def test_what_a_product_refuses_its_plan_refuses(args):
+    with pytest.raises(Exception):
+        K.gemm_plan(*args)
+
+
+def test_known_routes():
+    # the last round of large tiles nearly empty: cut along columns, the rest divided where there is room
+    assert K.gemm_plan(4096, 4256, 17024) == [(K.PRODUCT_LARGE, 4096, 4096, 1), (K.PRODUCT_SMALL, 4096, 160, 1)]
+    assert K.gemm_plan(4096, 4256, 17024, ws_bytes=64 << 20)[1][3] > 1
+    assert K.gemm_plan(32768, 4096, 1024) == [(K.PRODUCT_LARGE, 32768, 4096, 1)]
+    assert K.gemm_plan(64, 1000, 2048)[0][0] == K.PRODUCT_SMALL
+    assert K.gemm_plan(132, 236, 776, misaligned=True)[0][0] == K.PRODUCT_STAGED_SMALL
+    assert K.gemm_plan(3940, 3084, 16304, A | B)[0][0] == K.PRODUCT_STAGED_LARGE
+    # 64 output channels on large images
+    assert K.conv_plan(K.ConvShape(8, 256, 256, 64, 64, 3, 3, 1, 1), K.CONV_FWD)[0][0] == K.PRODUCT_NARROW
+    # a stride-2 input gradient by parity, and one whose tensor is beyond 32-bit offsets
+    assert K.conv_plan(K.ConvShape(32, 57, 57, 96, 192, 3, 3, 2, 1), K.CONV_DGRAD) == [(K.PRODUCT_SMALL, 32 * 57 * 57, 96, 1)]
