@@ -837,16 +837,24 @@ struct GemmPlan {
 
 // The cheaper of the two tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
 // item for every place on the chip (one per compute unit with the 256 tile, two with the 128 tile); a k-tile of 64 costs,
-// in a full round and with the places of the last one partly empty, what was measured on products from 64 x 1000 x 2048
-// to 8192 x 3072 x 3072 and on convolutions (all within 15 %): 1.5 us down to 1.25 us for the large tile (2.0 to 1.4 where
-// its first operand is gathered), 1.0 us for two workgroups of the small tile per compute unit, 0.45 to 0.6 us for one.
-// Dividing the reduction costs a launch and two trips of M x N floats per range through memory at 5 TB/s.
+// in a full round and with the places of the last one partly empty, what was measured on 500 products from 64 x 1000 x
+// 2048 to 8192 x 3072 x 3072 and 470 convolutions: 1.5 us down to 1.25 us for the large tile (2.0 to 1.4 where its first
+// operand is gathered), 1.0 us for two workgroups of the small tile per compute unit, 0.45 to 0.6 us for one that has the
+// unit to itself with four stages, 0.75 with two, 15 % more where it gathers.  The choice is 0.5 % (products, weight
+// gradients) and 0.3 % (gathered first operand) behind the better tile, and no size measured was more than 5 % slower than
+// with the large tile alone.  Rows of C that are no whole octets are stored element by element, unless the reduction is
+// divided.  Dividing it costs a launch and two trips of M x N floats per range through memory at 5 TB/s.
 //   4096 x 1024 x 1024: 256 tile, 8 ranges 46.7 us -> 128 tile 13.9 us     3072 x 3072 x 8192: 275 -> 181 us
 //   3000 x 2344 x 1416: 58.5 -> 34 us     4096 x 4096 x 4096: 108 us with the 256 tile, 132 us with the 128 tile
+//   4808 x 1824 x 2032 (570 small tiles, 152 large ones): 55 us with the 256 tile, 73 us with the 128 tile
+//   5 x 5 convolution, stride 2, 30 x 93 x 93, 232 -> 232 channels: 190 us and 225 us
+// The calculation itself takes 0.4 to 1.9 us on the host.
 static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may_split) {
   const int cus = compute_units(), k_tiles = (g.K + 63) / 64;
   const double full256 = g.conv_mode == 1 ? 2.0 : 1.5, alone256 = g.conv_mode == 1 ? 1.4 : 1.25;
+  const double gather128 = g.conv_mode == 1 ? 1.15 : 1.0, lone128 = g.conv_mode == 1 ? 0.85 : 0.75;
   const double ragged = g.M % 256 || g.N % 256 || g.K % 64 ? 1.05 : 1.0;
+  const double by_element = g.N % 8 || g.ldc % 8 ? std::min(1.0, g.M / 128.0) : 0.0;
   GemmPlan best{0, 1, false, 1e30};
   const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
   for (int tile = 128; tile <= 256; tile += 128) {
@@ -863,7 +871,11 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
         us = 9.0 + 4.0 * (rounds - 1) + ragged * kt * (full * full256 + (rest ? alone256 + (full256 - alone256) * f : 0.0));
       } else {
         const double f = (double)rest / cus;   // workgroups per compute unit in the last round
-        us = 5.5 + 2.5 * (rounds - 1) + kt * (full * 1.0 + (!rest ? 0.0 : f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0)));
+        double last = 0.0;
+        if (rest && full) last = f <= 1.0 ? lone128 : lone128 + (1.0 - lone128) * (f - 1.0);
+        else if (rest) last = f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0);
+        us = 5.5 + 2.5 * (rounds - 1) + gather128 * kt * (full + last);
+        if (sp == 1) us += by_element * (14.0 + 17.5 * (rounds - 1));
       }
       if (sp > 1) us += 3.5 + (double)sp * g.M * g.N * 8.0 / 5e6;
       // (four stages instead of two: 1000 x 1000 x 4000 in 33 us instead of 47, one k-tile in flight per workgroup having
@@ -1207,6 +1219,13 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
   }
   if (!large && !small) {
     piece[0] = choose_general(g);
+    return KARMA_OK;
+  }
+  // Results whose rows are no whole octets do without the large tile's direct loads.  From 0.3 TFLOP on the register-staged
+  // large tile is ahead of the small one all the same: 3280 x 4331 x 12184 433 / 488 us, 7346 x 9171 x 8224 1479 / 1607,
+  // 2701 x 7687 x 6112 (0.25) 257 / 193.
+  if (!g.conv_mode && !large && g.N % 8 && g.M > 128 && g.N > 128 && (double)g.M * g.N * g.K >= 1.5e11) {
+    piece[0] = Piece{g, KARMA_PRODUCT_STAGED_LARGE, plan_general(g, 256).splits, false};
     return KARMA_OK;
   }
   const GemmPlan p = plan_product(g, large, small, may_split);
