@@ -1228,6 +1228,13 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
     piece[0] = Piece{g, KARMA_PRODUCT_STAGED_LARGE, plan_general(g, 256).splits, false};
     return KARMA_OK;
   }
+  // One k-tile, one column of tiles and more than a round of them: nothing to pipeline within an item, and the staged
+  // kernel's workgroups, which stay for several, fetch the next item before they write one out.  us, small / staged:
+  // 1954597 x 64 x 32 158 / 124, 475061 x 40 x 32 36 / 31, 224225 x 32 x 48 18 / 16; 242215 x 88 x 72 26 / 28.
+  if (!g.conv_mode && g.a_kc && g.b_kc && g.K <= 64 && g.N <= 128 && (g.M + 127) / 128 > 2 * compute_units()) {
+    piece[0] = Piece{g, KARMA_PRODUCT_STAGED_SMALL, 1, false};
+    return KARMA_OK;
+  }
   const GemmPlan p = plan_product(g, large, small, may_split);
   if (large && small && !g.conv_mode && !g.colsum_partial && plan_cut(g, p.us, piece)) *pieces = 2;
   else piece[0] = planned(g, p);

@@ -56,6 +56,23 @@ def test_layouts(g, m, n, k, off, flags, with_ws):
     assert (guard[0] == 7).all() and (guard[-1] == 7).all()
 
 
+@pytest.mark.parametrize("m,n,k", [(65537, 8, 8), (65664, 128, 64), (140001, 37, 24)])
+def test_one_k_tile_and_one_column_of_tiles(g, m, n, k):
+    import torch
+    assert K.gemm_plan(m, n, k) == [(K.PRODUCT_STAGED_SMALL, m, n, 1)]
+    a, av = operand(m, k, False, 0, 9)
+    b, bv = operand(n, k, False, 0, 10)
+    bias, bias_v = operand(n, 1, False, 0, 11)
+    res, res_v = operand(m, n, False, 0, 12)
+    guard = torch.full((m + 2, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = guard[1:-1]
+    g.call(K.lib().karma_k_gemm_bf16, g.ptr(a), g.ptr(b), g.ptr(out), g.ptr(bias), g.ptr(res), m, n, k, 0, None, C.c_uint64(0),
+           g.stream_ptr())
+    want = av @ bv.T + bias_v.T + res_v
+    assert ((out.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all()
+    assert (guard[0] == 7).all() and (guard[-1] == 7).all()
+
+
 @pytest.mark.parametrize("m,n,k", [(264, 520, 136), (3844, 4092, 1032)])
 def test_output_stages(g, m, n, k):
     import torch

@@ -103,3 +103,10 @@ def test_tiles_that_leave_a_round_nearly_empty_are_not_split_finer():
     assert K.gemm_plan(77, 2647, 616, ws_bytes=64 << 20)[0][3] > 1
     assert K.gemm_plan(7346, 9171, 8224)[0][0] == K.PRODUCT_STAGED_LARGE
     assert K.gemm_plan(2701, 7687, 6112)[0][0] == K.PRODUCT_SMALL
+
+
+def test_one_k_tile_and_one_column_of_tiles():
+    for m, n, k, kernel in [(475061, 40, 32, K.PRODUCT_STAGED_SMALL), (65537, 128, 64, K.PRODUCT_STAGED_SMALL), (65536, 128, 64, K.PRODUCT_SMALL),
+                            (475061, 136, 32, K.PRODUCT_SMALL), (475061, 40, 72, K.PRODUCT_SMALL)]:
+        assert K.gemm_plan(m, n, k)[0][0] == kernel
+    assert K.gemm_plan(475064, 40, 32, B)[0][0] == K.PRODUCT_SMALL
