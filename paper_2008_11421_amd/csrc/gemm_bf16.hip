@@ -1129,6 +1129,8 @@ static Piece choose_general(const GemmArgs& g) {
 //   4096 x 4256 x 17024 (272 tiles on 256 compute units): 795 -> 681 / 492      4096 x 4256 x 4256: 187 -> 161 / 143
 //   8192 x 3072 x 12288 (one and a half rounds): 549 -> 515 / 497               8192 x 9216 x 3072: 385 -> 372
 //   12768 x 4256 x 4096: 439 -> 407
+// From 1024 k on: below, writing the tiles out is most of a round, and the model puts that too low (412776 x 560 x 216:
+// 290 -> 325, 4512 x 8128 x 680: 72, 68 with the small tile throughout).
 static bool plan_cut(const GemmArgs& g, double whole_us, Piece* part) {
   const int cus = compute_units(), tm = (g.M + 255) / 256, tn = (g.N + 255) / 256;
   const long whole_rounds = (long)tm * tn / cus * cus;      // tiles in them
@@ -1236,7 +1238,7 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
     return KARMA_OK;
   }
   const GemmPlan p = plan_product(g, large, small, may_split);
-  if (large && small && !g.conv_mode && !g.colsum_partial && plan_cut(g, p.us, piece)) *pieces = 2;
+  if (large && small && !g.conv_mode && !g.colsum_partial && g.K >= 1024 && plan_cut(g, p.us, piece)) *pieces = 2;
   else piece[0] = planned(g, p);
   return KARMA_OK;
 }

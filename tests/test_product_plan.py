@@ -110,3 +110,9 @@ def test_one_k_tile_and_one_column_of_tiles():
                             (475061, 136, 32, K.PRODUCT_SMALL), (475061, 40, 72, K.PRODUCT_SMALL)]:
         assert K.gemm_plan(m, n, k)[0][0] == kernel
     assert K.gemm_plan(475064, 40, 32, B)[0][0] == K.PRODUCT_SMALL
+
+
+def test_short_reductions_are_not_cut():
+    assert K.gemm_plan(412776, 560, 216) == [(K.PRODUCT_LARGE, 412776, 560, 1)]
+    assert all(len(K.gemm_plan(m, n, k)) == 1 for m, n, k in [(4512, 8128, 680), (6296, 5624, 840), (4096, 4256, 1016)])
+    assert len(K.gemm_plan(4096, 4256, 1024)) == 2
