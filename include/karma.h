@@ -512,9 +512,10 @@ int karma_k_attention_bwd_colsum_bf16(const void* qkv_dev, const void* ctx_dev, 
                                       void* stream);
 
 /* KARMA_GEMM_GELU_BWD (b_dev strided) together with the column sums of its result, colsum_out_dev[j] = sum over i
- * of c[i][j], fp32 [n]: the gradient of the bias of the layer whose pre-activation aux_dev holds.  Whole 256-tiles
- * take the sums in the kernel's output stage (from the fp32 values, before they are rounded to bf16); other shapes
- * run the product and then sum the stored bf16 result.  ws_dev: ceil(m/64)*n floats (KARMA_E_OOM if smaller). */
+ * of c[i][j], fp32 [n]: the gradient of the bias of the layer whose pre-activation aux_dev holds.  Products whose
+ * operands come in 16-byte pieces take the sums in the kernel's output stage (from the fp32 values, before they are
+ * rounded to bf16); other shapes, and products of up to 64 rows, run the product and then sum the stored bf16
+ * result.  ws_dev: ceil(m/64)*n floats (KARMA_E_OOM if smaller). */
 int karma_k_gemm_gelu_bwd_colsum_bf16(const void* a_dev, const void* b_dev, void* c_dev, const void* aux_dev,
                                       float* colsum_out_dev, float* ws_dev, uint64_t ws_bytes, uint32_t m, uint32_t n,
                                       uint32_t k, void* stream);

@@ -912,6 +912,12 @@ static bool large_tile_takes(const GemmArgs& g) {
 static GemmEpilogue epilogue_of(const GemmArgs& g) {
   return GemmEpilogue{g.C, g.bias, g.residual, g.ldc, g.out_f32, g.accumulate, (bf16_t*)g.aux, nullptr};
 }
+// Column sums of the result, `rows` partial rows of them, where the caller asked for them and gave room
+static void take_colsum(const GemmArgs& g, int rows, GemmEpilogue& ep) {
+  if (g.act != 2 || !g.colsum_partial || !g.colsum_rows || g.ldc != g.N || g.N % 8 || (size_t)rows * g.N * sizeof(float) > g.colsum_bytes) return;
+  ep.colsum = g.colsum_partial;
+  *g.colsum_rows = rows;
+}
 // k per range: whole k-tiles, and the number of ranges that are then not empty
 static int range_length(int K, int& splits) {
   const int len = ((K + splits - 1) / splits + 63) / 64 * 64;
@@ -930,10 +936,7 @@ static int launch_large(const GemmArgs& g, int splits, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const int k_per_split = range_length(g.K, splits);
   GemmEpilogue ep = epilogue_of(g);
-  if (g.act == 2 && g.colsum_partial && splits == 1 && g.ldc == g.N) {
-    ep.colsum = g.colsum_partial;
-    if (g.colsum_rows) *g.colsum_rows = tiles_m * WGM;
-  }
+  if (splits == 1) take_colsum(g, tiles_m * WGM, ep);
   // a multiple of 8 workgroups, at most what runs at once: the kernel deals work items out per XCD
   const int cus = compute_units() * (BN == 64 ? 2 : 1);
   const dim3 grid(std::min((tiles_m * tiles_n * splits + 7) / 8 * 8, std::max(8, cus / 8 * 8))), block(WGM * WGN * 64);
@@ -1028,12 +1031,7 @@ static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s);
 static int launch_ring(const GemmArgs& g, int splits, bool deep, hipStream_t s) {
   const int k_per_split = range_length(g.K, splits);
   GemmEpilogue ep = epilogue_of(g);
-  const int tiles_m = (g.M + RING_TILE - 1) / RING_TILE;
-  // (two rows of sums per tile: not where that is more than the caller's room of one per 64 rows)
-  if (g.act == 2 && g.colsum_partial && splits == 1 && g.ldc == g.N && g.N % 8 == 0 && 2 * tiles_m <= (g.M + 63) / 64) {
-    ep.colsum = g.colsum_partial;
-    if (g.colsum_rows) *g.colsum_rows = 2 * tiles_m;
-  }
+  if (splits == 1) take_colsum(g, 2 * ((g.M + RING_TILE - 1) / RING_TILE), ep);
   RingConv rc{};
   if (g.conv_mode) {
     const ConvGather& cg = g.conv;
@@ -1308,6 +1306,7 @@ extern "C" int karma_k_gemm_gelu_bwd_colsum_bf16(const void* a, const void* b, v
   g.aux = const_cast<void*>(aux);
   int rows = 0;
   g.colsum_partial = ws;
+  g.colsum_bytes = colsum_ws_bytes((int)m, (int)n);
   g.colsum_rows = &rows;
   int st = gemm_bf16(g, (hipStream_t)stream);
   if (st) return st;

@@ -59,10 +59,12 @@ struct GemmArgs {
   // act 2: C = (A B^T) * GELU'(aux), aux (read) holding the pre-activation.  bf16 C, no residual, no split.
   int act;
   void* aux;
-  // act 2, optional: room for ceil(M / 128) rows of N floats.  When the product runs on the kernel that can do
-  // it, partial column sums of C (fp32, before rounding) are left there and *colsum_rows (preset to 0 by the
-  // caller) is set to their number; colsum_finish adds them up.  Otherwise nothing is written.
+  // act 2, optional: colsum_bytes of room at colsum_partial.  When the product runs on a kernel that can do it and its
+  // sums fit there (two rows of N floats per row of tiles, which are 256 or 128 rows of C), partial column sums of C
+  // (fp32, before rounding) are left there and *colsum_rows (preset to 0 by the caller) is set to the number of rows;
+  // colsum_finish adds them up.  Otherwise nothing is written.
   float* colsum_partial;
+  size_t colsum_bytes;
   int* colsum_rows;
 };
 int gemm_bf16(const GemmArgs& g, hipStream_t s);

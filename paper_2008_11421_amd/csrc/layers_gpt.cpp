@@ -144,7 +144,7 @@ int gemm(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, const bf
 // the product with the feed-forward GELU folded into its output stage (mode 1: aux = GELU(C) written;
 // mode 2: C = (A B^T) * GELU'(aux))
 int gemm_gelu(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, bf16_t* aux, int M, int N, int K, bool a_kc,
-              bool b_kc, int mode, hipStream_t s, float* colsum_partial = nullptr, int* colsum_rows = nullptr) {
+              bool b_kc, int mode, hipStream_t s, float* colsum_partial = nullptr, size_t colsum_bytes = 0, int* colsum_rows = nullptr) {
   GemmArgs g{};
   g.A = A; g.B = B; g.C = C; g.bias = bias;
   g.M = M; g.N = N; g.K = K;
@@ -155,6 +155,7 @@ int gemm_gelu(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, bf1
   g.act = mode;
   g.aux = aux;
   g.colsum_partial = colsum_partial;
+  g.colsum_bytes = colsum_bytes;
   g.colsum_rows = colsum_rows;
   return gemm_bf16(g, s);
 }
@@ -302,7 +303,7 @@ int ffn_half_bwd(const Dims& d, const bf16_t* dy, const bf16_t* r1, const FfnBuf
                  GF G, hipStream_t s) {
   // df1 = (dy W2) * GELU'(f1); where the kernel can, it leaves partial column sums of df1 (FC1's bias gradient)
   int sum_rows = 0;
-  TRY(gemm_gelu(dy, W(W2), w.wide, nullptr, b.f1, d.T, d.ffn, d.h, true, false, 2, s, w.part, &sum_rows));
+  TRY(gemm_gelu(dy, W(W2), w.wide, nullptr, b.f1, d.T, d.ffn, d.h, true, false, 2, s, w.part, colsum_ws_bytes(d.T, d.ffn), &sum_rows));
   if (sum_rows) TRY(colsum_finish(w.part, sum_rows, d.ffn, (float*)G(B1), s));
   TRY(gemm(dy, b.g, G(W2), nullptr, nullptr, d.h, d.ffn, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));        // dW2 = dy^T g
   TRY(gemm(w.wide, W(W1), w.t1, nullptr, nullptr, d.T, d.h, d.ffn, true, false, false, false, s, w.splitk, w.splitk_bytes));  // dm = df1 W1
