@@ -566,8 +566,8 @@ int karma_k_sum_f32(const float* x_dev, float* out_dev, float* ws_dev, uint64_t 
  * seq must be a multiple of 128, d 64, 128 or 152 (else KARMA_E_INVAL). */
 int karma_k_attention_fwd_bf16(const void* qkv_dev, void* ctx_dev, float* lse_dev, uint32_t batch, uint32_t seq,
                                uint32_t heads, uint32_t d, void* stream);
-/* Its backward: dqkv_dev (same layout as qkv) from dctx_dev, the forward's ctx and lse.
- * delta_ws_dev: batch*heads*seq floats of workspace.  No atomics: results are reproducible. */
+/* Its backward: dqkv_dev (same layout as qkv) from dctx_dev, the forward's ctx and lse.  dqkv_dev may lie over ctx_dev
+ * (a launch more).  delta_ws_dev: batch*heads*seq floats of workspace.  No atomics: results are reproducible. */
 int karma_k_attention_bwd_bf16(const void* qkv_dev, const void* ctx_dev, const void* dctx_dev, const float* lse_dev,
                                float* delta_ws_dev, void* dqkv_dev, uint32_t batch, uint32_t seq, uint32_t heads,
                                uint32_t d, void* stream);

@@ -344,11 +344,32 @@ __global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __rest
   if (g == 0) lse[((size_t)b * H + head) * S + query] = m * c + log2f(l);
 }
 
+// ------------------------------------------------------------------ backward: delta
+// delta[b][head][q] = sum_d dO[b][q][head*D + d] * O[b][q][head*D + d], in a launch of its own where dqkv lies over ctx
+__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
+                                                         float* __restrict__ delta, int S, int H, int D, size_t total) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;   // (b, q, head), head fastest
+  if (i >= total) return;
+  const int head = (int)(i % H);
+  const size_t bq = i / H, q = bq % S, b = bq / S;
+  const bf16_t* po = o + (bq * H + head) * D;
+  const bf16_t* pd = dout + (bq * H + head) * D;
+  float acc = 0.f;
+  for (int v = 0; v < D; v += 8) {
+    float a[8], d[8];
+    unpack8(*(const u32x4*)(po + v), a);
+    unpack8(*(const u32x4*)(pd + v), d);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = fmaf(a[e], d[e], acc);
+  }
+  delta[(b * H + head) * S + q] = acc;
+}
+
 // ------------------------------------------------------------------ backward: dQ
 // K and V tiles as they lie in memory; K is read by
 // rows for the scores and transposed for dQ^T += K^T dS^T.
 // It also computes delta[q] = sum_d dO[q][d] O[q][d] for its queries (each lane holds half a row of dO
-// as MFMA fragments anyway) and stores it for the dK/dV pass.
+// as MFMA fragments anyway) and stores it for the dK/dV pass; without `o` it takes delta as it finds it.
 template <int D, int KT, int WGS>
 __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                                  const bf16_t* __restrict__ dout, const float* __restrict__ lse,
@@ -388,19 +409,23 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __r
   }
   const float my_lse = lse[((size_t)b * H + head) * S + query];
   float my_delta = 0.f;
+  if (o) {
 #pragma unroll
-  for (int ks = 0; ks < DP / 16; ++ks) {
-    Frag fo, fd;
-    fo.v = row_frag<D>(o + ((size_t)b * S + query) * h + (size_t)head * D, ks * 16 + g * 8);
-    fd.v = dof[ks];
+    for (int ks = 0; ks < DP / 16; ++ks) {
+      Frag fo, fd;
+      fo.v = row_frag<D>(o + ((size_t)b * S + query) * h + (size_t)head * D, ks * 16 + g * 8);
+      fd.v = dof[ks];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      my_delta = fmaf(__uint_as_float(fo.u[e] << 16), __uint_as_float(fd.u[e] << 16), my_delta);
-      my_delta = fmaf(__uint_as_float(fo.u[e] & 0xffff0000u), __uint_as_float(fd.u[e] & 0xffff0000u), my_delta);
+      for (int e = 0; e < 4; ++e) {
+        my_delta = fmaf(__uint_as_float(fo.u[e] << 16), __uint_as_float(fd.u[e] << 16), my_delta);
+        my_delta = fmaf(__uint_as_float(fo.u[e] & 0xffff0000u), __uint_as_float(fd.u[e] & 0xffff0000u), my_delta);
+      }
     }
+    my_delta += __shfl_xor(my_delta, 32, 64);   // the other half of the row
+    if (g == 0) delta[((size_t)b * H + head) * S + query] = my_delta;
+  } else {
+    my_delta = delta[((size_t)b * H + head) * S + query];
   }
-  my_delta += __shfl_xor(my_delta, 32, 64);   // the other half of the row
-  if (g == 0) delta[((size_t)b * H + head) * S + query] = my_delta;
   f32x16 dq[DP / 32];
 #pragma unroll
   for (int i = 0; i < DP / 32; ++i)
@@ -679,6 +704,12 @@ int attention_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, cons
   if (seq % 128 || (d != 64 && d != 128 && d != 152) || batch <= 0 || heads <= 0) return KARMA_E_INVAL;
   dim3 grid(seq / 128, heads, batch);
   float* sums = colsum_rows ? colsum_partial : nullptr;
+  const size_t tokens = (size_t)batch * seq, width = (size_t)heads * d;
+  if (dqkv < ctx + tokens * width && ctx < dqkv + tokens * 3 * width) {   // gradients over the outputs: these are read first
+    const size_t total = tokens * heads;
+    hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, ctx, dctx, delta, seq, heads, d, total);
+    ctx = nullptr;
+  }
   if (d == 64) launch_bwd<64>(grid, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, sums);
   else if (d == 128) launch_bwd<128>(grid, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, sums);
   else launch_bwd<152>(grid, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, sums);
