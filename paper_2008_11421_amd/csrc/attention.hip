@@ -745,9 +745,15 @@ extern "C" int karma_k_attention_bwd_colsum_bf16(const void* qkv, const void* ct
   const int rows = (int)(batch * seq), cols = (int)(3 * heads * d);
   if (ws_bytes < std::max(attention_bwd_colsum_bytes((int)batch, (int)seq, (int)heads, (int)d), colsum_ws_bytes(rows, cols)))
     return KARMA_E_OOM;
+  // partial sums over what the kernels still read: the sums are taken from dqkv afterwards
+  const size_t used = attention_bwd_colsum_bytes((int)batch, (int)seq, (int)heads, (int)d), tensor = (size_t)rows * heads * d * sizeof(bf16_t);
+  auto meets = [&](const void* p, size_t bytes) { return (const char*)ws < (const char*)p + bytes && (const char*)p < (const char*)ws + used; };
+  const size_t stats = (size_t)rows * heads * sizeof(float);
+  const bool over = meets(qkv, 3 * tensor) || meets(ctx, tensor) || meets(dctx, tensor) || meets(lse, stats) || meets(delta_ws, stats);
   int parts = 0;
   int st = attention_bwd((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta_ws, (bf16_t*)dqkv,
-                         (int)batch, (int)seq, (int)heads, (int)d, (hipStream_t)stream, ws, &parts);
+                         (int)batch, (int)seq, (int)heads, (int)d, (hipStream_t)stream, over ? nullptr : ws, over ? nullptr : &parts);
   if (st) return st;
+  if (over) return colsum_bf16((const bf16_t*)dqkv, colsum_out, ws, rows, cols, (hipStream_t)stream);
   return colsum_finish(ws, parts, cols, colsum_out, (hipStream_t)stream);
 }
