@@ -683,7 +683,7 @@ static void launch_bwd(dim3 grid, hipStream_t s, const bf16_t* qkv, const bf16_t
   constexpr int l1 = 2 * 2 * tile_bytes(D, T::DQ_KT);                             // two stages of (K tile, V tile)
   constexpr int l2 = 2 * 2 * tile_bytes(D, T::DKV_QT) + 2 * 2 * T::DKV_QT * 4;    // two stages of (Q tile, dO tile) + their lse, delta
   auto kq = attn_bwd_dq_kernel<D, T::DQ_KT, T::DQ_WGS>;
-  const bool few = (size_t)grid.x * grid.y * grid.z <= 256;   // one workgroup per compute unit
+  const bool few = (size_t)grid.x * grid.y * grid.z <= (size_t)compute_units();   // no second workgroup for one of them
   auto kkv = few ? attn_bwd_dkv_kernel<D, T::DKV_QT, T::DKV_WGS_FEW> : attn_bwd_dkv_kernel<D, T::DKV_QT, T::DKV_WGS>;
   (void)hipFuncSetAttribute((const void*)kq, hipFuncAttributeMaxDynamicSharedMemorySize, l1);
   (void)hipFuncSetAttribute((const void*)kkv, hipFuncAttributeMaxDynamicSharedMemorySize, l2);

@@ -747,7 +747,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_octets_kernel(const float* 
 }
 
 static int g_cus = 0;
-static int compute_units() {
+int compute_units() {
   if (!g_cus) {
     int dev = 0;
     hipDeviceProp_t p;

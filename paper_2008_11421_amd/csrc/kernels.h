@@ -14,6 +14,9 @@ namespace karma {
 
 typedef uint16_t bf16_t;   // bit pattern of a bfloat16
 
+// Compute units of the current device (256 where there is none: plans can be made without a GPU)
+int compute_units();
+
 // ---- fp32 MLP kernels (kernels_f32.hip)
 int linear_relu_fwd_f32(const float* x, const float* w, const float* b, float* z, float* y, int m, int n, int k,
                         hipStream_t s);
