@@ -1,7 +1,8 @@
 """The 256 x 256 tile of the bf16 product where its stream of operand tiles crosses from one work item to the next: two
 rounds of items and more with two, three and four k-tiles, whole and ragged, every layout and output stage; divided
-reductions; and weight gradients, whose second operand is gathered, the last range a single k-tile among them.  Each case
-states through the plan that it runs on this tile.  Against float64 sums of the same bf16 operands, tile by tile: a bf16
+reductions; weight gradients, whose second operand is gathered, the last range a single k-tile among them; and convolutions
+and their input gradients, whose first operand is gathered, with the 256 x 64 tile too.  Each case states through the plan
+that it runs on this tile.  Against float64 sums of the same bf16 operands, tile by tile: a bf16
 result carries one rounding (2^-9 of an element; 2^-8 of a tile's norm is allowed), fp32 sums less than 1e-5 at these
 lengths."""
 import ctypes as C
@@ -115,3 +116,44 @@ def test_weight_gradient(g, n, h, ci, co, r, stride, single):
         for j in range(r):
             tap = xp[:, i:i + (ho - 1) * stride + 1:stride, j:j + (ho - 1) * stride + 1:stride].reshape(-1, ci).double()
             assert close_by_tiles(dw[:, i, j], left @ tap, 2.0 ** -8), (i, j)
+
+
+# several items per workgroup with two to four k-tiles, a gathered first operand, ragged in every direction
+@pytest.mark.parametrize("n,h,ci,co,r,stride,pad,kernel", [(35, 55, 16, 136, 3, 1, 0, K.PRODUCT_LARGE), (35, 105, 16, 136, 3, 2, 1, K.PRODUCT_LARGE),
+                                                           (13, 87, 16, 200, 3, 1, 1, K.PRODUCT_LARGE), (25, 113, 24, 64, 3, 1, 1, K.PRODUCT_NARROW),
+                                                           (25, 224, 8, 64, 7, 2, 3, K.PRODUCT_NARROW)])
+def test_gathered_first_operand(g, n, h, ci, co, r, stride, pad, kernel):
+    import torch
+    lib, ho = K.lib(), (h + 2 * pad - r) // stride + 1
+    shape = K.ConvShape(n, h, h, ci, co, r, r, stride, pad)
+    assert K.conv_plan(shape, K.CONV_FWD) == [(kernel, n * ho * ho, co, 1)]
+    x, w, add = bf(14, n, h, h, ci), bf(15, co, r, r, ci), bf(16, n, ho, ho, co)
+    y = torch.full((n + 1, ho, ho, co), 7.0, dtype=torch.bfloat16, device="cuda")
+    g.call(lib.karma_k_conv2d_fwd_add_bf16, g.ptr(x), g.ptr(w), g.ptr(add), g.ptr(y), C.byref(shape), g.stream_ptr())
+    want = add.double().reshape(-1, co)
+    xp = torch.nn.functional.pad(x, (0, 0, pad, pad, pad, pad))
+    for i in range(r):
+        for j in range(r):
+            tap = xp[:, i:i + (ho - 1) * stride + 1:stride, j:j + (ho - 1) * stride + 1:stride].reshape(-1, ci).double()
+            want += tap @ w[:, i, j].double().T.contiguous()
+    assert close_by_tiles(y[:n].reshape(-1, co), want, 2.0 ** -8) and (y[n] == 7).all()
+
+
+@pytest.mark.parametrize("n,h,ci,co,r,pad,kernel", [(35, 53, 136, 16, 3, 0, K.PRODUCT_LARGE), (13, 87, 200, 16, 3, 1, K.PRODUCT_LARGE),
+                                                    (25, 113, 64, 24, 3, 1, K.PRODUCT_NARROW)])
+def test_input_gradient(g, n, h, ci, co, r, pad, kernel):
+    import torch
+    ho = h + 2 * pad - r + 1
+    shape = K.ConvShape(n, h, h, ci, co, r, r, 1, pad)
+    assert K.conv_plan(shape, K.CONV_DGRAD) == [(kernel, n * h * h, ci, 1)]
+    dy, w, wt = bf(17, n, ho, ho, co), bf(18, co, r, r, ci), torch.empty(r * r * ci * co, dtype=torch.bfloat16, device="cuda")
+    dx = torch.full((n + 1, h, h, ci), 7.0, dtype=torch.bfloat16, device="cuda")
+    g.call(K.lib().karma_k_conv2d_dgrad_bf16, g.ptr(dy), g.ptr(w), g.ptr(wt), None, g.ptr(dx), C.byref(shape), g.stream_ptr())
+    want = torch.zeros(n * h * h, ci, dtype=torch.float64, device="cuda")
+    edge = r - 1 - pad
+    dyp = torch.nn.functional.pad(dy, (0, 0, edge, edge, edge, edge))
+    for i in range(r):
+        for j in range(r):
+            tap = dyp[:, r - 1 - i:r - 1 - i + h, r - 1 - j:r - 1 - j + h].reshape(-1, co).double()
+            want += tap @ w[:, i, j].double()
+    assert close_by_tiles(dx[:n].reshape(-1, ci), want, 2.0 ** -8) and (dx[n] == 7).all()
