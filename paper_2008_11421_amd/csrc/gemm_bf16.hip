@@ -860,28 +860,34 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
   for (int tile = 128; tile <= 256; tile += 128) {
     if (!(tile == 256 ? large : small)) continue;
     const long tiles = (long)((g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile);
+    GemmPlan own{tile, 1, false, 1e30};   // the best number of ranges with this tile ...
+    double late = 0.0;                    // ... and what its k-tiles take beyond two workgroups' pace
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && ((uint64_t)sp * g.M * g.N * sizeof(float) > g.ws_bytes || tiles * sp > 8l * cus)) break;
       const long items = tiles * sp, places = tile == 256 ? cus : 2l * cus, full = items / places, rest = items % places;
       const int kt = (k_tiles + sp - 1) / sp;
       const long rounds = full + (rest ? 1 : 0);
-      double us;
+      const double f = (double)rest / cus;   // workgroups per compute unit in the last round
+      double us, more = 0.0;
       if (tile == 256) {
-        const double f = (double)rest / cus;
         us = 9.0 + 4.0 * (rounds - 1) + ragged * kt * (full * full256 + (rest ? alone256 + (full256 - alone256) * f : 0.0));
       } else {
-        const double f = (double)rest / cus;   // workgroups per compute unit in the last round
-        double last = 0.0;
-        if (rest && full) last = f <= 1.0 ? lone128 : lone128 + (1.0 - lone128) * (f - 1.0);
-        else if (rest) last = f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0);
-        us = 5.5 + 2.5 * (rounds - 1) + gather128 * kt * (full + last);
+        const double last = !rest ? 0.0 : f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0);
+        const double slow = !rest || !full ? last : lone128 + (1.0 - lone128) * std::max(0.0, f - 1.0);
+        us = 5.5 + 2.5 * (rounds - 1) + kt * (full + last);
+        more = kt * (gather128 * (full + slow) - (full + last));
         if (sp == 1) us += by_element * (14.0 + 17.5 * (rounds - 1));
       }
       if (sp > 1) us += 3.5 + (double)sp * g.M * g.N * 8.0 / 5e6;
       // (four stages instead of two: 1000 x 1000 x 4000 in 33 us instead of 47, one k-tile in flight per workgroup having
       // nobody to hide behind; below 24 k-tiles per item there is no difference)
-      if (us < best.us) best = GemmPlan{tile, sp, items <= cus && kt >= 24, us};
+      if (us < own.us) {
+        own = GemmPlan{tile, sp, items <= cus && kt >= 24, us};
+        late = more;
+      }
     }
+    own.us += late;
+    if (own.us < best.us) best = own;
   }
   return best;
 }
