@@ -38,6 +38,9 @@ constexpr float LOG2E = 1.4426950408889634f;
 //     dK/dV (32, 1) 224, (32, 2) 365, (64, 1) 181, (64, 2) 476
 // The two larger head dimensions with tiles staged through registers, and transposed there: forward 208 and 165, dQ 276
 // and 196 (+ 61 and 26 for delta), dK/dV 367 and 290.
+// FWD_SLACK: by how many powers of two a query's maximum may grow before the forward pass rescales.  0 for the larger
+// heads: with 8 (their forward in the sweep above; 0 takes 4 to 9 % longer, 91 -> 95 and 75 -> 79 us) the output was 2 to
+// 14 % further from 64 bits, as a largest probability of one is exact in bf16.
 // DKV_WGS_FEW: where there is no second workgroup for a compute unit, the kernel that may use all its registers
 // (2 x 5 heads x 384 x 128: 28 -> 24 us).
 template <int D>
@@ -45,14 +48,17 @@ struct AttnTiles;
 template <>
 struct AttnTiles<64> {
   static constexpr int FWD_KT = 64, FWD_WGS = 3, DQ_KT = 64, DQ_WGS = 4, DKV_QT = 32, DKV_WGS = 3, DKV_WGS_FEW = 3;
+  static constexpr float FWD_SLACK = 8.f;
 };
 template <>
 struct AttnTiles<128> {
   static constexpr int FWD_KT = 64, FWD_WGS = 3, DQ_KT = 64, DQ_WGS = 2, DKV_QT = 64, DKV_WGS = 2, DKV_WGS_FEW = 1;
+  static constexpr float FWD_SLACK = 0.f;
 };
 template <>
 struct AttnTiles<152> {
   static constexpr int FWD_KT = 32, FWD_WGS = 2, DQ_KT = 32, DQ_WGS = 2, DKV_QT = 64, DKV_WGS = 1, DKV_WGS_FEW = 1;
+  static constexpr float FWD_SLACK = 0.f;
 };
 
 // Head dimensions that are no multiple of 32 (152) run with padded columns: zeros in the tiles, so that they add
@@ -290,11 +296,12 @@ __global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __rest
     }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     // The reference maximum m follows the true maximum lazily: the accumulators are rescaled only when
-    // some query's maximum has grown by more than 2^8 in the exponent's domain; until then its
-    // probabilities are computed against the old reference and may reach 256 (harmless in fp32
-    // accumulators and in bf16, whose relative precision does not depend on the magnitude).
+    // some query's maximum has grown by more than 2^FWD_SLACK in the exponent's domain; until then its
+    // probabilities are computed against the old reference and may reach that (harmless in fp32
+    // accumulators and in bf16, whose relative precision does not depend on the magnitude; but a largest
+    // probability of one is exact in bf16).
     const float m_new = fmaxf(m, tmax);
-    if (__any((m_new - m) * c > 8.f)) {
+    if (__any((m_new - m) * c > AttnTiles<D>::FWD_SLACK)) {
       const float alpha = fast_exp2((m - m_new) * c);
       l *= alpha;
 #pragma unroll
