@@ -43,21 +43,25 @@ constexpr float LOG2E = 1.4426950408889634f;
 // 14 % further from 64 bits, as a largest probability of one is exact in bf16.
 // DKV_WGS_FEW: where there is no second workgroup for a compute unit, the kernel that may use all its registers
 // (2 x 5 heads x 384 x 128: 28 -> 24 us).
+// FWD_SPLIT_SEQ, BOTH_*: see the launchers (queries per tile, workgroups and groups of wavefronts of the joint backward launch).
 template <int D>
 struct AttnTiles;
 template <>
 struct AttnTiles<64> {
   static constexpr int FWD_KT = 64, FWD_WGS = 3, DQ_KT = 64, DQ_WGS = 4, DKV_QT = 32, DKV_WGS = 3, DKV_WGS_FEW = 3;
+  static constexpr int FWD_SPLIT_SEQ = 512, BOTH_QT = 64, BOTH_WGS = 2, BOTH_GROUPS = 2;
   static constexpr float FWD_SLACK = 8.f;
 };
 template <>
 struct AttnTiles<128> {
   static constexpr int FWD_KT = 64, FWD_WGS = 3, DQ_KT = 64, DQ_WGS = 2, DKV_QT = 64, DKV_WGS = 2, DKV_WGS_FEW = 1;
+  static constexpr int FWD_SPLIT_SEQ = 512, BOTH_QT = 64, BOTH_WGS = 1, BOTH_GROUPS = 1;
   static constexpr float FWD_SLACK = 0.f;
 };
 template <>
 struct AttnTiles<152> {
   static constexpr int FWD_KT = 32, FWD_WGS = 2, DQ_KT = 32, DQ_WGS = 2, DKV_QT = 64, DKV_WGS = 1, DKV_WGS_FEW = 1;
+  static constexpr int FWD_SPLIT_SEQ = 256, BOTH_QT = 64, BOTH_WGS = 1, BOTH_GROUPS = 1;
   static constexpr float FWD_SLACK = 0.f;
 };
 
@@ -109,21 +113,22 @@ __device__ __forceinline__ float half_wave_sum(float v) {
 // grid (seq/128, heads, batch), 256 threads; wavefront w owns queries q0+32w .. q0+32w+31
 // and walks the keys in tiles made of 32-key sub-tiles (those entirely after the
 // wavefront's queries are skipped).
-// Workgroup -> (tile, head, batch).  Workgroup ids go round-robin over the 8 XCDs; all tiles
-// of one (batch, head) are given to the same XCD, so that head's K and V are fetched into one
-// L2 only, and the heaviest tile of the causal triangle goes first (heavy_high: the last
-// tile is the heaviest).
-__device__ __forceinline__ void attn_block(int& tile, int& head, int& b, bool heavy_high) {
-  const int nt = gridDim.x, H = gridDim.y, hb_total = gridDim.y * gridDim.z;
-  const int L = blockIdx.x + nt * (blockIdx.y + H * blockIdx.z);
+// Workgroup -> (tile, head, batch), L its number among nt * H * batches.  Workgroup ids go round-robin over the 8 XCDs;
+// all tiles of one (batch, head) are given to the same XCD, so that head's K and V are fetched into one L2 only, and the
+// heaviest tile of the causal triangle goes first (heavy_high: the last tile is the heaviest).  The (batch, head) pairs
+// beyond a multiple of eight are dealt tile by tile, heaviest tiles first.
+__device__ __forceinline__ int workgroup_number() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
+__device__ __forceinline__ void attn_block(int L, int nt, int H, int hb_total, int& tile, int& head, int& b, bool heavy_high) {
+  const int local = hb_total / 8 * 8, rest = hb_total - local;
   int t, hb;
-  if (hb_total % 8 == 0) {
+  if (L < local * nt) {
     const int slot = L / 8;
     hb = (slot / nt) * 8 + L % 8;
     t = slot % nt;
   } else {
-    t = L % nt;
-    hb = L / nt;
+    const int at = L - local * nt;
+    hb = local + at % rest;
+    t = at / rest;
   }
   tile = heavy_high ? nt - 1 - t : t;
   head = hb % H;
@@ -206,18 +211,50 @@ struct PanelFrag {
   }
 };
 
-template <int D, int KT, int WGS>
-__global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
-                                                              float* __restrict__ lse, int S, int H) {
+// Walks a workgroup's tiles with SP groups of four wavefronts, group k on tiles k, k + SP, ...; each group has two stages
+// of its own and its first tile has been requested.  The first n_full tiles need no masking; n_full and n are multiples of SP.
+template <int SP, class Issue, class Step>
+__device__ __forceinline__ void for_tiles(int n_full, int n, int group, Issue issue, Step step) {
+  auto arrive = [&](int t) {
+    wait_vm<0>();            // this wavefront's share of tile t has landed
+    lds_barrier_visible();   // ... and everybody's; the tile before it is no longer read
+    if (t + SP < n) issue(t + SP);
+  };
+  for (int t = group; t < n_full; t += SP) { arrive(t); step(t, std::true_type{}); }
+  for (int t = n_full + group; t < n; t += SP) { arrive(t); step(t, std::false_type{}); }
+}
+
+// Adds the accumulators of the other groups of four wavefronts to group 0's, in the groups' order, through LDS (which holds
+// no tile any more).  N registers per lane; mine(r) / theirs(r, v) read and add register r.
+template <int SP, int N, class Mine, class Theirs>
+__device__ __forceinline__ void join_groups(float* lds, int group, int tid, Mine mine, Theirs theirs) {
+#pragma unroll
+  for (int o = 1; o < SP; ++o) {
+    lds_barrier_visible();
+    if (group == o)
+#pragma unroll
+      for (int r = 0; r < N; ++r) lds[r * 256 + tid] = mine(r);
+    lds_barrier_visible();
+    if (group == 0)
+#pragma unroll
+      for (int r = 0; r < N; ++r) theirs(r, lds[r * 256 + tid]);
+  }
+}
+
+// SP groups of four wavefronts share the workgroup's queries; group k takes the key tiles k, k + SP, ...
+template <int D, int KT, int WGS, int SP>
+__global__ __launch_bounds__(256 * SP, WGS) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
+                                                                   float* __restrict__ lse, int S, int H) {
   constexpr int DP = padded_d(D), NMT = KT / 32, TILE = tile_bytes(D, KT), STAGE = 2 * TILE;   // stage = K tile | V tile
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
-  const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn);
   const int h = H * D;
   const size_t ld = 3 * (size_t)h;
   int tile, head, b;
-  attn_block(tile, head, b, true);
+  attn_block(workgroup_number(), S / 128, H, gridDim.y * gridDim.z, tile, head, b, true);
   const int q0 = tile * 128;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, g = lane >> 5;
+  const int group = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn) + group * 2 * STAGE;
+  const int tid = threadIdx.x & 255, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, g = lane >> 5;
   const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * D;
   const bf16_t* Kg = base + h;
   const bf16_t* Vg = base + 2 * h;
@@ -229,12 +266,13 @@ __global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __rest
   TileLoader<D, KT, 4> tl;
   tl.init(ld, w, lane);
   auto issue = [&](int kt) {
-    const unsigned st = lds0 + (kt & 1) * STAGE;
+    const unsigned st = lds0 + (kt / SP & 1) * STAGE;
     tl.issue(Kg + (size_t)kt * KT * ld, st, w);
     tl.issue(Vg + (size_t)kt * KT * ld, st + TILE, w);
   };
   const int n_kt = (q0 + 128) / KT;
-  issue(0);
+  static_assert(128 / KT % SP == 0, "the groups have as many tiles each");
+  issue(group);
 
   bf16x8 qf[DP / 16];
 #pragma unroll
@@ -252,10 +290,7 @@ __global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __rest
   auto tile_step = [&](int kt, auto full_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
     const int key0 = kt * KT;
-    wait_vm<0>();            // this wavefront's share of tile kt has landed
-    lds_barrier_visible();   // ... and everybody's; tile kt - 1 is no longer read
-    if (kt + 1 < n_kt) issue(kt + 1);
-    const unsigned Ks = lds0 + (kt & 1) * STAGE, Vs = Ks + TILE;
+    const unsigned Ks = lds0 + (kt / SP & 1) * STAGE, Vs = Ks + TILE;
     // sub-tiles this wavefront needs: keys key0 + 32*mt <= last query
     const int n_mt = FULL ? NMT : min(NMT, (qbase + 31 - key0) / 32 + 1);
     f32x16 s[NMT];
@@ -310,14 +345,16 @@ __global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __rest
         for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
       m = m_new;
     }
-    const float mc = m * c;
+    // A group other than the first may have met no key of a query that counts: none at all, or only scores that are minus
+    // infinity or so low that m * c, rounded, is far from them.  Its probabilities are then at most one, not infinite or NaN.
+    const float mc = m * c, ms = m == -INFINITY ? 0.f : m;
     float psum = 0.f;
 #pragma unroll
     for (int mt = 0; mt < NMT; ++mt) {
       if (FULL || mt < n_mt) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float p = fast_exp2(fmaf(s[mt][r], c, -mc));
+          const float p = fast_exp2(SP > 1 ? (s[mt][r] - ms) * c : fmaf(s[mt][r], c, -mc));
           s[mt][r] = p;
           psum += p;
         }
@@ -334,9 +371,36 @@ __global__ __launch_bounds__(256, WGS) void attn_fwd_kernel(const bf16_t* __rest
     l += psum;
   };
   const int n_full = q0 / KT;   // tiles whose keys all precede the workgroup's first query
-  for (int kt = 0; kt < n_full; ++kt) tile_step(kt, std::true_type{});
-  for (int kt = n_full; kt < n_kt; ++kt) tile_step(kt, std::false_type{});
+  for_tiles<SP>(n_full, n_kt, group, issue, tile_step);
   l += __shfl_xor(l, 32, 64);
+  if constexpr (SP > 1) {
+    // the groups' sums against the larger of two references; group 0 has met every query's first key
+    float* join = (float*)smem_attn;
+#pragma unroll
+    for (int x = 1; x < SP; ++x) {
+      lds_barrier_visible();
+      if (group == x) {
+        join[tid] = m;
+        join[256 + tid] = l;
+#pragma unroll
+        for (int i = 0; i < DP / 32; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) join[(2 + i * 16 + r) * 256 + tid] = o[i][r];
+      }
+      lds_barrier_visible();
+      if (group == 0) {
+        const float m2 = join[tid], m_new = fmaxf(m, m2);
+        const float mine = fast_exp2((m - m_new) * c), theirs = m2 == -INFINITY ? 0.f : fast_exp2((m2 - m_new) * c);
+        l = l * mine + join[256 + tid] * theirs;
+#pragma unroll
+        for (int i = 0; i < DP / 32; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[i][r] = o[i][r] * mine + join[(2 + i * 16 + r) * 256 + tid] * theirs;
+        m = m_new;
+      }
+    }
+    if (group != 0) return;
+  }
   const float inv = 1.f / l;
   bf16_t* out = ctx + ((size_t)b * S + query) * h + (size_t)head * D;
 #pragma unroll
@@ -372,25 +436,41 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t* __restric
   delta[(b * H + head) * S + q] = acc;
 }
 
+struct AttnBwd {
+  const bf16_t* qkv;
+  const bf16_t* o;      // the forward's output, or null: delta is there already
+  const bf16_t* dout;
+  const float* lse;
+  float* delta;
+  bf16_t* dqkv;
+  float* colsum;        // or null
+  int S, H;
+};
+
 // ------------------------------------------------------------------ backward: dQ
 // K and V tiles as they lie in memory; K is read by
 // rows for the scores and transposed for dQ^T += K^T dS^T.
 // It also computes delta[q] = sum_d dO[q][d] O[q][d] for its queries (each lane holds half a row of dO
 // as MFMA fragments anyway) and stores it for the dK/dV pass; without `o` it takes delta as it finds it.
-template <int D, int KT, int WGS>
-__global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
-                                                                 const bf16_t* __restrict__ dout, const float* __restrict__ lse,
-                                                                 float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S, int H,
-                                                                 float* __restrict__ colsum) {
+// L: the workgroup's number among hb_total * S / 128.
+template <int D, int KT, int SP>
+__device__ __forceinline__ void attn_bwd_dq(const AttnBwd& p, int L, int hb_total, unsigned char* smem_attn) {
   constexpr int DP = padded_d(D), NMT = KT / 32, TILE = tile_bytes(D, KT), STAGE = 2 * TILE;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
-  const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn);
-  const int h = H * D;
+  const bf16_t* __restrict__ const qkv = p.qkv;
+  const bf16_t* __restrict__ const o = p.o;
+  const bf16_t* __restrict__ const dout = p.dout;
+  const float* __restrict__ const lse = p.lse;
+  float* __restrict__ const delta = p.delta;
+  bf16_t* __restrict__ const dqkv = p.dqkv;
+  float* __restrict__ const colsum = p.colsum;
+  const int S = p.S, H = p.H, h = H * D;
   const size_t ld = 3 * (size_t)h;
   int tile, head, b;
-  attn_block(tile, head, b, true);
+  attn_block(L, S / 128, H, hb_total, tile, head, b, true);
   const int q0 = tile * 128;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, g = lane >> 5;
+  const int group = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn) + group * 2 * STAGE;
+  const int tid = threadIdx.x & 255, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, g = lane >> 5;
   const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * D;
   const bf16_t* Kg = base + h;
   const bf16_t* Vg = base + 2 * h;
@@ -401,12 +481,13 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __r
   TileLoader<D, KT, 4> tl;
   tl.init(ld, w, lane);
   auto issue = [&](int kt) {
-    const unsigned st = lds0 + (kt & 1) * STAGE;
+    const unsigned st = lds0 + (kt / SP & 1) * STAGE;
     tl.issue(Kg + (size_t)kt * KT * ld, st, w);
     tl.issue(Vg + (size_t)kt * KT * ld, st + TILE, w);
   };
   const int n_kt = (q0 + 128) / KT;
-  issue(0);
+  static_assert(128 / KT % SP == 0, "the groups have as many tiles each");
+  issue(group);
 
   bf16x8 qf[DP / 16], dof[DP / 16];
 #pragma unroll
@@ -429,7 +510,7 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __r
       }
     }
     my_delta += __shfl_xor(my_delta, 32, 64);   // the other half of the row
-    if (g == 0) delta[((size_t)b * H + head) * S + query] = my_delta;
+    if (g == 0 && group == 0) delta[((size_t)b * H + head) * S + query] = my_delta;
   } else {
     my_delta = delta[((size_t)b * H + head) * S + query];
   }
@@ -442,10 +523,7 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __r
   auto tile_step = [&](int kt, auto full_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
     const int key0 = kt * KT;
-    wait_vm<0>();
-    lds_barrier_visible();
-    if (kt + 1 < n_kt) issue(kt + 1);
-    const unsigned Ks = lds0 + (kt & 1) * STAGE, Vs = Ks + TILE;
+    const unsigned Ks = lds0 + (kt / SP & 1) * STAGE, Vs = Ks + TILE;
     const int n_mt = FULL ? NMT : min(NMT, (qbase + 31 - key0) / 32 + 1);
 #pragma unroll
     for (int mt = 0; mt < NMT; ++mt) {
@@ -478,8 +556,12 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __r
     }
   };
   const int n_full = q0 / KT;   // tiles whose keys all precede the workgroup's first query
-  for (int kt = 0; kt < n_full; ++kt) tile_step(kt, std::true_type{});
-  for (int kt = n_full; kt < n_kt; ++kt) tile_step(kt, std::false_type{});
+  for_tiles<SP>(n_full, n_kt, group, issue, tile_step);
+  if constexpr (SP > 1) {
+    join_groups<SP, DP / 2>((float*)smem_attn, group, tid, [&](int r) { return dq[r / 16][r % 16]; },
+                            [&](int r, float v) { dq[r / 16][r % 16] += v; });
+    if (group != 0) return;
+  }
 
   bf16_t* out = dqkv + ((size_t)b * S + query) * ld + (size_t)head * D;
 #pragma unroll
@@ -513,21 +595,26 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(const bf16_t* __r
 // ------------------------------------------------------------------ backward: dK, dV
 // Wavefront w owns keys k0+32w .. +31 and walks the query tiles at or after them.  Q and dO tiles lie as in
 // memory, read by rows for S = Q K^T and dP = dO V^T and transposed for dV += P^T dO, dK += dS^T Q.
-template <int D, int QT, int WGS>
-__global__ __launch_bounds__(256, WGS) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                                  const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                  bf16_t* __restrict__ dqkv, int S, int H,
-                                                                  float* __restrict__ colsum) {
+// OWN_DELTA: delta of a tile's queries is taken from their rows of O and dO here (256 / QT threads a query, fetched one tile
+// ahead like the log-sum-exps), for launches that do not wait for the dQ pass.
+template <int D, int QT, int SP, bool OWN_DELTA>
+__device__ __forceinline__ void attn_bwd_dkv(const AttnBwd& p, int L, int hb_total, unsigned char* smem_attn) {
   constexpr int DP = padded_d(D), TILE = tile_bytes(D, QT), STAGE = 2 * TILE;   // stage = Q tile | dO tile
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
-  const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn);
-  float* stat = (float*)(smem_attn + 2 * STAGE);   // [2 stages][lse | delta][QT]
-  const int h = H * D;
+  const bf16_t* __restrict__ const qkv = p.qkv;
+  const bf16_t* __restrict__ const dout = p.dout;
+  const float* __restrict__ const lse = p.lse;
+  const float* __restrict__ const delta = p.delta;
+  bf16_t* __restrict__ const dqkv = p.dqkv;
+  float* __restrict__ const colsum = p.colsum;
+  const int S = p.S, H = p.H, h = H * D;
   const size_t ld = 3 * (size_t)h;
   int tile, head, b;
-  attn_block(tile, head, b, false);
+  attn_block(L, S / 128, H, hb_total, tile, head, b, false);
   const int k0 = tile * 128;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, g = lane >> 5;
+  const int group = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn) + group * 2 * STAGE;
+  float* stat = (float*)(smem_attn + SP * 2 * STAGE) + group * 4 * QT;   // [2 stages][lse | delta][QT]
+  const int tid = threadIdx.x & 255, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, g = lane >> 5;
   const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * D;
   const bf16_t* dOg = dout + (size_t)b * S * h + (size_t)head * D;
   const float* lse_g = lse + ((size_t)b * H + head) * S;
@@ -540,13 +627,12 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dkv_kernel(const bf16_t* __
   tlq.init(ld, w, lane);
   tlo.init((size_t)h, w, lane);
   auto issue = [&](int t) {   // query tile t of this workgroup: queries k0 + QT t ..
-    const unsigned st = lds0 + (t & 1) * STAGE;
+    const unsigned st = lds0 + (t / SP & 1) * STAGE;
     const int qq = k0 + t * QT;
     tlq.issue(base + (size_t)qq * ld, st, w);
     tlo.issue(dOg + (size_t)qq * h, st + TILE, w);
   };
   const int n_t = (S - k0) / QT;
-  issue(0);
 
   bf16x8 kf[DP / 16], vf[DP / 16];
 #pragma unroll
@@ -559,31 +645,56 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dkv_kernel(const bf16_t* __
   for (int i = 0; i < DP / 32; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dk[i][r] = 0.f; dv[i][r] = 0.f; }
+  // per-query statistics of the next tile, in registers
+  constexpr int TPQ = 256 / QT, VPT = OWN_DELTA ? (D / 8 + TPQ - 1) / TPQ : 1;
+  const int dq_row = tid / TPQ, dq_part = tid % TPQ;
   float lse_r = 0.f, delta_r = 0.f;
-  if (tid < QT) {
-    lse_r = lse_g[k0 + tid];
-    delta_r = delta_g[k0 + tid];
-  }
+  u32x4 o_r[VPT], do_r[VPT];
+  auto fetch_stats = [&](int t) {
+    const int qq = k0 + t * QT;
+    if (tid < QT) {
+      lse_r = lse_g[qq + tid];
+      if (!OWN_DELTA) delta_r = delta_g[qq + tid];
+    }
+    if constexpr (OWN_DELTA) {
+      const size_t at = ((size_t)b * S + qq + dq_row) * h + (size_t)head * D;
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) {
+        const int col = (dq_part + v * TPQ) * 8;
+        o_r[v] = col < D ? *(const u32x4*)(p.o + at + col) : u32x4{0, 0, 0, 0};
+        do_r[v] = col < D ? *(const u32x4*)(dout + at + col) : u32x4{0, 0, 0, 0};
+      }
+    }
+  };
+  auto store_stats = [&](int t) {   // (the buffer was last read two of this group's tiles ago)
+    float* lse_s = stat + (t / SP & 1) * 2 * QT;
+    if (tid < QT) lse_s[tid] = lse_r;
+    if constexpr (!OWN_DELTA) {
+      if (tid < QT) lse_s[QT + tid] = delta_r;
+    } else {
+      float sum = 0.f;
+#pragma unroll
+      for (int v = 0; v < VPT; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sum = fmaf(__uint_as_float(o_r[v][e] << 16), __uint_as_float(do_r[v][e] << 16), sum);
+          sum = fmaf(__uint_as_float(o_r[v][e] & 0xffff0000u), __uint_as_float(do_r[v][e] & 0xffff0000u), sum);
+        }
+#pragma unroll
+      for (int x = 1; x < TPQ; x *= 2) sum += __shfl_xor(sum, x, 64);
+      if (dq_part == 0) lse_s[QT + dq_row] = sum;
+    }
+  };
+  static_assert(128 / QT % SP == 0, "the groups have as many tiles each");
+  fetch_stats(group);
+  issue(group);
 
   auto tile_step = [&](int t, auto full_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
     const int qq0 = k0 + t * QT;
-    float* lse_s = stat + (t & 1) * 2 * QT;
-    float* delta_s = lse_s + QT;
-    if (tid < QT) {   // this tile's per-query statistics (fetched one tile ago); the buffer was last read two tiles ago
-      lse_s[tid] = lse_r;
-      delta_s[tid] = delta_r;
-    }
-    wait_vm<0>();
-    lds_barrier_visible();
-    if (t + 1 < n_t) {
-      issue(t + 1);
-      if (tid < QT) {
-        lse_r = lse_g[qq0 + QT + tid];
-        delta_r = delta_g[qq0 + QT + tid];
-      }
-    }
-    const unsigned Qs = lds0 + (t & 1) * STAGE, Os = Qs + TILE;
+    const float* lse_s = stat + (t / SP & 1) * 2 * QT;
+    const float* delta_s = lse_s + QT;
+    const unsigned Qs = lds0 + (t / SP & 1) * STAGE, Os = Qs + TILE;
     // sub-tiles of 32 queries; those entirely before this wavefront's keys contribute nothing
     const int first_mt = FULL ? 0 : max(0, (kbase - qq0) / 32);
 #pragma unroll
@@ -628,8 +739,25 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dkv_kernel(const bf16_t* __
     }
   };
   // the first 128 queries are the workgroup's own keys (the diagonal); all later tiles lie after them
-  for (int t = 0; t < 128 / QT; ++t) tile_step(t, std::false_type{});
-  for (int t = 128 / QT; t < n_t; ++t) tile_step(t, std::true_type{});
+  auto arrive = [&](int t) {
+    store_stats(t);   // fetched one tile ago
+    wait_vm<0>();
+    lds_barrier_visible();
+    if (t + SP < n_t) {
+      issue(t + SP);
+      fetch_stats(t + SP);
+    }
+  };
+  for (int t = group; t < 128 / QT; t += SP) { arrive(t); tile_step(t, std::false_type{}); }
+  for (int t = 128 / QT + group; t < n_t; t += SP) { arrive(t); tile_step(t, std::true_type{}); }
+  if constexpr (SP > 1) {
+    join_groups<SP, DP>((float*)smem_attn, group, tid, [&](int r) { return r < DP / 2 ? dk[r / 16][r % 16] : dv[(r - DP / 2) / 16][r % 16]; },
+                        [&](int r, float v) {
+                          if (r < DP / 2) dk[r / 16][r % 16] += v;
+                          else dv[(r - DP / 2) / 16][r % 16] += v;
+                        });
+    if (group != 0) return;
+  }
 
   // dk[i][r]: key = kbase + (r/4)*8 + 4g + r%4, d = i*32 + lane%32
 #pragma unroll
@@ -662,16 +790,48 @@ __global__ __launch_bounds__(256, WGS) void attn_bwd_dkv_kernel(const bf16_t* __
   }
 }
 
+template <int D, int KT, int WGS>
+__global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(AttnBwd p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
+  attn_bwd_dq<D, KT, 1>(p, workgroup_number(), gridDim.y * gridDim.z, smem_attn);
+}
+template <int D, int QT, int WGS>
+__global__ __launch_bounds__(256, WGS) void attn_bwd_dkv_kernel(AttnBwd p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
+  attn_bwd_dkv<D, QT, 1, false>(p, workgroup_number(), gridDim.y * gridDim.z, smem_attn);
+}
+// Both passes in one launch of twice as many workgroups, the longer dK/dV ones first
+template <int D, int KT, int QT, int WGS, int SP, bool OWN_DELTA>
+__global__ __launch_bounds__(256 * SP, WGS) void attn_bwd_both_kernel(AttnBwd p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
+  const int hb = gridDim.y * gridDim.z, n = p.S / 128 * hb, L = workgroup_number();
+  if (L < n) attn_bwd_dkv<D, QT, SP, OWN_DELTA>(p, L, hb, smem_attn);
+  else attn_bwd_dq<D, KT, SP>(p, L - n, hb, smem_attn);
+}
+
 // ------------------------------------------------------------------------------ launchers
 static inline int ok() { return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP; }
 
+template <int D, int KT, int WGS, int SP>
+static void launch_fwd_as(dim3 grid, hipStream_t s, const bf16_t* qkv, bf16_t* ctx, float* lse, int seq, int heads) {
+  // two stages of (K tile, V tile) per group; the other groups' sums on their way to group 0
+  constexpr int lds = std::max(SP * 2 * 2 * tile_bytes(D, KT), SP > 1 ? (2 + padded_d(D) / 2) * 1024 : 0);
+  auto kern = attn_fwd_kernel<D, KT, WGS, SP>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipLaunchKernelGGL(kern, grid, dim3(256 * SP), lds, s, qkv, ctx, lse, seq, heads);
+}
 template <int D>
 static void launch_fwd(dim3 grid, hipStream_t s, const bf16_t* qkv, bf16_t* ctx, float* lse, int seq, int heads) {
   using T = AttnTiles<D>;
-  constexpr int lds = 2 * 2 * tile_bytes(D, T::FWD_KT);   // two stages of (K tile, V tile)
-  auto kern = attn_fwd_kernel<D, T::FWD_KT, T::FWD_WGS>;
-  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, qkv, ctx, lse, seq, heads);
+  // Where no compute unit has a second workgroup, two groups of wavefronts share the key tiles of one: each walks half of
+  // them and the other's MFMAs fill its gaps.  From a sweep, us, one group -> two: 1 x 16 heads x 1024 x 64 16.6 -> 14.4,
+  // 2 x 16 x 512 x 64 10.1 -> 9.6, 1 x 8 x 1024 x 128 25.6 -> 22.2, 2 x 5 x 384 x 152 17.2 -> 15.1, 1 x 18 x 1536 x 152
+  // 63.5 -> 48.1.  On short sequences adding the groups up takes longer than that saves (4 x 256 x 4 x 64 6.5 -> 6.9, 2 x 5
+  // x 384 x 128 12.1 -> 12.6, 1 x 4 x 128 x 152 8.3 -> 9.2), and with two workgroups for a unit nothing is idle (8 x 16 x
+  // 512 x 64 14.6 -> 15.6).
+  const size_t wgs = (size_t)grid.x * grid.y * grid.z;
+  if (wgs <= (size_t)compute_units() && seq >= T::FWD_SPLIT_SEQ) launch_fwd_as<D, T::FWD_KT, 2, 2>(grid, s, qkv, ctx, lse, seq, heads);
+  else launch_fwd_as<D, T::FWD_KT, T::FWD_WGS, 1>(grid, s, qkv, ctx, lse, seq, heads);
 }
 
 int attention_fwd(const bf16_t* qkv, bf16_t* ctx, float* lse, int batch, int seq, int heads, int d, hipStream_t s) {
@@ -683,19 +843,40 @@ int attention_fwd(const bf16_t* qkv, bf16_t* ctx, float* lse, int batch, int seq
   return ok();
 }
 
+template <int D, int KT, int QT, int WGS, int SP>
+static void launch_bwd_both(dim3 grid, hipStream_t s, const AttnBwd& p) {
+  constexpr int dq = SP * 2 * 2 * tile_bytes(D, KT), dkv = SP * (2 * 2 * tile_bytes(D, QT) + 2 * 2 * QT * 4);
+  constexpr int lds = std::max({dq, dkv, SP > 1 ? padded_d(D) * 1024 : 0});
+  auto kern = p.o ? attn_bwd_both_kernel<D, KT, QT, WGS, SP, true> : attn_bwd_both_kernel<D, KT, QT, WGS, SP, false>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  grid.x *= 2;
+  hipLaunchKernelGGL(kern, grid, dim3(256 * SP), lds, s, p);
+}
 template <int D>
-static void launch_bwd(dim3 grid, hipStream_t s, const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse,
-                       float* delta, bf16_t* dqkv, int seq, int heads, float* colsum) {
+static void launch_bwd(dim3 grid, hipStream_t s, const AttnBwd& p) {
   using T = AttnTiles<D>;
+  // Few workgroups: both passes in one launch, side by side on the chip; the dK/dV pass then takes delta from O and dO
+  // itself, which larger grids would pay for again and again.  From a sweep, us, two launches -> one (with the column sums'):
+  //   heads of 64, two groups of wavefronts per workgroup: 4 x 4 heads x 256 26.2 -> 15.7, 1 x 16 x 1024 60.0 -> 31.9,
+  //     1 x 16 x 1536 81.5 -> 44.6 (one group 53.7; 4 x 16 x 512: two groups 32.0, one 25.2)
+  //   heads of 64, one group: 4 x 12 x 384 33.2 -> 22.0, 2 x 16 x 1024 60.7 -> 39.4, 8 x 16 x 512 50.3 -> 47.5,
+  //     32 x 16 x 1024 422 -> 497
+  //   heads of 128: 2 x 5 x 384 43.3 -> 28.8, 1 x 8 x 1024 81.2 -> 55.4, 2 x 16 x 768 68.8 -> 56.1, 3 x 16 x 512 54.0 -> 56.3
+  //   heads of 152: 2 x 5 x 384 50.4 -> 33.1, 1 x 15 x 1536 145 -> 110, 3 x 16 x 512 68.7 -> 74.6
+  const size_t wgs = (size_t)grid.x * grid.y * grid.z, cus = (size_t)compute_units();
+  if (wgs * 2 <= cus || (wgs * 4 <= cus * 3 && p.S >= 640)) return launch_bwd_both<D, T::DQ_KT, T::BOTH_QT, T::BOTH_WGS, T::BOTH_GROUPS>(grid, s, p);
+  if constexpr (D == 64) {
+    if (wgs <= 2 * cus) return launch_bwd_both<D, 64, 64, 2, 1>(grid, s, p);
+  }
   constexpr int l1 = 2 * 2 * tile_bytes(D, T::DQ_KT);                             // two stages of (K tile, V tile)
   constexpr int l2 = 2 * 2 * tile_bytes(D, T::DKV_QT) + 2 * 2 * T::DKV_QT * 4;    // two stages of (Q tile, dO tile) + their lse, delta
   auto kq = attn_bwd_dq_kernel<D, T::DQ_KT, T::DQ_WGS>;
-  const bool few = (size_t)grid.x * grid.y * grid.z <= (size_t)compute_units();   // no second workgroup for one of them
+  const bool few = wgs <= cus;   // no second workgroup for one of them
   auto kkv = few ? attn_bwd_dkv_kernel<D, T::DKV_QT, T::DKV_WGS_FEW> : attn_bwd_dkv_kernel<D, T::DKV_QT, T::DKV_WGS>;
   (void)hipFuncSetAttribute((const void*)kq, hipFuncAttributeMaxDynamicSharedMemorySize, l1);
   (void)hipFuncSetAttribute((const void*)kkv, hipFuncAttributeMaxDynamicSharedMemorySize, l2);
-  hipLaunchKernelGGL(kq, grid, dim3(256), l1, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, colsum);
-  hipLaunchKernelGGL(kkv, grid, dim3(256), l2, s, qkv, dctx, lse, delta, dqkv, seq, heads, colsum);
+  hipLaunchKernelGGL(kq, grid, dim3(256), l1, s, p);
+  hipLaunchKernelGGL(kkv, grid, dim3(256), l2, s, p);
 }
 
 size_t attention_bwd_colsum_bytes(int batch, int seq, int heads, int d) {
@@ -717,9 +898,10 @@ int attention_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, cons
     hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, ctx, dctx, delta, seq, heads, d, total);
     ctx = nullptr;
   }
-  if (d == 64) launch_bwd<64>(grid, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, sums);
-  else if (d == 128) launch_bwd<128>(grid, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, sums);
-  else launch_bwd<152>(grid, s, qkv, ctx, dctx, lse, delta, dqkv, seq, heads, sums);
+  const AttnBwd p{qkv, ctx, dctx, lse, delta, dqkv, sums, seq, heads};
+  if (d == 64) launch_bwd<64>(grid, s, p);
+  else if (d == 128) launch_bwd<128>(grid, s, p);
+  else launch_bwd<152>(grid, s, p);
   if (sums) *colsum_rows = batch * (seq / 32);
   return ok();
 }
