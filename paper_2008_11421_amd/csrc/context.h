@@ -84,6 +84,8 @@ struct ProgOp {
   uint64_t hold_elems = 0;            // elements of that tensor
 };
 
+constexpr int IMAGE_STORED = 8;   // channels an image has on the device (zeros behind its own): one 16-byte vector a pixel
+
 struct Ctx {
   karma_model_desc desc{};
   karma_config cfg{};
@@ -96,6 +98,7 @@ struct Ctx {
   uint64_t fixed_bytes = 0;
   uint64_t in_off = 0, lab_off = 0, loss_off = 0, misc_off = 0;   // fixed-region offsets
   uint64_t in_bytes = 0, lab_bytes = 0, misc_bytes = 0;
+  int image_channels = 0;        // the inputs are fp32 images of this many channels, stored as IMAGE_STORED of bf16
   void* stage_in = nullptr;      // pinned staging of inputs, labels, loss
   void* stage_lab = nullptr;
   float* stage_loss = nullptr;

@@ -299,6 +299,39 @@ __global__ void relu_mask_kernel(const bf16_t* __restrict__ dy, const bf16_t* __
   ((u32x4*)dz)[i] = o;
 }
 
+// Channels of an image, [pixels][CH] in host memory, spread out to eight a pixel.  Bound by the link the source lies behind:
+// every byte of it is read once, 16 a lane and 4 KiB a workgroup and load, and parked in LDS, from where each lane takes a
+// pixel and writes its 16 bytes.
+constexpr int EXPAND_PIXELS = 2048;   // per workgroup
+template <int CH>
+__global__ __launch_bounds__(256) void image_expand_kernel(const bf16_t* __restrict__ compact, bf16_t* __restrict__ y, size_t pixels) {
+  __shared__ __attribute__((aligned(16))) bf16_t part[EXPAND_PIXELS * CH];
+  const size_t first = (size_t)blockIdx.x * EXPAND_PIXELS;
+  const int n = (int)min((size_t)EXPAND_PIXELS, pixels - first), elems = n * CH;
+  const bf16_t* src = compact + first * CH;
+  constexpr int LOADS = EXPAND_PIXELS * CH / 8 / 256;
+  u32x4 v[LOADS];
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    const int at = (i * 256 + (int)threadIdx.x) * 8;
+    if (at + 8 <= elems) v[i] = *(const u32x4*)(src + at);
+  }
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    const int at = (i * 256 + (int)threadIdx.x) * 8;
+    if (at + 8 <= elems) *(u32x4*)(part + at) = v[i];
+    else
+      for (int e = at; e < elems; ++e) part[e] = src[e];
+  }
+  __syncthreads();
+  for (int p = threadIdx.x; p < n; p += 256) {
+    u32x4 o = {0, 0, 0, 0};
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) o[ch / 2] |= (unsigned)part[p * CH + ch] << (16 * (ch & 1));
+    *(u32x4*)(y + (first + p) * 8) = o;
+  }
+}
+
 // 3x3 max pooling, stride 2, padding 1 (padding never wins)
 __global__ void maxpool_fwd_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, int N, int H, int W, int C,
                                    int Ho, int Wo) {
@@ -683,6 +716,15 @@ int bn_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const bf16_t* 
 int relu_mask_bwd(const bf16_t* dy, const bf16_t* y, bf16_t* dz, size_t n, hipStream_t s) {
   if (!dy || !y || !dz || n % 8) return KARMA_E_INVAL;
   hipLaunchKernelGGL(relu_mask_kernel, dim3(blocks_for(n / 8, 256)), dim3(256), 0, s, dy, y, dz, n / 8);
+  return ok();
+}
+
+int image_expand(const bf16_t* compact, bf16_t* y, size_t pixels, int channels, hipStream_t s) {
+  if (!compact || !y || !pixels || ((uintptr_t)compact % 16) || ((uintptr_t)y % 16)) return KARMA_E_INVAL;
+  const unsigned blocks = (unsigned)((pixels + EXPAND_PIXELS - 1) / EXPAND_PIXELS);
+  if (channels == 1) hipLaunchKernelGGL(image_expand_kernel<1>, dim3(blocks), dim3(256), 0, s, compact, y, pixels);
+  else if (channels == 3) hipLaunchKernelGGL(image_expand_kernel<3>, dim3(blocks), dim3(256), 0, s, compact, y, pixels);
+  else return KARMA_E_INVAL;
   return ok();
 }
 

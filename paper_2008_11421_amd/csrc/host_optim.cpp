@@ -97,6 +97,7 @@ void sgd_momentum_update(float* w, float* buf, const void* g, bool g_is_bf16, si
                          bool out_is_bf16);
 void adam_update(float* w, float* m, float* v, const void* g, bool g_is_bf16, size_t n, float lr, float beta1, float beta2,
                  float eps, float c1, float c2, void* out, bool out_is_bf16);
+void to_bf16(const float* x, size_t n, uint16_t* out);
 }  // namespace avx512
 
 static bool g_force_narrow = false;
@@ -106,6 +107,11 @@ static bool wide_vectors() {
   static const bool yes = __builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512bw") &&
                           __builtin_cpu_supports("avx512vl") && __builtin_cpu_supports("avx512dq");
   return yes && !g_force_narrow;
+}
+
+void to_bf16(const float* x, size_t n, uint16_t* out) {
+  if (wide_vectors()) avx512::to_bf16(x, n, out);
+  else avx2::to_bf16_entry(x, n, out);
 }
 
 void sgd_momentum_update(float* w, float* buf, const void* g, bool g_is_bf16, size_t n, float lr, float mu, void* out,

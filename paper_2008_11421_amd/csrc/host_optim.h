@@ -33,6 +33,7 @@ class HostPool {
 
 float bf16_to_f32(uint16_t b);
 uint16_t f32_to_bf16_rne(float f);
+void to_bf16(const float* x, size_t n, uint16_t* out);   // the same for n values, in the widest vectors there are
 
 // w -= lr * g ; new weights also written in device format to `out`.
 void sgd_update(float* w, const void* g, bool g_is_bf16, size_t n, float lr, void* out, bool out_is_bf16);

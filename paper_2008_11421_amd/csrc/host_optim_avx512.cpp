@@ -19,5 +19,7 @@ void adam_update(float* w, float* m, float* v, const void* g, bool g_is_bf16, si
   avx512_impl::adam_entry(w, m, v, g, g_is_bf16, n, lr, beta1, beta2, eps, c1, c2, out, out_is_bf16);
 }
 
+void to_bf16(const float* x, size_t n, uint16_t* out) { avx512_impl::to_bf16_entry(x, n, out); }
+
 }  // namespace avx512
 }  // namespace karma

@@ -42,6 +42,11 @@ static inline void store_w(void* out, size_t i, float w) {
   }
 }
 
+static void to_bf16_loop(const float* __restrict__ x, size_t n, uint16_t* __restrict__ out) {
+  for (size_t i = 0; i < n; ++i) store_w<true>(out, i, x[i]);
+}
+inline void to_bf16_entry(const float* x, size_t n, uint16_t* out) { to_bf16_loop(x, n, out); }
+
 // INPLACE: the gradient lies in the output buffer (same element type) and each element is replaced by its new
 // weight; only `out` is then used, so that no two restrict-qualified pointers name the same memory.
 template <bool G_BF16, bool O_BF16, bool INPLACE>

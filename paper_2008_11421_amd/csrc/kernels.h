@@ -137,6 +137,8 @@ int bn_apply(const bf16_t* x, const float* stats, const bf16_t* g, const bf16_t*
 int bn_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const bf16_t* g, const bf16_t* b, int relu, bf16_t* dx,
            float* dgamma, float* dbeta, float* ws, int rows, int c, hipStream_t s, const bf16_t* add = nullptr);
 int relu_mask_bwd(const bf16_t* dy, const bf16_t* y, bf16_t* dz, size_t n, hipStream_t s);
+// compact: bf16 [pixels][channels] in pinned host memory, 16-byte aligned; y: [pixels][8] on the device, zeros behind them
+int image_expand(const bf16_t* compact, bf16_t* y, size_t pixels, int channels, hipStream_t s);
 int maxpool_fwd(const bf16_t* x, bf16_t* y, int n, int h, int w, int c, hipStream_t s);   // 3x3, stride 2, pad 1
 int maxpool_bwd(const bf16_t* x, const bf16_t* dy, bf16_t* dx, int n, int h, int w, int c, hipStream_t s);
 int maxpool2_fwd(const bf16_t* x, bf16_t* y, int n, int h, int w, int c, hipStream_t s);  // 2x2, stride 2; h, w even

@@ -191,14 +191,15 @@ int unet_build_records(Ctx& c) {
   head.ws_bytes = HeadWs(net).total;
   c.rec.push_back(std::move(head));
   c.in_bytes = (uint64_t)net.N * net.S * net.S * IMG_C * 2;
+  c.image_channels = 1;
   c.lab_bytes = (uint64_t)net.N * net.S * net.S * 4;
   c.misc_bytes = 0;
   return unet_skips(d, c.skips);
 }
 
-// images fp32 [N][S][S] (one channel) -> bf16 [N][S][S][8] (round to nearest even, channels 1..7 zero);
+// labels are checked here; the images (fp32 [N][S][S]) are stored as bf16 [N][S][S][8] by the executor
 // labels int32 [N][S][S]
-int unet_prepare_step(Ctx& c, const void* in, const void* lab) {
+int unet_prepare_step(Ctx& c, const void*, const void* lab) {
   UNet net(c.desc);
   const size_t pixels = (size_t)net.N * net.S * net.S;
   const int32_t* labels = (const int32_t*)lab;
@@ -212,15 +213,6 @@ int unet_prepare_step(Ctx& c, const void* in, const void* lab) {
     c.err = "label outside the classes";
     return KARMA_E_INVAL;
   }
-  const float* img = (const float*)in;
-  uint16_t* out = (uint16_t*)c.stage_in;
-  c.pool->parallel_for(pixels, [&](size_t lo, size_t hi) {
-    for (size_t p = lo; p < hi; ++p) {
-      uint16_t* o = out + p * IMG_C;
-      o[0] = f32_to_bf16_rne(img[p]);
-      for (int ch = 1; ch < IMG_C; ++ch) o[ch] = 0;
-    }
-  });
   std::memcpy(c.stage_lab, lab, c.lab_bytes);
   return KARMA_OK;
 }

@@ -191,13 +191,14 @@ int wrn_build_records(Ctx& c) {
   head.ws_bytes = HeadWs(net).total;
   c.rec.push_back(std::move(head));
   c.in_bytes = (uint64_t)net.N * net.S * net.S * IMG_C * 2;
+  c.image_channels = 3;
   c.lab_bytes = (uint64_t)net.N * 4;
   c.misc_bytes = 0;
   return KARMA_OK;
 }
 
-// images fp32 [N][S][S][3] -> bf16 [N][S][S][8] (round to nearest even, channels 3..7 zero)
-int wrn_prepare_step(Ctx& c, const void* in, const void* lab) {
+// labels are checked here; the images (fp32 [N][S][S][3]) are stored as bf16 [N][S][S][8] by the executor
+int wrn_prepare_step(Ctx& c, const void*, const void* lab) {
   WideNet net(c.desc);
   const int32_t* labels = (const int32_t*)lab;
   for (int i = 0; i < net.N; ++i)
@@ -205,16 +206,6 @@ int wrn_prepare_step(Ctx& c, const void* in, const void* lab) {
       c.err = "label outside the classes";
       return KARMA_E_INVAL;
     }
-  const float* img = (const float*)in;
-  uint16_t* out = (uint16_t*)c.stage_in;
-  const size_t pixels = (size_t)net.N * net.S * net.S;
-  c.pool->parallel_for(pixels, [&](size_t lo, size_t hi) {
-    for (size_t p = lo; p < hi; ++p) {
-      uint16_t* o = out + p * IMG_C;
-      for (int ch = 0; ch < 3; ++ch) o[ch] = f32_to_bf16_rne(img[p * 3 + ch]);
-      for (int ch = 3; ch < IMG_C; ++ch) o[ch] = 0;
-    }
-  });
   std::memcpy(c.stage_lab, lab, c.lab_bytes);
   return KARMA_OK;
 }
