@@ -493,7 +493,7 @@ int karma_k_gemm_gelu_bf16(const void* a_dev, const void* b_dev, void* c_dev, co
  * that do not start on 16-byte boundaries.  parts_out: room for two.  Errors: KARMA_E_INVAL. */
 #define KARMA_PRODUCT_STAGED_SMALL 0u /* 128 x 128, through registers */
 #define KARMA_PRODUCT_STAGED_LARGE 1u /* 256 x 256, through registers */
-#define KARMA_PRODUCT_SMALL 2u        /* 128 x 128, straight into LDS */
+#define KARMA_PRODUCT_SMALL 2u        /* 128 x 128 or 64 x 64, straight into LDS */
 #define KARMA_PRODUCT_LARGE 3u        /* 256 x 256, straight into LDS */
 #define KARMA_PRODUCT_NARROW 4u       /* 256 x 64, straight into LDS */
 typedef struct {

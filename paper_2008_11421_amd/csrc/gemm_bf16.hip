@@ -18,6 +18,7 @@
 #include "device_utils.h"
 #include "gemm_epilogue.h"
 #include "gemm_ring.h"
+#include "gemm_slices.h"
 #include "kernels.h"
 
 namespace karma {
@@ -829,13 +830,30 @@ static void launch_direct(const GemmArgs& g, hipStream_t s, dim3 grid, dim3 bloc
 
 // How a product is cut up: tile and number of ranges of the reduction
 struct GemmPlan {
-  int tile;     // 256: the direct-load kernel above, 128: gemm_ring.hip
+  int tile;     // 256: the direct-load kernel above, 128: gemm_ring.hip, 64: gemm_slices.hip
   int splits;
   bool deep;    // 128: four stages
   double us;    // modelled time
 };
 
-// The cheaper of the two tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
+// Modelled time of a launch of the 64 x 64 tile in us: `items` workgroups of kt k-tiles each.  Up to four k-tiles two
+// workgroups share a compute unit; from there on one has it to itself and its wavefronts take every fourth k-tile.
+//   us, this tile / the better of the other two with its ranges added up: 1024 x 256 x 256 4.9 / 6.4, 1024 x 1024 x 256
+//   5.2 / 6.6, 1024 x 256 x 1024 6.9 / 10.6, 64 x 2048 x 1000 7.0 / 10.4, 1024 x 1024 x 1024 7.6 / 11.5, 64 x 1000 x 2048 in
+//   four ranges 8.1 / 10.1; 4096 x 1024 x 256 10.3 / 7.4, 2048 x 1024 x 1024 13.1 / 12.0, 2048 x 2048 x 2048 34 / 21
+// SLICES_MAX_KT: as far as this was measured; a workgroup fetches as many bytes per k-tile as it multiplies 64 x 64 by.
+constexpr double SLICES_BASE = 1.4, SLICES_ROUND = 2.8, SLICES_TILE = 0.68;
+constexpr int SLICES_MAX_KT = 32;
+static double slices_us(long items, int kt, int cus) {
+  if (kt <= SLICE_WAVES) {
+    const long rounds = (items + 2l * cus - 1) / (2l * cus), rest = items - (rounds - 1) * 2l * cus;
+    return SLICES_BASE + SLICES_ROUND + SLICES_TILE + 3.9 * (rounds - 1) + 0.33 * kt * std::max(0.0, (double)(rest - cus) / cus);
+  }
+  const long rounds = (items + cus - 1) / cus;
+  return SLICES_BASE + rounds * (SLICES_ROUND + SLICES_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES));
+}
+
+// The cheapest of the three tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
 // item for every place on the chip (one per compute unit with the 256 tile, two with the 128 tile); a k-tile of 64 costs,
 // in a full round and with the places of the last one partly empty, what was measured on 500 products from 64 x 1000 x
 // 2048 to 8192 x 3072 x 3072 and 470 convolutions: 1.5 us down to 1.25 us for the large tile (2.0 to 1.4 where its first
@@ -857,19 +875,22 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
   const double by_element = g.N % 8 || g.ldc % 8 ? std::min(1.0, g.M / 128.0) : 0.0;
   GemmPlan best{0, 1, false, 1e30};
   const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
-  for (int tile = 128; tile <= 256; tile += 128) {
-    if (!(tile == 256 ? large : small)) continue;
+  for (int tile = 64; tile <= 256; tile *= 2) {
+    if (!(tile == 256 ? large : tile == 128 ? small : small && !g.conv_mode && g.N % 8 == 0 && g.ldc % 8 == 0)) continue;
     const long tiles = (long)((g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile);
     GemmPlan own{tile, 1, false, 1e30};   // the best number of ranges with this tile ...
     double late = 0.0;                    // ... and what its k-tiles take beyond two workgroups' pace
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && ((uint64_t)sp * g.M * g.N * sizeof(float) > g.ws_bytes || tiles * sp > 8l * cus)) break;
-      const long items = tiles * sp, places = tile == 256 ? cus : 2l * cus, full = items / places, rest = items % places;
       const int kt = (k_tiles + sp - 1) / sp;
+      const long items = tiles * sp, places = tile == 256 ? cus : 2l * cus, full = items / places, rest = items % places;
       const long rounds = full + (rest ? 1 : 0);
       const double f = (double)rest / cus;   // workgroups per compute unit in the last round
       double us, more = 0.0;
-      if (tile == 256) {
+      if (tile == 64) {
+        if (kt > SLICES_MAX_KT) continue;
+        us = slices_us(items, kt, cus) + 0.4 + 0.09 * kt;   // (by which the small tile's figure below is too high at few k-tiles)
+      } else if (tile == 256) {
         us = 9.0 + 4.0 * (rounds - 1) + ragged * kt * (full * full256 + (rest ? alone256 + (full256 - alone256) * f : 0.0));
       } else {
         const double last = !rest ? 0.0 : f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0);
@@ -1031,7 +1052,18 @@ static int launch_general(const GemmArgs& g, int splits, hipStream_t s) {
 
 thread_local GemmTimer* g_gemm_timer = nullptr;
 
-static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s);
+// The 64 x 64 tile
+static SliceWork slice_work(const GemmArgs& g, int& splits) {
+  const int k_per_split = range_length(g.K, splits);
+  SliceWork w{g.A, g.B, epilogue_of(g), (float*)g.ws, g.M, g.N, g.K, g.lda, g.ldb, splits, k_per_split};
+  if (splits == 1) take_colsum(g, (g.M + SLICE_TILE - 1) / SLICE_TILE, w.ep);
+  return w;
+}
+static int launch_slices(const GemmArgs& g, int splits, hipStream_t s) {
+  const SliceWork w = slice_work(g, splits);
+  const int st = gemm_slices_launch(w, SliceForm{g.a_kc, g.b_kc, g.act}, nullptr, s);
+  return st == KARMA_OK ? finish(g, w.ep, splits, s) : st;
+}
 
 // The 128 x 128 tile: geometry of the gathered forms, then the launch
 static int launch_ring(const GemmArgs& g, int splits, bool deep, hipStream_t s) {
@@ -1077,38 +1109,24 @@ static int launch_ring(const GemmArgs& g, int splits, bool deep, hipStream_t s) 
   return st == KARMA_OK ? finish(g, ep, splits, s) : st;
 }
 
-int gemm_bf16(const GemmArgs& g, hipStream_t s) {
-  GemmTimer* t = g_gemm_timer;
-  if (!t) return gemm_bf16_launch(g, s);
-  if (t->stride > 1 && (t->seq++ % t->stride) != t->phase % t->stride) return gemm_bf16_launch(g, s);
-  while (t->events->size() < *t->used + 2) {
-    hipEvent_t e;
-    if (hipEventCreate(&e) != hipSuccess) return KARMA_E_HIP;
-    t->events->push_back(e);
-  }
-  if (hipEventRecord((*t->events)[*t->used], s) != hipSuccess) return KARMA_E_HIP;
-  const int st = gemm_bf16_launch(g, s);
-  if (hipEventRecord((*t->events)[*t->used + 1], s) != hipSuccess) return KARMA_E_HIP;
-  *t->used += 2;
-  t->flops->push_back(2.0 * g.M * g.N * g.K);
-  return st;
-}
+constexpr uint32_t PRODUCT_SLICES = 16;   // the 64 x 64 tile: reported as KARMA_PRODUCT_SMALL
 
 // One launch of a product (with the sum of its ranges): what gemm_choose decides and launch_piece carries out
 struct Piece {
   GemmArgs g;
-  uint32_t kernel;   // KARMA_PRODUCT_*
+  uint32_t kernel;   // KARMA_PRODUCT_*, or PRODUCT_SLICES
   int splits;
   bool deep;    // the 128 x 128 tile: four stages
 };
 static Piece planned(const GemmArgs& g, const GemmPlan& p) {
-  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : KARMA_PRODUCT_SMALL, p.splits, p.deep};
+  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : PRODUCT_SLICES, p.splits, p.deep};
 }
 static int launch_piece(const Piece& p, hipStream_t s) {
   switch (p.kernel) {
     case KARMA_PRODUCT_LARGE: return launch_large<256, 2, 4>(p.g, p.splits, s);
     case KARMA_PRODUCT_NARROW: return launch_large<64, 4, 2>(p.g, p.splits, s);
     case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, s);
+    case PRODUCT_SLICES: return launch_slices(p.g, p.splits, s);
     case KARMA_PRODUCT_STAGED_LARGE: return launch_general<256, 256, 2, 4>(p.g, p.splits, s);
     default: return launch_general<128, 128, 2, 2>(p.g, p.splits, s);
   }
@@ -1254,6 +1272,67 @@ static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
   return st;
 }
 
+// Both gradients of a layer in one launch of the 64 x 64 tile where that is modelled to be the shorter way
+static bool pair_of_slices(const GemmArgs& dx, const GemmArgs& dw) {
+  const GemmArgs* g[2] = {&dx, &dw};
+  const int cus = compute_units();
+  double apart = 0.0, work = 0.0, longest = 0.0;
+  long items = 0;
+  for (int i = 0; i < 2; ++i) {
+    Piece piece[2];
+    int pieces = 0;
+    if (gemm_choose(*g[i], piece, &pieces) != KARMA_OK || pieces != 1) return false;
+    // (products of which one alone fills the chip are better off with tiles of their own)
+    if (piece[0].kernel != PRODUCT_SLICES && piece[0].kernel != KARMA_PRODUCT_SMALL) return false;
+    if (!gemm_ring_takes(*g[i])) return false;
+    apart += plan_product(*g[i], false, true, g[i]->ws && g[i]->ldc == g[i]->N && !g[i]->act).us;
+    const long n = (long)((g[i]->M + SLICE_TILE - 1) / SLICE_TILE) * ((g[i]->N + SLICE_TILE - 1) / SLICE_TILE);
+    const int kt = (g[i]->K + SLICE_BK - 1) / SLICE_BK;
+    const double one = SLICES_ROUND + SLICES_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES);
+    items += n;
+    work += n * one;
+    longest = std::max(longest, one);
+  }
+  const double together = SLICES_BASE + (items <= cus ? longest : work / cus + 0.5 * longest);
+  return together < apart;
+}
+
+static int gemm_pair_launch(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
+  if (dx.a_kc && !dx.b_kc && dx.act != 1 && !dw.a_kc && !dw.b_kc && !dw.act && !dx.conv_mode && !dw.conv_mode && pair_of_slices(dx, dw)) {
+    int one = 1;
+    const SliceWork a = slice_work(dx, one), b = slice_work(dw, one);
+    return gemm_slices_launch(a, SliceForm{true, false, dx.act}, &b, s);
+  }
+  const int st = gemm_bf16_launch(dx, s);
+  return st == KARMA_OK ? gemm_bf16_launch(dw, s) : st;
+}
+
+// Launches with events around them when the caller samples them
+template <class Launch>
+static int timed(double flops, hipStream_t s, Launch launch) {
+  GemmTimer* t = g_gemm_timer;
+  if (!t) return launch();
+  if (t->stride > 1 && (t->seq++ % t->stride) != t->phase % t->stride) return launch();
+  while (t->events->size() < *t->used + 2) {
+    hipEvent_t e;
+    if (hipEventCreate(&e) != hipSuccess) return KARMA_E_HIP;
+    t->events->push_back(e);
+  }
+  if (hipEventRecord((*t->events)[*t->used], s) != hipSuccess) return KARMA_E_HIP;
+  const int st = launch();
+  if (hipEventRecord((*t->events)[*t->used + 1], s) != hipSuccess) return KARMA_E_HIP;
+  *t->used += 2;
+  t->flops->push_back(flops);
+  return st;
+}
+
+int gemm_bf16(const GemmArgs& g, hipStream_t s) {
+  return timed(2.0 * g.M * g.N * g.K, s, [&] { return gemm_bf16_launch(g, s); });
+}
+int gemm_bf16_pair(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
+  return timed(2.0 * dx.M * dx.N * dx.K + 2.0 * dw.M * dw.N * dw.K, s, [&] { return gemm_pair_launch(dx, dw, s); });
+}
+
 int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n) {
   Piece piece[2];
   int pieces = 0;
@@ -1262,7 +1341,7 @@ int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n) {
   for (int i = 0; i < pieces; ++i) {
     int splits = piece[i].splits;
     (void)range_length(piece[i].g.K, splits);   // (ranges are whole k-tiles: the last may come to nothing)
-    parts[i] = karma_product_part{piece[i].kernel, (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
+    parts[i] = karma_product_part{piece[i].kernel == PRODUCT_SLICES ? KARMA_PRODUCT_SMALL : piece[i].kernel, (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
   }
   *n = (uint32_t)pieces;
   return KARMA_OK;

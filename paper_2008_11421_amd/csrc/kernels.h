@@ -71,6 +71,10 @@ struct GemmArgs {
   int* colsum_rows;
 };
 int gemm_bf16(const GemmArgs& g, hipStream_t s);
+// The two products a layer's gradient dy goes into, independent of each other: dx = dy w (A k-contiguous, B strided; act 0 or
+// 2) and dw = dy^T x (both strided).  Small ones run side by side in one launch.  A workspace may be the same: it is used by
+// one after the other or not at all.
+int gemm_bf16_pair(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
 // How gemm_bf16 would carry the product out (at most two parts; host only, addresses are looked at and not followed)
 int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n);
 // While non-null on the calling thread, gemm_bf16 calls record an event before and after

@@ -122,8 +122,8 @@ Param make_param(uint64_t n, bool matrix) {
   return p;
 }
 
-int gemm_raw(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, const bf16_t* res, int M, int N, int K,
-             bool a_kc, bool b_kc, bool out_f32, bool acc, hipStream_t s, void* ws, size_t ws_bytes) {
+GemmArgs product(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, const bf16_t* res, int M, int N, int K,
+                 bool a_kc, bool b_kc, bool out_f32 = false, bool acc = false, void* ws = nullptr, size_t ws_bytes = 0) {
   GemmArgs g{};
   g.A = A; g.B = B; g.C = C; g.bias = bias; g.residual = res;
   g.M = M; g.N = N; g.K = K;
@@ -133,31 +133,32 @@ int gemm_raw(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, cons
   g.ldc = N;
   g.out_f32 = out_f32; g.accumulate = acc;
   g.ws = ws; g.ws_bytes = ws_bytes;
-  return gemm_bf16(g, s);
+  return g;
 }
 
 int gemm(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, const bf16_t* res, int M, int N, int K,
          bool a_kc, bool b_kc, bool out_f32, bool acc, hipStream_t s, void* ws = nullptr, size_t ws_bytes = 0) {
-  return gemm_raw(A, B, C, bias, res, M, N, K, a_kc, b_kc, out_f32, acc, s, ws, ws_bytes);
+  return gemm_bf16(product(A, B, C, bias, res, M, N, K, a_kc, b_kc, out_f32, acc, ws, ws_bytes), s);
 }
 
 // the product with the feed-forward GELU folded into its output stage (mode 1: aux = GELU(C) written;
 // mode 2: C = (A B^T) * GELU'(aux))
-int gemm_gelu(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, bf16_t* aux, int M, int N, int K, bool a_kc,
-              bool b_kc, int mode, hipStream_t s, float* colsum_partial = nullptr, size_t colsum_bytes = 0, int* colsum_rows = nullptr) {
-  GemmArgs g{};
-  g.A = A; g.B = B; g.C = C; g.bias = bias;
-  g.M = M; g.N = N; g.K = K;
-  g.a_kc = a_kc; g.b_kc = b_kc;
-  g.lda = a_kc ? K : M;
-  g.ldb = b_kc ? K : N;
-  g.ldc = N;
+GemmArgs product_gelu(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, bf16_t* aux, int M, int N, int K, bool a_kc,
+                      bool b_kc, int mode, float* colsum_partial = nullptr, size_t colsum_bytes = 0, int* colsum_rows = nullptr) {
+  GemmArgs g = product(A, B, C, bias, nullptr, M, N, K, a_kc, b_kc);
   g.act = mode;
   g.aux = aux;
   g.colsum_partial = colsum_partial;
   g.colsum_bytes = colsum_bytes;
   g.colsum_rows = colsum_rows;
-  return gemm_bf16(g, s);
+  return g;
+}
+
+// dx = dy w and dw = dy^T x (dy [rows][n], w [n][k], x [rows][k])
+int gradients(const bf16_t* dy, const bf16_t* w, const bf16_t* x, bf16_t* dx, void* dw, int rows, int n, int k, hipStream_t s,
+              void* ws, size_t ws_bytes) {
+  return gemm_bf16_pair(product(dy, w, dx, nullptr, nullptr, rows, k, n, true, false, false, false, ws, ws_bytes),
+                        product(dy, x, dw, nullptr, nullptr, n, k, rows, false, false, false, false, ws, ws_bytes), s);
 }
 
 #define TRY(call)          \
@@ -292,7 +293,7 @@ int attn_half_fwd(const Dims& d, const bf16_t* x, const AttnBufs& b, const Split
 template <class WF>
 int ffn_half_fwd(const Dims& d, const bf16_t* r1, const FfnBufs& b, const SplitWs& w, bf16_t* out, WF W, hipStream_t s) {
   TRY(layernorm_fwd(r1, W(LN2_G), W(LN2_B), b.m, b.stats2, d.T, d.h, s));
-  TRY(gemm_gelu(b.m, W(W1), b.f1, W(B1), b.g, d.T, d.ffn, d.h, true, true, 1, s));   // f1 = m W1^T + b1, g = GELU(f1)
+  TRY(gemm_bf16(product_gelu(b.m, W(W1), b.f1, W(B1), b.g, d.T, d.ffn, d.h, true, true, 1), s));   // f1 = m W1^T + b1, g = GELU(f1)
   if (out) TRY(gemm(b.g, W(W2), out, W(B2), r1, d.T, d.h, d.ffn, true, true, false, false, s, w.at, w.bytes));
   return KARMA_OK;
 }
@@ -303,11 +304,10 @@ int ffn_half_bwd(const Dims& d, const bf16_t* dy, const bf16_t* r1, const FfnBuf
                  GF G, hipStream_t s) {
   // df1 = (dy W2) * GELU'(f1); where the kernel can, it leaves partial column sums of df1 (FC1's bias gradient)
   int sum_rows = 0;
-  TRY(gemm_gelu(dy, W(W2), w.wide, nullptr, b.f1, d.T, d.ffn, d.h, true, false, 2, s, w.part, colsum_ws_bytes(d.T, d.ffn), &sum_rows));
+  TRY(gemm_bf16_pair(product_gelu(dy, W(W2), w.wide, nullptr, b.f1, d.T, d.ffn, d.h, true, false, 2, w.part, colsum_ws_bytes(d.T, d.ffn), &sum_rows),
+                     product(dy, b.g, G(W2), nullptr, nullptr, d.h, d.ffn, d.T, false, false, false, false, w.splitk, w.splitk_bytes), s));  // dW2 = dy^T g
   if (sum_rows) TRY(colsum_finish(w.part, sum_rows, d.ffn, (float*)G(B1), s));
-  TRY(gemm(dy, b.g, G(W2), nullptr, nullptr, d.h, d.ffn, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));        // dW2 = dy^T g
-  TRY(gemm(w.wide, W(W1), w.t1, nullptr, nullptr, d.T, d.h, d.ffn, true, false, false, false, s, w.splitk, w.splitk_bytes));  // dm = df1 W1
-  TRY(gemm(w.wide, b.m, G(W1), nullptr, nullptr, d.ffn, d.h, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));    // dW1 = df1^T m
+  TRY(gradients(w.wide, W(W1), b.m, w.t1, G(W1), d.T, d.ffn, d.h, s, w.splitk, w.splitk_bytes));   // dm = df1 W1, dW1 = df1^T m
   if (!sum_rows) TRY(colsum_bf16(w.wide, (float*)G(B1), w.part, d.T, d.ffn, s));
   // dr1 = LN2'(dm) + dy; the same pass sums dy's columns: the gradient of FC2's bias
   TRY(layernorm_bwd(w.t1, r1, b.stats2, W(LN2_G), dy, dr1, (float*)G(LN2_G), (float*)G(LN2_B), w.part, d.T, d.h, s,
@@ -319,14 +319,12 @@ int ffn_half_bwd(const Dims& d, const bf16_t* dy, const bf16_t* r1, const FfnBuf
 template <class WF, class GF>
 int attn_half_bwd(const Dims& d, const bf16_t* dr1, const bf16_t* x, const AttnBufs& b, const BwdBufs& w, bf16_t* dx, WF W,
                   GF G, hipStream_t s) {
-  TRY(gemm(dr1, W(WO), w.t1, nullptr, nullptr, d.T, d.h, d.h, true, false, false, false, s, w.splitk, w.splitk_bytes));  // dctx = dr1 Wo
-  TRY(gemm(dr1, b.ctx, G(WO), nullptr, nullptr, d.h, d.h, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));       // dWo = dr1^T ctx
+  TRY(gradients(dr1, W(WO), b.ctx, w.t1, G(WO), d.T, d.h, d.h, s, w.splitk, w.splitk_bytes));   // dctx = dr1 Wo, dWo = dr1^T ctx
   // the kernels leave partial column sums of dqkv (the QKV bias gradient) in the workspace
   int sum_rows = 0;
   TRY(attention_bwd(b.qkv, b.ctx, w.t1, b.lse, w.delta, w.wide, d.B, d.S, d.H, d.D, s, w.part, &sum_rows));
   TRY(colsum_finish(w.part, sum_rows, 3 * d.h, (float*)G(BQKV), s));
-  TRY(gemm(w.wide, W(WQKV), w.t3, nullptr, nullptr, d.T, d.h, 3 * d.h, true, false, false, false, s, w.splitk, w.splitk_bytes));  // da = dqkv Wqkv
-  TRY(gemm(w.wide, b.a, G(WQKV), nullptr, nullptr, 3 * d.h, d.h, d.T, false, false, false, false, s, w.splitk, w.splitk_bytes));  // dWqkv = dqkv^T a
+  TRY(gradients(w.wide, W(WQKV), b.a, w.t3, G(WQKV), d.T, 3 * d.h, d.h, s, w.splitk, w.splitk_bytes));   // da = dqkv Wqkv, dWqkv = dqkv^T a
   // dx = LN1'(da) + dr1; the same pass sums dr1's columns: the gradient of the output projection's bias
   TRY(layernorm_bwd(w.t3, x, b.stats1, W(LN1_G), dr1, dx, (float*)G(LN1_G), (float*)G(LN1_B), w.part, d.T, d.h, s,
                     (float*)G(BO)));
@@ -430,9 +428,9 @@ int gpt_loss(Ctx& c, const LayerIO& io, hipStream_t s) {
     const bf16_t* xc = xf + (size_t)t0 * d.h;
     TRY(gemm(xc, wte, logits, nullptr, nullptr, n, d.V, d.h, true, true, false, false, s));          // logits = xf wte^T
     TRY(softmax_ce(logits, labels + t0, rowloss + t0, n, d.V, 1.0f / (float)d.T, s));                 // -> dlogits
-    TRY(gemm(logits, wte, dxf + (size_t)t0 * d.h, nullptr, nullptr, n, d.h, d.V, true, false, false, false, s,
-             Wk + wl.splitk, wl.splitk_bytes));
-    TRY(gemm(logits, xc, dwte, nullptr, nullptr, d.V, d.h, n, false, false, true, true, s));          // dwte += dlogits^T xf
+    TRY(gemm_bf16_pair(product(logits, wte, dxf + (size_t)t0 * d.h, nullptr, nullptr, n, d.h, d.V, true, false, false, false,
+                               Wk + wl.splitk, wl.splitk_bytes),
+                       product(logits, xc, dwte, nullptr, nullptr, d.V, d.h, n, false, false, true, true), s));   // dwte += dlogits^T xf
   }
   TRY(sum_f32(rowloss, (float*)c.fixed_ptr(c.loss_off), part, (size_t)d.T, 1.0f / (float)d.T, s));
   TRY(layernorm_bwd(dxf, x, stats, (const bf16_t*)c.w_ptr(R, 0), nullptr, (bf16_t*)io.dx, (float*)c.g_ptr(R, 0),
