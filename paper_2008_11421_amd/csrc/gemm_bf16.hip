@@ -830,7 +830,7 @@ static void launch_direct(const GemmArgs& g, hipStream_t s, dim3 grid, dim3 bloc
 
 // How a product is cut up: tile and number of ranges of the reduction
 struct GemmPlan {
-  int tile;     // 256: the direct-load kernel above, 128: gemm_ring.hip, 64: gemm_slices.hip
+  int tile;     // 256: the direct-load kernel above, 128 and 160 (RING_BROAD): gemm_ring.hip, 64: gemm_slices.hip
   int splits;
   bool deep;    // 128: four stages
   double us;    // modelled time
@@ -853,7 +853,7 @@ static double slices_us(long items, int kt, int cus) {
   return SLICES_BASE + rounds * (SLICES_ROUND + SLICES_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES));
 }
 
-// The cheapest of the three tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
+// The cheapest of the tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
 // item for every place on the chip (one per compute unit with the 256 tile, two with the 128 tile); a k-tile of 64 costs,
 // in a full round and with the places of the last one partly empty, what was measured on 500 products from 64 x 1000 x
 // 2048 to 8192 x 3072 x 3072 and 470 convolutions: 1.5 us down to 1.25 us for the large tile (2.0 to 1.4 where its first
@@ -866,6 +866,10 @@ static double slices_us(long items, int kt, int cus) {
 //   3000 x 2344 x 1416: 58.5 -> 34 us     4096 x 4096 x 4096: 108 us with the 256 tile, 132 us with the 128 tile
 //   4808 x 1824 x 2032 (570 small tiles, 152 large ones): 55 us with the 256 tile, 73 us with the 128 tile
 //   5 x 5 convolution, stride 2, 30 x 93 x 93, 232 -> 232 channels: 190 us and 225 us
+// Convolutions also have 256 pixels x 160 channels (weight gradients 160 x 256), one workgroup per compute unit: 1.14 us a
+// k-tile, and 14.5 us more for every round, which begins and ends with nobody to hide behind.  us, the better of the others ->
+// this one, 3 x 3: 256 x 32 x 32 x 160 -> 160 216 -> 159, 256 x 8 x 8 x 640 -> 640 153 -> 115, 256 x 16 x 16 x 320 -> 320
+// 144 -> 128, its weight gradient 155 -> 138; 8 x 128 x 128 x 128 -> 128 50 -> 68, 16 x 30 x 30 x 192 -> 192 24 -> 39.
 // The calculation itself takes 0.4 to 1.9 us on the host.
 static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may_split) {
   const int cus = compute_units(), k_tiles = (g.K + 63) / 64;
@@ -875,21 +879,26 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
   const double by_element = g.N % 8 || g.ldc % 8 ? std::min(1.0, g.M / 128.0) : 0.0;
   GemmPlan best{0, 1, false, 1e30};
   const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
-  for (int tile = 64; tile <= 256; tile *= 2) {
-    if (!(tile == 256 ? large : tile == 128 ? small : small && !g.conv_mode && g.N % 8 == 0 && g.ldc % 8 == 0)) continue;
-    const long tiles = (long)((g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile);
+  for (int tile : {64, 128, RING_BROAD, 256}) {
+    const bool taken = tile == 256 ? large : tile == 128 ? small : tile == 64 ? small && !g.conv_mode && g.N % 8 == 0 && g.ldc % 8 == 0
+                                                                              : small && g.conv_mode;
+    if (!taken) continue;
+    const int rows = tile == RING_BROAD && g.conv_mode == 1 ? 256 : tile, cols = tile == RING_BROAD && g.conv_mode == 2 ? 256 : tile;
+    const long tiles = (long)((g.M + rows - 1) / rows) * ((g.N + cols - 1) / cols);
     GemmPlan own{tile, 1, false, 1e30};   // the best number of ranges with this tile ...
     double late = 0.0;                    // ... and what its k-tiles take beyond two workgroups' pace
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && ((uint64_t)sp * g.M * g.N * sizeof(float) > g.ws_bytes || tiles * sp > 8l * cus)) break;
       const int kt = (k_tiles + sp - 1) / sp;
-      const long items = tiles * sp, places = tile == 256 ? cus : 2l * cus, full = items / places, rest = items % places;
+      const long items = tiles * sp, places = tile >= RING_BROAD ? cus : 2l * cus, full = items / places, rest = items % places;
       const long rounds = full + (rest ? 1 : 0);
       const double f = (double)rest / cus;   // workgroups per compute unit in the last round
       double us, more = 0.0;
       if (tile == 64) {
         if (kt > SLICES_MAX_KT) continue;
         us = slices_us(items, kt, cus) + 0.4 + 0.09 * kt;   // (by which the small tile's figure below is too high at few k-tiles)
+      } else if (tile == RING_BROAD) {
+        us = 12.5 + 14.5 * (rounds - 1) + kt * (full * 1.14 + (rest ? 0.95 + 0.19 * f : 0.0));
       } else if (tile == 256) {
         us = 9.0 + 4.0 * (rounds - 1) + ragged * kt * (full * full256 + (rest ? alone256 + (full256 - alone256) * f : 0.0));
       } else {
@@ -1066,7 +1075,7 @@ static int launch_slices(const GemmArgs& g, int splits, hipStream_t s) {
 }
 
 // The 128 x 128 tile: geometry of the gathered forms, then the launch
-static int launch_ring(const GemmArgs& g, int splits, bool deep, hipStream_t s) {
+static int launch_ring(const GemmArgs& g, int splits, bool deep, bool broad, hipStream_t s) {
   const int k_per_split = range_length(g.K, splits);
   GemmEpilogue ep = epilogue_of(g);
   if (splits == 1) take_colsum(g, 2 * ((g.M + RING_TILE - 1) / RING_TILE), ep);
@@ -1105,27 +1114,31 @@ static int launch_ring(const GemmArgs& g, int splits, bool deep, hipStream_t s) 
       rc.p[0] = RingPhase{cg, g.M, g.K, 0u, magic(cg.S), 0, 0, cg.pad, cg.pad};
     }
   }
-  const int st = gemm_ring_launch(g, ep, splits, k_per_split, deep, g.conv_mode ? &rc : nullptr, s);
+  const int st = gemm_ring_launch(g, ep, splits, k_per_split, deep, broad, g.conv_mode ? &rc : nullptr, s);
   return st == KARMA_OK ? finish(g, ep, splits, s) : st;
 }
 
-constexpr uint32_t PRODUCT_SLICES = 16;   // the 64 x 64 tile: reported as KARMA_PRODUCT_SMALL
+// Reported as KARMA_PRODUCT_SMALL: the 64 x 64 tile, and the 128 x 128 tile's kernel with 256 x 160 or 160 x 256
+constexpr uint32_t PRODUCT_SLICES = 16, PRODUCT_BROAD = 17;
+static uint32_t reported(uint32_t kernel) { return kernel >= PRODUCT_SLICES ? KARMA_PRODUCT_SMALL : kernel; }
 
 // One launch of a product (with the sum of its ranges): what gemm_choose decides and launch_piece carries out
 struct Piece {
   GemmArgs g;
-  uint32_t kernel;   // KARMA_PRODUCT_*, or PRODUCT_SLICES
+  uint32_t kernel;   // KARMA_PRODUCT_* or one of those above
   int splits;
   bool deep;    // the 128 x 128 tile: four stages
 };
 static Piece planned(const GemmArgs& g, const GemmPlan& p) {
-  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : PRODUCT_SLICES, p.splits, p.deep};
+  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? PRODUCT_SLICES : PRODUCT_BROAD,
+               p.splits, p.deep};
 }
 static int launch_piece(const Piece& p, hipStream_t s) {
   switch (p.kernel) {
     case KARMA_PRODUCT_LARGE: return launch_large<256, 2, 4>(p.g, p.splits, s);
     case KARMA_PRODUCT_NARROW: return launch_large<64, 4, 2>(p.g, p.splits, s);
-    case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, s);
+    case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, false, s);
+    case PRODUCT_BROAD: return launch_ring(p.g, p.splits, false, true, s);
     case PRODUCT_SLICES: return launch_slices(p.g, p.splits, s);
     case KARMA_PRODUCT_STAGED_LARGE: return launch_general<256, 256, 2, 4>(p.g, p.splits, s);
     default: return launch_general<128, 128, 2, 2>(p.g, p.splits, s);
@@ -1205,7 +1218,11 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
   }
   const bool small = gemm_ring_takes(g);
   if (g.conv_mode && g.conv.phased) {
-    piece[0] = Piece{g, KARMA_PRODUCT_SMALL, 1, false};
+    // by parity of the pixel.  The broad tile where it leaves less than 0.7 of the columns to multiply and fills the chip twice:
+    // 256 x 32 x 32 x 160 from 320 channels 131 -> 120 us; 320 from 640 channels (0.83) 97 and 99
+    const long wide = 4l * ((g.M / 4 + 255) / 256) * ((g.N + RING_BROAD - 1) / RING_BROAD);
+    const bool broad = (g.N + RING_BROAD - 1) / RING_BROAD * RING_BROAD * 10 < (g.N + RING_TILE - 1) / RING_TILE * RING_TILE * 7 && wide >= 2 * compute_units();
+    piece[0] = Piece{g, broad ? PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
     return KARMA_OK;
   }
   const bool may_split = g.ws && g.ldc == g.N && !g.act;
@@ -1341,7 +1358,7 @@ int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n) {
   for (int i = 0; i < pieces; ++i) {
     int splits = piece[i].splits;
     (void)range_length(piece[i].g.K, splits);   // (ranges are whole k-tiles: the last may come to nothing)
-    parts[i] = karma_product_part{piece[i].kernel == PRODUCT_SLICES ? KARMA_PRODUCT_SMALL : piece[i].kernel, (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
+    parts[i] = karma_product_part{reported(piece[i].kernel), (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
   }
   *n = (uint32_t)pieces;
   return KARMA_OK;

@@ -32,20 +32,66 @@ struct NoConv {};
 template <int CONV>
 using ConvArg = std::conditional_t<CONV != 0, RingConv, NoConv>;
 
-template <bool A_KC, bool B_KC, int ACT, int CONV, int NST>
-__global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int M_, int N,
+// The tile of a workgroup of WGM x WGN wavefronts, WGS of which (workgroups) share a compute unit
+template <int BM_, int BN_, int WGM_, int WGN_, int WGS_>
+struct Shape {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, WGS = WGS_;
+};
+using Square = Shape<RING_TILE, RING_TILE, 2, 2, 2>;
+using Wide = Shape<256, RING_BROAD, 4, 1, 1>;   // wavefronts of 64 x 160
+using Tall = Shape<RING_BROAD, 256, 1, 4, 1>;   // wavefronts of 160 x 64
+
+// Where a strided operand tile of T columns keeps what.  In LDS a k-row is T / 8 pieces of 16 bytes; a transposing read takes
+// four k-rows times four pieces at once, which have to lie in different banks: a row of 160 columns sees to that by itself,
+// the others exchange pieces by the k-row.  256 columns: a lane would meet two columns in turn, as 1 KiB is two
+// k-rows, so rows are placed such that a wavefront's all have the same k / 2 % 2.
+template <int T>
+struct Strided {
+  static constexpr int PPR = T / 8, CH = T * RING_BK * 2 / 1024 / 4;
+  static_assert(T == 128 || T == 160 || T == 256, "a layout below");
+  // k-row and first column of lane `lane` of wavefront `wave`'s piece i
+  static __device__ __forceinline__ int row(int wave, int i, int lane) {
+    if (T == 256) return 32 * (wave >> 1) + 4 * i + 2 * (wave & 1) + (lane >> 5);
+    return ((wave * CH + i) * 64 + lane) / PPR;
+  }
+  static __device__ __forceinline__ int col(int wave, int i, int lane) {
+    const int k = row(wave, i, lane), p = T == 256 ? lane & 31 : ((wave * CH + i) * 64 + lane) % PPR;
+    return (p ^ swizzle(k)) * 8;
+  }
+  static __device__ __forceinline__ int swizzle(int k) {
+    return T == 160 ? 0 : (k & 3) << 2;
+  }
+  // byte address in the tile of column m, k = 8 half + e (half 0 or 1, e below 4); k + 4 lies NEXT further, k-step kk at step(kk)
+  static constexpr int NEXT = (T == 256 ? 2 : 4) * T * 2;
+  static __device__ __forceinline__ unsigned at(int half, int e, int m) {
+    const int r = T == 256 ? 16 * (e >> 1) + 4 * half + (e & 1) : 8 * half + e;
+    return (unsigned)(r * T * 2 + ((m >> 3) ^ swizzle(e)) * 16 + (m & 7) * 2);
+  }
+  static __device__ __forceinline__ constexpr unsigned step(int kk) {
+    return (unsigned)((T == 256 ? 32 * (kk >> 1) + 8 * (kk & 1) : 16 * kk) * T * 2);
+  }
+};
+
+template <bool A_KC, bool B_KC, int ACT, int CONV, int NST, class SH>
+__global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int M_, int N,
                                                            int K_, int lda, int ldb, int splits, int k_per_split, GemmEpilogue ep,
                                                            float* __restrict__ partial, ConvArg<CONV> rc) {
   static_assert(CONV == 0 || (CONV == 1 && A_KC && B_KC) || (CONV == 2 && !A_KC && !B_KC), "the gathered forms");
-  constexpr int BT = RING_TILE, BK = RING_BK, KSTEPS = BK / 16, WT = 64, TM = 2, TN = 2;
-  constexpr int OP_BYTES = BT * BK * 2, STAGE = 2 * OP_BYTES, CH = 4, LPT = 2 * CH;   // CH 1-KiB pieces per wavefront and operand
-  constexpr int SP = WT + 4;
+  constexpr int BM = SH::BM, BN = SH::BN, BK = RING_BK, KSTEPS = BK / 16, WTM = BM / SH::WGM, WTN = BN / SH::WGN, TM = WTM / 32, TN = WTN / 32;
+  static_assert(SH::WGM * SH::WGN == 4 && WTM % 32 == 0 && WTN % 32 == 0, "four wavefronts");
+  constexpr int A_BYTES = BM * BK * 2, STAGE = (BM + BN) * BK * 2;
+  constexpr int CH_A = BM * BK * 2 / 4096, CH_B = BN * BK * 2 / 4096, LPT = CH_A + CH_B;   // 1-KiB pieces per wavefront
+  constexpr int SP = WTN + 4;
   static_assert(4 * 32 * SP * 4 <= NST * STAGE && (NST - 1) * LPT < 64, "strip fits; outstanding loads can be counted");
+  static_assert(CONV != 1 || CH_A % 2 == 0, "a lane meets two values of k");
+  static_assert(CONV != 2 || BN == 128 || BN == 256, "a lane meets one column");
+  static_assert(SH::WGS == 1 || NST == 2 || NST == 4, "as the waits below");
+  static_assert(ACT != 2 || WTN == 64, "column sums: a lane's octets lie in the same columns");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1, lrow = lane & 31;
+  const int wm = wave / SH::WGN, wn = wave % SH::WGN, lrow = lane & 31;
   int M = M_, K = K_;
   if constexpr (CONV == 1) {
     M = rc.p[blockIdx.y].M;
@@ -54,52 +100,61 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
     ldb = K;
   }
   // work item: as in gemm_bf16.hip, eight contiguous ranges of (split, tile), one per XCD, tiles in bands of 8 tile rows
-  const int tiles_m = (M + BT - 1) / BT, tiles_n = (N + BT - 1) / BT, total_tiles = tiles_m * tiles_n;
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, total_tiles = tiles_m * tiles_n;
   const int total_items = total_tiles * splits, per_xcd = (total_items + 7) / 8;
   const int item = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if ((int)(blockIdx.x / 8) >= per_xcd || item >= total_items) return;
   const int split = item / total_tiles, id = item % total_tiles;
   const int band_sz = 8 * tiles_n, first_m = (id / band_sz) * 8, rows_in_band = min(tiles_m - first_m, 8);
-  const int m0 = (first_m + (id % band_sz) % rows_in_band) * BT, n0 = ((id % band_sz) / rows_in_band) * BT;
+  const int m0 = (first_m + (id % band_sz) % rows_in_band) * BM, n0 = ((id % band_sz) / rows_in_band) * BN;
   const int kb = split * k_per_split, klen = min(K, kb + k_per_split) - kb, KT = (klen + BK - 1) / BK;
 
-  // ---- global side: 1-KiB piece i of wavefront w is rows 32 w + 8 i .. + 7 of a k-contiguous tile (eight 16-byte pieces per
-  // row, piece p of row r stored at p ^ (r / 2) % 8) or k-rows 16 w + 4 i .. + 3 of a strided one (16 pieces per k-row,
-  // piece p of k-row k stored at p ^ 4 (k % 4)).
-  auto piece_row = [&](bool kc, int i) { return kc ? wave * 32 + 8 * i + (lane >> 3) : wave * 16 + 4 * i + (lane >> 4); };
-  auto piece_col = [&](bool kc, int i) {
-    return kc ? ((lane & 7) ^ ((4 * (i & 1) + (lane >> 4)) & 7)) * 8 : ((lane & 15) ^ ((lane >> 4) << 2)) * 8;
-  };
-  unsigned a_off[CH], b_off[CH];
+  // ---- global side: 1-KiB piece i of wavefront w is piece g = w * CH + i of the tile: rows 8 g .. + 7 of a k-contiguous
+  // one (eight 16-byte pieces per row, piece p of row r stored at p ^ (r / 2) % 8), or the k-rows of a strided one that
+  // Strided says.
+  auto kc_row = [&](int g) { return 8 * g + (lane >> 3); };
+  auto kc_col = [&](int g) { return ((lane & 7) ^ ((4 * (g & 1) + (lane >> 4)) & 7)) * 8; };
+  using SA = Strided<BM>;
+  using SB = Strided<BN>;
+  auto a_row = [&](int i) { return A_KC ? kc_row(wave * CH_A + i) : SA::row(wave, i, lane); };
+  auto a_col = [&](int i) { return A_KC ? kc_col(wave * CH_A + i) : SA::col(wave, i, lane); };
+  auto b_row = [&](int i) { return B_KC ? kc_row(wave * CH_B + i) : SB::row(wave, i, lane); };
+  auto b_col = [&](int i) { return B_KC ? kc_col(wave * CH_B + i) : SB::col(wave, i, lane); };
+  unsigned a_off[CH_A], b_off[CH_B];
 #pragma unroll
-  for (int i = 0; i < CH; ++i) {
-    if (CONV != 1)
-      a_off[i] = (m0 + (A_KC ? piece_row(true, i) : piece_col(false, i)) < M)
-                     ? (unsigned)(((size_t)piece_row(A_KC, i) * lda + piece_col(A_KC, i)) * 2) : LOAD_NOTHING;
-    if (CONV != 2)
-      b_off[i] = (n0 + (B_KC ? piece_row(true, i) : piece_col(false, i)) < N)
-                     ? (unsigned)(((size_t)piece_row(B_KC, i) * ldb + piece_col(B_KC, i)) * 2) : LOAD_NOTHING;
-  }
+  for (int i = 0; i < CH_A; ++i)
+    if (CONV != 1) a_off[i] = (m0 + (A_KC ? a_row(i) : a_col(i)) < M) ? (unsigned)(((size_t)a_row(i) * lda + a_col(i)) * 2) : LOAD_NOTHING;
+#pragma unroll
+  for (int i = 0; i < CH_B; ++i)
+    if (CONV != 2) b_off[i] = (n0 + (B_KC ? b_row(i) : b_col(i)) < N) ? (unsigned)(((size_t)b_row(i) * ldb + b_col(i)) * 2) : LOAD_NOTHING;
   const bf16_t* a_base = CONV == 1 ? A : A + (A_KC ? (size_t)m0 * lda + kb : (size_t)kb * lda + m0);
   const bf16_t* b_base = CONV == 2 ? B : B + (B_KC ? (size_t)n0 * ldb + kb : (size_t)kb * ldb + n0);
 
-  // CONV 1: input position of tap (0, 0) for this lane's CH pixels and its element offset (modulo 2^32)
-  int ch0[CONV == 1 ? CH : 1], cw0[CONV == 1 ? CH : 1];
-  unsigned cpix[CONV == 1 ? CH : 1];
-  // CONV 2: this lane's tap and channel are fixed; its CH pixels advance by BK per k-tile
-  int gr = 0, gs = 0, gho[CONV == 2 ? CH : 1], gwo[CONV == 2 ? CH : 1];
-  unsigned goff[CONV == 2 ? CH : 1];
+  // The gathered tensor's geometry, in registers once: read where it is used it would be fetched from the kernel's arguments
+  // again and again in the k-loop, each time waited for.
+  struct Geometry { int H, W, C, S, Ho, Wo, stride, transposed; unsigned magic_s, magic_c; } cg{};
+  if constexpr (CONV != 0) {
+    const RingPhase& ph = rc.p[CONV == 1 ? blockIdx.y : 0];
+    auto keep = [](auto v) { return (decltype(v))__builtin_amdgcn_readfirstlane((int)v); };
+    cg = Geometry{keep(ph.cg.H), keep(ph.cg.W), keep(ph.cg.C), keep(ph.cg.S), keep(ph.cg.Ho), keep(ph.cg.Wo), keep(ph.cg.stride),
+                  keep(ph.cg.transposed), keep(ph.magic_s), keep(rc.magic_c)};
+  }
+  // CONV 1: input position of tap (0, 0) for this lane's CH_A pixels and its element offset (modulo 2^32)
+  int ch0[CONV == 1 ? CH_A : 1], cw0[CONV == 1 ? CH_A : 1];
+  unsigned cpix[CONV == 1 ? CH_A : 1];
+  // CONV 2: this lane's tap and channel are fixed; its CH_B pixels advance by BK per k-tile
+  int gr = 0, gs = 0, gho[CONV == 2 ? CH_B : 1], gwo[CONV == 2 ? CH_B : 1];
+  unsigned goff[CONV == 2 ? CH_B : 1];
   int adv_h = 0, adv_w = 0;
   unsigned adv_off = 0, row_off = 0, img_off = 0;
   bool g_in = false;
   if constexpr (CONV == 1) {
-    const ConvGather& cg = rc.p[blockIdx.y].cg;
     const unsigned grid = (unsigned)(cg.Ho * cg.Wo);
+    const int pad_y = rc.p[blockIdx.y].pad_y, pad_x = rc.p[blockIdx.y].pad_x;
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
-      const unsigned row = (unsigned)(m0 + piece_row(true, i)), img = row / grid, rem = row - img * grid;
+    for (int i = 0; i < CH_A; ++i) {
+      const unsigned row = (unsigned)(m0 + a_row(i)), img = row / grid, rem = row - img * grid;
       const int ho = (int)(rem / (unsigned)cg.Wo), wo = (int)rem - ho * cg.Wo;
-      const int pad_y = rc.p[blockIdx.y].pad_y, pad_x = rc.p[blockIdx.y].pad_x;
       const int h = cg.transposed ? ho + pad_y : ho * cg.stride - pad_y, w = cg.transposed ? wo + pad_x : wo * cg.stride - pad_x;
       ch0[i] = (int)row < M ? h : -(1 << 20);     // (rows outside the matrix: no tap lies inside the tensor)
       cw0[i] = w;
@@ -108,17 +163,16 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
   }
   if constexpr (CONV == 2) {
     const RingPhase& ph = rc.p[0];
-    const ConvGather& cg = ph.cg;
-    const int n = n0 + piece_col(false, 0);       // (the same for every i)
+    const int n = n0 + b_col(0);                  // (the same for every i)
     g_in = n < N;
-    const int tap = (int)__umulhi((unsigned)n, rc.magic_c), c = n - tap * cg.C;
-    const int r = ph.magic_s ? (int)__umulhi((unsigned)tap, ph.magic_s) : tap, sx = tap - r * cg.S;
+    const int tap = (int)__umulhi((unsigned)n, cg.magic_c), c = n - tap * cg.C;
+    const int r = cg.magic_s ? (int)__umulhi((unsigned)tap, cg.magic_s) : tap, sx = tap - r * cg.S;
     gr = r - ph.pad_y;
     gs = sx - ph.pad_x;
     const unsigned grid = (unsigned)(cg.Ho * cg.Wo);
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
-      const unsigned p = (unsigned)(kb + piece_row(false, i)), img = p / grid, rem = p - img * grid;
+    for (int i = 0; i < CH_B; ++i) {
+      const unsigned p = (unsigned)(kb + b_row(i)), img = p / grid, rem = p - img * grid;
       gho[i] = (int)(rem / (unsigned)cg.Wo);
       gwo[i] = (int)rem - gho[i] * cg.Wo;
       goff[i] = ((((unsigned)((int)img * cg.H + gho[i] * cg.stride + gr)) * (unsigned)cg.W + (unsigned)(gwo[i] * cg.stride + gs)) *
@@ -132,93 +186,95 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
     img_off = (unsigned)((cg.H - cg.Ho * cg.stride) * cg.W) * (unsigned)cg.C * 2u;             // an image on, Ho rows back
   }
 
-  auto issue_a = [&](int t, int stage) {
-    const unsigned sa = lds0 + stage * STAGE + wave * (CH * 1024);
-    const int left = klen - t * BK;   // k from this tile's first one on
+  // A tile's loads, piece by piece.  What a tile's pieces share comes from begin_a / begin_b.
+  unsigned a_to = 0, b_to = 0, c_delta[2] = {0u, 0u};
+  int a_left = 0, b_left = 0, c_r[2] = {0, 0}, c_s[2] = {0, 0};
+  bool c_in[2] = {false, false};
+  u32x4 a_desc, b_desc;
+  auto begin_a = [&](int t, int stage) {
+    a_to = lds0 + stage * STAGE + wave * (CH_A * 1024);
+    a_left = klen - t * BK;   // k from this tile's first one on
     if constexpr (CONV == 1) {
-      const RingPhase& ph = rc.p[blockIdx.y];
-      const ConvGather& cg = ph.cg;
-      const u32x4 d = buffer_desc(A);
-      int r[2], sx[2];
-      unsigned delta[2];
-      bool in[2];
+      a_desc = buffer_desc(A);
 #pragma unroll
       for (int par = 0; par < 2; ++par) {   // a lane's pieces lie at two values of k
-        const int col = piece_col(true, par), k = kb + t * BK + col;
-        const int tap = (int)__umulhi((unsigned)k, rc.magic_c), c = k - tap * cg.C;
-        r[par] = ph.magic_s ? (int)__umulhi((unsigned)tap, ph.magic_s) : tap;
-        sx[par] = tap - r[par] * cg.S;
-        if (cg.transposed) { r[par] = -r[par]; sx[par] = -sx[par]; }
-        delta[par] = (unsigned)((r[par] * cg.W + sx[par]) * cg.C + c);
-        in[par] = col < left;
-      }
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const int par = i & 1;
-        const bool ok = in[par] && (unsigned)(ch0[i] + r[par]) < (unsigned)cg.H && (unsigned)(cw0[i] + sx[par]) < (unsigned)cg.W;
-        buffer_load_to_lds16(d, ok ? (cpix[i] + delta[par]) * 2u : LOAD_NOTHING, sa + i * 1024);
+        const int col = a_col(par), k = kb + t * BK + col;
+        const int tap = (int)__umulhi((unsigned)k, cg.magic_c), c = k - tap * cg.C;
+        c_r[par] = cg.magic_s ? (int)__umulhi((unsigned)tap, cg.magic_s) : tap;
+        c_s[par] = tap - c_r[par] * cg.S;
+        if (cg.transposed) { c_r[par] = -c_r[par]; c_s[par] = -c_s[par]; }
+        c_delta[par] = (unsigned)((c_r[par] * cg.W + c_s[par]) * cg.C + c);
+        c_in[par] = col < a_left;
       }
     } else {
-      const u32x4 d = buffer_desc(a_base + (A_KC ? (size_t)t * BK : (size_t)t * BK * lda));
-#pragma unroll
-      for (int i = 0; i < CH; ++i)
-        buffer_load_to_lds16(d, (left >= BK || (A_KC ? piece_col(true, i) : piece_row(false, i)) < left) ? a_off[i] : LOAD_NOTHING,
-                             sa + i * 1024);
+      a_desc = buffer_desc(a_base + (A_KC ? (size_t)t * BK : (size_t)t * BK * lda));
     }
+  };
+  auto piece_a = [&](int i) {
+    if constexpr (CONV == 1) {
+      const int par = i & 1;   // (& and not &&: no branches)
+      const bool ok = c_in[par] & ((unsigned)(ch0[i] + c_r[par]) < (unsigned)cg.H) & ((unsigned)(cw0[i] + c_s[par]) < (unsigned)cg.W);
+      buffer_load_to_lds16(a_desc, ok ? (cpix[i] + c_delta[par]) * 2u : LOAD_NOTHING, a_to + i * 1024);
+    } else {
+      buffer_load_to_lds16(a_desc, (A_KC ? a_col(i) : a_row(i)) < a_left ? a_off[i] : LOAD_NOTHING, a_to + i * 1024);
+    }
+  };
+  auto begin_b = [&](int t, int stage) {
+    b_to = lds0 + stage * STAGE + A_BYTES + wave * (CH_B * 1024);
+    b_left = klen - t * BK;
+    b_desc = buffer_desc(CONV == 2 ? B : b_base + (B_KC ? (size_t)t * BK : (size_t)t * BK * ldb));
+  };
+  auto piece_b = [&](int i) {
+    if constexpr (CONV == 2) {
+      const bool ok = g_in & (b_row(i) < b_left) & ((unsigned)(gho[i] * cg.stride + gr) < (unsigned)cg.H) &
+                      ((unsigned)(gwo[i] * cg.stride + gs) < (unsigned)cg.W);
+      buffer_load_to_lds16(b_desc, ok ? goff[i] : LOAD_NOTHING, b_to + i * 1024);
+      // the pixel this lane fetches for the next k-tile
+      gwo[i] += adv_w;
+      const bool cw = gwo[i] >= cg.Wo;
+      gwo[i] -= cw ? cg.Wo : 0;
+      gho[i] += adv_h + (cw ? 1 : 0);
+      const bool chh = gho[i] >= cg.Ho;
+      gho[i] -= chh ? cg.Ho : 0;
+      goff[i] += adv_off + (cw ? row_off : 0u) + (chh ? img_off : 0u);
+    } else {
+      buffer_load_to_lds16(b_desc, (B_KC ? b_col(i) : b_row(i)) < b_left ? b_off[i] : LOAD_NOTHING, b_to + i * 1024);
+    }
+  };
+  auto issue_a = [&](int t, int stage) {
+    begin_a(t, stage);
+#pragma unroll
+    for (int i = 0; i < CH_A; ++i) piece_a(i);
   };
   auto issue_b = [&](int t, int stage) {
-    const unsigned sb = lds0 + stage * STAGE + OP_BYTES + wave * (CH * 1024);
-    const int left = klen - t * BK;
-    if constexpr (CONV == 2) {
-      const ConvGather& cg = rc.p[0].cg;
-      const u32x4 d = buffer_desc(B);
+    begin_b(t, stage);
 #pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const bool ok = g_in && piece_row(false, i) < left && (unsigned)(gho[i] * cg.stride + gr) < (unsigned)cg.H &&
-                        (unsigned)(gwo[i] * cg.stride + gs) < (unsigned)cg.W;
-        buffer_load_to_lds16(d, ok ? goff[i] : LOAD_NOTHING, sb + i * 1024);
-        // the pixel this lane fetches for the next k-tile
-        gwo[i] += adv_w;
-        const bool cw = gwo[i] >= cg.Wo;
-        gwo[i] -= cw ? cg.Wo : 0;
-        gho[i] += adv_h + (cw ? 1 : 0);
-        const bool chh = gho[i] >= cg.Ho;
-        gho[i] -= chh ? cg.Ho : 0;
-        goff[i] += adv_off + (cw ? row_off : 0u) + (chh ? img_off : 0u);
-      }
-    } else {
-      const u32x4 d = buffer_desc(b_base + (B_KC ? (size_t)t * BK : (size_t)t * BK * ldb));
-#pragma unroll
-      for (int i = 0; i < CH; ++i)
-        buffer_load_to_lds16(d, (left >= BK || (B_KC ? piece_col(true, i) : piece_row(false, i)) < left) ? b_off[i] : LOAD_NOTHING,
-                             sb + i * 1024);
-    }
+    for (int i = 0; i < CH_B; ++i) piece_b(i);
   };
 
-  // ---- LDS side: fragment addresses as in the 256 x 256 kernel, strided tiles with 256-byte k-rows
+  // ---- LDS side: fragment addresses as in the 256 x 256 kernel
   const int grp = lane >> 4, e4 = (lane >> 2) & 3, q4 = lane & 3;
-  auto frag_base = [&](bool kc, int row0) -> unsigned {
-    if (kc) return (unsigned)((row0 + lrow) * (BK * 2)) + (unsigned)(((lane >> 5) ^ ((lrow >> 1) & 7)) * 16);
-    const int m = row0 + 16 * (grp & 1) + 4 * q4;
-    return (unsigned)((8 * (grp >> 1) + e4) * (BT * 2) + ((m >> 3) ^ (e4 << 2)) * 16 + (m & 7) * 2);
-  };
+  auto kc_frag = [&](int row0) { return (unsigned)((row0 + lrow) * (BK * 2)) + (unsigned)(((lane >> 5) ^ ((lrow >> 1) & 7)) * 16); };
   unsigned a_fb[TM], b_fb[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) a_fb[i] = frag_base(A_KC, wm * WT + i * 32);
+  for (int i = 0; i < TM; ++i) a_fb[i] = A_KC ? kc_frag(wm * WTM + i * 32) : SA::at(grp >> 1, e4, wm * WTM + i * 32 + 16 * (grp & 1) + 4 * q4);
 #pragma unroll
-  for (int j = 0; j < TN; ++j) b_fb[j] = frag_base(B_KC, wn * WT + j * 32);
-  auto read_one = [&](bool kc, unsigned tile, unsigned fb, int kk) -> bf16x8 {
-    if (kc) return *(const KARMA_LDS(bf16x8)*)(uintptr_t)(tile + (fb ^ (unsigned)(kk << 5)));
-    const unsigned at = tile + fb + (unsigned)(kk * 16 * (BT * 2));
-    return read_tr_pair(at, at + 4 * (BT * 2));
-  };
+  for (int j = 0; j < TN; ++j) b_fb[j] = B_KC ? kc_frag(wn * WTN + j * 32) : SB::at(grp >> 1, e4, wn * WTN + j * 32 + 16 * (grp & 1) + 4 * q4);
+  auto read_kc = [&](unsigned tile, unsigned fb, int kk) { return *(const KARMA_LDS(bf16x8)*)(uintptr_t)(tile + (fb ^ (unsigned)(kk << 5))); };
   bf16x8 af[2][TM], bfr[2][TN];
+  auto read_b = [&](int buf, int stage, int kk, int x) {
+    const unsigned tb = lds0 + stage * STAGE + A_BYTES;
+    bfr[buf][x] = B_KC ? read_kc(tb, b_fb[x], kk) : read_tr_pair(tb + b_fb[x] + SB::step(kk), tb + b_fb[x] + SB::step(kk) + SB::NEXT);
+  };
+  auto read_a = [&](int buf, int stage, int kk, int x) {
+    const unsigned ta = lds0 + stage * STAGE;
+    af[buf][x] = A_KC ? read_kc(ta, a_fb[x], kk) : read_tr_pair(ta + a_fb[x] + SA::step(kk), ta + a_fb[x] + SA::step(kk) + SA::NEXT);
+  };
   auto read_frags = [&](int buf, int stage, int kk) {
-    const unsigned ta = lds0 + stage * STAGE, tb = ta + OP_BYTES;
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      bfr[buf][x] = read_one(B_KC, tb, b_fb[x], kk);
-      af[buf][x] = read_one(A_KC, ta, a_fb[x], kk);
+    for (int x = 0; x < (TM > TN ? TM : TN); ++x) {
+      if (x < TN) read_b(buf, stage, kk, x);
+      if (x < TM) read_a(buf, stage, kk, x);
     }
   };
 
@@ -237,12 +293,64 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
     else if (tiles == 1) wait_vm<LPT>();
     else wait_vm<0>();
   };
+  int st = 0;
+  if constexpr (SH::WGS == 1) {
+    // One wavefront per SIMD: what it does beside its MFMAs is done in their shadow, some of the next step's fragments and of
+    // a tile's loads after each.  A tile's first operand is requested during the last step of the tile whose stage it takes,
+    // the second during the step after that; beyond the range's last tile the requests go on and bring zeros, so that how
+    // many are outstanding is always the same.
+    constexpr int Q = TM * TN;
+#pragma unroll
+    for (int t = 0; t < NST; ++t) {
+      issue_a(t, t);
+      if (t + 1 < NST) issue_b(t, t);
+    }
+    wait_vm<(NST - 2) * LPT + CH_A>();
+    lds_barrier_visible();
+    read_frags(0, 0, 0);
+    for (int t = 0; t < KT; ++t) {
+      const int stn = st + 1 == NST ? 0 : st + 1, stp = st == 0 ? NST - 1 : st - 1;
+#pragma unroll
+      for (int kk = 0; kk < KSTEPS; ++kk) {
+        const int nb = (kk + 1) & 1, nst = kk + 1 < KSTEPS ? st : stn, nk = kk + 1 < KSTEPS ? kk + 1 : 0;
+        if (kk == KSTEPS - 1) begin_a(t + NST, st);
+        if (kk == 0) begin_b(t + NST - 1, stp);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const int i = q / TN, j = q % TN;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
+#pragma unroll
+          for (int f = q * (TM + TN) / Q; f < (q + 1) * (TM + TN) / Q; ++f) {
+            if (f < TN) read_b(nb, nst, nk, f);
+            else read_a(nb, nst, nk, f - TN);
+          }
+          if (kk == KSTEPS - 1) {
+#pragma unroll
+            for (int f = q * CH_A / Q; f < (q + 1) * CH_A / Q; ++f) piece_a(f);
+          }
+          if (kk == 0) {
+#pragma unroll
+            for (int f = q * CH_B / Q; f < (q + 1) * CH_B / Q; ++f) piece_b(f);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (kk == KSTEPS - 2) {
+          // the next tile has landed, for every wavefront (those behind it may be on their way); past the barrier nobody
+          // reads this stage any more
+          wait_vm<(NST - 2) * LPT>();
+          lds_barrier_visible();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      st = stn;
+    }
+    wait_vm<0>();   // (the requests beyond the last tile)
+  } else {
 #pragma unroll
   for (int t = 0; t < NST; ++t)
     if (t < KT) { issue_a(t, t); issue_b(t, t); }
   wait_tiles(min(NST, KT) - 1);
   lds_barrier_visible();
-  int st = 0;
   if (KT > 0) read_frags(0, 0, 0);
   for (int t = 0; t < KT; ++t) {
     const int stn = st + 1 == NST ? 0 : st + 1;
@@ -271,17 +379,20 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
     }
     st = stn;
   }
+  }
   lds_barrier_visible();   // every wavefront's reads are done (and no load is in flight): the strips may overlay the stages
 
   // ---- epilogue as in gemm_bf16.hip: the accumulators hold the transposed tile; each wavefront parks a 32-row strip in its
   // own fp32 patch of LDS and reads it back row-contiguously
   float* strip = (float*)smem + wave * 32 * SP;
-  constexpr int PASSES = 4;   // 8 octets per row, 8 rows per pass
-  const int q = (lane & 3) | (((lane >> 3) & 1) << 2);
-  const int rr = ((lane >> 2) & 1) | ((lane >> 4) << 1);
-  const int n = n0 + wn * WT + q * 8;
+  // Octet and row of a lane in a pass: for 64 columns eight consecutive lanes read two rows' worth of alternate 16-byte units
+  // (no bank is met twice) and keep their columns from pass to pass; else one octet after the other.
+  constexpr int QPR = WTN / 8, PASSES = QPR / 2;
+  auto octet_of = [&](int pass) { return WTN == 64 ? (lane & 3) | (((lane >> 3) & 1) << 2) : (pass * 64 + lane) % QPR; };
+  auto row_of = [&](int pass) { return WTN == 64 ? pass * 8 + (((lane >> 2) & 1) | ((lane >> 4) << 1)) : (pass * 64 + lane) / QPR; };
+  auto col_of = [&](int pass) { return n0 + wn * WTN + octet_of(pass) * 8; };
   const bf16_t* ein = ACT == 2 ? ep.aux : (ep.out_f32 ? nullptr : ep.residual);
-  const bool fetch_in = ein != nullptr && splits == 1 && (ep.ldc & 7) == 0 && n + 8 <= N;
+  const bool fetches = ein != nullptr && splits == 1 && (ep.ldc & 7) == 0;
   auto out_row = [&](int m) {   // row of C that row m of this product is
     if constexpr (CONV == 1) {
       if (rc.out_stride == 1) return m;
@@ -295,8 +406,8 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
   };
   u32x4 pre[PASSES];
   auto fetch = [&](int i, int pass) {
-    const int m = m0 + wm * WT + i * 32 + pass * 8 + rr;
-    return fetch_in && m < M ? *(const u32x4*)(ein + (size_t)out_row(m) * ep.ldc + n) : u32x4{0, 0, 0, 0};
+    const int m = m0 + wm * WTM + i * 32 + row_of(pass), n = col_of(pass);
+    return fetches && m < M && n + 8 <= N ? *(const u32x4*)(ein + (size_t)out_row(m) * ep.ldc + n) : u32x4{0, 0, 0, 0};
   };
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) pre[pass] = fetch(0, pass);
@@ -312,7 +423,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
             make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
-      const int row = pass * 8 + rr, m = m0 + wm * WT + i * 32 + row;
+      const int row = row_of(pass), q = octet_of(pass), m = m0 + wm * WTM + i * 32 + row, n = col_of(pass);
       const float4 v = *(const float4*)(strip + row * SP + q * 8);
       const float4 u = *(const float4*)(strip + row * SP + q * 8 + 4);
       if (splits > 1) {
@@ -325,7 +436,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
       } else {
         const u32x4 cur = pre[pass];
         if (i + 1 < TM) pre[pass] = fetch(i + 1, pass);
-        if (m < M && n < N) ep.template octet<ACT>(out_row(m), n, min(8, N - n), v, u, fetch_in, cur, col_sums, cs);
+        if (m < M && n < N) ep.template octet<ACT>(out_row(m), n, min(8, N - n), v, u, fetches && n + 8 <= N, cur, col_sums, cs);
       }
     }
   }
@@ -337,18 +448,20 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const bf16_t* __restr
       cs[e] += __shfl_xor(cs[e], 16, 64);
       cs[e] += __shfl_xor(cs[e], 32, 64);
     }
-    if (rr == 0 && n < N) {
-      float* dst = ep.colsum + ((size_t)(m0 / BT) * 2 + wm) * N + n;
+    const int n = col_of(0);
+    if (row_of(0) == 0 && n < N) {
+      float* dst = ep.colsum + ((size_t)(m0 / BM) * SH::WGM + wm) * N + n;
       *(float4*)dst = make_float4(cs[0], cs[1], cs[2], cs[3]);
       *(float4*)(dst + 4) = make_float4(cs[4], cs[5], cs[6], cs[7]);
     }
   }
 }
 
-template <bool AK, bool BKC, int ACT, int CONV, int NST>
+template <bool AK, bool BKC, int ACT, int CONV, int NST, class SH>
 void launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, const RingConv* rc, hipStream_t s) {
-  constexpr int lds = NST * 2 * RING_TILE * RING_BK * 2;
-  auto kern = gemm_ring_kernel<AK, BKC, ACT, CONV, NST>;
+  constexpr int lds = NST * (SH::BM + SH::BN) * RING_BK * 2;
+  static_assert(lds * SH::WGS <= 160 * 1024 || NST > 2, "the stages fit");
+  auto kern = gemm_ring_kernel<AK, BKC, ACT, CONV, NST, SH>;
   if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   int rows = g.M, phases = 1;
   ConvArg<CONV> arg{};
@@ -360,21 +473,21 @@ void launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_spl
       for (int p = 0; p < phases; ++p) rows = rows > rc->p[p].M ? rows : rc->p[p].M;
     }
   }
-  const int tiles = ((rows + RING_TILE - 1) / RING_TILE) * ((g.N + RING_TILE - 1) / RING_TILE);
+  const int tiles = ((rows + SH::BM - 1) / SH::BM) * ((g.N + SH::BN - 1) / SH::BN);
   hipLaunchKernelGGL(kern, dim3((unsigned)((tiles * splits + 7) / 8 * 8), (unsigned)phases), dim3(256), lds, s, g.A, g.B, g.M, g.N, g.K,
                      g.lda, g.ldb, splits, k_per_split, ep, (float*)g.ws, arg);
 }
 
 template <int NST>
 void launch_form(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, const RingConv* rc, hipStream_t s) {
-  if (g.conv_mode == 1) launch<true, true, 0, 1, NST>(g, ep, splits, k_per_split, rc, s);
-  else if (g.conv_mode == 2) launch<false, false, 0, 2, NST>(g, ep, splits, k_per_split, rc, s);
-  else if (g.act == 1) launch<true, true, 1, 0, NST>(g, ep, splits, k_per_split, rc, s);      // the layouts were checked by the caller
-  else if (g.act == 2) launch<true, false, 2, 0, NST>(g, ep, splits, k_per_split, rc, s);
-  else if (g.a_kc && g.b_kc) launch<true, true, 0, 0, NST>(g, ep, splits, k_per_split, rc, s);
-  else if (g.a_kc) launch<true, false, 0, 0, NST>(g, ep, splits, k_per_split, rc, s);
-  else if (g.b_kc) launch<false, true, 0, 0, NST>(g, ep, splits, k_per_split, rc, s);
-  else launch<false, false, 0, 0, NST>(g, ep, splits, k_per_split, rc, s);
+  if (g.conv_mode == 1) launch<true, true, 0, 1, NST, Square>(g, ep, splits, k_per_split, rc, s);
+  else if (g.conv_mode == 2) launch<false, false, 0, 2, NST, Square>(g, ep, splits, k_per_split, rc, s);
+  else if (g.act == 1) launch<true, true, 1, 0, NST, Square>(g, ep, splits, k_per_split, rc, s);      // the layouts were checked by the caller
+  else if (g.act == 2) launch<true, false, 2, 0, NST, Square>(g, ep, splits, k_per_split, rc, s);
+  else if (g.a_kc && g.b_kc) launch<true, true, 0, 0, NST, Square>(g, ep, splits, k_per_split, rc, s);
+  else if (g.a_kc) launch<true, false, 0, 0, NST, Square>(g, ep, splits, k_per_split, rc, s);
+  else if (g.b_kc) launch<false, true, 0, 0, NST, Square>(g, ep, splits, k_per_split, rc, s);
+  else launch<false, false, 0, 0, NST, Square>(g, ep, splits, k_per_split, rc, s);
 }
 
 }  // namespace
@@ -401,9 +514,12 @@ bool gemm_ring_takes(const GemmArgs& g) {
   return true;
 }
 
-int gemm_ring_launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, bool deep, const RingConv* rc,
+int gemm_ring_launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, bool deep, bool broad, const RingConv* rc,
                      hipStream_t s) {
-  if (deep) launch_form<4>(g, ep, splits, k_per_split, rc, s);
+  if (broad && g.conv_mode == 1) launch<true, true, 0, 1, 3, Wide>(g, ep, splits, k_per_split, rc, s);
+  else if (broad && g.conv_mode == 2) launch<false, false, 0, 2, 3, Tall>(g, ep, splits, k_per_split, rc, s);
+  else if (broad) return KARMA_E_INVAL;
+  else if (deep) launch_form<4>(g, ep, splits, k_per_split, rc, s);
   else launch_form<2>(g, ep, splits, k_per_split, rc, s);
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
 }
