@@ -242,13 +242,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM <= 128 && BN <= 128 ? 2 : 1)) vo
 // The tile stream is continuous across work items: while the last k-tile of an item is being
 // multiplied, the first k-tile of the next item is already landing in the other stage; the
 // epilogue's fp32 strip aliases the stage of the last tile (plus a small margin).
-// EDGE: the matrix need not be made of whole tiles.  Pieces of an operand tile that lie outside the matrix are
-// not fetched (their lanes are masked out of the direct load) and their 16 bytes of LDS are zeroed instead, so
-// that the products they enter vanish; results outside the matrix are not stored.
+// EDGE: the matrix need not be made of whole tiles.  Loads go through a buffer descriptor: lanes whose piece of an operand
+// tile lies outside the matrix are beyond its record count and bring zeros, so that the products they enter vanish, and a
+// wavefront issues as many loads for every tile, without a branch; results outside the matrix are not stored.
 // CONV 1 (with EDGE, both operands k-contiguous): A is an NHWC tensor gathered through a convolution, rows =
 // pixels of the grid cg.Ho x cg.Wo, k = (tap, channel).  A 16-byte piece is eight channels of one (pixel, tap), so
 // the direct load takes it from wherever the convolution reads it, and pieces that fall on padding (or on the
-// holes of a strided convolution's gradient) are zeroed in LDS like pieces outside the matrix.  The pixel of each
+// holes of a strided convolution's gradient) come as zeros like pieces outside the matrix.  The pixel of each
 // of a lane's rows is decoded once per work item; per k-tile only (tap, channel) of the lane's two k offsets are
 // (multiplications by reciprocals: magic_c = 2^32 / C + 1, magic_s = 2^32 / S + 1, exact for the sizes admitted).
 // CONV 2 (with EDGE, both operands strided): B is gathered, k = pixels of the grid cg.Ho x cg.Wo, n = (tap, channel):
@@ -338,26 +338,21 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
     const int odd = (i + odd0) & 1;
     if (kc) {
       const int r = rowbase + i * 8, k = ((lane & 7) ^ ((4 * odd + (lane >> 4)) & 7)) * 8;
-      return r < rows && k < ks;
+      return (r < rows) & (k < ks);
     }
     const int k = rowbase + i * 2, r = ((lane & 31) ^ ((2 * odd + (lane >> 5)) << 2)) * 8;
-    return r < rows && k < ks;
+    return (r < rows) & (k < ks);
   };
-  auto fetch_piece = [&](const bf16_t* base, unsigned off, unsigned lds, bool inside) {
-    if (!EDGE) {
-      load_to_lds16_s(base, off, lds);
-    } else if (inside) {
-      load_to_lds16_s(base, off, lds);
-    } else {
-      *(KARMA_LDS(u32x4)*)(uintptr_t)(lds + 16 * lane) = u32x4{0, 0, 0, 0};
-    }
+  auto fetch_piece = [&](const bf16_t* base, const u32x4& desc, unsigned off, unsigned lds, bool inside) {
+    if (!EDGE) load_to_lds16_s(base, off, lds);
+    else buffer_load_to_lds16(desc, inside ? off : LOAD_NOTHING, lds);
   };
   // CONV: where the pixels of this lane's CH_A rows lie, for the item whose tiles are being issued (dec_m0)
   // one register per row: image << 20 | (h0 + CBIAS) << 10 | (w0 + CBIAS), (h0, w0) = top-left input position of
   // the pixel's window (or, transposed, the pixel's own position plus the padding); image 4095 = row outside the matrix
   constexpr int CBIAS = 64;   // keeps the packed coordinates non-negative
   unsigned c_pix[CONV ? CH_A : 1], c_pix_next[CONV ? CH_A : 1];   // of the current item's rows, of the next item's
-  const int c_shift = cg.stride == 2 ? 1 : 0;
+  const int c_shift = cg.transposed && cg.stride == 2 ? 1 : 0, c_sign = cg.transposed ? -1 : 1;
   auto conv_decode = [&](int m0x, unsigned (&pix)[CONV ? CH_A : 1]) {
     const int grid = cg.Ho * cg.Wo;
 #pragma unroll
@@ -375,6 +370,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
   auto issue_a = [&](int stage, size_t ao, int t, int m0 = 0, int k0 = 0, int kend = 0, bool nxt = false) {
     const unsigned sa = lds0 + EXTRA + stage * STAGE + wave * (CH_A * 1024);
     if constexpr (CONV == 1) {
+      const u32x4 desc = buffer_desc(A);
 #pragma unroll
       for (int i = 0; i < CH_A; ++i) {
         // (tap, channel) of this piece's k; recomputed per piece: a few multiplications against registers held
@@ -385,33 +381,27 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
         const int r = (int)__umulhi((unsigned)tap, magic_s), sx = tap - r * cg.S;
         const unsigned px = nxt ? c_pix_next[i] : c_pix[i];
         const int img = (int)(px >> 20), h0 = (int)((px >> 10) & 1023u) - CBIAS, w0 = (int)(px & 1023u) - CBIAS;
-        int hi, wi;
-        bool ok = k < kend && img != 4095;
-        if (!cg.transposed) {
-          hi = h0 + r;
-          wi = w0 + sx;
-        } else {
-          const int th = h0 - r, tw = w0 - sx;
-          ok = ok && th >= 0 && tw >= 0 && !((th | tw) & c_shift);
-          hi = th >> c_shift;
-          wi = tw >> c_shift;
-        }
-        ok = ok && (unsigned)hi < (unsigned)cg.H && (unsigned)wi < (unsigned)cg.W;
+        // (transposed: taps count backwards, and where the stride leaves holes only whole positions are in the tensor)
+        const int th = h0 + r * c_sign, tw = w0 + sx * c_sign, hi = th >> c_shift, wi = tw >> c_shift;
+        const bool ok = (k < kend) & (img != 4095) & !((th | tw) & c_shift) & ((unsigned)hi < (unsigned)cg.H) &
+                        ((unsigned)wi < (unsigned)cg.W);   // (& and not &&: no branches)
         const unsigned off = (unsigned)(((img * cg.H + hi) * cg.W + wi) * cg.C + ch) * 2u;
-        fetch_piece(A, off, sa + i * 1024, ok);
+        fetch_piece(A, desc, off, sa + i * 1024, ok);
         __builtin_amdgcn_sched_barrier(0);
       }
       return;
     }
     const bf16_t* pa = A + ao + (A_KC ? (size_t)t * BK : (size_t)t * BK * lda);
+    const u32x4 desc = buffer_desc(pa);
 #pragma unroll
     for (int i = 0; i < CH_A; ++i)
-      fetch_piece(pa, a_off[i], sa + i * 1024, !EDGE || piece_inside(A_KC, a_row, i, M - m0, kend - k0 - t * BK));
+      fetch_piece(pa, desc, a_off[i], sa + i * 1024, !EDGE || piece_inside(A_KC, a_row, i, M - m0, kend - k0 - t * BK));
   };
   auto issue_b = [&](int stage, size_t bo, int t, int n0 = 0, int k0 = 0, int kend = 0) {
     const unsigned sb = lds0 + EXTRA + stage * STAGE + A_BYTES + wave * (CH_B * 1024);
     if constexpr (CONV == 2) {
       const int grid = cg.Ho * cg.Wo;
+      const u32x4 desc = buffer_desc(B);
 #pragma unroll
       for (int i = 0; i < CH_B; ++i) {
         // n = (tap, channel) of this piece's eight columns
@@ -427,17 +417,18 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
         if (rem >= grid) { ++img; rem -= grid; }
         const int ho = (int)__umulhi((unsigned)rem, magic_w), wo = rem - ho * cg.Wo;
         const int hi = ho * cg.stride - cg.pad + r, wi = wo * cg.stride - cg.pad + sx;
-        const bool ok = p < kend && n < N && (unsigned)hi < (unsigned)cg.H && (unsigned)wi < (unsigned)cg.W;
+        const bool ok = (p < kend) & (n < N) & ((unsigned)hi < (unsigned)cg.H) & ((unsigned)wi < (unsigned)cg.W);
         const unsigned off = (unsigned)(((img * cg.H + hi) * cg.W + wi) * cg.C + ch) * 2u;
-        fetch_piece(B, off, sb + i * 1024, ok);
+        fetch_piece(B, desc, off, sb + i * 1024, ok);
         __builtin_amdgcn_sched_barrier(0);
       }
       return;
     }
     const bf16_t* pb = B + bo + (B_KC ? (size_t)t * BK : (size_t)t * BK * ldb);
+    const u32x4 desc = buffer_desc(pb);
 #pragma unroll
     for (int i = 0; i < CH_B; ++i)
-      fetch_piece(pb, b_off[i], sb + i * 1024, !EDGE || piece_inside(B_KC, b_row, i, N - n0, kend - k0 - t * BK, B_ODD0));
+      fetch_piece(pb, desc, b_off[i], sb + i * 1024, !EDGE || piece_inside(B_KC, b_row, i, N - n0, kend - k0 - t * BK, B_ODD0));
   };
   auto issue = [&](int stage, size_t ao, size_t bo, int t, int m0 = 0, int n0 = 0, int k0 = 0, int kend = 0, bool nxt = false) {
     issue_a(stage, ao, t, m0, k0, kend, nxt);
@@ -501,17 +492,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
       bon = b_origin(n0n, kbn);
       if constexpr (CONV == 1) conv_decode(m0n, c_pix_next);
     }
-    // (EDGE: a wavefront issues no load for a piece that lies outside with all its lanes, so how many loads are
-    // younger than tile 0's is not known: tile 0 is waited for before tile 1 is requested)
-    if (EDGE) wait_vm<0>();
     lds_barrier_visible();   // the previous item's strip (which overlays stage s0 ^ 1) has been read out by every wavefront
     if (KT > 1) issue(s0 ^ 1, ao, bo, 1, m0, n0, kb, ke);
     else if (have_next) issue(s0 ^ 1, aon, bon, 0, m0n, n0n, kbn, ken, true);
-    if (!EDGE) {
-      if (KT > 1 || have_next) wait_vm<LPT>();   // everything older than the loads just issued: tile 0 has landed
-      else wait_vm<0>();
-      lds_barrier_visible();
-    }
+    if (KT > 1 || have_next) wait_vm<LPT>();   // everything older than the loads just issued: tile 0 has landed
+    else wait_vm<0>();
+    lds_barrier_visible();
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
