@@ -11,7 +11,8 @@
 
 namespace karma {
 
-// Persistent worker pool; parallel_for splits [0, n) into one contiguous range per worker.
+// Persistent worker pool; parallel_for cuts [0, n) into contiguous parts, which the caller and whichever workers are awake
+// take one after the other.
 class HostPool {
  public:
   explicit HostPool(unsigned threads);
@@ -20,14 +21,14 @@ class HostPool {
   unsigned size() const { return (unsigned)workers_.size() + 1; }
 
  private:
-  void worker(unsigned id);
+  void worker();
+  void take_parts(std::unique_lock<std::mutex>& lk);
   std::vector<std::thread> workers_;
   std::mutex mu_;
   std::condition_variable cv_, done_cv_;
   const std::function<void(size_t, size_t)>* fn_ = nullptr;
-  size_t n_ = 0;
-  uint64_t epoch_ = 0;
-  unsigned pending_ = 0;
+  size_t n_ = 0, part_ = 0;                        // elements, and how many of them a part has
+  unsigned next_ = 0, parts_ = 0, pending_ = 0;    // the next part to take, all of them, those not done yet
   bool stop_ = false;
 };
 
