@@ -5,6 +5,7 @@
 // shuffle reductions for the normalisations, fixed-order two-stage sums wherever a
 // reduction crosses workgroups (no atomics, so results are reproducible bit for bit).
 #include <hip/hip_runtime.h>
+#include <type_traits>
 
 #include "karma.h"
 #include "device_utils.h"
@@ -212,14 +213,13 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
   }
 }
 
-// The same in two launches, rows and columns apart.  dx: a wavefront per row, which holds the row's vectors as they came
+// The same with rows and columns apart, in different workgroups.  dx: a wavefront per row, which holds the row's vectors as they came
 // (no running column sums beside them, so that wide rows do not spill and every row has a wavefront of its own).
 template <int LN_MAXV>
-__global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
-                                                                  const float* __restrict__ stats, const bf16_t* __restrict__ g,
-                                                                  const bf16_t* __restrict__ add, bf16_t* __restrict__ dx, int rows,
-                                                                  int h) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void layernorm_bwd_rows(int block, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                   const float* __restrict__ stats, const bf16_t* __restrict__ g,
+                                                   const bf16_t* __restrict__ add, bf16_t* __restrict__ dx, int rows, int h) {
+  const int lane = threadIdx.x & 63, row = block * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const int nv = h / 8;
   const size_t at = (size_t)row * h;
@@ -276,15 +276,14 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const bf16_t* _
 // otherwise one partial row of NS * h per band, finished as those of the kernel above.  Workgroup (band, column group) is
 // number band * col_groups + group of a one-dimensional grid (4 million rows are more bands than a second dimension holds).
 template <int VC, bool ADDSUM>
-__global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
-                                                                  const float* __restrict__ stats, const bf16_t* __restrict__ add,
-                                                                  float* __restrict__ partial, float* __restrict__ dgamma,
-                                                                  float* __restrict__ dbeta, float* __restrict__ addsum, int rows,
-                                                                  int h, int band, int col_groups) {
+__device__ __forceinline__ void layernorm_bwd_cols(int block, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                   const float* __restrict__ stats, const bf16_t* __restrict__ add,
+                                                   float* __restrict__ partial, float* __restrict__ dgamma, float* __restrict__ dbeta,
+                                                   float* __restrict__ addsum, int rows, int h, int band, int col_groups) {
   constexpr int NS = ADDSUM ? 3 : 2, RL = 256 / VC, U = 4;
   __shared__ float red[NS][RL][VC * 8];
   const int vc = threadIdx.x % VC, rl = threadIdx.x / VC;
-  const int group = blockIdx.x % col_groups, part = blockIdx.x / col_groups;
+  const int group = block % col_groups, part = block / col_groups;
   const int c8 = (group * VC + vc) * 8;
   const int r0 = part * band, r1 = min(rows, r0 + band);
   float sum[NS][8];
@@ -344,6 +343,30 @@ __global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(const bf16_t* _
     if (!partial) (k == 0 ? dgamma : k == 1 ? dbeta : addsum)[col] = v;
     else partial[((size_t)part * NS + k) * h + col] = v;
   }
+}
+
+// The two of them: first all columns, then all rows (`only` one of them, where results may lie over inputs), or side by side.
+struct LayerNormBwd {
+  const bf16_t* dy; const bf16_t* x; const float* stats; const bf16_t* g; const bf16_t* add;
+  bf16_t* dx; float* partial; float* dgamma; float* dbeta; float* addsum;
+  int rows, h, band, col_groups;
+};
+template <int MAXV>
+__global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(LayerNormBwd p) {
+  layernorm_bwd_rows<MAXV>((int)blockIdx.x, p.dy, p.x, p.stats, p.g, p.add, p.dx, p.rows, p.h);
+}
+template <int VC, bool ADDSUM>
+__global__ __launch_bounds__(256) void layernorm_bwd_cols_kernel(LayerNormBwd p) {
+  layernorm_bwd_cols<VC, ADDSUM>((int)blockIdx.x, p.dy, p.x, p.stats, p.add, p.partial, p.dgamma, p.dbeta, p.addsum, p.rows, p.h, p.band, p.col_groups);
+}
+// col_blocks workgroups of columns, then those of rows
+template <int MAXV, int VC, bool ADDSUM>
+__global__ __launch_bounds__(256) void layernorm_bwd_both_kernel(LayerNormBwd p, int col_blocks) {
+  if ((int)blockIdx.x < col_blocks)
+    layernorm_bwd_cols<VC, ADDSUM>((int)blockIdx.x, p.dy, p.x, p.stats, p.add, p.partial, p.dgamma, p.dbeta, p.addsum, p.rows, p.h, p.band,
+                                   p.col_groups);
+  else
+    layernorm_bwd_rows<MAXV>((int)blockIdx.x - col_blocks, p.dy, p.x, p.stats, p.g, p.add, p.dx, p.rows, p.h);
 }
 
 // out[c] = sum_p partial[p][c]: eight slices of threads sum every eighth partial, then the
@@ -695,8 +718,8 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
   const int per_lane = (h / 8 + 63) / 64;
   const int ns = add_colsum ? 3 : 2;
   // One pass where its workgroups of 64 rows fill the chip with work enough to hide their start and end, and a row fits
-  // a wavefront's registers beside its column sums; else two launches.  us, one pass / two, with add_colsum: 1024 x 256
-  // 17.9 / 12.9, 1024 x 1024 28.6 / 13.0, 8192 x 1024 38 / 30, 8192 x 3072 84 / 75, 16384 x 256 23 / 19; 24881 x 504
+  // a wavefront's registers beside its column sums; else rows and columns apart.  us, one pass / apart in two
+  // launches, with add_colsum: 1024 x 256 17.9 / 12.9, 1024 x 1024 28.6 / 13.0, 8192 x 1024 38 / 30, 8192 x 3072 84 / 75, 16384 x 256 23 / 19; 24881 x 504
   // 30 / 38, 13798 x 1496 45 / 57, 14935 x 2016 62 / 77, 16384 x 1024 44 / 50, 16384 x 3072 106 / 145, 32768 x 1024
   // 66 / 92.  4096 x 4256 (spilled registers, and a third pass for the column sums of add): 295 + 20 / 64.  Over 590 sizes
   // none takes more than 3 % longer than the one pass did.
@@ -716,9 +739,8 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
     launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
     return ok();
   }
-  // The columns before the rows: dx may replace dy, x or add.  Their results after the rows, as they may lie over what the
-  // rows read.  Up to 512 rows, where they do not, a workgroup of two vector columns walks all rows and writes the results
-  // itself, which saves the launch that adds partial rows (512 x 512: 12.9 -> 10.7 us; 1024 x 1024: 13.0 -> 14.8).
+  // The columns' results come after the rows, as they may lie over what the rows read.  Up to 512 rows, where they do not,
+  // a workgroup of two vector columns walks all rows and writes the results itself, which saves the launch that adds partial rows (512 x 512: 12.9 -> 10.7 us; 1024 x 1024: 13.0 -> 14.8).
   auto over_inputs = [&](const float* out) {
     auto meets = [&](const void* in, size_t bytes) {
       return out && in && (const char*)out < (const char*)in + bytes && (const char*)in < (const char*)(out + h);
@@ -728,17 +750,33 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
            meets(stats, (size_t)rows * 2 * sizeof(float));
   };
   const bool direct = rows <= 512 && !over_inputs(dgamma) && !over_inputs(dbeta) && !over_inputs(add_colsum);
+  // Columns and rows side by side in one launch; where the gradient lies over an input, the columns have a launch of their
+  // own before it.  us, two launches / one, with add_colsum: 128 x 256 7.9 / 5.0, 1024 x 256 11.4 / 7.3, 4096 x 1024
+  // 17.2 / 12.7, 8192 x 1024 25.4 / 20.8, 8192 x 3072 62.5 / 59.4, 4096 x 4256 57.0 / 56.7.
+  const size_t tensor_bytes = (size_t)rows * h * sizeof(bf16_t);
+  auto dx_over = [&](const bf16_t* in) { return in && (const char*)dx < (const char*)in + tensor_bytes && (const char*)in < (const char*)dx + tensor_bytes; };
+  const bool apart = dx_over(dy) || dx_over(x) || dx_over(add);
   const int vc = direct ? 2 : 32, band = direct ? rows : LNB_ROWS, col_groups = (h / 8 + vc - 1) / vc;
-  auto cols = direct ? (add_colsum ? layernorm_bwd_cols_kernel<2, true> : layernorm_bwd_cols_kernel<2, false>)
-                     : (add_colsum ? layernorm_bwd_cols_kernel<32, true> : layernorm_bwd_cols_kernel<32, false>);
-  hipLaunchKernelGGL(cols, dim3((unsigned)col_groups * (direct ? 1u : (unsigned)parts)), dim3(256), 0, s, dy, x, stats, add,
-                     direct ? nullptr : partial_ws, dgamma, dbeta, add_colsum, rows, h, band, col_groups);
-  auto rowk = per_lane <= 2   ? layernorm_bwd_rows_kernel<2>
-              : per_lane <= 4 ? layernorm_bwd_rows_kernel<4>
-              : per_lane <= 6 ? layernorm_bwd_rows_kernel<6>
-              : per_lane <= 9 ? layernorm_bwd_rows_kernel<9>
-                              : layernorm_bwd_rows_kernel<12>;
-  hipLaunchKernelGGL(rowk, dim3((rows + 3) / 4), dim3(256), 0, s, dy, x, stats, g, add, dx, rows, h);
+  const LayerNormBwd p{dy, x, stats, g, add, dx, direct ? nullptr : partial_ws, dgamma, dbeta, add_colsum, rows, h, band, col_groups};
+  const unsigned col_blocks = (unsigned)col_groups * (direct ? 1u : (unsigned)parts), row_blocks = (unsigned)(rows + 3) / 4;
+  auto launch = [&](auto maxv) {
+    constexpr int V = decltype(maxv)::value;
+    if (apart) {
+      auto cols = direct ? (add_colsum ? layernorm_bwd_cols_kernel<2, true> : layernorm_bwd_cols_kernel<2, false>)
+                         : (add_colsum ? layernorm_bwd_cols_kernel<32, true> : layernorm_bwd_cols_kernel<32, false>);
+      hipLaunchKernelGGL(cols, dim3(col_blocks), dim3(256), 0, s, p);
+      hipLaunchKernelGGL(layernorm_bwd_rows_kernel<V>, dim3(row_blocks), dim3(256), 0, s, p);
+    } else {
+      auto both = direct ? (add_colsum ? layernorm_bwd_both_kernel<V, 2, true> : layernorm_bwd_both_kernel<V, 2, false>)
+                         : (add_colsum ? layernorm_bwd_both_kernel<V, 32, true> : layernorm_bwd_both_kernel<V, 32, false>);
+      hipLaunchKernelGGL(both, dim3(col_blocks + row_blocks), dim3(256), 0, s, p, (int)col_blocks);
+    }
+  };
+  if (per_lane <= 2) launch(std::integral_constant<int, 2>{});
+  else if (per_lane <= 4) launch(std::integral_constant<int, 4>{});
+  else if (per_lane <= 6) launch(std::integral_constant<int, 6>{});
+  else if (per_lane <= 9) launch(std::integral_constant<int, 9>{});
+  else launch(std::integral_constant<int, 12>{});
   if (!direct) launch_colsum_finish(partial_ws, parts, ns * h, ns * h, dgamma, h, dbeta, 2 * h, add_colsum, s);
   return ok();
 }
