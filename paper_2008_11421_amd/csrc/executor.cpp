@@ -538,12 +538,12 @@ int run_step(Ctx* c, const void* in, const void* lab, uint32_t flags, float* los
       if (!c->rec[r].p.empty() && c->rec[r].p[0].dev_opt) {
         // updated where they are, behind the backward op on the compute stream
         const karma_config& g = c->cfg;
-        for (Param& q : c->rec[r].p) {
-          st = optim_update_dev((int)g.optimizer, (float*)(c->arena + q.dmaster_off), (float*)(c->arena + q.dm_off),
-                                (float*)(c->arena + q.dv_off), c->arena + q.g_off, q.grad_bf16, (size_t)q.n, g.lr, g.beta1,
-                                g.beta2, g.eps, c->step_no, c->arena + q.w_off, q.dev_bf16, s);
-          if (st) return st;
-        }
+        std::vector<OptimTensor> all;
+        for (Param& q : c->rec[r].p)
+          all.push_back(OptimTensor{(float*)(c->arena + q.dmaster_off), (float*)(c->arena + q.dm_off), (float*)(c->arena + q.dv_off),
+                                    c->arena + q.g_off, c->arena + q.w_off, (size_t)q.n, q.grad_bf16, q.dev_bf16});
+        st = optim_update_dev((int)g.optimizer, all.data(), (int)all.size(), g.lr, g.beta1, g.beta2, g.eps, c->step_no, s);
+        if (st) return st;
       } else if (!c->rec[r].p.empty() && !c->rec[r].streamed) {
         st = send_grads(c, r, c->ev[k]);
         if (st) return st;

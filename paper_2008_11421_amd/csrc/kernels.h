@@ -151,10 +151,17 @@ int add_inplace_bf16(bf16_t* y, const bf16_t* a, size_t n, hipStream_t s);      
 int avgpool_fwd(const bf16_t* x, bf16_t* y, int n, int hw, int c, hipStream_t s);         // global
 int avgpool_bwd(const bf16_t* dy, bf16_t* dx, int n, int hw, int c, hipStream_t s);
 
-// ---- the optimiser's update on the device (optim_dev.hip): kind = karma_opt_kind; fp32 master weights and state,
-// g the gradient (bf16 or fp32), out the device copy of the weight (bf16 or fp32); step counts from 1
-int optim_update_dev(int kind, float* w, float* m, float* v, const void* g, bool g_bf16, size_t n, float lr, float beta1,
-                     float beta2, float eps, uint64_t step, void* out, bool out_bf16, hipStream_t s);
+// ---- the optimiser's update on the device (optim_dev.hip): kind = karma_opt_kind; step counts from 1.  n tensors in
+// launches of OPTIM_TENSORS each
+struct OptimTensor {
+  float* w; float* m; float* v;   // fp32 master weights and state
+  const void* g;                  // gradient, bf16 or fp32
+  void* out;                      // the device copy of the weight, bf16 or fp32
+  size_t n;
+  bool g_bf16, out_bf16;
+};
+constexpr int OPTIM_TENSORS = 16;
+int optim_update_dev(int kind, const OptimTensor* tensors, int n, float lr, float beta1, float beta2, float eps, uint64_t step, hipStream_t s);
 
 // ---- fused causal attention (attention.hip); seq multiple of 128, d in {64, 128, 152}
 int attention_fwd(const bf16_t* qkv, bf16_t* ctx, float* lse, int batch, int seq, int heads, int d, hipStream_t s);
