@@ -6,9 +6,10 @@
 // Operands may have the reduction index contiguous ("k-contiguous": A[M][K], B[N][K]) or
 // strided (A[K][M], B[K][N]); strided tiles are transposed in registers on their way into
 // LDS, so the MFMA loop always reads 16-byte k-runs.  v_mfma_f32_32x32x16_bf16 does the arithmetic; the workgroup ->
-// tile map keeps each XCD's L2 on a compact patch of C.  Three kernels: the direct-load one below (256 x 256 and 256 x 64
-// tiles, persistent), gemm_ring.hip (128 x 128, what does not fill the chip with the large tile), and for sizes and
-// alignments neither takes the first one here, which stages tiles through registers; gemm_bf16_launch chooses.
+// tile map keeps each XCD's L2 on a compact patch of C.  Four kernels: the direct-load one below (256 x 256 tiles,
+// persistent), gemm_ring.hip (128 x 128, what does not fill the chip with the large tile, and other tiles for convolutions),
+// gemm_slices.hip (64 x 64, small products), and for sizes and alignments none of these takes the first one here, which
+// stages tiles through registers; gemm_bf16_launch chooses.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cstdint>
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM <= 128 && BN <= 128 ? 2 : 1)) vo
 // (image by a float reciprocal with an exact correction, row and column by reciprocal multiplication: magic_w =
 // 2^32 / Wo + 1, inv_grid = 1 / (Ho * Wo)).
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int ACT = 0, bool EDGE = false, int CONV = 0>
-__global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) void gemm_bf16_dl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+__global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_dl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                                          int M, int N, int K, int lda, int ldb, int tiles_m,
                                                                          int tiles_n, int splits, int k_per_split,
                                                                          GemmEpilogue ep, float* __restrict__ partial,
@@ -269,8 +270,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
   constexpr int TM = WTM / 32, TN = WTN / 32;
   constexpr int KSTEPS = BK / 16;
   static_assert(BK == 64 && KSTEPS == 4, "swizzles below are written for 128-byte k-rows");
-  // the narrow tile (BN = 64: convolutions with 64 output channels) exists for k-contiguous operands only
-  static_assert((BM == 256 && BN == 256) || (BM == 256 && BN == 64 && A_KC && B_KC), "strided swizzle assumes 512-byte k-rows");
+  static_assert(BM == 256 && BN == 256, "strided swizzle assumes 512-byte k-rows");
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
   constexpr int CH_A = A_BYTES / 1024 / WAVES, CH_B = B_BYTES / 1024 / WAVES;   // 1 KiB pieces per wavefront
   constexpr int LPT = CH_A + CH_B;                                               // direct loads per lane per k-tile
@@ -309,11 +309,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
   // 512-byte k-row).  The lane at LDS piece p of a row fetches global piece p ^ swizzle(row):
   //   k-contiguous: swizzle = (row / 2) % 8     strided: swizzle = (k % 4) * 4
   // Both depend on i only through its parity, so two column offsets per lane suffice.
-  // (a wavefront whose share of a k-contiguous B tile is a single piece of eight rows, BN / WAVES = 8, starts on an
-  // odd or even piece depending on its number: B_ODD0 below)
-  static_assert((BM / WAVES) % 16 == 0 && ((BN / WAVES) % 16 == 0 || (BN / WAVES == 8 && B_KC)) && (BK / WAVES) % 4 == 0,
-                "swizzle parity per piece");
-  const int B_ODD0 = (B_KC && (BN / WAVES) % 16 != 0) ? (wave & 1) : 0;
+  static_assert((BM / WAVES) % 16 == 0 && (BN / WAVES) % 16 == 0 && (BK / WAVES) % 4 == 0, "swizzle parity per piece");
   const int a_row = A_KC ? wave * (BM / WAVES) + (lane >> 3) : wave * (BK / WAVES) + (lane >> 5);
   const int b_row = B_KC ? wave * (BN / WAVES) + (lane >> 3) : wave * (BK / WAVES) + (lane >> 5);
   // byte offset of each of this lane's pieces from the tile's first element; a tile is then a uniform
@@ -321,12 +317,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
   unsigned a_off[CH_A], b_off[CH_B];
 #pragma unroll
   for (int i = 0; i < (CH_A > CH_B ? CH_A : CH_B); ++i) {
-    const int odd = i & 1, odd_b = (i + B_ODD0) & 1;
+    const int odd = i & 1;
     const int kc_col = ((lane & 7) ^ ((4 * odd + (lane >> 4)) & 7)) * 8;
-    const int kc_col_b = ((lane & 7) ^ ((4 * odd_b + (lane >> 4)) & 7)) * 8;
     const int st_col = ((lane & 31) ^ ((2 * odd + (lane >> 5)) << 2)) * 8;
     if (i < CH_A) a_off[i] = (unsigned)(((size_t)(a_row + i * (A_KC ? 8 : 2)) * lda + (A_KC ? kc_col : st_col)) * sizeof(bf16_t));
-    if (i < CH_B) b_off[i] = (unsigned)(((size_t)(b_row + i * (B_KC ? 8 : 2)) * ldb + (B_KC ? kc_col_b : st_col)) * sizeof(bf16_t));
+    if (i < CH_B) b_off[i] = (unsigned)(((size_t)(b_row + i * (B_KC ? 8 : 2)) * ldb + (B_KC ? kc_col : st_col)) * sizeof(bf16_t));
   }
   // element offset of an item's k-tile 0 (the same in every lane)
   auto a_origin = [&](int m0, int kb) { return A_KC ? (size_t)m0 * lda + kb : (size_t)kb * lda + m0; };
@@ -334,8 +329,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
   // EDGE: where piece i of this lane lies inside a tile: (row of the operand, k) for a k-contiguous tile,
   // (k, first of its eight rows) for a strided one; `rows` is how many rows the operand has from the tile's
   // first row on, `ks` how many k are left from the tile's first k on
-  auto piece_inside = [&](bool kc, int rowbase, int i, int rows, int ks, int odd0 = 0) {
-    const int odd = (i + odd0) & 1;
+  auto piece_inside = [&](bool kc, int rowbase, int i, int rows, int ks) {
+    const int odd = i & 1;
     if (kc) {
       const int r = rowbase + i * 8, k = ((lane & 7) ^ ((4 * odd + (lane >> 4)) & 7)) * 8;
       return (r < rows) & (k < ks);
@@ -428,7 +423,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, (BM == 256 && BN == 64) ? 4 : 1) voi
     const u32x4 desc = buffer_desc(pb);
 #pragma unroll
     for (int i = 0; i < CH_B; ++i)
-      fetch_piece(pb, desc, b_off[i], sb + i * 1024, !EDGE || piece_inside(B_KC, b_row, i, N - n0, kend - k0 - t * BK, B_ODD0));
+      fetch_piece(pb, desc, b_off[i], sb + i * 1024, !EDGE || piece_inside(B_KC, b_row, i, N - n0, kend - k0 - t * BK));
   };
   auto issue = [&](int stage, size_t ao, size_t bo, int t, int m0 = 0, int n0 = 0, int k0 = 0, int kend = 0, bool nxt = false) {
     issue_a(stage, ao, t, m0, k0, kend, nxt);
@@ -763,19 +758,6 @@ static void launch_reduce(const GemmArgs& g, const GemmEpilogue& ep, int splits,
 template <int BM, int BN, int BK, int WGM, int WGN, bool EDGE>
 static void launch_direct(const GemmArgs& g, hipStream_t s, dim3 grid, dim3 block, int tiles_m, int tiles_n, int splits,
                           int k_per_split, const GemmEpilogue& ep) {
-  if constexpr (BM == 256 && BN == 64 && BK == 64 && EDGE) {
-    // the narrow tile: a gathered first operand against 64 output channels
-    constexpr int STAGE = (BM + BN) * BK * 2, STRIP = WGM * WGN * 32 * (BN / WGN + 4) * 4;
-    constexpr int EXTRA = STRIP > STAGE ? STRIP - STAGE : 0;
-    const int lds = 2 * STAGE + 2 * EXTRA;
-    if (g.conv_mode == 1) {
-      const unsigned magic_c = (unsigned)((1ull << 32) / (unsigned)g.conv.C + 1), magic_s = (unsigned)((1ull << 32) / (unsigned)g.conv.S + 1);
-      auto kern = gemm_bf16_dl_kernel<BM, BN, BK, WGM, WGN, true, true, 0, true, 1>;
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-      hipLaunchKernelGGL(kern, grid, block, lds, s, g.A, g.B, g.M, g.N, g.K, g.lda, g.ldb, tiles_m, tiles_n, splits,
-                         k_per_split, ep, (float*)g.ws, g.conv, magic_c, magic_s, 0u, 0.f);
-    }
-  }
   if constexpr (BM == 256 && BN == 256 && BK == 64) {
     constexpr int STAGE = (BM + BN) * BK * 2, STRIP = WGM * WGN * 32 * (BN / WGN + 4) * 4;
     constexpr int EXTRA = STRIP > STAGE ? STRIP - STAGE : 0;
@@ -856,6 +838,10 @@ static double slices_us(long items, int kt, int cus) {
 // k-tile, and 14.5 us more for every round, which begins and ends with nobody to hide behind.  us, the better of the others ->
 // this one, 3 x 3: 256 x 32 x 32 x 160 -> 160 216 -> 159, 256 x 8 x 8 x 640 -> 640 153 -> 115, 256 x 16 x 16 x 320 -> 320
 // 144 -> 128, its weight gradient 155 -> 138; 8 x 128 x 128 x 128 -> 128 50 -> 68, 16 x 30 x 30 x 192 -> 192 24 -> 39.
+// And 256 x 64 (weight gradients 64 x 256), two workgroups per compute unit: 1.5 and 1.18 us a k-tile.  us, the better of the
+// others (for 64 channels until then 256 x 64 with eight wavefronts) -> this one, 3 x 3 but for the last: 8 x 256 x 256 x 64
+// -> 64 74.7 -> 69.2, 64 -> 8 (input gradient) 93 -> 59, weight gradients 8 x 256 x 256 x 64 -> 64 95 -> 76 and from 128
+// channels 155 -> 115; 7 x 7 at stride 2, 64 x 224 x 224 x 8 -> 64 87 -> 78, weight gradient 99 -> 73, input gradient 698 -> 409.
 // The calculation itself takes 0.4 to 1.9 us on the host.
 static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may_split) {
   const int cus = compute_units(), k_tiles = (g.K + 63) / 64;
@@ -866,10 +852,10 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
   GemmPlan best{0, 1, false, 1e30};
   const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
   for (int tile : {64, 128, RING_BROAD, 256}) {
-    const bool taken = tile == 256 ? large : tile == 128 ? small : tile == 64 ? small && !g.conv_mode && g.N % 8 == 0 && g.ldc % 8 == 0
-                                                                              : small && g.conv_mode;
-    if (!taken) continue;
-    const int rows = tile == RING_BROAD && g.conv_mode == 1 ? 256 : tile, cols = tile == RING_BROAD && g.conv_mode == 2 ? 256 : tile;
+    const bool gathers = tile == RING_BROAD || (tile == RING_SLIM && g.conv_mode);   // 256 on one side
+    const bool taken = tile == 256 ? large : small && (tile == 128 || (gathers ? g.conv_mode : g.N % 8 == 0 && g.ldc % 8 == 0));
+    if (!taken || (tile == RING_SLIM && g.conv_mode == 1 && g.N > RING_SLIM)) continue;   // (beyond 64 channels its gathers are read twice)
+    const int rows = gathers && g.conv_mode == 1 ? 256 : tile, cols = gathers && g.conv_mode == 2 ? 256 : tile;
     const long tiles = (long)((g.M + rows - 1) / rows) * ((g.N + cols - 1) / cols);
     GemmPlan own{tile, 1, false, 1e30};   // the best number of ranges with this tile ...
     double late = 0.0;                    // ... and what its k-tiles take beyond two workgroups' pace
@@ -880,7 +866,10 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
       const long rounds = full + (rest ? 1 : 0);
       const double f = (double)rest / cus;   // workgroups per compute unit in the last round
       double us, more = 0.0;
-      if (tile == 64) {
+      if (tile == RING_SLIM && g.conv_mode) {
+        const double slim = g.conv_mode == 1 ? 1.5 : 1.18, lone = g.conv_mode == 1 ? 0.75 : 0.85;   // (full, and next to alone)
+        us = 5.5 + 2.5 * (rounds - 1) + kt * (full * slim + (!rest ? 0.0 : f <= 1.0 ? lone + 0.15 * f : lone + 0.15 + (slim - lone - 0.15) * (f - 1.0)));
+      } else if (tile == 64) {
         if (kt > SLICES_MAX_KT) continue;
         us = slices_us(items, kt, cus) + 0.4 + 0.09 * kt;   // (by which the small tile's figure below is too high at few k-tiles)
       } else if (tile == RING_BROAD) {
@@ -951,17 +940,15 @@ static int finish(const GemmArgs& g, const GemmEpilogue& ep, int splits, hipStre
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
 }
 
-// The direct-load kernel with the 256 x 256 or (64 output channels) 256 x 64 tile; eligibility was checked by the caller.
-template <int BN, int WGM, int WGN>
+// The direct-load kernel with the 256 x 256 tile; eligibility was checked by the caller.
 static int launch_large(const GemmArgs& g, int splits, hipStream_t s) {
-  constexpr int BM = 256, BK = 64;
+  constexpr int BM = 256, BN = 256, BK = 64, WGM = 2, WGN = 4;
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const int k_per_split = range_length(g.K, splits);
   GemmEpilogue ep = epilogue_of(g);
   if (splits == 1) take_colsum(g, tiles_m * WGM, ep);
   // a multiple of 8 workgroups, at most what runs at once: the kernel deals work items out per XCD
-  const int cus = compute_units() * (BN == 64 ? 2 : 1);
-  const dim3 grid(std::min((tiles_m * tiles_n * splits + 7) / 8 * 8, std::max(8, cus / 8 * 8))), block(WGM * WGN * 64);
+  const dim3 grid(std::min((tiles_m * tiles_n * splits + 7) / 8 * 8, std::max(8, compute_units() / 8 * 8))), block(WGM * WGN * 64);
   if (!g.conv_mode && g.M % BM == 0 && g.N % BN == 0 && g.K % BK == 0)
     launch_direct<BM, BN, BK, WGM, WGN, false>(g, s, grid, block, tiles_m, tiles_n, splits, k_per_split, ep);
   else
@@ -1061,7 +1048,7 @@ static int launch_slices(const GemmArgs& g, int splits, hipStream_t s) {
 }
 
 // The 128 x 128 tile: geometry of the gathered forms, then the launch
-static int launch_ring(const GemmArgs& g, int splits, bool deep, bool broad, hipStream_t s) {
+static int launch_ring(const GemmArgs& g, int splits, bool deep, int side, hipStream_t s) {
   const int k_per_split = range_length(g.K, splits);
   GemmEpilogue ep = epilogue_of(g);
   if (splits == 1) take_colsum(g, 2 * ((g.M + RING_TILE - 1) / RING_TILE), ep);
@@ -1100,12 +1087,12 @@ static int launch_ring(const GemmArgs& g, int splits, bool deep, bool broad, hip
       rc.p[0] = RingPhase{cg, g.M, g.K, 0u, magic(cg.S), 0, 0, cg.pad, cg.pad};
     }
   }
-  const int st = gemm_ring_launch(g, ep, splits, k_per_split, deep, broad, g.conv_mode ? &rc : nullptr, s);
+  const int st = gemm_ring_launch(g, ep, splits, k_per_split, deep, side, g.conv_mode ? &rc : nullptr, s);
   return st == KARMA_OK ? finish(g, ep, splits, s) : st;
 }
 
-// Reported as KARMA_PRODUCT_SMALL: the 64 x 64 tile, and the 128 x 128 tile's kernel with 256 x 160 or 160 x 256
-constexpr uint32_t PRODUCT_SLICES = 16, PRODUCT_BROAD = 17;
+// Reported as KARMA_PRODUCT_SMALL: the 64 x 64 tile, and the 128 x 128 tile's kernel with 256 x 160, 160 x 256 and 64 x 256
+constexpr uint32_t PRODUCT_SLICES = 16, PRODUCT_BROAD = 17, PRODUCT_FLAT = 18;
 static uint32_t reported(uint32_t kernel) { return kernel >= PRODUCT_SLICES ? KARMA_PRODUCT_SMALL : kernel; }
 
 // One launch of a product (with the sum of its ranges): what gemm_choose decides and launch_piece carries out
@@ -1116,15 +1103,16 @@ struct Piece {
   bool deep;    // the 128 x 128 tile: four stages
 };
 static Piece planned(const GemmArgs& g, const GemmPlan& p) {
-  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? PRODUCT_SLICES : PRODUCT_BROAD,
-               p.splits, p.deep};
+  const uint32_t of64 = !g.conv_mode ? PRODUCT_SLICES : g.conv_mode == 1 ? KARMA_PRODUCT_NARROW : PRODUCT_FLAT;
+  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? of64 : PRODUCT_BROAD, p.splits, p.deep};
 }
 static int launch_piece(const Piece& p, hipStream_t s) {
   switch (p.kernel) {
-    case KARMA_PRODUCT_LARGE: return launch_large<256, 2, 4>(p.g, p.splits, s);
-    case KARMA_PRODUCT_NARROW: return launch_large<64, 4, 2>(p.g, p.splits, s);
-    case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, false, s);
-    case PRODUCT_BROAD: return launch_ring(p.g, p.splits, false, true, s);
+    case KARMA_PRODUCT_LARGE: return launch_large(p.g, p.splits, s);
+    case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, RING_TILE, s);
+    case PRODUCT_BROAD: return launch_ring(p.g, p.splits, false, RING_BROAD, s);
+    case KARMA_PRODUCT_NARROW:
+    case PRODUCT_FLAT: return launch_ring(p.g, p.splits, false, RING_SLIM, s);
     case PRODUCT_SLICES: return launch_slices(p.g, p.splits, s);
     case KARMA_PRODUCT_STAGED_LARGE: return launch_general<256, 256, 2, 4>(p.g, p.splits, s);
     default: return launch_general<128, 128, 2, 2>(p.g, p.splits, s);
@@ -1208,7 +1196,10 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
     // 256 x 32 x 32 x 160 from 320 channels 131 -> 120 us; 320 from 640 channels (0.83) 97 and 99
     const long wide = 4l * ((g.M / 4 + 255) / 256) * ((g.N + RING_BROAD - 1) / RING_BROAD);
     const bool broad = (g.N + RING_BROAD - 1) / RING_BROAD * RING_BROAD * 10 < (g.N + RING_TILE - 1) / RING_TILE * RING_TILE * 7 && wide >= 2 * compute_units();
-    piece[0] = Piece{g, broad ? PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
+    // Up to 64 columns the slim tile, where it has a workgroup for every compute unit: 64 x 224 x 224 x 8 from 64 channels, 7 x 7,
+    // 698 -> 409 us.
+    const bool slim = g.N <= RING_SLIM && 4l * ((g.M / 4 + 255) / 256) >= compute_units();
+    piece[0] = Piece{g, slim ? KARMA_PRODUCT_NARROW : broad ? PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
     return KARMA_OK;
   }
   const bool may_split = g.ws && g.ldc == g.N && !g.act;
@@ -1231,14 +1222,6 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
       large = large && g.M >= 64 && g.N >= 512 && g.K >= 4096 && g.M % 8 == 0 && g.lda % 8 == 0 && g.ws != nullptr &&
               (uint64_t)g.N * cg.C < (1ull << 31) && (uint64_t)pixels * cg.Wo < (1ull << 32) && g.K < (1 << 24) &&
               (uint64_t)g.lda * 2 * 256 < (1ull << 31);
-    // 64 output channels (the first stage of the bottleneck network, the full-resolution level of the fully convolutional
-    // one): a 256 x 64 tile, eight wavefronts of 64 x 32, two workgroups per compute unit (a k-tile of this shape carries
-    // 16 MFMAs per wavefront, less than its loads' round trip: the second workgroup multiplies while the first one waits).
-    // 8 x 256 x 256 pixels, 3 x 3 x 64: 84 us, 99 us with half of a 128 x 128 tile empty.
-    if (g.conv_mode == 1 && large && g.N == 64 && (g.M + 255) / 256 >= 384) {
-      piece[0] = Piece{g, KARMA_PRODUCT_NARROW, 1, false};
-      return KARMA_OK;
-    }
     // below 128 output channels most of the large tile is empty
     if (g.conv_mode == 1 && g.N < 128) large = false;
   } else {

@@ -23,14 +23,15 @@ struct RingConv {
 };
 
 constexpr int RING_TILE = 128, RING_BK = 64;
-constexpr int RING_BROAD = 160;   // the other tile: 256 pixels x 160 channels (conv_mode 1), 160 x 256 (conv_mode 2)
+// the other tiles, for the gathered forms: 256 pixels x this many channels (conv_mode 1), or as many x 256 (conv_mode 2)
+constexpr int RING_BROAD = 160, RING_SLIM = 64;
 
 // Whether the operands' sizes and alignment are what the kernel's 16-byte pieces and 32-bit offsets need.
 bool gemm_ring_takes(const GemmArgs& g);
 // Launches the product over `splits` ranges of k_per_split (partials in g.ws when splits > 1; the caller adds them up).
-// deep: four stages instead of two.  broad: the tile of 256 x 160 or 160 x 256 (gathered forms only).
+// deep: four stages instead of two.  side: RING_TILE, RING_BROAD or RING_SLIM.
 // rc: the gathered forms, else null.  ep.colsum is honoured with act 2.
-int gemm_ring_launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, bool deep, bool broad, const RingConv* rc,
+int gemm_ring_launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, bool deep, int side, const RingConv* rc,
                      hipStream_t s);
 
 }  // namespace karma

@@ -40,6 +40,8 @@ struct Shape {
 using Square = Shape<RING_TILE, RING_TILE, 2, 2, 2>;
 using Wide = Shape<256, RING_BROAD, 4, 1, 1>;   // wavefronts of 64 x 160
 using Tall = Shape<RING_BROAD, 256, 1, 4, 1>;   // wavefronts of 160 x 64
+using Slim = Shape<256, RING_SLIM, 4, 1, 2>;    // wavefronts of 64 x 64, as Square's
+using Flat = Shape<RING_SLIM, 256, 1, 4, 2>;
 
 // Where a strided operand tile of T columns keeps what.  In LDS a k-row is T / 8 pieces of 16 bytes; a transposing read takes
 // four k-rows times four pieces at once, which have to lie in different banks: a row of 160 columns sees to that by itself,
@@ -48,7 +50,7 @@ using Tall = Shape<RING_BROAD, 256, 1, 4, 1>;   // wavefronts of 160 x 64
 template <int T>
 struct Strided {
   static constexpr int PPR = T / 8, CH = T * RING_BK * 2 / 1024 / 4;
-  static_assert(T == 128 || T == 160 || T == 256, "a layout below");
+  static_assert(T == 64 || T == 128 || T == 160 || T == 256, "a layout below");
   // k-row and first column of lane `lane` of wavefront `wave`'s piece i
   static __device__ __forceinline__ int row(int wave, int i, int lane) {
     if (T == 256) return 32 * (wave >> 1) + 4 * i + 2 * (wave & 1) + (lane >> 5);
@@ -59,7 +61,7 @@ struct Strided {
     return (p ^ swizzle(k)) * 8;
   }
   static __device__ __forceinline__ int swizzle(int k) {
-    return T == 160 ? 0 : (k & 3) << 2;
+    return T == 160 ? 0 : T == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2;
   }
   // byte address in the tile of column m, k = 8 half + e (half 0 or 1, e below 4); k + 4 lies NEXT further, k-step kk at step(kk)
   static constexpr int NEXT = (T == 256 ? 2 : 4) * T * 2;
@@ -190,12 +192,10 @@ __global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* _
   unsigned a_to = 0, b_to = 0, c_delta[2] = {0u, 0u};
   int a_left = 0, b_left = 0, c_r[2] = {0, 0}, c_s[2] = {0, 0};
   bool c_in[2] = {false, false};
-  u32x4 a_desc, b_desc;
   auto begin_a = [&](int t, int stage) {
     a_to = lds0 + stage * STAGE + wave * (CH_A * 1024);
     a_left = klen - t * BK;   // k from this tile's first one on
     if constexpr (CONV == 1) {
-      a_desc = buffer_desc(A);
 #pragma unroll
       for (int par = 0; par < 2; ++par) {   // a lane's pieces lie at two values of k
         const int col = a_col(par), k = kb + t * BK + col;
@@ -206,11 +206,12 @@ __global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* _
         c_delta[par] = (unsigned)((c_r[par] * cg.W + c_s[par]) * cg.C + c);
         c_in[par] = col < a_left;
       }
+      return buffer_desc(A);
     } else {
-      a_desc = buffer_desc(a_base + (A_KC ? (size_t)t * BK : (size_t)t * BK * lda));
+      return buffer_desc(a_base + (A_KC ? (size_t)t * BK : (size_t)t * BK * lda));
     }
   };
-  auto piece_a = [&](int i) {
+  auto piece_a = [&](int i, const u32x4& a_desc) {
     if constexpr (CONV == 1) {
       const int par = i & 1;   // (& and not &&: no branches)
       const bool ok = c_in[par] & ((unsigned)(ch0[i] + c_r[par]) < (unsigned)cg.H) & ((unsigned)(cw0[i] + c_s[par]) < (unsigned)cg.W);
@@ -222,9 +223,9 @@ __global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* _
   auto begin_b = [&](int t, int stage) {
     b_to = lds0 + stage * STAGE + A_BYTES + wave * (CH_B * 1024);
     b_left = klen - t * BK;
-    b_desc = buffer_desc(CONV == 2 ? B : b_base + (B_KC ? (size_t)t * BK : (size_t)t * BK * ldb));
+    return buffer_desc(CONV == 2 ? B : b_base + (B_KC ? (size_t)t * BK : (size_t)t * BK * ldb));
   };
-  auto piece_b = [&](int i) {
+  auto piece_b = [&](int i, const u32x4& b_desc) {
     if constexpr (CONV == 2) {
       const bool ok = g_in & (b_row(i) < b_left) & ((unsigned)(gho[i] * cg.stride + gr) < (unsigned)cg.H) &
                       ((unsigned)(gwo[i] * cg.stride + gs) < (unsigned)cg.W);
@@ -242,14 +243,14 @@ __global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* _
     }
   };
   auto issue_a = [&](int t, int stage) {
-    begin_a(t, stage);
+    const u32x4 d = begin_a(t, stage);
 #pragma unroll
-    for (int i = 0; i < CH_A; ++i) piece_a(i);
+    for (int i = 0; i < CH_A; ++i) piece_a(i, d);
   };
   auto issue_b = [&](int t, int stage) {
-    begin_b(t, stage);
+    const u32x4 d = begin_b(t, stage);
 #pragma unroll
-    for (int i = 0; i < CH_B; ++i) piece_b(i);
+    for (int i = 0; i < CH_B; ++i) piece_b(i, d);
   };
 
   // ---- LDS side: fragment addresses as in the 256 x 256 kernel
@@ -313,8 +314,9 @@ __global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* _
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) {
         const int nb = (kk + 1) & 1, nst = kk + 1 < KSTEPS ? st : stn, nk = kk + 1 < KSTEPS ? kk + 1 : 0;
-        if (kk == KSTEPS - 1) begin_a(t + NST, st);
-        if (kk == 0) begin_b(t + NST - 1, stp);
+        u32x4 desc{};
+        if (kk == KSTEPS - 1) desc = begin_a(t + NST, st);
+        if (kk == 0) desc = begin_b(t + NST - 1, stp);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
           const int i = q / TN, j = q % TN;
@@ -326,11 +328,11 @@ __global__ __launch_bounds__(256, SH::WGS) void gemm_ring_kernel(const bf16_t* _
           }
           if (kk == KSTEPS - 1) {
 #pragma unroll
-            for (int f = q * CH_A / Q; f < (q + 1) * CH_A / Q; ++f) piece_a(f);
+            for (int f = q * CH_A / Q; f < (q + 1) * CH_A / Q; ++f) piece_a(f, desc);
           }
           if (kk == 0) {
 #pragma unroll
-            for (int f = q * CH_B / Q; f < (q + 1) * CH_B / Q; ++f) piece_b(f);
+            for (int f = q * CH_B / Q; f < (q + 1) * CH_B / Q; ++f) piece_b(f, desc);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -514,11 +516,13 @@ bool gemm_ring_takes(const GemmArgs& g) {
   return true;
 }
 
-int gemm_ring_launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, bool deep, bool broad, const RingConv* rc,
+int gemm_ring_launch(const GemmArgs& g, const GemmEpilogue& ep, int splits, int k_per_split, bool deep, int side, const RingConv* rc,
                      hipStream_t s) {
-  if (broad && g.conv_mode == 1) launch<true, true, 0, 1, 3, Wide>(g, ep, splits, k_per_split, rc, s);
-  else if (broad && g.conv_mode == 2) launch<false, false, 0, 2, 3, Tall>(g, ep, splits, k_per_split, rc, s);
-  else if (broad) return KARMA_E_INVAL;
+  if (side == RING_BROAD && g.conv_mode == 1) launch<true, true, 0, 1, 3, Wide>(g, ep, splits, k_per_split, rc, s);
+  else if (side == RING_BROAD && g.conv_mode == 2) launch<false, false, 0, 2, 3, Tall>(g, ep, splits, k_per_split, rc, s);
+  else if (side == RING_SLIM && g.conv_mode == 1) launch<true, true, 0, 1, 2, Slim>(g, ep, splits, k_per_split, rc, s);
+  else if (side == RING_SLIM && g.conv_mode == 2) launch<false, false, 0, 2, 2, Flat>(g, ep, splits, k_per_split, rc, s);
+  else if (side != RING_TILE) return KARMA_E_INVAL;
   else if (deep) launch_form<4>(g, ep, splits, k_per_split, rc, s);
   else launch_form<2>(g, ep, splits, k_per_split, rc, s);
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
