@@ -32,13 +32,11 @@ __host__ __device__ inline int bn_band(int C) {
 
 // Rows of pixels that a thread has in flight.
 constexpr int BN_U = 4;
-// Rows per workgroup of the partial sums: the band above, or longer when that would make more than `most` bands, which the
-// few workgroups of the finishing kernel then take longer to add up than more bands save here.  us, forward / backward, at
-// most 2048, 1024 and 512 bands: 200704 x 256 59.9 / 93.3, 55.6 / 86.7, 58.8 / 89.9; 802816 x 64 58.0 / 90.6, 56.0 / 87.7,
-// 59.8 / 92.1; 262144 x 160 48.9 / 74.9, 46.3 / 70.0, 50.3 / 69.8.
-constexpr int BN_BANDS = 1024, BN_WS_BANDS = 2048;   // (the workspace that is asked for has room for twice as many)
-__host__ __device__ inline int bn_sum_band(int rows, int C, int most = BN_BANDS) {
-  const int b = bn_band(C), cap = (rows + most - 1) / most;
+// Rows per workgroup of the partial sums: the band above, or longer when that would make more than 2048 bands (a
+// million pixels in 96-row bands are 11 000 partial rows, which the few workgroups of the finishing kernel then
+// take longer to add up than the sums themselves took).
+__host__ __device__ inline int bn_sum_band(int rows, int C) {
+  const int b = bn_band(C), cap = (rows + 2047) / 2048;
   return b >= cap ? b : (cap + 7) / 8 * 8;
 }
 
@@ -678,7 +676,7 @@ int conv2d_wgrad(const bf16_t* dy, const bf16_t* x, bf16_t* dw, void* ws, size_t
 }
 
 size_t bn_ws_bytes(int rows, int c) {
-  const int band = bn_sum_band(rows, c > 8 ? c : 8, BN_WS_BANDS);
+  const int band = bn_sum_band(rows, c > 8 ? c : 8);
   return (size_t)((rows + band - 1) / band) * 2 * c * sizeof(float);
 }
 
