@@ -600,6 +600,7 @@ static GemmArgs fwd_product(const bf16_t* x, const bf16_t* w, bf16_t* y, const C
   g.a_kc = g.b_kc = true;
   g.lda = g.K; g.ldb = g.K; g.ldc = g.N;
   g.ws = ws; g.ws_bytes = ws_bytes;   // late stages: few output tiles, long reductions
+  g.keep_sums = c.keep_sums;
   if (!plain_gemm(c)) {
     g.conv_mode = 1;
     g.conv = ConvGather{c.H, c.W, c.Cin, Ho, Wo, c.R, c.S, c.stride, c.pad, 0};
@@ -614,6 +615,7 @@ static GemmArgs dgrad_product(const bf16_t* dy, const bf16_t* w, const bf16_t* w
   g.A = dy; g.C = dx; g.residual = add;
   g.M = c.N * c.H * c.W; g.N = c.Cin; g.ldc = g.N;
   g.ws = ws; g.ws_bytes = ws_bytes;
+  g.keep_sums = c.keep_sums;
   if (plain_gemm(c)) {
     g.B = w;            // B(n = ci, k = co) = w[co][ci]: strided
     g.K = c.Cout;
@@ -642,6 +644,7 @@ static GemmArgs wgrad_product(const bf16_t* dy, const bf16_t* x, bf16_t* dw, voi
   g.a_kc = g.b_kc = false;
   g.lda = c.Cout; g.ldb = c.Cin; g.ldc = g.N;
   g.ws = ws; g.ws_bytes = ws_bytes;
+  g.keep_sums = c.keep_sums;
   if (!plain_gemm(c)) {
     g.conv_mode = 2;
     g.conv = ConvGather{c.H, c.W, c.Cin, Ho, Wo, c.R, c.S, c.stride, c.pad, 0};

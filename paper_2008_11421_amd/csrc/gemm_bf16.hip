@@ -849,17 +849,19 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
   const double gather128 = g.conv_mode == 1 ? 1.15 : 1.0, lone128 = g.conv_mode == 1 ? 0.85 : 0.75;
   const double ragged = g.M % 256 || g.N % 256 || g.K % 64 ? 1.05 : 1.0;
   const double by_element = g.N % 8 || g.ldc % 8 ? std::min(1.0, g.M / 128.0) : 0.0;
-  GemmPlan best{0, 1, false, 1e30};
+  GemmPlan best{0, 1, false, 1e30}, square = best, slim = best;
   const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
   for (int tile : {64, 128, RING_BROAD, 256}) {
     const bool gathers = tile == RING_BROAD || (tile == RING_SLIM && g.conv_mode);   // 256 on one side
     const bool taken = tile == 256 ? large : small && (tile == 128 || (gathers ? g.conv_mode : g.N % 8 == 0 && g.ldc % 8 == 0));
+    // (sums in the order they always had: only unsplit gathers, see below, are free to take another tile)
+    if (g.keep_sums && (gathers ? g.conv_mode != 1 : tile == SLICE_TILE)) continue;
     if (!taken || (tile == RING_SLIM && g.conv_mode == 1 && g.N > RING_SLIM)) continue;   // (beyond 64 channels its gathers are read twice)
     const int rows = gathers && g.conv_mode == 1 ? 256 : tile, cols = gathers && g.conv_mode == 2 ? 256 : tile;
     const long tiles = (long)((g.M + rows - 1) / rows) * ((g.N + cols - 1) / cols);
     GemmPlan own{tile, 1, false, 1e30};   // the best number of ranges with this tile ...
     double late = 0.0;                    // ... and what its k-tiles take beyond two workgroups' pace
-    for (int sp = 1; sp <= max_splits; ++sp) {
+    for (int sp = 1; sp <= (gathers && g.keep_sums ? 1 : max_splits); ++sp) {
       if (sp > 1 && ((uint64_t)sp * g.M * g.N * sizeof(float) > g.ws_bytes || tiles * sp > 8l * cus)) break;
       const int kt = (k_tiles + sp - 1) / sp;
       const long items = tiles * sp, places = tile >= RING_BROAD ? cus : 2l * cus, full = items / places, rest = items % places;
@@ -892,8 +894,16 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
       }
     }
     own.us += late;
+    if (tile == RING_SLIM) slim = own;
     if (own.us < best.us) best = own;
+    if (!gathers && own.us < square.us) square = own;
   }
+  // keep_sums: ranges only as the two square tiles would have them (forward passes of 64 channels on large images: none).  A tile
+  // alone doesn't change a sum, its ranges do.  A step of 4 bottleneck blocks, 64 images of 224 x 224: 4535 us so, 4458 us free,
+  // but by then 2 % of its update apart at small batches.
+  const bool whole = g.conv_mode == 1 && large && g.N == RING_SLIM && (g.M + 255) / 256 >= 384;
+  if (g.keep_sums && whole && slim.tile) return slim;
+  if (g.keep_sums && square.splits > 1 && square.us < 1e30) return square;
   return best;
 }
 

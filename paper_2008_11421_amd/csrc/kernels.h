@@ -69,6 +69,9 @@ struct GemmArgs {
   float* colsum_partial;
   size_t colsum_bytes;
   int* colsum_rows;
+  // The sums keep the order that the 128 x 128 and 256 x 256 tiles and their ranges of the reduction give them: results are
+  // the same in bits whatever other tile takes the product.
+  bool keep_sums;
 };
 int gemm_bf16(const GemmArgs& g, hipStream_t s);
 // The two products a layer's gradient dy goes into, independent of each other: dx = dy w (A k-contiguous, B strided; act 0 or
@@ -114,7 +117,7 @@ int fill_zero(void* p, size_t bytes, hipStream_t s);
 int cast_f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s);
 
 // ---- convolutional workload (conv_bn.hip): NHWC bf16, weights [c_out][r][s][c_in]
-struct ConvShape { int N, H, W, Cin, Cout, R, S, stride, pad; };
+struct ConvShape { int N, H, W, Cin, Cout, R, S, stride, pad; bool keep_sums = false; };   // keep_sums: see GemmArgs
 int conv_out_dim(int n, int k, int stride, int pad);
 // ws / ws_bytes: optional fp32 workspace that lets a product with few output tiles split its reduction;
 // add (may be null): a tensor of y's shape added to the result (a residual sum)

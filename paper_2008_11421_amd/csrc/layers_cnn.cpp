@@ -163,6 +163,8 @@ struct HeadWs {
     if (st_) return st_;   \
   } while (0)
 
+// Every product keeps the order of its sums (true in the shapes below, keep_sums here): where a batch is small, a ReLU behind a
+// normalisation turns the last bit of a sum into another update within a few steps, and a step is to give what it gave.
 int gemm_plain(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, int M, int N, int K, bool a_kc, bool b_kc,
                hipStream_t s) {
   GemmArgs g{};
@@ -172,6 +174,7 @@ int gemm_plain(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* bias, in
   g.lda = a_kc ? K : M;
   g.ldb = b_kc ? K : N;
   g.ldc = N;
+  g.keep_sums = true;
   return gemm_bf16(g, s);
 }
 
@@ -257,7 +260,7 @@ int cnn_forward(Ctx& c, uint32_t i, const LayerIO& io, hipStream_t s) {
     bf16_t* c0 = (bf16_t*)(S + sv.c0);
     bf16_t* a0 = (bf16_t*)(S + sv.a0);
     const int rows = g.N * g.H1 * g.H1;
-    TRY(conv2d_fwd((const bf16_t*)io.x, W(SW), c0, ConvShape{g.N, g.S, g.S, IMG_C, g.C, 7, 7, 2, 3}, s, Wk + wl.splitk, wl.splitk_bytes));
+    TRY(conv2d_fwd((const bf16_t*)io.x, W(SW), c0, ConvShape{g.N, g.S, g.S, IMG_C, g.C, 7, 7, 2, 3, true}, s, Wk + wl.splitk, wl.splitk_bytes));
     TRY(bn_fwd(c0, W(SG), W(SB), nullptr, a0, (float*)(S + sv.st), (float*)(Wk + wl.bn), rows, g.C, 1, s));
     if (io.out) TRY(maxpool_fwd(a0, (bf16_t*)io.out, g.N, g.H1, g.H1, g.C, s));
     return KARMA_OK;
@@ -273,17 +276,17 @@ int cnn_forward(Ctx& c, uint32_t i, const LayerIO& io, hipStream_t s) {
   bf16_t* c3 = (bf16_t*)(S + sv.c3);
   bf16_t* cp = (bf16_t*)(S + sv.cp);
   float* bnws = (float*)(Wk + wl.bn);
-  TRY(conv2d_fwd(x, W(W1), c1, ConvShape{g.N, g.H, g.W, g.cin, g.mid, 1, 1, 1, 0}, s, Wk + wl.splitk, wl.splitk_bytes));
+  TRY(conv2d_fwd(x, W(W1), c1, ConvShape{g.N, g.H, g.W, g.cin, g.mid, 1, 1, 1, 0, true}, s, Wk + wl.splitk, wl.splitk_bytes));
   TRY(bn_fwd(c1, W(G1), W(B1), nullptr, a1, (float*)(S + sv.st1), bnws, g.P(), g.mid, 1, s));
-  TRY(conv2d_fwd(a1, W(W2), c2, ConvShape{g.N, g.H, g.W, g.mid, g.mid, 3, 3, g.stride, 1}, s, Wk + wl.splitk, wl.splitk_bytes));
+  TRY(conv2d_fwd(a1, W(W2), c2, ConvShape{g.N, g.H, g.W, g.mid, g.mid, 3, 3, g.stride, 1, true}, s, Wk + wl.splitk, wl.splitk_bytes));
   TRY(bn_fwd(c2, W(G2), W(B2), nullptr, a2, (float*)(S + sv.st2), bnws, g.P2(), g.mid, 1, s));
-  TRY(conv2d_fwd(a2, W(W3), c3, ConvShape{g.N, g.Ho, g.Wo, g.mid, g.cout, 1, 1, 1, 0}, s, Wk + wl.splitk, wl.splitk_bytes));
+  TRY(conv2d_fwd(a2, W(W3), c3, ConvShape{g.N, g.Ho, g.Wo, g.mid, g.cout, 1, 1, 1, 0, true}, s, Wk + wl.splitk, wl.splitk_bytes));
   // a recompute whose output nobody needs still has to produce every saved tensor, statistics
   // included; only the last elementwise pass can be dropped
   bf16_t* y = io.out ? (bf16_t*)io.out : (bf16_t*)(Wk + wl.big) + (size_t)g.P2() * g.cout;
   if (g.proj) {
     bf16_t* sc = (bf16_t*)(Wk + wl.big);
-    TRY(conv2d_fwd(x, W(WP), cp, ConvShape{g.N, g.H, g.W, g.cin, g.cout, 1, 1, g.stride, 0}, s, Wk + wl.splitk, wl.splitk_bytes));
+    TRY(conv2d_fwd(x, W(WP), cp, ConvShape{g.N, g.H, g.W, g.cin, g.cout, 1, 1, g.stride, 0, true}, s, Wk + wl.splitk, wl.splitk_bytes));
     TRY(bn_fwd(cp, W(GP), W(BP), nullptr, sc, (float*)(S + sv.stp), bnws, g.P2(), g.cout, 0, s));
     TRY(bn_fwd(c3, W(G3), W(B3), sc, y, (float*)(S + sv.st3), bnws, g.P2(), g.cout, 1, s));
   } else {
@@ -311,7 +314,7 @@ int cnn_backward(Ctx& c, uint32_t i, const LayerIO& io, hipStream_t s) {
     TRY(bn_bwd(da0, c0, (const float*)(S + sv.st), W(SG), W(SB), 1, da0, (float*)G(SG), (float*)G(SB), (float*)(Wk + wl.bn),
                rows, g.C, s));
     TRY(conv2d_wgrad(da0, (const bf16_t*)io.x, (bf16_t*)G(SW), Wk + wl.splitk, wl.splitk_bytes,
-                     ConvShape{g.N, g.S, g.S, IMG_C, g.C, 7, 7, 2, 3}, s));
+                     ConvShape{g.N, g.S, g.S, IMG_C, g.C, 7, 7, 2, 3, true}, s));
     return KARMA_OK;
   }
   const BlockGeom& g = net.blocks[i - 1];
@@ -336,8 +339,8 @@ int cnn_backward(Ctx& c, uint32_t i, const LayerIO& io, hipStream_t s) {
   bf16_t* wt = (bf16_t*)(Wk + wl.wt);
   float* bnws = (float*)(Wk + wl.bn);
   void* sk = Wk + wl.splitk;
-  const ConvShape s1{g.N, g.H, g.W, g.cin, g.mid, 1, 1, 1, 0}, s2{g.N, g.H, g.W, g.mid, g.mid, 3, 3, g.stride, 1},
-      s3{g.N, g.Ho, g.Wo, g.mid, g.cout, 1, 1, 1, 0}, sp{g.N, g.H, g.W, g.cin, g.cout, 1, 1, g.stride, 0};
+  const ConvShape s1{g.N, g.H, g.W, g.cin, g.mid, 1, 1, 1, 0, true}, s2{g.N, g.H, g.W, g.mid, g.mid, 3, 3, g.stride, 1, true},
+      s3{g.N, g.Ho, g.Wo, g.mid, g.cout, 1, 1, 1, 0, true}, sp{g.N, g.H, g.W, g.cin, g.cout, 1, 1, g.stride, 0, true};
   // gradient through the last ReLU: the block's output is recomputed from saved tensors
   // (it is the next block's input and may be gone by now)
   if (g.proj) {
