@@ -337,7 +337,8 @@ __global__ __launch_bounds__(256 * SP, WGS) void attn_fwd_kernel(const bf16_t* _
     // probability of one is exact in bf16).
     const float m_new = fmaxf(m, tmax);
     if (__any((m_new - m) * c > AttnTiles<D>::FWD_SLACK)) {
-      const float alpha = fast_exp2((m - m_new) * c);
+      // (a query of a group other than the first that has met only minus infinity: nothing to rescale, and no difference to take)
+      const float alpha = SP > 1 && m_new == -INFINITY ? 1.f : fast_exp2((m - m_new) * c);
       l *= alpha;
 #pragma unroll
       for (int i = 0; i < DP / 32; ++i)

@@ -4,6 +4,7 @@ the rules that choose them, on a chip of 256 compute units: tiles * heads * batc
 512 and 640.  Against float64.
 Tolerance as for the other attention tests: three chained bf16 roundings leave about 1 % of a head's gradient."""
 import ctypes as C
+import math
 
 import pytest
 
@@ -87,3 +88,26 @@ def test_scores_of_minus_infinity(g, s):
         out.append((ctx.clone(), lse.clone()))
     assert torch.isfinite(out[1][0].float()).all() and torch.isfinite(out[1][1]).all()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("s,d,first", [(256, 152, 32), (384, 152, 32), (512, 64, 64), (640, 64, 64), (512, 128, 64), (768, 128, 64)])
+def test_minus_infinity_for_some_queries(g, s, d, first):
+    """Finite values whose scores overflow to minus infinity for every other query, on the second group's first tile (and, for
+    one head, on the first group's as well): what a wavefront rescales for its other queries is not to touch these."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(s + d)
+    qkv = torch.randn((1, s, 3, 2, d), device="cuda", generator=gen).bfloat16()
+    qkv[:, :, 0, :, 0] = 2.0 * (torch.arange(s, device="cuda") % 2)[None, :, None]
+    qkv[:, first:2 * first, 1, :, 0] = -3e38
+    qkv[:, 1:first, 1, 1, 0] = -3e38
+    ctx, lse = torch.empty((1, s, 2 * d), device="cuda", dtype=torch.bfloat16), torch.empty((2, s), device="cuda")
+    g.call(K.lib().karma_k_attention_fwd_bf16, g.ptr(qkv), g.ptr(ctx), g.ptr(lse), 1, s, 2, d, g.stream_ptr())
+    x = qkv.double().permute(2, 0, 3, 1, 4).contiguous()[:, 0]
+    sc = torch.matmul(x[0], x[1].transpose(-1, -2).contiguous()) / d ** 0.5
+    sc = sc.masked_fill(torch.ones(s, s, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    want = torch.matmul(torch.softmax(sc, -1), x[2])
+    got = ctx.double().view(s, 2, d).permute(1, 0, 2)
+    assert torch.isfinite(got).all() and torch.isfinite(lse).all()
+    assert ((got - want).pow(2).sum((-1, -2)) / want.pow(2).sum((-1, -2))).sqrt().max().item() <= TOL
+    assert (lse.double() - torch.logsumexp(sc, -1) / math.log(2)).abs().max().item() <= 1e-3       # fp32 sums of exact products
