@@ -9,7 +9,8 @@ namespace karma {
 
 HostPool::HostPool(unsigned threads) {
   if (threads < 1) threads = 1;
-  for (unsigned i = 1; i < threads; ++i) workers_.emplace_back([this] { worker(); });
+  left_.resize(threads);
+  for (unsigned i = 1; i < threads; ++i) workers_.emplace_back([this, i] { worker(i); });
 }
 
 HostPool::~HostPool() {
@@ -21,10 +22,19 @@ HostPool::~HostPool() {
   for (auto& t : workers_) t.join();
 }
 
-// Takes parts of the current call until none is left; mu_ is held on entry and on return.
-void HostPool::take_parts(std::unique_lock<std::mutex>& lk) {
-  while (next_ < parts_) {
-    const size_t lo = (size_t)next_++ * part_, hi = std::min(n_, lo + part_);
+// Takes parts of the current call, thread `id`'s own and then the last ones of whoever has most left, until none is left;
+// mu_ is held on entry and on return.
+void HostPool::take_parts(unsigned id, std::unique_lock<std::mutex>& lk) {
+  while (untaken_) {
+    unsigned at;
+    if (left_[id].next < left_[id].end) {
+      at = left_[id].next++;
+    } else {
+      auto less = [](const Run& a, const Run& b) { return a.end - a.next < b.end - b.next; };
+      at = --std::max_element(left_.begin(), left_.end(), less)->end;
+    }
+    --untaken_;
+    const size_t lo = (size_t)at * part_, hi = std::min(n_, lo + part_);
     const std::function<void(size_t, size_t)>& fn = *fn_;
     lk.unlock();
     fn(lo, hi);
@@ -33,18 +43,21 @@ void HostPool::take_parts(std::unique_lock<std::mutex>& lk) {
   }
 }
 
-void HostPool::worker() {
+void HostPool::worker(unsigned id) {
   std::unique_lock<std::mutex> lk(mu_);
   for (;;) {
-    cv_.wait(lk, [&] { return stop_ || next_ < parts_; });
+    cv_.wait(lk, [&] { return stop_ || untaken_; });
     if (stop_) return;
-    take_parts(lk);
+    take_parts(id, lk);
   }
 }
 
 // Waking the workers takes longer (40 to 60 us) than small calls do, and the caller need not wait for it: it takes parts
 // itself until none is left, and is done when those that others took are.  A step of eight layers of 256 x 256, 65792
-// parameters each: 570 us with every worker given its share of each call, 390 with this.
+// parameters each: 570 us with every worker given its share of each call and waited for, 390 with this.
+// Each thread has a run of parts of its own, the same in every call of a size, so that it finds in its cache what it updated last
+// time.  Adam again and again on one tensor, 16 threads, us, parts dealt to whoever is awake -> runs: 1 Mi elements 108 -> 80,
+// 4 Mi 303 -> 127, 16 Mi 1850 -> 690; on 80 tensors of 4 Mi, which no cache holds, 345 -> 340.
 void HostPool::parallel_for(size_t n, const std::function<void(size_t, size_t)>& fn) {
   constexpr size_t ALONE = 128 * 1024, LEAST = 32 * 1024;   // elements: at most this many for the caller alone; a part's least
   if (workers_.empty() || n <= ALONE) {
@@ -55,14 +68,16 @@ void HostPool::parallel_for(size_t n, const std::function<void(size_t, size_t)>&
   fn_ = &fn;
   n_ = n;
   part_ = std::max(LEAST, ((n + 4 * size() - 1) / (4 * size()) + 63) / 64 * 64);
-  next_ = 0;
-  parts_ = pending_ = (unsigned)((n + part_ - 1) / part_);
+  untaken_ = pending_ = (unsigned)((n + part_ - 1) / part_);
+  for (unsigned t = 0, at = 0; t < size(); ++t) {
+    left_[t].next = at;
+    left_[t].end = at += untaken_ / size() + (t < untaken_ % size() ? 1 : 0);
+  }
   lk.unlock();
   cv_.notify_all();
   lk.lock();
-  take_parts(lk);
+  take_parts(0, lk);
   done_cv_.wait(lk, [&] { return pending_ == 0; });
-  parts_ = 0;
 }
 
 float bf16_to_f32(uint16_t b) {

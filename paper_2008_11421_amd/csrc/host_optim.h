@@ -11,8 +11,8 @@
 
 namespace karma {
 
-// Persistent worker pool; parallel_for cuts [0, n) into contiguous parts, which the caller and whichever workers are awake
-// take one after the other.
+// Persistent worker pool; parallel_for cuts [0, n) into contiguous parts and gives each thread a run of them, the caller among
+// them; who has done its own takes what others have not begun.
 class HostPool {
  public:
   explicit HostPool(unsigned threads);
@@ -21,14 +21,16 @@ class HostPool {
   unsigned size() const { return (unsigned)workers_.size() + 1; }
 
  private:
-  void worker();
-  void take_parts(std::unique_lock<std::mutex>& lk);
+  void worker(unsigned id);
+  void take_parts(unsigned id, std::unique_lock<std::mutex>& lk);
   std::vector<std::thread> workers_;
   std::mutex mu_;
   std::condition_variable cv_, done_cv_;
   const std::function<void(size_t, size_t)>* fn_ = nullptr;
+  struct Run { unsigned next, end; };
+  std::vector<Run> left_;                          // by thread: its parts that nobody has taken yet
   size_t n_ = 0, part_ = 0;                        // elements, and how many of them a part has
-  unsigned next_ = 0, parts_ = 0, pending_ = 0;    // the next part to take, all of them, those not done yet
+  unsigned untaken_ = 0, pending_ = 0;             // parts that nobody has taken, and that are not done yet
   bool stop_ = false;
 };
 
