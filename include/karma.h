@@ -599,10 +599,12 @@ int karma_k_conv2d_wgrad_bf16(const void* dy_dev, const void* x_dev, void* dw_de
                               const karma_conv_shape* shape, void* stream);
 
 /* karma_k_gemm_plan for a convolution's products (which: forward, input gradient, weight gradient).  A stride-2 input
- * gradient that runs by parity of its pixels is one part. */
+ * gradient that runs by parity of its pixels is one part.  which | KARMA_CONV_KEEP_SUMS: as the bottleneck network asks for
+ * its products, whose sums keep their order: divided only as the 128 x 128 and 256 x 256 tiles would be. */
 #define KARMA_CONV_FWD 0u
 #define KARMA_CONV_DGRAD 1u
 #define KARMA_CONV_WGRAD 2u
+#define KARMA_CONV_KEEP_SUMS 4u
 int karma_k_conv2d_plan(const karma_conv_shape* shape, uint32_t which, uint64_t ws_bytes, karma_product_part* parts_out,
                         uint32_t* n_out);
 

@@ -20,7 +20,7 @@ STEP_KERNEL_TIMES = 4
 GEMM_A_STRIDED, GEMM_B_STRIDED, GEMM_OUT_F32, GEMM_ACCUMULATE = 1, 2, 4, 8
 GEMM_GELU_FWD, GEMM_GELU_BWD = 1, 2
 PRODUCT_STAGED_SMALL, PRODUCT_STAGED_LARGE, PRODUCT_SMALL, PRODUCT_LARGE, PRODUCT_NARROW = range(5)
-CONV_FWD, CONV_DGRAD, CONV_WGRAD = range(3)
+CONV_FWD, CONV_DGRAD, CONV_WGRAD, CONV_KEEP_SUMS = 0, 1, 2, 4
 
 
 class LayerCost(C.Structure):
@@ -122,7 +122,7 @@ def gemm_plan(m, n, k, flags=0, gelu_mode=0, misaligned=False, ws_bytes=0):
 
 
 def conv_plan(shape, which, ws_bytes=0):
-    """gemm_plan for one of a convolution's three products (CONV_FWD, CONV_DGRAD, CONV_WGRAD)."""
+    """gemm_plan for one of a convolution's three products (CONV_FWD, CONV_DGRAD, CONV_WGRAD, with or without CONV_KEEP_SUMS)."""
     return _parts(lib().karma_k_conv2d_plan, C.byref(shape), which, C.c_uint64(ws_bytes))
 
 

@@ -849,7 +849,7 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
   const double gather128 = g.conv_mode == 1 ? 1.15 : 1.0, lone128 = g.conv_mode == 1 ? 0.85 : 0.75;
   const double ragged = g.M % 256 || g.N % 256 || g.K % 64 ? 1.05 : 1.0;
   const double by_element = g.N % 8 || g.ldc % 8 ? std::min(1.0, g.M / 128.0) : 0.0;
-  GemmPlan best{0, 1, false, 1e30}, square = best, slim = best;
+  GemmPlan best{0, 1, false, 1e30}, square = best;
   const int max_splits = may_split ? std::min(256, std::max(1, g.K / (4 * 64))) : 1;
   for (int tile : {64, 128, RING_BROAD, 256}) {
     const bool gathers = tile == RING_BROAD || (tile == RING_SLIM && g.conv_mode);   // 256 on one side
@@ -894,15 +894,11 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
       }
     }
     own.us += late;
-    if (tile == RING_SLIM) slim = own;
     if (own.us < best.us) best = own;
     if (!gathers && own.us < square.us) square = own;
   }
-  // keep_sums: ranges only as the two square tiles would have them (forward passes of 64 channels on large images: none).  A tile
-  // alone doesn't change a sum, its ranges do.  A step of 4 bottleneck blocks, 64 images of 224 x 224: 4535 us so, 4458 us free,
-  // but by then 2 % of its update apart at small batches.
-  const bool whole = g.conv_mode == 1 && large && g.N == RING_SLIM && (g.M + 255) / 256 >= 384;
-  if (g.keep_sums && whole && slim.tile) return slim;
+  // keep_sums: ranges only as the two square tiles would have them.  A tile alone doesn't change a sum, its ranges do.  A step of
+  // 4 bottleneck blocks, 64 images of 224 x 224: 4535 us so, 4458 us free, but by then 2 % of its update apart at small batches.
   if (g.keep_sums && square.splits > 1 && square.us < 1e30) return square;
   return best;
 }
@@ -1212,7 +1208,7 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
     piece[0] = Piece{g, slim ? KARMA_PRODUCT_NARROW : broad ? PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
     return KARMA_OK;
   }
-  const bool may_split = g.ws && g.ldc == g.N && !g.act;
+  bool may_split = g.ws && g.ldc == g.N && !g.act;
   bool large;
   if (g.conv_mode) {
     const ConvGather& cg = g.conv;
@@ -1232,6 +1228,8 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
       large = large && g.M >= 64 && g.N >= 512 && g.K >= 4096 && g.M % 8 == 0 && g.lda % 8 == 0 && g.ws != nullptr &&
               (uint64_t)g.N * cg.C < (1ull << 31) && (uint64_t)pixels * cg.Wo < (1ull << 32) && g.K < (1 << 24) &&
               (uint64_t)g.lda * 2 * 256 < (1ull << 31);
+    // Sums that keep their order: those of 64 channels on large images have never been divided
+    if (g.keep_sums && g.conv_mode == 1 && large && g.N == 64 && (g.M + 255) / 256 >= 384) may_split = false;
     // below 128 output channels most of the large tile is empty
     if (g.conv_mode == 1 && g.N < 128) large = false;
   } else {

@@ -116,3 +116,22 @@ def test_short_reductions_are_not_cut():
     assert K.gemm_plan(412776, 560, 216) == [(K.PRODUCT_LARGE, 412776, 560, 1)]
     assert all(len(K.gemm_plan(m, n, k)) == 1 for m, n, k in [(4512, 8128, 680), (6296, 5624, 840), (4096, 4256, 1016)])
     assert len(K.gemm_plan(4096, 4256, 1024)) == 2
+
+
+def test_products_that_keep_their_sums():
+    """64 channels on large images are not divided, whatever the model of times says; weight gradients and small products are
+    divided as the 128 x 128 and 256 x 256 tiles are, whatever other tile a free product takes."""
+    keep, room = K.CONV_KEEP_SUMS, 1 << 30
+    for args in [(49, 47, 47, 560, 64, 7, 7, 1, 3), (6, 272, 272, 648, 64, 7, 7, 2, 3), (64, 224, 224, 8, 64, 7, 7, 2, 3), (64, 56, 56, 64, 64, 3, 3, 1, 1)]:
+        shape = K.ConvShape(*args)
+        m = args[0] * ((args[1] + 2 * args[8] - args[5]) // args[7] + 1) ** 2
+        (_, rows, cols, splits), = K.conv_plan(shape, K.CONV_FWD | keep, room)
+        assert rows == m > 383 * 256 and (cols, splits) == (64, 1)
+    shape = K.ConvShape(2, 228, 228, 64, 1328, 7, 7, 1, 3)
+    assert K.conv_plan(shape, K.CONV_DGRAD | keep, room)[0][3] == 1
+    # (ranges of the square tiles, ranges where the order is free)
+    for args, which, kept, free in [((64, 56, 56, 64, 64, 3, 3, 1, 1), K.CONV_WGRAD, 102, 166), ((64, 224, 224, 8, 64, 7, 7, 2, 3), K.CONV_WGRAD, 128, 256),
+                                    ((8, 56, 56, 64, 256, 1, 1, 1, 0), K.CONV_WGRAD, 79, 49), ((4, 14, 14, 256, 256, 3, 3, 1, 1), K.CONV_FWD, 6, 6)]:
+        assert [K.conv_plan(K.ConvShape(*args), w, room)[0][3] for w in (which | keep, which)] == [kept, free]
+    with pytest.raises(Exception):
+        K.conv_plan(shape, 3 | keep)
