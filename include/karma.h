@@ -502,6 +502,19 @@ typedef struct {
 int karma_k_gemm_plan(uint32_t m, uint32_t n, uint32_t k, uint32_t flags, uint32_t gelu_mode, uint32_t misaligned,
                       uint64_t ws_bytes, karma_product_part* parts_out, uint32_t* n_out);
 
+/* Both gradients of a linear layer y = x w^T, x bf16 [rows][k], w bf16 [n][k], from dy bf16 [rows][n]: dx_dev = dy w, bf16
+ * [rows][k], and dw_dev = dy^T x, [n][k], bf16 or as flags say (KARMA_GEMM_OUT_F32, KARMA_GEMM_ACCUMULATE).  Small ones run
+ * side by side in one launch.  aux_dev (may be NULL), bf16 [rows][k]: dx is multiplied by GELU'(aux), as KARMA_GEMM_GELU_BWD
+ * does; then colsum_out_dev (may be NULL), fp32 [k], receives dx's column sums.  ws_dev (may be NULL): ceil(rows/64)*k floats,
+ * rounded up to 256 bytes, where column sums are asked for (KARMA_E_OOM if smaller), and what is left of ws_bytes lets the
+ * reductions be divided.  dx and dw overlap nothing else.  Errors as karma_k_gemm_bf16. */
+int karma_k_linear_bwd_bf16(const void* dy_dev, const void* w_dev, const void* x_dev, void* dx_dev, void* dw_dev,
+                            const void* aux_dev, float* colsum_out_dev, void* ws_dev, uint64_t ws_bytes, uint32_t rows,
+                            uint32_t n, uint32_t k, uint32_t flags, void* stream);
+/* Whether that would be one launch (host only; gelu != 0: with aux_dev; ws_bytes: what is left for the reductions). */
+int karma_k_linear_bwd_plan(uint32_t rows, uint32_t n, uint32_t k, uint32_t gelu, uint32_t flags, uint64_t ws_bytes,
+                            uint32_t* together_out);
+
 /* karma_k_attention_bwd_bf16 together with the column sums of dqkv over all batch * seq tokens, colsum_out_dev fp32
  * [3 * heads * d]: the gradient of the QKV projection's bias.  They are taken inside the kernels (one row of partial
  * sums per 32 tokens, from the fp32 values).

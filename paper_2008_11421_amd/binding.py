@@ -126,6 +126,13 @@ def conv_plan(shape, which, ws_bytes=0):
     return _parts(lib().karma_k_conv2d_plan, C.byref(shape), which, C.c_uint64(ws_bytes))
 
 
+def linear_bwd_together(rows, n, k, gelu=False, flags=0, ws_bytes=0):
+    """Whether karma_k_linear_bwd_bf16 would be one launch."""
+    out = C.c_uint32()
+    _check(lib().karma_k_linear_bwd_plan(rows, n, k, int(gelu), flags, C.c_uint64(ws_bytes), C.byref(out)), "karma_k_linear_bwd_plan")
+    return bool(out.value)
+
+
 def _layers_array(layers):
     arr = (LayerCost * len(layers))()
     for k, l in enumerate(layers):

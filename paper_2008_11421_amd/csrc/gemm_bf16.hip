@@ -1107,10 +1107,11 @@ struct Piece {
   uint32_t kernel;   // KARMA_PRODUCT_* or one of those above
   int splits;
   bool deep;    // the 128 x 128 tile: four stages
+  double us = 0.0;   // modelled, where the tile was chosen by that
 };
 static Piece planned(const GemmArgs& g, const GemmPlan& p) {
   const uint32_t of64 = !g.conv_mode ? PRODUCT_SLICES : g.conv_mode == 1 ? KARMA_PRODUCT_NARROW : PRODUCT_FLAT;
-  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? of64 : PRODUCT_BROAD, p.splits, p.deep};
+  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? of64 : PRODUCT_BROAD, p.splits, p.deep, p.us};
 }
 static int launch_piece(const Piece& p, hipStream_t s) {
   switch (p.kernel) {
@@ -1266,39 +1267,71 @@ static int gemm_bf16_launch(const GemmArgs& g, hipStream_t s) {
   return st;
 }
 
-// Both gradients of a layer in one launch of the 64 x 64 tile where that is modelled to be the shorter way
-static bool pair_of_slices(const GemmArgs& dx, const GemmArgs& dw) {
+// A product as gemm_choose would have it carried out
+struct Choice {
+  Piece piece[2];
+  int pieces = 0;
+};
+
+// Both gradients of a layer in one launch of the 64 x 64 tile where that is modelled to be the shorter way by 5 %: one workgroup
+// per compute unit, those of dx first, those of dw as units become free; beside other work a round of k-tiles takes longer than
+// SLICES_TILE says of a launch alone.  Of 700 layers of transformers (widths from 128 to 1280, 128 to 24576 tokens) 291 take
+// it: 1.56 times as fast as the two products with tiles of their own up to 32 k-tiles, 1.33 up to 48, 1.15 up to 64, and three
+// of them more than 3 % slower (41.1 / 38.8, 39.1 / 37.9, 59.1 / 52.4 us).  us, one launch / two: 1024 x 256 x 256 8 / 16,
+// 640 x 2560 x 640 (rows, n, k) 17.1 / 22.3, 2304 x 2560 x 640 35.9 / 43.9, 3200 x 512 x 128 13.7 / 17.8.  An estimate that shared the
+// work out evenly had taken 481, 113 of them slower, by up to 1.6: 6912 x 768 x 256 31.4 / 24.0, 3840 x 3040 x 760 100 / 62.
+// PAIR_MAX_KT: beyond it gains and losses were alike (27 layers, 0.82 to 1.35).
+constexpr double PAIR_TILE = 0.95;
+constexpr int PAIR_MAX_KT = 64;
+static bool pair_of_slices(const GemmArgs& dx, const GemmArgs& dw, const Choice (&own)[2]) {
+  if (!dx.a_kc || dx.b_kc || dx.act == 1 || dw.a_kc || dw.b_kc || dw.act || dx.conv_mode || dw.conv_mode) return false;
   const GemmArgs* g[2] = {&dx, &dw};
-  const int cus = compute_units();
-  double apart = 0.0, work = 0.0, longest = 0.0;
-  long items = 0;
+  double apart = 0.0, each[2];
+  long items[2];
   for (int i = 0; i < 2; ++i) {
-    Piece piece[2];
-    int pieces = 0;
-    if (gemm_choose(*g[i], piece, &pieces) != KARMA_OK || pieces != 1) return false;
+    if (own[i].pieces != 1) return false;
     // (products of which one alone fills the chip are better off with tiles of their own)
-    if (piece[0].kernel != PRODUCT_SLICES && piece[0].kernel != KARMA_PRODUCT_SMALL) return false;
-    if (!gemm_ring_takes(*g[i])) return false;
-    apart += plan_product(*g[i], false, true, g[i]->ws && g[i]->ldc == g[i]->N && !g[i]->act).us;
-    const long n = (long)((g[i]->M + SLICE_TILE - 1) / SLICE_TILE) * ((g[i]->N + SLICE_TILE - 1) / SLICE_TILE);
+    const Piece& p = own[i].piece[0];
+    if (p.kernel != PRODUCT_SLICES && p.kernel != KARMA_PRODUCT_SMALL) return false;
     const int kt = (g[i]->K + SLICE_BK - 1) / SLICE_BK;
-    const double one = SLICES_ROUND + SLICES_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES);
-    items += n;
-    work += n * one;
-    longest = std::max(longest, one);
+    if (kt > PAIR_MAX_KT) return false;
+    apart += p.us;
+    items[i] = (long)((g[i]->M + SLICE_TILE - 1) / SLICE_TILE) * ((g[i]->N + SLICE_TILE - 1) / SLICE_TILE);
+    each[i] = SLICES_ROUND + PAIR_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES);
   }
-  const double together = SLICES_BASE + (items <= cus ? longest : work / cus + 0.5 * longest);
-  return together < apart;
+  // dx leaves `late` units busy until `then`, the others from `now` on take dw's workgroups, and so on
+  const long cus = compute_units(), late = items[0] % cus;
+  double now = items[0] / cus * each[0], then = now + each[0], end = late ? then : now;
+  for (long left = items[1]; left > 0;) {
+    const bool first = !late || now <= then;
+    double& at = first ? now : then;
+    left -= first ? cus - late : late;
+    at += each[1];
+    end = std::max(end, at);
+    if (SLICES_BASE + end >= 0.95 * apart) return false;
+  }
+  return SLICES_BASE + end < 0.95 * apart;
+}
+
+static int gemm_pair_choose(const GemmArgs& dx, const GemmArgs& dw, Choice (&own)[2], bool* together) {
+  int st = gemm_choose(dx, own[0].piece, &own[0].pieces);
+  if (st == KARMA_OK) st = gemm_choose(dw, own[1].piece, &own[1].pieces);
+  *together = st == KARMA_OK && pair_of_slices(dx, dw, own);
+  return st;
 }
 
 static int gemm_pair_launch(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
-  if (dx.a_kc && !dx.b_kc && dx.act != 1 && !dw.a_kc && !dw.b_kc && !dw.act && !dx.conv_mode && !dw.conv_mode && pair_of_slices(dx, dw)) {
+  Choice own[2];
+  bool together = false;
+  int st = gemm_pair_choose(dx, dw, own, &together);
+  if (together) {
     int one = 1;
     const SliceWork a = slice_work(dx, one), b = slice_work(dw, one);
     return gemm_slices_launch(a, SliceForm{true, false, dx.act}, &b, s);
   }
-  const int st = gemm_bf16_launch(dx, s);
-  return st == KARMA_OK ? gemm_bf16_launch(dw, s) : st;
+  for (const Choice& c : own)
+    for (int i = 0; i < c.pieces && st == KARMA_OK; ++i) st = launch_piece(c.piece[i], s);
+  return st;
 }
 
 // Launches with events around them when the caller samples them
@@ -1428,6 +1461,50 @@ extern "C" int karma_k_gemm_plan(uint32_t m, uint32_t n, uint32_t k, uint32_t fl
   g.act = (int)gelu_mode;
   g.aux = gelu_mode ? somewhere : nullptr;
   return gemm_plan(g, parts_out, n_out);
+}
+
+// dx = dy w (with aux: times GELU'(aux)) and dw = dy^T x
+static void linear_bwd_products(const void* dy, const void* w, const void* x, void* dx, void* dw, const void* aux, void* ws, uint64_t ws_bytes,
+                                uint32_t rows, uint32_t n, uint32_t k, uint32_t flags, GemmArgs (&g)[2]) {
+  const bool room = !aux;   // (GELU' is taken in the output stage of an undivided product)
+  g[0] = product_args(dy, w, dx, nullptr, nullptr, rows, k, n, KARMA_GEMM_B_STRIDED, room ? ws : nullptr, ws_bytes);
+  g[1] = product_args(dy, x, dw, nullptr, nullptr, n, k, rows, KARMA_GEMM_A_STRIDED | KARMA_GEMM_B_STRIDED | flags, ws, ws_bytes);
+  g[0].act = aux ? 2 : 0;
+  g[0].aux = const_cast<void*>(aux);
+}
+
+extern "C" int karma_k_linear_bwd_bf16(const void* dy, const void* w, const void* x, void* dx, void* dw, const void* aux, float* colsum_out,
+                                       void* ws, uint64_t ws_bytes, uint32_t rows, uint32_t n, uint32_t k, uint32_t flags, void* stream) {
+  if ((flags & ~(KARMA_GEMM_OUT_F32 | KARMA_GEMM_ACCUMULATE)) || (colsum_out && !aux)) return KARMA_E_INVAL;
+  const size_t sums = colsum_out ? (colsum_ws_bytes((int)rows, (int)k) + 255) / 256 * 256 : 0;
+  if (colsum_out && (!ws || ws_bytes < sums)) return KARMA_E_OOM;
+  if (!ws) ws_bytes = 0;
+  void* const rest = ws_bytes > sums ? (char*)ws + sums : nullptr;
+  GemmArgs g[2];
+  linear_bwd_products(dy, w, x, dx, dw, aux, rest, rest ? ws_bytes - sums : 0, rows, n, k, flags, g);
+  int parts = 0;
+  if (colsum_out) {
+    g[0].colsum_partial = (float*)ws;
+    g[0].colsum_bytes = colsum_ws_bytes((int)rows, (int)k);
+    g[0].colsum_rows = &parts;
+  }
+  const int st = gemm_bf16_pair(g[0], g[1], (hipStream_t)stream);
+  if (st || !colsum_out) return st;
+  if (parts) return colsum_finish((float*)ws, parts, (int)k, colsum_out, (hipStream_t)stream);
+  return colsum_bf16((const bf16_t*)dx, colsum_out, (float*)ws, (int)rows, (int)k, (hipStream_t)stream);
+}
+
+extern "C" int karma_k_linear_bwd_plan(uint32_t rows, uint32_t n, uint32_t k, uint32_t gelu, uint32_t flags, uint64_t ws_bytes, uint32_t* together_out) {
+  if (!together_out || (flags & ~(KARMA_GEMM_OUT_F32 | KARMA_GEMM_ACCUMULATE))) return KARMA_E_INVAL;
+  void* const somewhere = (void*)(uintptr_t)4096;   // (addresses are only looked at)
+  GemmArgs g[2];
+  linear_bwd_products(somewhere, somewhere, somewhere, somewhere, somewhere, gelu ? somewhere : nullptr, ws_bytes ? somewhere : nullptr, ws_bytes, rows,
+                      n, k, flags, g);
+  Choice own[2];
+  bool together = false;
+  const int st = gemm_pair_choose(g[0], g[1], own, &together);
+  *together_out = together ? 1u : 0u;
+  return st;
 }
 
 // ---- the product for callers that cannot allocate -------------------------------------------

@@ -135,3 +135,18 @@ def test_products_that_keep_their_sums():
         assert [K.conv_plan(K.ConvShape(*args), w, room)[0][3] for w in (which | keep, which)] == [kept, free]
     with pytest.raises(Exception):
         K.conv_plan(shape, 3 | keep)
+
+
+def test_pairs_of_gradients():
+    """One launch for small layers, not where the products alone are known to be faster, nor beyond 64 k-tiles."""
+    ask = lambda rows, n, k, gelu=False, flags=0: K.linear_bwd_together(rows, n, k, gelu, flags, 8 * n * k * 4)
+    assert ask(1024, 256, 256) and ask(1024, 1024, 256) and ask(1024, 256, 1024, True) and ask(640, 2560, 640) and ask(3200, 512, 128)
+    assert ask(1024, 2048, 256, False, K.GEMM_OUT_F32 | K.GEMM_ACCUMULATE)
+    for rows, n, k in [(6912, 768, 256), (8960, 768, 192), (3840, 3040, 760), (4864, 2560, 640), (8192, 960, 320), (6144, 192, 192), (4160, 64, 64),
+                       (64, 4160, 64), (8192, 3072, 3072)]:
+        assert not ask(rows, n, k)
+    for bad in [(0, 8, 8), (8, 4, 8), (8, 8, 10)]:
+        with pytest.raises(Exception):
+            ask(*bad)
+    with pytest.raises(Exception):
+        ask(8, 8, 8, False, K.GEMM_A_STRIDED)
