@@ -493,9 +493,14 @@ int karma_k_gemm_gelu_bf16(const void* a_dev, const void* b_dev, void* c_dev, co
  * that do not start on 16-byte boundaries.  parts_out: room for two.  Errors: KARMA_E_INVAL. */
 #define KARMA_PRODUCT_STAGED_SMALL 0u /* 128 x 128, through registers */
 #define KARMA_PRODUCT_STAGED_LARGE 1u /* 256 x 256, through registers */
-#define KARMA_PRODUCT_SMALL 2u        /* 128 x 128 or 64 x 64, straight into LDS */
+#define KARMA_PRODUCT_SMALL 2u        /* 128 x 128, straight into LDS; or one of the last three below */
 #define KARMA_PRODUCT_LARGE 3u        /* 256 x 256, straight into LDS */
-#define KARMA_PRODUCT_NARROW 4u       /* 256 x 64, straight into LDS */
+#define KARMA_PRODUCT_NARROW 4u       /* 256 x 64, straight into LDS: convolutions but for weight gradients */
+/* With this bit in flags (a convolution's plan: in which) these three are told from KARMA_PRODUCT_SMALL: */
+#define KARMA_PLAN_TILES 0x80000000u
+#define KARMA_PRODUCT_SLICES 5u       /* 64 x 64, the reduction divided over a workgroup's wavefronts */
+#define KARMA_PRODUCT_BROAD 6u        /* convolutions: 256 x 160, weight gradients 160 x 256 */
+#define KARMA_PRODUCT_FLAT 7u         /* weight gradients of convolutions: 64 x 256 */
 typedef struct {
   uint32_t kernel, m, n, splits;
 } karma_product_part;

@@ -20,6 +20,7 @@ STEP_KERNEL_TIMES = 4
 GEMM_A_STRIDED, GEMM_B_STRIDED, GEMM_OUT_F32, GEMM_ACCUMULATE = 1, 2, 4, 8
 GEMM_GELU_FWD, GEMM_GELU_BWD = 1, 2
 PRODUCT_STAGED_SMALL, PRODUCT_STAGED_LARGE, PRODUCT_SMALL, PRODUCT_LARGE, PRODUCT_NARROW = range(5)
+PRODUCT_SLICES, PRODUCT_BROAD, PRODUCT_FLAT, PLAN_TILES = 5, 6, 7, 1 << 31
 CONV_FWD, CONV_DGRAD, CONV_WGRAD, CONV_KEEP_SUMS = 0, 1, 2, 4
 
 
@@ -117,12 +118,14 @@ def _parts(fn, *args):
 
 
 def gemm_plan(m, n, k, flags=0, gelu_mode=0, misaligned=False, ws_bytes=0):
-    """How the product would be carried out: [(kernel, rows, columns, ranges of the reduction)], one or two parts."""
+    """How the product would be carried out: [(kernel, rows, columns, ranges of the reduction)], one or two parts.  PLAN_TILES in
+    flags (in conv_plan's which): PRODUCT_SLICES, _BROAD and _FLAT are told from PRODUCT_SMALL."""
     return _parts(lib().karma_k_gemm_plan, m, n, k, flags, gelu_mode, int(misaligned), C.c_uint64(ws_bytes))
 
 
 def conv_plan(shape, which, ws_bytes=0):
-    """gemm_plan for one of a convolution's three products (CONV_FWD, CONV_DGRAD, CONV_WGRAD, with or without CONV_KEEP_SUMS)."""
+    """gemm_plan for one of a convolution's three products (CONV_FWD, CONV_DGRAD, CONV_WGRAD, with or without CONV_KEEP_SUMS
+    and PLAN_TILES)."""
     return _parts(lib().karma_k_conv2d_plan, C.byref(shape), which, C.c_uint64(ws_bytes))
 
 

@@ -828,8 +828,8 @@ extern "C" int karma_k_conv2d_wgrad_bf16(const void* dy, const void* x, void* dw
 
 extern "C" int karma_k_conv2d_plan(const karma_conv_shape* c, uint32_t which, uint64_t ws_bytes, karma_product_part* parts_out,
                                    uint32_t* n_out) {
-  const bool keep = which & KARMA_CONV_KEEP_SUMS;
-  which &= ~KARMA_CONV_KEEP_SUMS;
+  const bool keep = which & KARMA_CONV_KEEP_SUMS, tiles = which & KARMA_PLAN_TILES;
+  which &= ~(KARMA_CONV_KEEP_SUMS | KARMA_PLAN_TILES);
   if (!c || !parts_out || !n_out || which > KARMA_CONV_WGRAD || !shape_ok(shape_of(c))) return KARMA_E_INVAL;
   bf16_t* const at = (bf16_t*)(uintptr_t)4096;   // (addresses are only looked at)
   void* const ws = ws_bytes ? at : nullptr;
@@ -838,7 +838,7 @@ extern "C" int karma_k_conv2d_plan(const karma_conv_shape* c, uint32_t which, ui
   return gemm_plan(which == KARMA_CONV_FWD     ? fwd_product(at, at, at, sh, ws, ws_bytes, nullptr)
                    : which == KARMA_CONV_DGRAD ? dgrad_product(at, at, at, nullptr, at, sh, ws, ws_bytes)
                                                : wgrad_product(at, at, at, ws, ws_bytes, sh),
-                   parts_out, n_out);
+                   parts_out, n_out, tiles);
 }
 
 extern "C" uint64_t karma_k_batchnorm_ws_bytes(uint32_t rows, uint32_t c) { return (uint64_t)bn_ws_bytes((int)rows, (int)c); }

@@ -1097,30 +1097,26 @@ static int launch_ring(const GemmArgs& g, int splits, bool deep, int side, hipSt
   return st == KARMA_OK ? finish(g, ep, splits, s) : st;
 }
 
-// Reported as KARMA_PRODUCT_SMALL: the 64 x 64 tile, and the 128 x 128 tile's kernel with 256 x 160, 160 x 256 and 64 x 256
-constexpr uint32_t PRODUCT_SLICES = 16, PRODUCT_BROAD = 17, PRODUCT_FLAT = 18;
-static uint32_t reported(uint32_t kernel) { return kernel >= PRODUCT_SLICES ? KARMA_PRODUCT_SMALL : kernel; }
-
 // One launch of a product (with the sum of its ranges): what gemm_choose decides and launch_piece carries out
 struct Piece {
   GemmArgs g;
-  uint32_t kernel;   // KARMA_PRODUCT_* or one of those above
+  uint32_t kernel;   // KARMA_PRODUCT_*
   int splits;
   bool deep;    // the 128 x 128 tile: four stages
   double us = 0.0;   // modelled, where the tile was chosen by that
 };
 static Piece planned(const GemmArgs& g, const GemmPlan& p) {
-  const uint32_t of64 = !g.conv_mode ? PRODUCT_SLICES : g.conv_mode == 1 ? KARMA_PRODUCT_NARROW : PRODUCT_FLAT;
-  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? of64 : PRODUCT_BROAD, p.splits, p.deep, p.us};
+  const uint32_t of64 = !g.conv_mode ? KARMA_PRODUCT_SLICES : g.conv_mode == 1 ? KARMA_PRODUCT_NARROW : KARMA_PRODUCT_FLAT;
+  return Piece{g, p.tile == 256 ? KARMA_PRODUCT_LARGE : p.tile == 128 ? KARMA_PRODUCT_SMALL : p.tile == 64 ? of64 : KARMA_PRODUCT_BROAD, p.splits, p.deep, p.us};
 }
 static int launch_piece(const Piece& p, hipStream_t s) {
   switch (p.kernel) {
     case KARMA_PRODUCT_LARGE: return launch_large(p.g, p.splits, s);
     case KARMA_PRODUCT_SMALL: return launch_ring(p.g, p.splits, p.deep, RING_TILE, s);
-    case PRODUCT_BROAD: return launch_ring(p.g, p.splits, false, RING_BROAD, s);
+    case KARMA_PRODUCT_BROAD: return launch_ring(p.g, p.splits, false, RING_BROAD, s);
     case KARMA_PRODUCT_NARROW:
-    case PRODUCT_FLAT: return launch_ring(p.g, p.splits, false, RING_SLIM, s);
-    case PRODUCT_SLICES: return launch_slices(p.g, p.splits, s);
+    case KARMA_PRODUCT_FLAT: return launch_ring(p.g, p.splits, false, RING_SLIM, s);
+    case KARMA_PRODUCT_SLICES: return launch_slices(p.g, p.splits, s);
     case KARMA_PRODUCT_STAGED_LARGE: return launch_general<256, 256, 2, 4>(p.g, p.splits, s);
     default: return launch_general<128, 128, 2, 2>(p.g, p.splits, s);
   }
@@ -1206,7 +1202,7 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
     // Up to 64 columns the slim tile, where it has a workgroup for every compute unit: 64 x 224 x 224 x 8 from 64 channels, 7 x 7,
     // 698 -> 409 us.
     const bool slim = g.N <= RING_SLIM && 4l * ((g.M / 4 + 255) / 256) >= compute_units();
-    piece[0] = Piece{g, slim ? KARMA_PRODUCT_NARROW : broad ? PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
+    piece[0] = Piece{g, slim ? KARMA_PRODUCT_NARROW : broad ? KARMA_PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
     return KARMA_OK;
   }
   bool may_split = g.ws && g.ldc == g.N && !g.act;
@@ -1292,7 +1288,7 @@ static bool pair_of_slices(const GemmArgs& dx, const GemmArgs& dw, const Choice 
     if (own[i].pieces != 1) return false;
     // (products of which one alone fills the chip are better off with tiles of their own)
     const Piece& p = own[i].piece[0];
-    if (p.kernel != PRODUCT_SLICES && p.kernel != KARMA_PRODUCT_SMALL) return false;
+    if (p.kernel != KARMA_PRODUCT_SLICES && p.kernel != KARMA_PRODUCT_SMALL) return false;
     const int kt = (g[i]->K + SLICE_BK - 1) / SLICE_BK;
     if (kt > PAIR_MAX_KT) return false;
     apart += p.us;
@@ -1360,7 +1356,7 @@ int gemm_bf16_pair(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
   return timed(2.0 * dx.M * dx.N * dx.K + 2.0 * dw.M * dw.N * dw.K, s, [&] { return gemm_pair_launch(dx, dw, s); });
 }
 
-int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n) {
+int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n, bool tiles) {
   Piece piece[2];
   int pieces = 0;
   const int st = gemm_choose(g, piece, &pieces);
@@ -1368,7 +1364,8 @@ int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n) {
   for (int i = 0; i < pieces; ++i) {
     int splits = piece[i].splits;
     (void)range_length(piece[i].g.K, splits);   // (ranges are whole k-tiles: the last may come to nothing)
-    parts[i] = karma_product_part{reported(piece[i].kernel), (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
+    const uint32_t kernel = !tiles && piece[i].kernel >= KARMA_PRODUCT_SLICES ? KARMA_PRODUCT_SMALL : piece[i].kernel;
+    parts[i] = karma_product_part{kernel, (uint32_t)piece[i].g.M, (uint32_t)piece[i].g.N, (uint32_t)splits};
   }
   *n = (uint32_t)pieces;
   return KARMA_OK;
@@ -1457,10 +1454,11 @@ extern "C" int karma_k_gemm_plan(uint32_t m, uint32_t n, uint32_t k, uint32_t fl
                                  uint64_t ws_bytes, karma_product_part* parts_out, uint32_t* n_out) {
   if (!parts_out || !n_out || gelu_mode > KARMA_GEMM_GELU_BWD) return KARMA_E_INVAL;
   void* const somewhere = (void*)(uintptr_t)(4096 + (misaligned ? 8 : 0));   // (addresses are only looked at)
-  GemmArgs g = product_args(somewhere, somewhere, somewhere, nullptr, nullptr, m, n, k, flags, ws_bytes ? somewhere : nullptr, ws_bytes);
+  GemmArgs g = product_args(somewhere, somewhere, somewhere, nullptr, nullptr, m, n, k, flags & ~KARMA_PLAN_TILES,
+                            ws_bytes ? somewhere : nullptr, ws_bytes);
   g.act = (int)gelu_mode;
   g.aux = gelu_mode ? somewhere : nullptr;
-  return gemm_plan(g, parts_out, n_out);
+  return gemm_plan(g, parts_out, n_out, (flags & KARMA_PLAN_TILES) != 0);
 }
 
 // dx = dy w (with aux: times GELU'(aux)) and dw = dy^T x

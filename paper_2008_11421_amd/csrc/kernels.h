@@ -78,8 +78,9 @@ int gemm_bf16(const GemmArgs& g, hipStream_t s);
 // 2) and dw = dy^T x (both strided).  Small ones run side by side in one launch.  A workspace may be the same: it is used by
 // one after the other or not at all.
 int gemm_bf16_pair(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
-// How gemm_bf16 would carry the product out (at most two parts; host only, addresses are looked at and not followed)
-int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n);
+// How gemm_bf16 would carry the product out (at most two parts; host only, addresses are looked at and not followed).
+// tiles: as KARMA_PLAN_TILES
+int gemm_plan(const GemmArgs& g, karma_product_part* parts, uint32_t* n, bool tiles);
 // While non-null on the calling thread, gemm_bf16 calls record an event before and after
 // their launch (pairs appended from *used on, created on demand) and their flop count: the
 // benchmark's per-launch timing of the dominant kernel.  One call in `stride` is timed (the

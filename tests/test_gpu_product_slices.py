@@ -1,6 +1,6 @@
 """The 64 x 64 tile whose reduction is divided over a workgroup's wavefronts: fewer k-tiles than wavefronts, one and two stages
 of them with and without a rest, rows, columns and k one piece past a tile or a piece long, ranges that a second launch adds
-up, and all output stages.  Beside it sizes of the 128 x 128 tile whose last tiles hang over the matrix.
+up, and all output stages.  Beside it sizes of the 128 x 128 and 256 x 256 tiles whose last tiles hang over the matrix.
 A bf16 result carries one rounding (2^-9 per element); fp32 sums add less than that at these lengths."""
 import ctypes as C
 
@@ -42,6 +42,9 @@ SHAPES = [(8, 8, 8), (64, 64, 64), (72, 56, 72), (56, 136, 184), (64, 72, 256), 
 def test_product(g, m, n, k, flags, with_ws):
     import torch
     make, a, b, ad, bd = operands(m, n, k, flags)
+    (kernel, _, _, splits), = K.gemm_plan(m, n, k, flags | K.PLAN_TILES, 0, False, 64 * m * n if with_ws else 0)
+    assert kernel == {2056: K.PRODUCT_SMALL, 1608: K.PRODUCT_SMALL, 5000: K.PRODUCT_LARGE}.get(m, K.PRODUCT_SLICES)
+    assert (splits > 1) == (with_ws and k == 2048)
     bias, res = make(n), make(m, n)
     ws = torch.empty(16 * m * n, device="cuda") if with_ws else None
     c = torch.full((m + 1, n), 7.0, dtype=torch.bfloat16, device="cuda")
@@ -60,6 +63,7 @@ def test_product(g, m, n, k, flags, with_ws):
 @pytest.mark.parametrize("m,n,k", [(8, 8, 8), (72, 136, 64), (200, 72, 264), (328, 264, 520), (1024, 1024, 256), (1096, 1032, 200)])
 def test_gelu_stages_and_column_sums(g, m, n, k):
     import torch
+    assert K.gemm_plan(m, n, k, K.PLAN_TILES, K.GEMM_GELU_FWD) == K.gemm_plan(m, n, k, B | K.PLAN_TILES, K.GEMM_GELU_BWD) == [(K.PRODUCT_SLICES, m, n, 1)]
     make, a, b, ad, bd = operands(m, n, k, 0)
     bias, b = make(n), b * 0.1
     c, act = torch.empty(m, n, dtype=torch.bfloat16, device="cuda"), torch.empty(m, n, dtype=torch.bfloat16, device="cuda")

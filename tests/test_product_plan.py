@@ -150,3 +150,19 @@ def test_pairs_of_gradients():
             ask(*bad)
     with pytest.raises(Exception):
         ask(8, 8, 8, False, K.GEMM_A_STRIDED)
+
+
+def test_tiles_told_apart():
+    """With PLAN_TILES the kernels that are PRODUCT_SMALL otherwise have names of their own, and nothing else changes."""
+    rng = random.Random(13)
+    seen = set()
+    for _ in range(1000):
+        m, n, k, flags, ws = log_int(rng, 8, 8000, 8), log_int(rng, 8, 8000, 8), log_int(rng, 8, 8000, 8), rng.choice([0, A, B, A | B]), rng.choice([0, 64 << 20])
+        c = K.ConvShape(log_int(rng, 1, 256), *[rng.randint(7, 128)] * 2, log_int(rng, 8, 320, 8), log_int(rng, 8, 320, 8), *[rng.choice([1, 3, 7])] * 2, rng.choice([1, 2]), 3)
+        which = rng.randrange(3)
+        for ask, f, own in [(lambda f: K.gemm_plan(m, n, k, f, 0, False, ws), flags, {K.PRODUCT_SLICES}),
+                            (lambda f: K.conv_plan(c, f, ws), which, {K.PRODUCT_BROAD, K.PRODUCT_FLAT} if which == K.CONV_WGRAD else {K.PRODUCT_BROAD})]:
+            for plain, told in zip(ask(f), ask(f | K.PLAN_TILES)):
+                assert plain[1:] == told[1:] and (plain[0] == told[0] or (plain[0] == K.PRODUCT_SMALL and told[0] in own)), (plain, told)
+                seen.add(told[0])
+    assert {K.PRODUCT_SLICES, K.PRODUCT_BROAD, K.PRODUCT_FLAT} <= seen
