@@ -64,7 +64,8 @@ __device__ __forceinline__ float gelu_sig(float x, float x2) {
 }
 __device__ __forceinline__ float gelu_f(float x) { return x * gelu_sig(x, x * x); }
 __device__ __forceinline__ float gelu_grad_f(float x) {
-  const float x2 = x * x, sg = gelu_sig(x, x2), y = x * sg;
+  // (sig is 0 or 1 long before the bound; beyond it x^2 goes to infinity, and with the zero sig (1 - sig) leaves NaN)
+  const float x2 = fminf(x * x, 1e38f), sg = gelu_sig(x, x2), y = x * sg;
   // sig + x sig (1 - sig) * 2 sqrt(2/pi) (1 + 3 * 0.044715 x^2)
   return fmaf(fmaf(-y, sg, y), fmaf(x2, 0.21406538f, 1.5957691f), sg);
 }

@@ -81,3 +81,17 @@ def test_gelu_stages_and_column_sums(g, m, n, k):
     want = plain * slope
     assert close(out, want, scale + 1)
     assert ((sums.double() - want.sum(0)).abs() <= 2.0 ** -8 * want.abs().sum(0) + 1e-3).all()
+
+
+@pytest.mark.parametrize("m,n,k,kernel", [(72, 136, 64, K.PRODUCT_SLICES), (1608, 2056, 456, K.PRODUCT_SMALL), (4096, 4096, 256, K.PRODUCT_LARGE)])
+def test_gelu_derivative_of_huge_values(g, m, n, k, kernel):
+    """The derivative is one on the far right and zero on the far left, up to the largest finite value: nothing becomes NaN."""
+    import torch
+    assert K.gemm_plan(m, n, k, B | K.PLAN_TILES, K.GEMM_GELU_BWD)[0][0] == kernel
+    make, a, b, ad, bd = operands(m, n, k, B)
+    at = torch.tensor([6.0, 1e4, 1e18, 1.8e19, 1.9e19, 3e19, 5e19, 1e25, 3e38], device="cuda")
+    pre = torch.cat([at, -at]).repeat((m * n + 17) // 18)[:m * n].view(m, n).bfloat16()
+    out = torch.empty(m, n, dtype=torch.bfloat16, device="cuda")
+    g.call(K.lib().karma_k_gemm_gelu_bf16, g.ptr(ad), g.ptr(bd), g.ptr(out), None, g.ptr(pre), m, n, k, B, K.GEMM_GELU_BWD, g.stream_ptr())
+    want = torch.where(pre > 0, a.double() @ b.double().t(), 0.0)
+    assert close(out, want, a.double().abs() @ b.double().abs().t())      # (at 6 the derivative is one to 1e-6)
