@@ -810,7 +810,9 @@ struct GemmPlan {
 //   5.2 / 6.6, 1024 x 256 x 1024 6.9 / 10.6, 64 x 2048 x 1000 7.0 / 10.4, 1024 x 1024 x 1024 7.6 / 11.5, 64 x 1000 x 2048 in
 //   four ranges 8.1 / 10.1; 4096 x 1024 x 256 10.3 / 7.4, 2048 x 1024 x 1024 13.1 / 12.0, 2048 x 2048 x 2048 34 / 21
 // SLICES_MAX_KT: as far as this was measured; a workgroup fetches as many bytes per k-tile as it multiplies 64 x 64 by.
-constexpr double SLICES_BASE = 1.4, SLICES_ROUND = 2.8, SLICES_TILE = 0.68;
+// SLICES_TILE_MORE: where one round follows another, those of the next already fetching: 1352 x 816 x 2008 in 286 workgroups 23.2
+// us, 21.0 on the 128 x 128 tile; 64 x 544 x 137384 in 693 38 and 34.
+constexpr double SLICES_BASE = 1.4, SLICES_ROUND = 2.8, SLICES_TILE = 0.68, SLICES_TILE_MORE = 0.95;
 constexpr int SLICES_MAX_KT = 32;
 static double slices_us(long items, int kt, int cus) {
   if (kt <= SLICE_WAVES) {
@@ -818,7 +820,7 @@ static double slices_us(long items, int kt, int cus) {
     return SLICES_BASE + SLICES_ROUND + SLICES_TILE + 3.9 * (rounds - 1) + 0.33 * kt * std::max(0.0, (double)(rest - cus) / cus);
   }
   const long rounds = (items + cus - 1) / cus;
-  return SLICES_BASE + rounds * (SLICES_ROUND + SLICES_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES));
+  return SLICES_BASE + rounds * (SLICES_ROUND + (rounds > 1 ? SLICES_TILE_MORE : SLICES_TILE) * ((kt + SLICE_WAVES - 1) / SLICE_WAVES));
 }
 
 // The cheapest of the tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
@@ -1270,14 +1272,13 @@ struct Choice {
 };
 
 // Both gradients of a layer in one launch of the 64 x 64 tile where that is modelled to be the shorter way by 5 %: one workgroup
-// per compute unit, those of dx first, those of dw as units become free; beside other work a round of k-tiles takes longer than
-// SLICES_TILE says of a launch alone.  Of 700 layers of transformers (widths from 128 to 1280, 128 to 24576 tokens) 291 take
+// per compute unit, those of dx first, those of dw as units become free; beside other work a round of k-tiles takes
+// SLICES_TILE_MORE.  Of 700 layers of transformers (widths from 128 to 1280, 128 to 24576 tokens) 291 take
 // it: 1.56 times as fast as the two products with tiles of their own up to 32 k-tiles, 1.33 up to 48, 1.15 up to 64, and three
 // of them more than 3 % slower (41.1 / 38.8, 39.1 / 37.9, 59.1 / 52.4 us).  us, one launch / two: 1024 x 256 x 256 8 / 16,
 // 640 x 2560 x 640 (rows, n, k) 17.1 / 22.3, 2304 x 2560 x 640 35.9 / 43.9, 3200 x 512 x 128 13.7 / 17.8.  An estimate that shared the
 // work out evenly had taken 481, 113 of them slower, by up to 1.6: 6912 x 768 x 256 31.4 / 24.0, 3840 x 3040 x 760 100 / 62.
 // PAIR_MAX_KT: beyond it gains and losses were alike (27 layers, 0.82 to 1.35).
-constexpr double PAIR_TILE = 0.95;
 constexpr int PAIR_MAX_KT = 64;
 static bool pair_of_slices(const GemmArgs& dx, const GemmArgs& dw, const Choice (&own)[2]) {
   if (!dx.a_kc || dx.b_kc || dx.act == 1 || dw.a_kc || dw.b_kc || dw.act || dx.conv_mode || dw.conv_mode) return false;
@@ -1293,7 +1294,7 @@ static bool pair_of_slices(const GemmArgs& dx, const GemmArgs& dw, const Choice 
     if (kt > PAIR_MAX_KT) return false;
     apart += p.us;
     items[i] = (long)((g[i]->M + SLICE_TILE - 1) / SLICE_TILE) * ((g[i]->N + SLICE_TILE - 1) / SLICE_TILE);
-    each[i] = SLICES_ROUND + PAIR_TILE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES);
+    each[i] = SLICES_ROUND + SLICES_TILE_MORE * ((kt + SLICE_WAVES - 1) / SLICE_WAVES);
   }
   // dx leaves `late` units busy until `then`, the others from `now` on take dw's workgroups, and so on
   const long cus = compute_units(), late = items[0] % cus;

@@ -166,3 +166,10 @@ def test_tiles_told_apart():
                 assert plain[1:] == told[1:] and (plain[0] == told[0] or (plain[0] == K.PRODUCT_SMALL and told[0] in own)), (plain, told)
                 seen.add(told[0])
     assert {K.PRODUCT_SLICES, K.PRODUCT_BROAD, K.PRODUCT_FLAT} <= seen
+
+
+def test_rounds_of_small_tiles():
+    """Many k-tiles in more than one round of workgroups are slower on 64 x 64 than on 128 x 128, in one round faster."""
+    for m, n, k in [(1352, 816, 2008), (2224, 744, 1960), (1032, 1424, 1752)]:
+        assert K.gemm_plan(m, n, k, A | B | K.PLAN_TILES)[0][0] == K.PRODUCT_SMALL
+    assert K.gemm_plan(1024, 1024, 2008, A | B | K.PLAN_TILES)[0][0] == K.PRODUCT_SLICES
