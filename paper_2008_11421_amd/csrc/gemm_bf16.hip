@@ -823,6 +823,20 @@ static double slices_us(long items, int kt, int cus) {
   return SLICES_BASE + rounds * (SLICES_ROUND + (rounds > 1 ? SLICES_TILE_MORE : SLICES_TILE) * ((kt + SLICE_WAVES - 1) / SLICE_WAVES));
 }
 
+// The same for a convolution's gathers on 256 pixels x 160 channels, one workgroup per compute unit ...
+static double broad_us(long items, double kt, int cus) {
+  const long full = items / cus, rest = items % cus;
+  return 12.5 + 14.5 * (full + (rest ? 1 : 0) - 1) + kt * (full * 1.14 + (rest ? 0.95 + 0.19 * rest / cus : 0.0));
+}
+// ... and on 128 x 128, two of them
+constexpr double SQUARE_GATHER = 1.15, SQUARE_GATHER_LONE = 0.85;
+static double square_gather_us(long items, double kt, int cus) {
+  const long full = items / (2l * cus), rest = items % (2l * cus);
+  const double f = (double)rest / cus, alone = f <= 1.0 ? 0.45 + 0.15 * f : 0.8 + 0.2 * (f - 1.0);
+  const double last = !rest ? 0.0 : !full ? alone : SQUARE_GATHER_LONE + (1.0 - SQUARE_GATHER_LONE) * std::max(0.0, f - 1.0);
+  return 5.5 + 2.5 * (full + (rest ? 1 : 0) - 1) + kt * SQUARE_GATHER * (full + last);
+}
+
 // The cheapest of the tiles, and the number of ranges, by their modelled times in microseconds.  A round is one work
 // item for every place on the chip (one per compute unit with the 256 tile, two with the 128 tile); a k-tile of 64 costs,
 // in a full round and with the places of the last one partly empty, what was measured on 500 products from 64 x 1000 x
@@ -844,11 +858,17 @@ static double slices_us(long items, int kt, int cus) {
 // others (for 64 channels until then 256 x 64 with eight wavefronts) -> this one, 3 x 3 but for the last: 8 x 256 x 256 x 64
 // -> 64 74.7 -> 69.2, 64 -> 8 (input gradient) 93 -> 59, weight gradients 8 x 256 x 256 x 64 -> 64 95 -> 76 and from 128
 // channels 155 -> 115; 7 x 7 at stride 2, 64 x 224 x 224 x 8 -> 64 87 -> 78, weight gradient 99 -> 73, input gradient 698 -> 409.
+// Its 256 pixels against 128 of the square tile are what the L2s have to hold until the next tap reads them again: 47 x 113 x
+// 113 x 232 -> 40, 7 x 7, 2183 us, 1669 on 128 x 128; 18 x 91 x 91 x 200 -> 8 109 and 84; 27 x 142 x 142 x 104 -> 16, 5 x 5, 102 and 75; but
+// 93 x 119 x 119 x 160 -> 48 464 and 572.  Of 583 convolutions to at most 64 channels that factor leaves 6 more than 3 % slower
+// than on the tiles that there were before, without it 137 (by up to 36 %); of 148 to 136 and more on 256 x 160 the 7 % leave 3, without
+// them 7 (by up to 8 %).
 // The calculation itself takes 0.4 to 1.9 us on the host.
+constexpr double L2_BYTES = 8.0 * (4 << 20);
 static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may_split) {
   const int cus = compute_units(), k_tiles = (g.K + 63) / 64;
   const double full256 = g.conv_mode == 1 ? 2.0 : 1.5, alone256 = g.conv_mode == 1 ? 1.4 : 1.25;
-  const double gather128 = g.conv_mode == 1 ? 1.15 : 1.0, lone128 = g.conv_mode == 1 ? 0.85 : 0.75;
+  const double gather128 = g.conv_mode == 1 ? SQUARE_GATHER : 1.0, lone128 = g.conv_mode == 1 ? SQUARE_GATHER_LONE : 0.75;
   const double ragged = g.M % 256 || g.N % 256 || g.K % 64 ? 1.05 : 1.0;
   const double by_element = g.N % 8 || g.ldc % 8 ? std::min(1.0, g.M / 128.0) : 0.0;
   GemmPlan best{0, 1, false, 1e30}, square = best;
@@ -871,13 +891,17 @@ static GemmPlan plan_product(const GemmArgs& g, bool large, bool small, bool may
       const double f = (double)rest / cus;   // workgroups per compute unit in the last round
       double us, more = 0.0;
       if (tile == RING_SLIM && g.conv_mode) {
-        const double slim = g.conv_mode == 1 ? 1.5 : 1.18, lone = g.conv_mode == 1 ? 0.75 : 0.85;   // (full, and next to alone)
+        // pixels are read again for the tap after the next `stride` ones: by then gone where the chip's do not fit its L2s
+        const int apart = g.conv_mode == 1 && !g.conv.transposed ? g.conv.stride : 1;
+        const double fill = g.conv_mode == 1 ? std::min(items, places) * 256.0 * g.conv.C * 2 * apart / L2_BYTES : 0.0;
+        const double again = 1.0 + std::min(0.8, 1.5 * std::max(0.0, fill - 1.0));
+        const double slim = again * (g.conv_mode == 1 ? 1.5 : 1.18), lone = again * (g.conv_mode == 1 ? 0.75 : 0.85);   // (full, and next to alone)
         us = 5.5 + 2.5 * (rounds - 1) + kt * (full * slim + (!rest ? 0.0 : f <= 1.0 ? lone + 0.15 * f : lone + 0.15 + (slim - lone - 0.15) * (f - 1.0)));
       } else if (tile == 64) {
         if (kt > SLICES_MAX_KT) continue;
         us = slices_us(items, kt, cus) + 0.4 + 0.09 * kt;   // (by which the small tile's figure below is too high at few k-tiles)
       } else if (tile == RING_BROAD) {
-        us = 12.5 + 14.5 * (rounds - 1) + kt * (full * 1.14 + (rest ? 0.95 + 0.19 * f : 0.0));
+        us = (g.conv_mode == 1 ? 1.07 : 1.0) * broad_us(items, kt, cus);   // (in doubt the other tiles)
       } else if (tile == 256) {
         us = 9.0 + 4.0 * (rounds - 1) + ragged * kt * (full * full256 + (rest ? alone256 + (full256 - alone256) * f : 0.0));
       } else {

@@ -15,7 +15,7 @@ SQUARE, LARGE, BROAD, SLIM = K.PRODUCT_SMALL, K.PRODUCT_LARGE, K.PRODUCT_BROAD, 
 
 
 @pytest.mark.parametrize("n,h,ci,co,more,k,stride,on", [(25, 113, 24, 64, 128, 3, 1, (SLIM, SQUARE)), (25, 113, 24, 40, 256, 3, 1, (SLIM, LARGE)), (11, 113, 8, 64, 128, 7, 2, (SLIM, SQUARE)),
-                                                        (43, 31, 8, 24, 128, 3, 1, (SLIM, SQUARE)), (64, 31, 40, 152, 512, 3, 1, (BROAD, LARGE)), (14, 98, 40, 152, 256, 3, 2, (BROAD, LARGE)),
+                                                        (43, 31, 8, 24, 128, 3, 1, (SLIM, SQUARE)), (64, 31, 40, 152, 512, 3, 1, (BROAD, LARGE)), (14, 98, 40, 152, 256, 3, 2, (LARGE, LARGE)),
                                                         (28, 30, 56, 152, 1024, 3, 1, (SQUARE, LARGE)), (16, 33, 64, 64, 128, 3, 1, (SQUARE, SQUARE)), (9, 65, 8, 48, 256, 7, 2, (SQUARE, SQUARE)),
                                                         (65, 30, 320, 160, 1024, 1, 1, (SQUARE, SQUARE))])
 def test_same_bits(g, n, h, ci, co, more, k, stride, on):      # noqa: F811

@@ -173,3 +173,17 @@ def test_rounds_of_small_tiles():
     for m, n, k in [(1352, 816, 2008), (2224, 744, 1960), (1032, 1424, 1752)]:
         assert K.gemm_plan(m, n, k, A | B | K.PLAN_TILES)[0][0] == K.PRODUCT_SMALL
     assert K.gemm_plan(1024, 1024, 2008, A | B | K.PLAN_TILES)[0][0] == K.PRODUCT_SLICES
+
+
+def fwd(*a):
+    return K.conv_plan(K.ConvShape(*a), K.CONV_FWD | K.PLAN_TILES)[0][0]
+
+
+def back(*a):
+    return K.conv_plan(K.ConvShape(*a), K.CONV_DGRAD | K.PLAN_TILES)[0][0]
+
+
+def test_gathers_beyond_the_caches():
+    """256 x 64 is slower than 128 x 128 where the L2 caches do not hold what its workgroups read again for the next tap."""
+    assert back(47, 113, 113, 40, 232, 7, 7, 1, 3) == fwd(27, 142, 142, 104, 16, 5, 5, 2, 2) == back(18, 91, 91, 8, 200, 3, 3, 1, 1) == K.PRODUCT_SMALL
+    assert fwd(93, 119, 119, 160, 48, 3, 3, 1, 1) == fwd(8, 256, 256, 64, 64, 3, 3, 1, 1) == K.PRODUCT_NARROW
