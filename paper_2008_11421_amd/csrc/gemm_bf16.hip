@@ -1221,13 +1221,22 @@ static int gemm_choose(const GemmArgs& g, Piece* piece, int* pieces) {
   }
   const bool small = gemm_ring_takes(g);
   if (g.conv_mode && g.conv.phased) {
-    // by parity of the pixel.  The broad tile where it leaves less than 0.7 of the columns to multiply and fills the chip twice:
-    // 256 x 32 x 32 x 160 from 320 channels 131 -> 120 us; 320 from 640 channels (0.83) 97 and 99
+    const ConvGather& cg = g.conv;
+    // by parity of the pixel: four products of a quarter of the rows, and of a quarter of the taps on average.  The broad tile where it
+    // leaves less than 0.7 of the columns to multiply, fills the chip twice and is modelled to be faster by a tenth: 256 x 32 x 32 x 160
+    // from 320 channels, 3 x 3, 131 -> 120 us, 31 x 160 x 160 x 160 from 264, 7 x 7, 1347 -> 1009; 7 x 168 x 168 x 160 from 16, 3 x 3, 48 and
+    // 60, 84 x 82 x 82 x 152 from 128, 1 x 1, 103 and 124 (of 51 one is left 5 % slower, without the model 37); 320 from 640 channels
+    // (0.83 of the columns) 97 and 99
+    const int cus = compute_units();
+    const double kt = g.K / (4.0 * 64.0);
     const long wide = 4l * ((g.M / 4 + 255) / 256) * ((g.N + RING_BROAD - 1) / RING_BROAD);
-    const bool broad = (g.N + RING_BROAD - 1) / RING_BROAD * RING_BROAD * 10 < (g.N + RING_TILE - 1) / RING_TILE * RING_TILE * 7 && wide >= 2 * compute_units();
+    const long square = 4l * ((g.M / 4 + 127) / 128) * ((g.N + RING_TILE - 1) / RING_TILE);
+    const bool broad = (g.N + RING_BROAD - 1) / RING_BROAD * RING_BROAD * 10 < (g.N + RING_TILE - 1) / RING_TILE * RING_TILE * 7 && wide >= 2 * cus &&
+                       1.1 * broad_us(wide, kt, cus) < square_gather_us(square, kt, cus);
     // Up to 64 columns the slim tile, where it has a workgroup for every compute unit: 64 x 224 x 224 x 8 from 64 channels, 7 x 7,
-    // 698 -> 409 us.
-    const bool slim = g.N <= RING_SLIM && 4l * ((g.M / 4 + 255) / 256) >= compute_units();
+    // 698 -> 409 us; not for the longest reductions, least where channels are no whole cache lines (5 x 236 x 236 x 8 from 320, 7 x 7,
+    // 311 -> 214; 21 x 227 x 227 x 32 from 264 898 and 1139, 21 x 182 x 182 x 40 from 424 1029 and 1259).
+    const bool slim = g.N <= RING_SLIM && 4l * ((g.M / 4 + 255) / 256) >= cus && g.K <= (cg.C % 64 ? 8192 : 16384);
     piece[0] = Piece{g, slim ? KARMA_PRODUCT_NARROW : broad ? KARMA_PRODUCT_BROAD : KARMA_PRODUCT_SMALL, 1, false};
     return KARMA_OK;
   }

@@ -34,7 +34,7 @@ SQUARE, LARGE, BROAD, SLIM, FLAT = K.PRODUCT_SMALL, K.PRODUCT_LARGE, K.PRODUCT_B
 
 
 @pytest.mark.parametrize("n,h,ci,co,k,stride,on", [(64, 31, 40, 152, 3, 1, [BROAD, SLIM, SQUARE]), (64, 31, 280, 152, 3, 1, [BROAD, BROAD, BROAD]),
-                                                   (100, 50, 40, 160, 3, 2, [BROAD, SLIM, SQUARE]), (128, 33, 152, 24, 3, 2, [SLIM, BROAD, FLAT]), (36, 61, 160, 160, 5, 2, [BROAD, BROAD, BROAD]),
+                                                   (100, 50, 40, 160, 3, 2, [BROAD, SLIM, SQUARE]), (128, 33, 152, 24, 3, 2, [SLIM, SQUARE, FLAT]), (36, 61, 160, 160, 5, 2, [BROAD, BROAD, BROAD]),
                                                    (65, 30, 312, 320, 1, 1, [SQUARE, SQUARE, SQUARE]), (61, 32, 160, 168, 3, 1, [LARGE, BROAD, FLAT]),
                                                    (37, 30, 152, 88, 3, 1, [SQUARE, BROAD, SQUARE]), (30, 54, 88, 160, 3, 1, [SQUARE, SQUARE, BROAD]),
                                                    (40, 51, 64, 160, 7, 2, [SQUARE, SLIM, BROAD])])

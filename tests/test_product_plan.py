@@ -187,3 +187,11 @@ def test_gathers_beyond_the_caches():
     """256 x 64 is slower than 128 x 128 where the L2 caches do not hold what its workgroups read again for the next tap."""
     assert back(47, 113, 113, 40, 232, 7, 7, 1, 3) == fwd(27, 142, 142, 104, 16, 5, 5, 2, 2) == back(18, 91, 91, 8, 200, 3, 3, 1, 1) == K.PRODUCT_SMALL
     assert fwd(93, 119, 119, 160, 48, 3, 3, 1, 1) == fwd(8, 256, 256, 64, 64, 3, 3, 1, 1) == K.PRODUCT_NARROW
+
+
+def test_input_gradients_by_parity():
+    """256 x 160 is slower than 128 x 128 with few taps and channels, 256 x 64 with very many."""
+    assert back(7, 168, 168, 160, 16, 3, 3, 2, 1) == back(84, 82, 82, 152, 128, 1, 1, 2, 0) == K.PRODUCT_SMALL
+    assert back(31, 160, 160, 160, 264, 7, 7, 2, 3) == back(256, 32, 32, 160, 320, 3, 3, 2, 1) == K.PRODUCT_BROAD
+    assert back(21, 182, 182, 40, 424, 7, 7, 2, 3) == back(21, 227, 227, 32, 264, 7, 7, 2, 3) == K.PRODUCT_SMALL
+    assert back(5, 236, 236, 8, 320, 7, 7, 2, 3) == back(64, 224, 224, 8, 64, 7, 7, 2, 3) == K.PRODUCT_NARROW
