@@ -752,10 +752,13 @@ int layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* stats, const b
   const bool direct = rows <= 512 && !over_inputs(dgamma) && !over_inputs(dbeta) && !over_inputs(add_colsum);
   // Columns and rows side by side in one launch; where the gradient lies over an input, the columns have a launch of their
   // own before it.  us, two launches / one, with add_colsum: 128 x 256 7.9 / 5.0, 1024 x 256 11.4 / 7.3, 4096 x 1024
-  // 17.2 / 12.7, 8192 x 1024 25.4 / 20.8, 8192 x 3072 62.5 / 59.4, 4096 x 4256 57.0 / 56.7.
+  // 17.2 / 12.7, 8192 x 1024 25.4 / 20.8, 8192 x 3072 62.5 / 59.4, 4096 x 4256 57.0 / 56.7.  Long wide tensors (beyond 3072
+  // columns the one pass above does not take them) keep two launches: the rows find more of them in the caches right behind
+  // the columns than beside them.  8731 x 5616 169 / 179, 24217 x 3160 263 / 277, 33574 x 3872 413 / 450, 46040 x 4344 617 / 670; of
+  // 21 below 16 Mi elements and wider than 3072 none takes more than 3 % longer in one.
   const size_t tensor_bytes = (size_t)rows * h * sizeof(bf16_t);
   auto dx_over = [&](const bf16_t* in) { return in && (const char*)dx < (const char*)in + tensor_bytes && (const char*)in < (const char*)dx + tensor_bytes; };
-  const bool apart = dx_over(dy) || dx_over(x) || dx_over(add);
+  const bool apart = dx_over(dy) || dx_over(x) || dx_over(add) || (h > 3072 && (size_t)rows * h >= ((size_t)16 << 20));
   const int vc = direct ? 2 : 32, band = direct ? rows : LNB_ROWS, col_groups = (h / 8 + vc - 1) / vc;
   const LayerNormBwd p{dy, x, stats, g, add, dx, direct ? nullptr : partial_ws, dgamma, dbeta, add_colsum, rows, h, band, col_groups};
   const unsigned col_blocks = (unsigned)col_groups * (direct ? 1u : (unsigned)parts), row_blocks = (unsigned)(rows + 3) / 4;
