@@ -115,11 +115,12 @@ __device__ __forceinline__ float half_wave_sum(float v) {
 // wavefront's queries are skipped).
 // Workgroup -> (tile, head, batch), L its number among nt * H * batches.  Workgroup ids go round-robin over the 8 XCDs;
 // all tiles of one (batch, head) are given to the same XCD, so that head's K and V are fetched into one L2 only, and the
-// heaviest tile of the causal triangle goes first (heavy_high: the last tile is the heaviest).  The (batch, head) pairs
-// beyond a multiple of eight are dealt tile by tile, heaviest tiles first.
+// heaviest tile of the causal triangle goes first (heavy_high: the last tile is the heaviest).  That holds for the first
+// `local` (batch, head) pairs, a multiple of eight; the others are dealt tile by tile, heaviest tiles first.
 __device__ __forceinline__ int workgroup_number() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
-__device__ __forceinline__ void attn_block(int L, int nt, int H, int hb_total, int& tile, int& head, int& b, bool heavy_high) {
-  const int local = hb_total / 8 * 8, rest = hb_total - local;
+__device__ __forceinline__ void attn_block(int L, int nt, int H, int hb_total, int local, int& tile, int& head, int& b,
+                                           bool heavy_high) {
+  const int rest = hb_total - local;
   int t, hb;
   if (L < local * nt) {
     const int slot = L / 8;
@@ -244,13 +245,13 @@ __device__ __forceinline__ void join_groups(float* lds, int group, int tid, Mine
 // SP groups of four wavefronts share the workgroup's queries; group k takes the key tiles k, k + SP, ...
 template <int D, int KT, int WGS, int SP>
 __global__ __launch_bounds__(256 * SP, WGS) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
-                                                                   float* __restrict__ lse, int S, int H) {
+                                                                   float* __restrict__ lse, int S, int H, int local) {
   constexpr int DP = padded_d(D), NMT = KT / 32, TILE = tile_bytes(D, KT), STAGE = 2 * TILE;   // stage = K tile | V tile
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_attn[];
   const int h = H * D;
   const size_t ld = 3 * (size_t)h;
   int tile, head, b;
-  attn_block(workgroup_number(), S / 128, H, gridDim.y * gridDim.z, tile, head, b, true);
+  attn_block(workgroup_number(), S / 128, H, gridDim.y * gridDim.z, local, tile, head, b, true);
   const int q0 = tile * 128;
   const int group = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
   const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn) + group * 2 * STAGE;
@@ -445,7 +446,7 @@ struct AttnBwd {
   float* delta;
   bf16_t* dqkv;
   float* colsum;        // or null
-  int S, H;
+  int S, H, local;      // local: see attn_block
 };
 
 // ------------------------------------------------------------------ backward: dQ
@@ -467,7 +468,7 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnBwd& p, int L, int hb_tota
   const int S = p.S, H = p.H, h = H * D;
   const size_t ld = 3 * (size_t)h;
   int tile, head, b;
-  attn_block(L, S / 128, H, hb_total, tile, head, b, true);
+  attn_block(L, S / 128, H, hb_total, p.local, tile, head, b, true);
   const int q0 = tile * 128;
   const int group = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
   const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn) + group * 2 * STAGE;
@@ -610,7 +611,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnBwd& p, int L, int hb_tot
   const int S = p.S, H = p.H, h = H * D;
   const size_t ld = 3 * (size_t)h;
   int tile, head, b;
-  attn_block(L, S / 128, H, hb_total, tile, head, b, false);
+  attn_block(L, S / 128, H, hb_total, p.local, tile, head, b, false);
   const int k0 = tile * 128;
   const int group = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
   const unsigned lds0 = (unsigned)(uintptr_t)((KARMA_LDS(unsigned char)*)smem_attn) + group * 2 * STAGE;
@@ -813,13 +814,32 @@ __global__ __launch_bounds__(256 * SP, WGS) void attn_bwd_both_kernel(AttnBwd p)
 // ------------------------------------------------------------------------------ launchers
 static inline int ok() { return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP; }
 
+// How many (batch, head) pairs stay on one XCD each, of pairs with nt tiles: all whole groups of eight; but none where the number
+// is no multiple of eight and up to four workgroups for a compute unit, which all start at once, would leave one of them
+// with a fifth more tiles than dealing all pairs tile by tile does.  (A unit's workgroups are 32 tiles of its XCD apart, one
+// eighth of the units: with 11 tiles these are neighbours.)  us, rounds of all workgroups -> local -> this: forward 51 pairs of 11
+// tiles, heads of 64 35.6 -> 39.8 -> 31.4, 13 of 31, heads of 128 106 -> 121 -> 100, backward 46 of 13, heads of 64 127 -> 130 -> 112; 85 of 9,
+// heads of 64, forward 34.4 -> 30.1, as it is.
+static int local_pairs(int nt, int pairs) {
+  const int cus = compute_units(), apart = std::max(1, cus / 8), each = (int)(((long)nt * pairs + cus - 1) / cus);
+  if (pairs % 8 == 0 || each < 2 || each > 4) return pairs / 8 * 8;
+  int most = 0, even = 0;
+  for (int t = 0; t < nt; ++t) {
+    int sum = 0;
+    for (int i = 0; i < each; ++i) sum += nt - (t + apart * i) % nt;
+    most = std::max(most, sum);
+  }
+  for (int i = 0; i < each; ++i) even += std::max(1, nt - cus * i / pairs);
+  return most * 5 >= even * 6 ? 0 : pairs / 8 * 8;
+}
+
 template <int D, int KT, int WGS, int SP>
 static void launch_fwd_as(dim3 grid, hipStream_t s, const bf16_t* qkv, bf16_t* ctx, float* lse, int seq, int heads) {
   // two stages of (K tile, V tile) per group; the other groups' sums on their way to group 0
   constexpr int lds = std::max(SP * 2 * 2 * tile_bytes(D, KT), SP > 1 ? (2 + padded_d(D) / 2) * 1024 : 0);
   auto kern = attn_fwd_kernel<D, KT, WGS, SP>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  hipLaunchKernelGGL(kern, grid, dim3(256 * SP), lds, s, qkv, ctx, lse, seq, heads);
+  hipLaunchKernelGGL(kern, grid, dim3(256 * SP), lds, s, qkv, ctx, lse, seq, heads, local_pairs((int)grid.x, (int)(grid.y * grid.z)));
 }
 template <int D>
 static void launch_fwd(dim3 grid, hipStream_t s, const bf16_t* qkv, bf16_t* ctx, float* lse, int seq, int heads) {
@@ -899,7 +919,7 @@ int attention_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, cons
     hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, ctx, dctx, delta, seq, heads, d, total);
     ctx = nullptr;
   }
-  const AttnBwd p{qkv, ctx, dctx, lse, delta, dqkv, sums, seq, heads};
+  const AttnBwd p{qkv, ctx, dctx, lse, delta, dqkv, sums, seq, heads, local_pairs(seq / 128, batch * heads)};
   if (d == 64) launch_bwd<64>(grid, s, p);
   else if (d == 128) launch_bwd<128>(grid, s, p);
   else launch_bwd<152>(grid, s, p);

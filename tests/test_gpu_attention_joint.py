@@ -23,7 +23,8 @@ def g():
 
 SHAPES = [(1, 128, 1, 64), (5, 256, 3, 64), (1, 384, 3, 64), (2, 512, 16, 64), (3, 512, 11, 64), (3, 640, 12, 64), (4, 1024, 8, 64), (4, 1024, 16, 64),
           (5, 896, 15, 64), (2, 384, 5, 128), (1, 512, 9, 128), (3, 640, 12, 128), (4, 512, 12, 128), (1, 256, 3, 152), (3, 640, 11, 152),
-          (4, 512, 16, 152)]
+          (4, 512, 16, 152),
+          (3, 1408, 17, 64), (1, 1408, 35, 152)]        # (the last two: all pairs dealt tile by tile)
 
 
 def reference(qkv, dctx, b, s, h, d):
