@@ -155,8 +155,8 @@ int add_inplace_bf16(bf16_t* y, const bf16_t* a, size_t n, hipStream_t s);      
 int avgpool_fwd(const bf16_t* x, bf16_t* y, int n, int hw, int c, hipStream_t s);         // global
 int avgpool_bwd(const bf16_t* dy, bf16_t* dx, int n, int hw, int c, hipStream_t s);
 
-// ---- the optimiser's update on the device (optim_dev.hip): kind = karma_opt_kind; step counts from 1.  n tensors in
-// launches of OPTIM_TENSORS each
+// ---- the optimiser's update on the device (optim_dev.hip): kind = karma_opt_kind; step counts from 1.  At
+// most OPTIM_TENSORS tensors, in one launch
 struct OptimTensor {
   float* w; float* m; float* v;   // fp32 master weights and state
   const void* g;                  // gradient, bf16 or fp32

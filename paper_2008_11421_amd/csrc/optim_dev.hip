@@ -71,26 +71,24 @@ __global__ __launch_bounds__(256) void optim_update_kernel(UpdateSet u, float lr
 }  // namespace
 
 int optim_update_dev(int kind, const OptimTensor* tensors, int n, float lr, float beta1, float beta2, float eps, uint64_t step, hipStream_t s) {
-  if (!tensors || n <= 0) return KARMA_E_INVAL;
+  if (!tensors || n <= 0 || n > OPTIM_TENSORS) return KARMA_E_INVAL;
   const float c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)step)));
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)step)));
-  for (int at = 0; at < n; at += OPTIM_TENSORS) {
-    UpdateSet u{};
-    u.n = std::min(OPTIM_TENSORS, n - at);
-    for (int k = 0; k < u.n; ++k) {
-      const OptimTensor& t = tensors[at + k];
-      if (!t.w || !t.g || !t.out || !t.n) return KARMA_E_INVAL;
-      if ((kind == KARMA_OPT_ADAM && (!t.m || !t.v)) || (kind == KARMA_OPT_SGD_MOMENTUM && !t.m)) return KARMA_E_INVAL;
-      u.t[k] = t;
-      u.first[k + 1] = u.first[k] + (unsigned)std::min<size_t>((t.n + 255) / 256, 256 * 16);
-    }
-#define KARMA_OPT_LAUNCH(K) hipLaunchKernelGGL(optim_update_kernel<K>, dim3(u.first[u.n]), dim3(256), 0, s, u, lr, beta1, beta2, eps, c1, c2)
-    if (kind == KARMA_OPT_ADAM) KARMA_OPT_LAUNCH(KARMA_OPT_ADAM);
-    else if (kind == KARMA_OPT_SGD_MOMENTUM) KARMA_OPT_LAUNCH(KARMA_OPT_SGD_MOMENTUM);
-    else if (kind == KARMA_OPT_SGD) KARMA_OPT_LAUNCH(KARMA_OPT_SGD);
-    else return KARMA_E_INVAL;
-#undef KARMA_OPT_LAUNCH
+  UpdateSet u{};
+  u.n = n;
+  for (int k = 0; k < n; ++k) {
+    const OptimTensor& t = tensors[k];
+    if (!t.w || !t.g || !t.out || !t.n) return KARMA_E_INVAL;
+    if ((kind == KARMA_OPT_ADAM && (!t.m || !t.v)) || (kind == KARMA_OPT_SGD_MOMENTUM && !t.m)) return KARMA_E_INVAL;
+    u.t[k] = t;
+    u.first[k + 1] = u.first[k] + (unsigned)std::min<size_t>((t.n + 255) / 256, 256 * 16);
   }
+#define KARMA_OPT_LAUNCH(K) hipLaunchKernelGGL(optim_update_kernel<K>, dim3(u.first[n]), dim3(256), 0, s, u, lr, beta1, beta2, eps, c1, c2)
+  if (kind == KARMA_OPT_ADAM) KARMA_OPT_LAUNCH(KARMA_OPT_ADAM);
+  else if (kind == KARMA_OPT_SGD_MOMENTUM) KARMA_OPT_LAUNCH(KARMA_OPT_SGD_MOMENTUM);
+  else if (kind == KARMA_OPT_SGD) KARMA_OPT_LAUNCH(KARMA_OPT_SGD);
+  else return KARMA_E_INVAL;
+#undef KARMA_OPT_LAUNCH
   return hipGetLastError() == hipSuccess ? KARMA_OK : KARMA_E_HIP;
 }
 
