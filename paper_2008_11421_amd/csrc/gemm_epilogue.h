@@ -13,7 +13,7 @@ struct GemmEpilogue {
   int out_f32;             // store fp32 instead of bf16
   int accumulate;          // fp32 output only: C += result
   bf16_t* aux;             // [M][ldc]: octet<1> writes GELU(C) there, octet<2> multiplies the result by GELU'(aux) (bf16 C only)
-  float* colsum;           // octet<2> only, or null: partial column sums of the result, two rows of N per row of tiles
+  float* colsum;           // octet<2> only, or null: partial column sums of the result, a row of N per 64 (256 x 256 tile: 128) rows
   // eight consecutive columns n..n+7 of row m (n multiple of 8); cols = how many are inside the matrix
   // pre (when have_pre): the eight residual (or, ACT 2, pre-activation) values of this octet, fetched by the caller
   template <int ACT = 0>

@@ -63,7 +63,7 @@ struct GemmArgs {
   int act;
   void* aux;
   // act 2, optional: colsum_bytes of room at colsum_partial.  When the product runs on a kernel that can do it and its
-  // sums fit there (two rows of N floats per row of tiles, which are 256 or 128 rows of C), partial column sums of C
+  // sums fit there (a row of N floats per 64 rows of C, or 128 with the 256 x 256 tile), partial column sums of C
   // (fp32, before rounding) are left there and *colsum_rows (preset to 0 by the caller) is set to the number of rows;
   // colsum_finish adds them up.  Otherwise nothing is written.
   float* colsum_partial;

@@ -48,12 +48,13 @@ def run(g, bufs, ws, rows, h):
            g.ptr(ws), C.c_uint64(ws.numel() * 4), rows, h, g.stream_ptr())
 
 
-# the pass that sums as it goes takes 12288 rows and more, from 8 Mi elements (10 Mi without add sums) and up to 3072 columns:
+# the pass that sums as it goes takes 12288 rows and more, from 8 Mi elements (10 Mi without add sums) and up to 3072 columns; else
+# rows and columns are apart, in one launch, or in two where the gradient lies over an input and for 16 Mi elements of more columns:
 # both sides of each line, each number of vectors per lane, last workgroups and last vectors that are not full
 @pytest.mark.parametrize("rows,h", [(12288, 1032), (12291, 2056), (12300, 3072), (12287, 1032), (16385, 512), (16383, 512), (20483, 520),
                                     (12289, 3080), (40000, 264)])
 @pytest.mark.parametrize("in_place", [False, True])
-def test_one_pass_and_two_launches(g, rows, h, in_place):
+def test_one_pass_and_rows_apart_from_columns(g, rows, h, in_place):
     import torch
     x, dy, add, gamma, stats = problem(rows, h, rows + h)
     dx, sums = reference(x, dy, add, gamma, stats)
@@ -97,7 +98,7 @@ def test_sums_over_inputs(g, rows, h, out, over):
 
 
 def test_more_bands_than_a_second_grid_dimension_holds(g):
-    """h above 3072 takes two launches at any number of rows; 65536 bands of 64 rows and one row more."""
+    """h above 3072 has rows and columns apart at any number of rows; 65536 bands of 64 rows and one row more."""
     import torch
     rows, h = 64 * 65536 + 1, 3080
     gen = torch.Generator(device="cuda")
