@@ -853,8 +853,8 @@ static double square_gather_us(long items, double kt, int cus) {
 // Convolutions also have 256 pixels x 160 channels (weight gradients 160 x 256), one workgroup per compute unit: 1.14 us a
 // k-tile, and 14.5 us more for every round, which begins and ends with nobody to hide behind.  us, the better of the others ->
 // this one, 3 x 3: 256 x 32 x 32 x 160 -> 160 216 -> 159, 256 x 8 x 8 x 640 -> 640 153 -> 115, 256 x 16 x 16 x 320 -> 320
-// 144 -> 128, its weight gradient 155 -> 138 (with room for 10 ranges; the wide residual network's records have room for fewer
-// ranges than this tile and 64 x 256 need, and their weight gradients stay on 128 x 128); 8 x 128 x 128 x 128 -> 128 50 -> 68, 16 x 30 x 30 x 192 -> 192 24 -> 39.
+// 144 -> 128, its weight gradient 155 -> 138 (with room for 10 ranges; the wide residual network's records have room for 8, and
+// their weight gradients of 160 channels and more stay on 128 x 128); 8 x 128 x 128 x 128 -> 128 50 -> 68, 16 x 30 x 30 x 192 -> 192 24 -> 39.
 // And 256 x 64 (weight gradients 64 x 256), two workgroups per compute unit: 1.5 and 1.18 us a k-tile.  us, the better of the
 // others (for 64 channels until then 256 x 64 with eight wavefronts) -> this one, 3 x 3 but for the last: 8 x 256 x 256 x 64
 // -> 64 74.7 -> 69.2, 64 -> 8 (input gradient) 93 -> 59, weight gradients 8 x 256 x 256 x 64 -> 64 95 -> 76 and from 128
